@@ -76,13 +76,13 @@ def load_library():
     lib.pb_static_arena_bytes.restype = C.c_size_t
     lib.pb_static_arena_bytes.argtypes = []
     lib.pb_tick.restype = C.c_int
-    lib.pb_tick.argtypes = [C.c_void_p, fp, C.c_int32]
+    lib.pb_tick.argtypes = [C.c_void_p, C.c_void_p, C.c_int32]
     lib.pb_run_resident.restype = C.c_int
     lib.pb_run_resident.argtypes = [C.c_void_p, C.c_void_p, C.c_void_p, C.c_int32, C.c_int64, C.c_int64]
     for name in ("pb_read_weights", "pb_read_velocity", "pb_loss_history"):
         f = getattr(lib, name)
         f.restype = C.c_int64
-        f.argtypes = [C.c_void_p, fp, C.c_int64]
+        f.argtypes = [C.c_void_p, C.c_void_p, C.c_int64]
     lib.pb_num_params.restype = C.c_int64
     lib.pb_num_params.argtypes = [C.c_void_p]
     lib.pb_num_ticks.restype = C.c_int64
@@ -195,9 +195,9 @@ class PBEngine:
         self._in_elems = net["in_c"] * net["in_h"] * net["in_w"]
 
     def tick(self, sample, label):
-        x = np.ascontiguousarray(sample, dtype=np.float32).reshape(-1)
+        x = np.ascontiguousarray(sample, dtype=np.float32)
         assert x.size == self._in_elems
-        _check(self.lib, self.lib.pb_tick(self.ctx, x.ctypes.data_as(C.POINTER(C.c_float)), int(label)))
+        _check(self.lib, self.lib.pb_tick(self.ctx, x.ctypes.data, int(label)))
 
     def run_resident(self, samples_dev, labels_dev, first_index, n_ticks):
         """samples_dev: float32 CUDA tensor [n_pool, ...]; labels_dev: int32 CUDA tensor [n_pool]."""
@@ -209,7 +209,7 @@ class PBEngine:
 
     def _read(self, fn, n):
         out = np.empty(n, dtype=np.float32)
-        got = _check(self.lib, fn(self.ctx, out.ctypes.data_as(C.POINTER(C.c_float)), n))
+        got = _check(self.lib, fn(self.ctx, out.ctypes.data, n))
         return out[:got]
 
     def read_weights(self):

@@ -4,12 +4,15 @@ from __future__ import annotations
 import os
 import subprocess
 import sys
+from concurrent.futures import ThreadPoolExecutor
 
 HERE = os.path.dirname(os.path.abspath(__file__))
 CSRC = os.path.join(HERE, "csrc")
 LIB = os.path.join(HERE, "libpb_hip.so")
-SOURCES = ["pb_kernels.hip", "pb_host.cpp"]
-FLAGS = ["-O3", "-std=c++17", "-fPIC", "-shared", "--offload-arch=gfx950", "-x", "hip",
+# One object per entry, compiled side by side: the two instantiations of the phase kernel take nearly all of the time.
+OBJECTS = [("phase_nt", "pb_kernels.hip", ["-DPB_PART=1"]), ("phase", "pb_kernels.hip", ["-DPB_PART=2"]),
+           ("kernels", "pb_kernels.hip", ["-DPB_PART=0"]), ("host", "pb_host.cpp", [])]
+FLAGS = ["-O3", "-std=c++17", "-fPIC", "--offload-arch=gfx950", "-x", "hip",
          "-Xclang", "-target-feature", "-Xclang", "-packed-fp32-ops",
          "-ffp-contract=off", "-Wall", "-Wno-unused-function"]
 
@@ -23,11 +26,23 @@ def build(verbose=True, timing=False, stamps=False):
     stamps inside the GEMM step as well (read by gemm_stamps.py; the stamps cost time themselves); the shipped library has none."""
     hipcc = os.environ.get("HIPCC", "/opt/rocm/bin/hipcc")
     out = TIMING_LIB if (timing or stamps) else LIB
-    cmd = [hipcc] + FLAGS + (["-DPB_TIMING=1"] if stamps else ["-DPB_TIMING=2"] if timing else []) + [os.path.join(CSRC, s) for s in SOURCES] + ["-o", out]
-    cmd += ["-Rpass-analysis=kernel-resource-usage"]
-    if verbose:
-        print(" ".join(cmd), flush=True)
-    r = subprocess.run(cmd, stderr=subprocess.PIPE, text=True)
+    define = ["-DPB_TIMING=1"] if stamps else ["-DPB_TIMING=2"] if timing else []
+    objects = [("kernels", "pb_kernels.hip", ["-DPB_PART=3"]), OBJECTS[-1]] if define else OBJECTS
+    objdir = os.path.join(HERE, "_build", os.path.basename(out))
+    os.makedirs(objdir, exist_ok=True)
+
+    def run(cmd):
+        if verbose:
+            print(" ".join(cmd), flush=True)
+        return cmd, subprocess.run(cmd, stderr=subprocess.PIPE, text=True)
+
+    with ThreadPoolExecutor(len(objects)) as pool:
+        done = list(pool.map(lambda o: run([hipcc] + FLAGS + define + o[2] + ["-c", os.path.join(CSRC, o[1]), "-Rpass-analysis=kernel-resource-usage",
+                                                                             "-o", os.path.join(objdir, o[0] + ".o")]), objects))
+    if all(r.returncode == 0 for _, r in done):
+        done.append(run([hipcc, "-shared", "--offload-arch=gfx950"] + [os.path.join(objdir, o[0] + ".o") for o in objects] + ["-o", out]))
+    cmd, r = next(((c, r) for c, r in done if r.returncode), done[-1])
+    r.stderr = "".join(x.stderr for _, x in done)
     usage = check_resources(r.stderr)
     noise = ("kernel-resource-usage", "is not a recognized feature")
     rest = [l for l in r.stderr.splitlines() if l.strip() and not any(n in l for n in noise)

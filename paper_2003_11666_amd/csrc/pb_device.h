@@ -206,12 +206,16 @@ struct Globals {
 constexpr int SYNC_ERR = 0, SYNC_SPIN = 1, SYNC_CNT = 16;
 void launch_phase(const StepDesc* recs_dev, int total_tiles, const Globals* G, int k, const float* sample_override,
                   int label_override, bool nt, hipStream_t s, int32_t* sync = nullptr, uint32_t tick_ordinal = 0);
-void launch_ingest(TRef ring0, int n_elems, const float* staging, int label, int32_t* label_ring,
-                   int n_stages, const Globals* G, int k, hipStream_t s);
+// (each instantiation is compiled on its own)
+void launch_phase_nt(const StepDesc* recs_dev, int total_tiles, const Globals* G, int k, const float* sample_override,
+                     int label_override, hipStream_t s, int32_t* sync, uint32_t tick_ordinal);
+void launch_phase_plain(const StepDesc* recs_dev, int total_tiles, const Globals* G, int k, const float* sample_override,
+                        int label_override, hipStream_t s, int32_t* sync, uint32_t tick_ordinal);
 void launch_update_flat(float* w, float* v, const float* g, float* what, int64_t n, float lr, float m,
                         float a, float b, float lrT, hipStream_t s);
-void launch_advance(Globals* G, int dt, int didx, hipStream_t s);
 void launch_set_globals(Globals* G, Globals val, hipStream_t s);
+// n floats of device memory to host-visible memory dst (16-byte aligned); err != nullptr: also *err_out = *err
+void launch_copy_out(float* dst, const float* src, int64_t n, const int32_t* err, int32_t* err_out, hipStream_t s);
 void launch_fill_zero(void* p, size_t bytes, hipStream_t s);   // bytes a multiple of 16, p 16-byte aligned
 
 // The library's own device array for contexts that must not allocate (pb_init_static): its

@@ -7,7 +7,9 @@
 #include <string.h>
 
 #include <algorithm>
+#include <atomic>
 #include <string>
+#include <thread>
 #include <vector>
 
 #include "../../include/pb.h"
@@ -415,13 +417,20 @@ struct pb_ctx {
   const int32_t* pool_labels = nullptr;
   int n_pool = 0;
   int idx_base = 0;
-  // host-fed ticks: the sample goes through a ring of pinned host buffers, so that the copy to the
-  // device is asynchronous and the caller's buffer is free again when pb_tick returns
-  static constexpr int N_PINNED = 8;
-  float* pinned[N_PINNED] = {};
-  hipEvent_t pinned_done[N_PINNED] = {};
-  bool pinned_used[N_PINNED] = {};
-  int pinned_next = 0;
+  // Pinned host memory, one allocation: a ring of sample slots for host-fed ticks (the ingest step reads the slot over
+  // PCIe itself), and a staging area for the read-back calls.  Contexts that must not allocate have none.
+  static constexpr int SLOT_GROUPS = 4;      // the ring is guarded by one event per quarter, not per slot
+  char* pinned = nullptr;
+  size_t slot_bytes = 0, stage_bytes = 0;
+  int n_slots = 0, next_slot = 0;
+  hipEvent_t slot_done[SLOT_GROUPS] = {};
+  bool slot_used[SLOT_GROUPS] = {};
+  float* stage_host() const { return (float*)(pinned + slot_bytes * n_slots); }
+  // read-backs larger than the staging area: a ring of chunks, made on the first such call
+  static constexpr int RING_CHUNKS = 8;
+  static constexpr int64_t RING_FLOATS = 512 << 10;
+  float* ring_host = nullptr;
+  hipEvent_t ring_done[RING_CHUNKS] = {};
   // profiling
   bool profiling = false;
   int max_events = 0;
@@ -2091,28 +2100,126 @@ int check_device_error(pb_ctx* c) {
   return PB_OK;
 }
 
+// A run of consecutive floats on the device.
+struct Run { const float* src; int64_t n; };
+
+// Device floats into the staging area by one small kernel per run (a few hundred KB at most: a kernel that writes host
+// memory costs about a third of a runtime copy into pageable memory), the error word of fused launches behind them, and
+// one synchronisation.  Returns false in *ok if the staging area is too small or absent.
+int stage_runs(pb_ctx* c, const Run* runs, int n_runs, bool* ok) {
+  int64_t total = 0;
+  for (int i = 0; i < n_runs; ++i) total += (runs[i].n + 3) / 4 * 4;
+  *ok = c->pinned && (size_t)(total + 4) * sizeof(float) <= c->stage_bytes;
+  if (!*ok) return PB_OK;
+  float* dst = c->stage_host();
+  volatile int32_t* err = (volatile int32_t*)(dst + total);
+  *err = 0;
+  for (int i = 0; i < n_runs; ++i) {
+    launch_copy_out(dst, runs[i].src, runs[i].n, c->fuse_from >= 0 && i == 0 ? c->sync_dev + SYNC_ERR : nullptr, (int32_t*)err, c->stream);
+    dst += (runs[i].n + 3) / 4 * 4;
+  }
+  HIP_TRY(hipGetLastError());
+  HIP_TRY(hipStreamSynchronize(c->stream));
+  if (*err) return fail(PB_E_HIP, "a workgroup's wait for the steps it depends on expired (phases sharing a launch): results are invalid");
+  return PB_OK;
+}
+
+// Parameters (or velocities) of every stage from the padded arena layout into the caller's packed array.
 int64_t copy_params_out(pb_ctx* c, int64_t arena_off, float* dst, int64_t cap) {
   if (!dst) return c->n_params;
-  if (hipStreamSynchronize(c->stream) != hipSuccess) return fail(PB_E_HIP, "stream synchronize failed");
-  if (int rc = check_device_error(c)) return rc;
-  std::vector<float> tmp(c->L.P);
-  if (hipMemcpy(tmp.data(), c->f(arena_off), sizeof(float) * c->L.P, hipMemcpyDeviceToHost) != hipSuccess)
-    return fail(PB_E_HIP, "device to host copy failed");
-  // stages with two copies of their master parameters: after an odd number of ticks the current ones are the second
-  if (arena_off == c->L.w && (c->ticks & 1))
-    for (size_t s = 0; s < c->st.size(); ++s)
-      if (c->pp_active[s] &&
-          hipMemcpy(tmp.data() + c->st[s].off, c->f(c->L.sb[s].w2), sizeof(float) * c->st[s].padded, hipMemcpyDeviceToHost) != hipSuccess)
-        return fail(PB_E_HIP, "device to host copy failed");
+  // (stages with two copies of their master parameters: after an odd number of ticks the current ones are the second)
+  const int64_t P = c->L.P;
+  std::vector<Run> runs;
+  std::vector<int64_t> run_at;       // padded offset a run starts at
+  struct Piece { int64_t off, n, to; };
+  std::vector<Piece> pieces;         // padded offset, floats, packed offset
   int64_t n = 0;
-  auto put = [&](const float* src, int64_t cnt) {
-    const int64_t take = std::min<int64_t>(cnt, cap - n);
-    if (take > 0) { memcpy(dst + n, src, sizeof(float) * take); n += take; }
-  };
-  for (const Stage& a : c->st) {
-    put(tmp.data() + a.off, a.n_head);
-    if (a.n_gn) put(tmp.data() + a.off + a.o_gamma, 2 * a.n_gn);
+  for (size_t s = 0; s < c->st.size(); ++s) {
+    const Stage& a = c->st[s];
+    const bool second = arena_off == c->L.w && (c->ticks & 1) && c->pp_active[s];
+    const float* src = second ? c->f(c->L.sb[s].w2) : c->f(arena_off + a.off);
+    if (!runs.empty() && runs.back().src + runs.back().n == src) runs.back().n += a.padded;
+    else { runs.push_back({src, a.padded}); run_at.push_back(a.off); }
+    auto put = [&](int64_t off, int64_t cnt) {
+      const int64_t take = std::min<int64_t>(cnt, cap - n);
+      if (take > 0) { pieces.push_back({a.off + off, take, n}); n += take; }
+    };
+    put(0, a.n_head);
+    if (a.n_gn) put(a.o_gamma, 2 * a.n_gn);
   }
+  // pieces inside [lo, hi) of the padded layout, of which src holds the floats from lo on
+  auto unpack = [&](const float* src, int64_t lo, int64_t hi) {
+    size_t i = std::lower_bound(pieces.begin(), pieces.end(), lo, [](const Piece& p, int64_t v) { return p.off + p.n <= v; }) - pieces.begin();
+    for (; i < pieces.size() && pieces[i].off < hi; ++i) {
+      const int64_t a = std::max(lo, pieces[i].off), b = std::min(hi, pieces[i].off + pieces[i].n);
+      memcpy(dst + pieces[i].to + (a - pieces[i].off), src + (a - lo), sizeof(float) * (b - a));
+    }
+  };
+  bool staged = false;
+  if (int rc = stage_runs(c, runs.data(), (int)runs.size(), &staged)) return rc;
+  if (staged) {
+    unpack(c->stage_host(), 0, P);   // (every run is a multiple of 4 floats: the staging area holds the padded layout)
+    return n;
+  }
+  if (c->pinned && !c->ring_host) {
+    if (hipHostMalloc((void**)&c->ring_host, sizeof(float) * pb_ctx::RING_FLOATS * pb_ctx::RING_CHUNKS, hipHostMallocDefault) != hipSuccess) {
+      (void)hipGetLastError();
+      c->ring_host = nullptr;
+    } else {
+      for (hipEvent_t& e : c->ring_done) HIP_TRY(hipEventCreateWithFlags(&e, hipEventDisableTiming));
+    }
+  }
+  if (!c->ring_host) {
+    if (hipStreamSynchronize(c->stream) != hipSuccess) return fail(PB_E_HIP, "stream synchronize failed");
+    if (int rc = check_device_error(c)) return rc;
+    std::vector<float> tmp(P);
+    for (size_t i = 0; i < runs.size(); ++i)
+      if (hipMemcpy(tmp.data() + run_at[i], runs[i].src, sizeof(float) * runs[i].n, hipMemcpyDeviceToHost) != hipSuccess)
+        return fail(PB_E_HIP, "device to host copy failed");
+    unpack(tmp.data(), 0, P);
+    return n;
+  }
+  // Large networks: chunks of 2 MB through the pinned ring, the copy engine filling some while host threads unpack
+  // others into the caller's array (whose first touch costs a page fault per page: several threads share that too).
+  const int64_t CH = pb_ctx::RING_FLOATS;
+  const int n_ch = (int)cdiv(P, CH);
+  int dev = 0;
+  HIP_TRY(hipGetDevice(&dev));
+  std::atomic<int> next{0}, bad{0};
+  std::atomic<int> queued[pb_ctx::RING_CHUNKS];   // the chunk whose copy into the slot has been put on the stream
+  for (auto& q : queued) q = -1;
+  auto enqueue = [&](int ch) -> bool {
+    const int64_t lo = ch * CH, hi = std::min(P, lo + CH);
+    float* to = c->ring_host + (ch % pb_ctx::RING_CHUNKS) * CH;
+    size_t i = std::upper_bound(run_at.begin(), run_at.end(), lo) - run_at.begin() - 1;
+    for (int64_t at = lo; at < hi; ++i) {
+      const int64_t end = std::min(hi, run_at[i] + runs[i].n);
+      if (hipMemcpyAsync(to + (at - lo), runs[i].src + (at - run_at[i]), sizeof(float) * (end - at), hipMemcpyDeviceToHost, c->stream) != hipSuccess) return false;
+      at = end;
+    }
+    if (hipEventRecord(c->ring_done[ch % pb_ctx::RING_CHUNKS], c->stream) != hipSuccess) return false;
+    queued[ch % pb_ctx::RING_CHUNKS] = ch;
+    return true;
+  };
+  for (int ch = 0; ch < std::min(n_ch, (int)pb_ctx::RING_CHUNKS); ++ch)
+    if (!enqueue(ch)) { (void)hipStreamSynchronize(c->stream); return fail(PB_E_HIP, "device to host copy failed"); }
+  auto work = [&]() {
+    if (hipSetDevice(dev) != hipSuccess) { bad = 1; return; }
+    for (int ch; !bad && (ch = next++) < n_ch;) {
+      // (the thread that unpacks the slot's previous chunk puts this one on the stream)
+      while (queued[ch % pb_ctx::RING_CHUNKS] != ch && !bad) std::this_thread::yield();
+      if (bad || hipEventSynchronize(c->ring_done[ch % pb_ctx::RING_CHUNKS]) != hipSuccess) { bad = 1; return; }
+      unpack(c->ring_host + (ch % pb_ctx::RING_CHUNKS) * CH, ch * CH, std::min(P, (ch + 1) * CH));
+      if (ch + pb_ctx::RING_CHUNKS < n_ch && !enqueue(ch + pb_ctx::RING_CHUNKS)) { bad = 1; return; }
+    }
+  };
+  const int n_thr = std::max(1, std::min({n_ch, 6, (int)std::thread::hardware_concurrency()}));
+  std::vector<std::thread> pool;
+  for (int i = 1; i < n_thr; ++i) pool.emplace_back(work);
+  work();
+  for (std::thread& t : pool) t.join();
+  if (bad) { (void)hipStreamSynchronize(c->stream); return fail(PB_E_HIP, "device to host copy failed"); }
+  if (int rc = check_device_error(c)) return rc;
   return n;
 }
 
@@ -2455,10 +2562,11 @@ int init_common(pb_ctx** out, const pb_net_desc* net, const int32_t* delays, flo
   INIT_TRY(hipStreamSynchronize(c->stream));
   if (!static_arena) {
     const size_t bytes = sizeof(float) * st[0].in_elems();
-    for (int i = 0; i < pb_ctx::N_PINNED; ++i) {
-      INIT_TRY(hipHostMalloc((void**)&c->pinned[i], bytes, hipHostMallocDefault));
-      INIT_TRY(hipEventCreateWithFlags(&c->pinned_done[i], hipEventDisableTiming));
-    }
+    c->slot_bytes = (bytes + 255) / 256 * 256;
+    c->n_slots = (int)std::min<size_t>(64, std::max<size_t>(8, ((size_t)1 << 20) / c->slot_bytes)) / pb_ctx::SLOT_GROUPS * pb_ctx::SLOT_GROUPS;
+    c->stage_bytes = std::min<size_t>((size_t)2 << 20, (size_t)(c->L.P + 64) * sizeof(float));
+    INIT_TRY(hipHostMalloc((void**)&c->pinned, c->slot_bytes * c->n_slots + c->stage_bytes, hipHostMallocDefault));
+    for (hipEvent_t& e : c->slot_done) INIT_TRY(hipEventCreateWithFlags(&e, hipEventDisableTiming));
   }
 #undef INIT_TRY
   *out = c;
@@ -2497,21 +2605,22 @@ int pb_init_static(pb_ctx** out, const pb_net_desc* net, const int32_t* delays, 
 int pb_tick(pb_ctx* c, const float* sample, int32_t label) {
   if (!c || !sample) return fail(PB_E_INVALID, "NULL argument");
   if (label < 0 || label >= c->st.back().K) return fail(PB_E_INVALID, "label %d out of range", label);
-  float* staging = c->f(c->L.staging);
   const size_t bytes = sizeof(float) * c->st[0].in_elems();
-  if (c->pinned[0]) {
-    const int i = c->pinned_next;
-    c->pinned_next = (i + 1) % pb_ctx::N_PINNED;
-    if (c->pinned_used[i]) HIP_TRY(hipEventSynchronize(c->pinned_done[i]));   // its copy of N_PINNED ticks ago has landed
-    memcpy(c->pinned[i], sample, bytes);
-    HIP_TRY(hipMemcpyAsync(staging, c->pinned[i], bytes, hipMemcpyHostToDevice, c->stream));
-    HIP_TRY(hipEventRecord(c->pinned_done[i], c->stream));
-    c->pinned_used[i] = true;
-  } else {
+  if (!c->pinned) {
     // (a context that must not allocate has no pinned buffers: the runtime stages the pageable copy itself)
+    float* staging = c->f(c->L.staging);
     HIP_TRY(hipMemcpyAsync(staging, sample, bytes, hipMemcpyHostToDevice, c->stream));
+    return run_one_tick(c, staging, label);
   }
-  return run_one_tick(c, staging, label);
+  const int i = c->next_slot, per = c->n_slots / pb_ctx::SLOT_GROUPS, g = i / per;
+  if (i % per == 0 && c->slot_used[g]) HIP_TRY(hipEventSynchronize(c->slot_done[g]));   // the group's ticks of the last round have read their samples
+  float* slot = (float*)(c->pinned + c->slot_bytes * i);
+  memcpy(slot, sample, bytes);
+  const int rc = run_one_tick(c, slot, label);
+  if (rc != PB_OK) return rc;
+  c->next_slot = (i + 1) % c->n_slots;
+  if ((i + 1) % per == 0) { HIP_TRY(hipEventRecord(c->slot_done[g], c->stream)); c->slot_used[g] = true; }
+  return PB_OK;
 }
 
 int pb_run_resident(pb_ctx* c, const float* samples_dev, const int32_t* labels_dev, int32_t n_pool,
@@ -2554,11 +2663,20 @@ int64_t pb_loss_history(pb_ctx* c, float* dst, int64_t cap) {
   if (!dst) return avail;
   const int64_t n = std::min(avail, cap);
   if (n <= 0) return 0;
+  // the last n entries of the ring: one run of it, or two
+  const int64_t first = (count - n) % c->loss_cap, n0 = std::min<int64_t>(n, c->loss_cap - first);
+  const Run runs[2] = {{c->f(c->L.loss + first), n0}, {c->f(c->L.loss), n - n0}};
+  bool staged = false;
+  if (int rc = stage_runs(c, runs, n > n0 ? 2 : 1, &staged)) return rc;
+  if (staged) {
+    memcpy(dst, c->stage_host(), sizeof(float) * n0);
+    memcpy(dst + n0, c->stage_host() + (n0 + 3) / 4 * 4, sizeof(float) * (n - n0));
+    return n;
+  }
   HIP_TRY(hipStreamSynchronize(c->stream));
   if (int rc = check_device_error(c)) return rc;
-  std::vector<float> ring_(c->loss_cap);
-  HIP_TRY(hipMemcpy(ring_.data(), c->f(c->L.loss), sizeof(float) * c->loss_cap, hipMemcpyDeviceToHost));
-  for (int64_t i = 0; i < n; ++i) dst[i] = ring_[(count - n + i) % c->loss_cap];
+  HIP_TRY(hipMemcpy(dst, runs[0].src, sizeof(float) * n0, hipMemcpyDeviceToHost));
+  if (n > n0) HIP_TRY(hipMemcpy(dst + n0, runs[1].src, sizeof(float) * (n - n0), hipMemcpyDeviceToHost));
   return n;
 }
 
@@ -2634,10 +2752,10 @@ void pb_destroy(pb_ctx* c) {
   (void)hipStreamSynchronize(c->stream);
   for (auto& e : c->evs) { (void)hipEventDestroy(e.a); (void)hipEventDestroy(e.b); }
   for (auto& e : c->ev_pool) { (void)hipEventDestroy(e.a); (void)hipEventDestroy(e.b); }
-  for (int i = 0; i < pb_ctx::N_PINNED; ++i) {
-    if (c->pinned[i]) (void)hipHostFree(c->pinned[i]);
-    if (c->pinned_done[i]) (void)hipEventDestroy(c->pinned_done[i]);
-  }
+  for (hipEvent_t e : c->slot_done) if (e) (void)hipEventDestroy(e);
+  for (hipEvent_t e : c->ring_done) if (e) (void)hipEventDestroy(e);
+  if (c->pinned) (void)hipHostFree(c->pinned);
+  if (c->ring_host) (void)hipHostFree(c->ring_host);
   if (c->own_arena && c->arena) (void)hipFree(c->arena);
   if (c->static_dev >= 0 && c->static_dev < MAX_STATIC_DEVS) g_static_busy[c->static_dev] = false;
   delete c;

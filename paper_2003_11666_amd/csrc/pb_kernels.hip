@@ -6,6 +6,9 @@
 // therefore goes out as a handful of launches (Appendix "GPU Bottlenecks for
 // Fine-Grained Pipelined Training" names the launch rate as the limit for
 // small networks).  Reductions use fixed trees: results are bit-reproducible.
+//
+// Compiled once per part (PB_PART), side by side: 1 and 2 hold one instantiation
+// of k_phase each, 0 everything else, 3 is all of it (builds with time stamps).
 #include "pb_device.h"
 
 namespace pb {
@@ -2283,6 +2286,7 @@ __device__ __forceinline__ void step_head(const LDesc& d, int t, lfloat* red, lf
 // that a single burst of scalar loads (one memory round trip) delivers all a
 // workgroup needs to know.
 // NT: bulk outputs are stored with the non-temporal hint (networks tiled for latency, see PB_ST).
+#if PB_PART != 0
 template <bool NT>
 __global__ void __launch_bounds__(BLK) __attribute__((amdgpu_waves_per_eu(2, 2)))
 k_phase(const StepDesc* __restrict__ recs, const Globals* __restrict__ G, int k,
@@ -2442,27 +2446,21 @@ k_phase(const StepDesc* __restrict__ recs, const Globals* __restrict__ G, int k,
 #endif
 }
 
-// Copies the tick's sample into the first stage's input ring and its label
-// into the label ring.  staging != nullptr: sample/label were handed over by
-// the host call; otherwise they come from the resident pool.
-__global__ void __launch_bounds__(BLK)
-k_ingest(TRef ring0, int n_elems, const float* __restrict__ staging, int label,
-         int32_t* __restrict__ label_ring, int n_stages, const Globals* __restrict__ G, int k) {
-  const int t = G->t_base + k;
-  const gfloat* src = (const gfloat*)staging;
-  int lab = label;
-  if (!staging) {
-    const int item = (int)(((int64_t)G->idx_base + k) % G->n_pool);
-    src = (const gfloat*)G->pool + (size_t)item * n_elems;
-    lab = ((const gint*)G->pool_labels)[item];
-  }
-  gfloat* dst = at(ring0, t);
-  const int i = blockIdx.x * BLK + threadIdx.x;
-  if (i < n_elems) dst[i] = src[i];
-  if (i == 0) label_ring[t % n_stages] = lab;
+#if PB_PART != 2
+void launch_phase_nt(const StepDesc* recs_dev, int total_tiles, const Globals* G, int k, const float* sample_override,
+                     int label_override, hipStream_t s, int32_t* sync, uint32_t tick_ordinal) {
+  hipLaunchKernelGGL(k_phase<true>, dim3(total_tiles), dim3(BLK), 0, s, recs_dev, G, k, sample_override, label_override, sync, tick_ordinal);
 }
+#endif
+#if PB_PART != 1
+void launch_phase_plain(const StepDesc* recs_dev, int total_tiles, const Globals* G, int k, const float* sample_override,
+                        int label_override, hipStream_t s, int32_t* sync, uint32_t tick_ordinal) {
+  hipLaunchKernelGGL(k_phase<false>, dim3(total_tiles), dim3(BLK), 0, s, recs_dev, G, k, sample_override, label_override, sync, tick_ordinal);
+}
+#endif
+#endif   // PB_PART != 0
 
-
+#if PB_PART == 0 || PB_PART == 3
 // Same arithmetic over plain arrays with one coefficient set.  A workgroup
 // takes U * 1024 consecutive floats; all 3 U loads of a thread are requested
 // before the first use, and every access carries the non-temporal hint: the
@@ -2501,15 +2499,21 @@ __global__ void k_set_globals(Globals* G, Globals val) {
   if (threadIdx.x == 0 && blockIdx.x == 0) *G = val;
 }
 
-__global__ void k_advance(Globals* G, int dt, int didx) {
-  if (threadIdx.x == 0 && blockIdx.x == 0) {
-    G->t_base += dt;
-    G->idx_base = (int)(((int64_t)G->idx_base + didx) % G->n_pool);
-  }
-}
-
 __global__ void __launch_bounds__(BLK) k_fill_zero(v4f* __restrict__ p, size_t n16) {
   for (size_t i = (size_t)blockIdx.x * BLK + threadIdx.x; i < n16; i += (size_t)gridDim.x * BLK) p[i] = (v4f){0.f, 0.f, 0.f, 0.f};
+}
+
+// Device floats into pinned host memory (parameters and losses of small networks): bound by the PCIe write, 16 bytes per
+// lane where the source allows it.
+__global__ void __launch_bounds__(BLK)
+k_copy_out(float* __restrict__ dst, const float* __restrict__ src, int64_t n, const int32_t* __restrict__ err, int32_t* __restrict__ err_out) {
+  const int64_t i0 = (int64_t)blockIdx.x * BLK + threadIdx.x, step = (int64_t)gridDim.x * BLK;
+  if (((uintptr_t)src & 15) == 0 && (n & 3) == 0) {
+    for (int64_t i = i0; i < n >> 2; i += step) ((v4f*)dst)[i] = ((const v4f*)src)[i];
+  } else {
+    for (int64_t i = i0; i < n; i += step) dst[i] = src[i];
+  }
+  if (err && i0 == 0) *err_out = *err;
 }
 
 // Device memory of contexts that must not allocate: one array per GPU, held from the moment the
@@ -2546,19 +2550,16 @@ void launch_fill_zero(void* p, size_t bytes, hipStream_t s) {
   hipLaunchKernelGGL(k_fill_zero, dim3(grid), dim3(BLK), 0, s, (v4f*)p, n16);
 }
 
+void launch_copy_out(float* dst, const float* src, int64_t n, const int32_t* err, int32_t* err_out, hipStream_t s) {
+  const int64_t want = (n + 4 * BLK - 1) / (4 * BLK);
+  hipLaunchKernelGGL(k_copy_out, dim3((unsigned)(want < 1 ? 1 : want < 256 ? want : 256)), dim3(BLK), 0, s, dst, src, n, err, err_out);
+}
+
 void launch_phase(const StepDesc* recs_dev, int total_tiles, const Globals* G, int k, const float* sample_override,
                   int label_override, bool nt, hipStream_t s, int32_t* sync, uint32_t tick_ordinal) {
   if (total_tiles <= 0) return;
-  if (nt) hipLaunchKernelGGL(k_phase<true>, dim3(total_tiles), dim3(BLK), 0, s, recs_dev, G, k, sample_override, label_override, sync, tick_ordinal);
-  else hipLaunchKernelGGL(k_phase<false>, dim3(total_tiles), dim3(BLK), 0, s, recs_dev, G, k, sample_override, label_override, sync, tick_ordinal);
+  (nt ? launch_phase_nt : launch_phase_plain)(recs_dev, total_tiles, G, k, sample_override, label_override, s, sync, tick_ordinal);
 }
-
-void launch_ingest(TRef ring0, int n_elems, const float* staging, int label, int32_t* label_ring,
-                   int n_stages, const Globals* G, int k, hipStream_t s) {
-  hipLaunchKernelGGL(k_ingest, dim3((n_elems + BLK - 1) / BLK), dim3(BLK), 0, s, ring0, n_elems,
-                     staging, label, label_ring, n_stages, G, k);
-}
-
 
 void launch_update_flat(float* w, float* v, const float* g, float* what, int64_t n, float lr, float m,
                         float a, float b, float lrT, hipStream_t s) {
@@ -2574,10 +2575,7 @@ void launch_update_flat(float* w, float* v, const float* g, float* what, int64_t
 void launch_set_globals(Globals* G, Globals val, hipStream_t s) {
   hipLaunchKernelGGL(k_set_globals, dim3(1), dim3(64), 0, s, G, val);
 }
-
-void launch_advance(Globals* G, int dt, int didx, hipStream_t s) {
-  hipLaunchKernelGGL(k_advance, dim3(1), dim3(64), 0, s, G, dt, didx);
-}
+#endif   // PB_PART == 0 || PB_PART == 3
 
 }  // namespace pb
 
