@@ -11,7 +11,7 @@ CSRC = os.path.join(HERE, "csrc")
 LIB = os.path.join(HERE, "libpb_hip.so")
 # One object per entry, compiled side by side: the two instantiations of the phase kernel take nearly all of the time.
 OBJECTS = [("phase_nt", "pb_kernels.hip", ["-DPB_PART=1"]), ("phase", "pb_kernels.hip", ["-DPB_PART=2"]),
-           ("kernels", "pb_kernels.hip", ["-DPB_PART=0"]), ("host", "pb_host.cpp", [])]
+           ("kernels", "pb_kernels.hip", ["-DPB_PART=0"]), ("mlp", "pb_mlp.hip", []), ("host", "pb_host.cpp", [])]
 FLAGS = ["-O3", "-std=c++17", "-fPIC", "--offload-arch=gfx950", "-x", "hip",
          "-Xclang", "-target-feature", "-Xclang", "-packed-fp32-ops",
          "-ffp-contract=off", "-Wall", "-Wno-unused-function"]
@@ -27,7 +27,7 @@ def build(verbose=True, timing=False, stamps=False):
     hipcc = os.environ.get("HIPCC", "/opt/rocm/bin/hipcc")
     out = TIMING_LIB if (timing or stamps) else LIB
     define = ["-DPB_TIMING=1"] if stamps else ["-DPB_TIMING=2"] if timing else []
-    objects = [("kernels", "pb_kernels.hip", ["-DPB_PART=3"]), OBJECTS[-1]] if define else OBJECTS
+    objects = [("kernels", "pb_kernels.hip", ["-DPB_PART=3"])] + OBJECTS[-2:] if define else OBJECTS
     objdir = os.path.join(HERE, "_build", os.path.basename(out))
     os.makedirs(objdir, exist_ok=True)
 

@@ -8,12 +8,14 @@
 
 #include <algorithm>
 #include <atomic>
+#include <mutex>
 #include <string>
 #include <thread>
 #include <vector>
 
 #include "../../include/pb.h"
 #include "pb_device.h"
+#include "pb_mlp.h"
 
 using namespace pb;
 
@@ -309,9 +311,20 @@ bool fusew_shape(const Stage& a) {
          !a.gap && !a.has_bias && a.C * 9 >= 1171 && a.C * a.H * a.W <= 8192 && a.n_w % 4 == 0 && a.n_w >= 65536;
 }
 
+// A perceptron whose parameters fit the register files runs in one kernel that keeps them there from tick to tick
+// (pb_mlp.hip): a workgroup of 8 wavefronts owns 8 rw rows of a stage, a lane nq columns, one workgroup per compute unit.
+struct MlpPlan {
+  bool on = false;
+  int nq = 0, rw = 0, grid = 0;
+  std::vector<int> wgs;              // workgroups per stage
+  int64_t recs = -1, lbox = -1;      // arena offsets
+  std::vector<int64_t> xbox, dybox;  // per stage: messages with its input, with the gradient of its output
+};
+constexpr int MLP_CUS = 256;         // compute units of the GPU the plan is made for
+
 int what_depth(const Stage& a, bool stash) { return stash ? a.De + 2 : a.De - a.D + 2; }
 
-void plan_arena(const std::vector<Stage>& st, bool stash, int loss_cap, Layout& L, Plan& pl, bool use_aring, int update_size) {
+void plan_arena(const std::vector<Stage>& st, bool stash, int loss_cap, Layout& L, Plan& pl, bool use_aring, int update_size, MlpPlan& mp) {
   const int S = (int)st.size();
   L.P = 0;
   for (const Stage& s : st) L.P += s.padded;
@@ -363,6 +376,15 @@ void plan_arena(const std::vector<Stage>& st, bool stash, int loss_cap, Layout& 
   L.globals = pl.alloc(64);
   L.zero = pl.alloc(64);
   L.sync = pl.alloc(SYNC_CNT + MAX_SYNC_PHASES * S);
+  if (mp.on) {
+    mp.recs = pl.alloc((int64_t)mp.grid * (sizeof(MlpRec) / 4));
+    mp.lbox = pl.alloc(2 * 2 * (int64_t)st.back().K);
+    mp.xbox.assign(S, -1); mp.dybox.assign(S, -1);
+    for (int s = 0; s < S; ++s) {
+      mp.xbox[s] = pl.alloc(2 * 2 * (int64_t)st[s].C);
+      if (s + 1 < S) mp.dybox[s] = pl.alloc(2 * 2 * (int64_t)mp.wgs[s + 1] * st[s].K);
+    }
+  }
 }
 
 // ---------------------------------------------------------------- context
@@ -397,6 +419,10 @@ struct pb_ctx {
   bool bf16 = false;   // bf16 activation mode: tensors that cross a stage boundary are rounded to bf16
   int N = 1;           // update size: samples per update
   pb_tuning tune = {0, 0, 0.f, 0, 0, 0, 0, 0, 0};
+  int dev = 0;
+  MlpPlan mlp;                   // on: ticks run in the kernel that keeps a perceptron's parameters in registers
+  bool mlp_messages = false;     // the tick before ran there: gradients between stages lie in its messages
+  bool waits() const { return fuse_from >= 0 || mlp.on; }   // launches hold workgroups that wait for each other
   std::vector<char> pp_active;   // per stage: the update alternates between two copies of the master parameters
   int fuse_from = -1;          // >= 0: the phases from this one on share one launch, dependencies through completion
                                // counters (0: one launch per tick)
@@ -448,7 +474,45 @@ void take_settings(pb_ctx* c, const pb_net_desc* net) {
   c->bf16 = net->act_dtype == 1;
   c->stash = net->bwd_weights == 1;
   c->N = net->update_size > 1 ? net->update_size : 1;
+  c->lwp_w = net->lwp_form == 1;
   if (net->tuning) c->tune = *net->tuning;
+}
+
+// Whether the network can run with its parameters in registers, and how.  Rows per wavefront: as few as let the grid fit
+// the compute units (the arithmetic of a tick is shared by more of them), but enough for a last stage in one workgroup,
+// which spares the exchange of logits inside the tick, where that is possible.  The register files set the limits: 16
+// columns per lane leave room for 3 rows per wavefront, or 2 when the predicted weights are state of their own.
+MlpPlan mlp_plan(const pb_ctx* c) {
+  MlpPlan p;
+  const std::vector<Stage>& st = c->st;
+  const int S = (int)st.size();
+  pb_tuning none = {0, 0, 0.f, 0, 0, 0, 0, 0, 0};
+  if (c->kernel_set != 0 || c->bf16 || c->stash || c->N != 1 || c->sequential || memcmp(&c->tune, &none, sizeof none) != 0) return p;
+  if (S < 2 || S > MLP_MAX_STAGES) return p;
+  int c_max = 0;
+  for (int s = 0; s < S; ++s) {
+    const Stage& a = st[s];
+    if (a.is_conv || a.pre_gn || a.post_gn || a.gap || a.pool || a.add || a.tap_dist || a.ce != (s == S - 1) || a.De != a.D) return p;
+    c_max = std::max(c_max, std::max(a.C, s + 1 < S ? a.K : 0));
+  }
+  if (c_max > MLP_MAX_C || st.back().K > MLP_MAX_K) return p;
+  p.nq = c_max <= 128 ? 2 : c_max <= 256 ? 4 : c_max <= 512 ? 8 : 16;
+  if (2 * (S - 1) + 2 > mlp_hist_slots(p.nq)) return p;
+  const int rw_max = p.nq < 16 ? 4 : c->lwp_w ? 2 : 3;
+  for (int want_single = 1; want_single >= 0 && !p.on; --want_single)
+    for (int rw = 2; rw <= rw_max && !p.on; ++rw) {
+      const int R = MLP_WAVES * rw;
+      p.wgs.clear();
+      p.grid = 0;
+      bool ok = !want_single || st.back().K <= R;
+      for (int s = 0; s < S; ++s) {
+        p.wgs.push_back((st[s].K + R - 1) / R);
+        p.grid += p.wgs.back();
+        if (s > 0 && p.wgs[s] * R > MLP_DYB) ok = false;
+      }
+      if (ok && p.grid <= MLP_CUS) { p.on = true; p.rw = rw; }
+    }
+  return p;
 }
 
 TRef ring(const pb_ctx* c, int64_t off, int depth, int stride, int lag) {
@@ -2092,11 +2156,11 @@ void init_weights_host(const std::vector<Stage>& st, uint64_t seed, std::vector<
 
 // After the stream has been synchronised: did a dependency wait of a one-launch tick expire?
 int check_device_error(pb_ctx* c) {
-  if (c->fuse_from < 0) return PB_OK;
+  if (!c->waits()) return PB_OK;
   int32_t err = 0;
   if (hipMemcpy(&err, c->sync_dev + SYNC_ERR, sizeof err, hipMemcpyDeviceToHost) != hipSuccess)
     return fail(PB_E_HIP, "device to host copy failed");
-  if (err) return fail(PB_E_HIP, "a workgroup's wait for the steps it depends on expired (phases sharing a launch): results are invalid");
+  if (err) return fail(PB_E_HIP, "a workgroup's wait for the steps it depends on expired (inside a launch): results are invalid");
   return PB_OK;
 }
 
@@ -2115,12 +2179,12 @@ int stage_runs(pb_ctx* c, const Run* runs, int n_runs, bool* ok) {
   volatile int32_t* err = (volatile int32_t*)(dst + total);
   *err = 0;
   for (int i = 0; i < n_runs; ++i) {
-    launch_copy_out(dst, runs[i].src, runs[i].n, c->fuse_from >= 0 && i == 0 ? c->sync_dev + SYNC_ERR : nullptr, (int32_t*)err, c->stream);
+    launch_copy_out(dst, runs[i].src, runs[i].n, c->waits() && i == 0 ? c->sync_dev + SYNC_ERR : nullptr, (int32_t*)err, c->stream);
     dst += (runs[i].n + 3) / 4 * 4;
   }
   HIP_TRY(hipGetLastError());
   HIP_TRY(hipStreamSynchronize(c->stream));
-  if (*err) return fail(PB_E_HIP, "a workgroup's wait for the steps it depends on expired (phases sharing a launch): results are invalid");
+  if (*err) return fail(PB_E_HIP, "a workgroup's wait for the steps it depends on expired (inside a launch): results are invalid");
   return PB_OK;
 }
 
@@ -2238,9 +2302,80 @@ struct ScopedEv {
   ~ScopedEv() { if (idx >= 0) (void)hipEventRecord(c->evs[idx].b, c->stream); }
 };
 
+// Launches of k_mlp wait for each other's workgroups, so the workgroups of one launch must all get a compute unit.  One
+// launch never has more than the GPU has; launches of several contexts (on different streams) could, together, and are
+// then put one behind the other with an event.
+struct MlpDevice {
+  std::mutex mu;
+  std::vector<pb_ctx*> live;
+  bool crowded = false;
+  pb_ctx* last = nullptr;        // crowded: context of the latest launch, which ev follows
+  hipEvent_t ev = nullptr;
+};
+MlpDevice g_mlp_dev[MAX_STATIC_DEVS];
+
+int mlp_enter(pb_ctx* c) {
+  MlpDevice& d = g_mlp_dev[c->dev];
+  std::lock_guard<std::mutex> lock(d.mu);
+  d.live.push_back(c);
+  int wgs = 0;
+  for (pb_ctx* o : d.live) wgs += o->mlp.grid;
+  if (wgs > MLP_CUS && !d.crowded) {
+    if (!d.ev) HIP_TRY(hipEventCreateWithFlags(&d.ev, hipEventDisableTiming));
+    HIP_TRY(hipDeviceSynchronize());   // (launches made so far have no event behind them)
+    d.crowded = true;
+    d.last = nullptr;
+  }
+  return PB_OK;
+}
+
+void mlp_leave(pb_ctx* c) {
+  if (!c->mlp.on) return;
+  MlpDevice& d = g_mlp_dev[c->dev];
+  std::lock_guard<std::mutex> lock(d.mu);
+  d.live.erase(std::remove(d.live.begin(), d.live.end(), c), d.live.end());
+  if (d.last == c) d.last = nullptr;   // (its stream has been synchronised)
+  if (d.live.size() <= 1) d.crowded = false;
+}
+
+// n ticks in the kernel that keeps a perceptron's parameters in registers.  staging: one tick's sample (n = 1), or
+// nullptr: samples from the resident pool.
+int run_mlp(pb_ctx* c, int n, const float* staging, int label) {
+  if (c->ticks + n > (int64_t)0x7fffff00) return fail(PB_E_UNSUPPORTED, "tick counter exhausted (2^31 ticks): start a new context");
+  MlpArgs a;
+  a.recs = (const MlpRec*)c->f(c->mlp.recs);
+  a.S = c->S; a.n_ticks = n; a.t0 = (int)c->ticks;
+  a.dy_plain = c->mlp_messages ? 0 : 1;
+  a.pool = c->pool; a.pool_labels = c->pool_labels; a.n_pool = std::max(1, c->n_pool); a.idx_base = c->idx_base;
+  a.sample = staging; a.label = label;
+  a.loss = c->f(c->L.loss); a.loss_cap = c->loss_cap;
+  a.labels = c->labels_dev;
+  a.sync = c->sync_dev;
+  a.lbox = (uint64_t*)c->f(c->mlp.lbox);
+  MlpDevice& d = g_mlp_dev[c->dev];
+  {
+    std::lock_guard<std::mutex> lock(d.mu);
+    if (d.crowded && d.last && d.last != c) HIP_TRY(hipStreamWaitEvent(c->stream, d.ev, 0));
+    {
+      ScopedEv ev(c, 0);
+      launch_mlp(a, c->mlp.grid, c->mlp.nq, c->mlp.rw, c->lwp_w, c->stream);
+    }
+    HIP_TRY(hipGetLastError());
+    if (d.crowded) { HIP_TRY(hipEventRecord(d.ev, c->stream)); d.last = c; }
+  }
+  c->ticks += n;
+  c->mlp_messages = true;
+  return PB_OK;
+}
+
 int run_one_tick(pb_ctx* c, const float* staging, int label) {
+  if (c->mlp.on && c->launch_mode == 0) return run_mlp(c, 1, staging, label);
   // the kernels index every ring with a 32-bit tick counter
   if (c->ticks >= (int64_t)0x7fffff00) return fail(PB_E_UNSUPPORTED, "tick counter exhausted (2^31 ticks): start a new context");
+  if (c->mlp_messages) {
+    launch_mlp_flush((const MlpRec*)c->f(c->mlp.recs), c->mlp.grid, MLP_WAVES * c->mlp.rw, (int)c->ticks, c->stream);
+    c->mlp_messages = false;
+  }
   const int k = (int)c->ticks;   // t_base stays 0 on this path
   if (c->launch_mode == 0) {
     bool counted = false;
@@ -2284,7 +2419,8 @@ size_t pb_arena_bytes(const pb_net_desc* net, const int32_t* delays) {
   const int cap = net->loss_capacity > 0 ? net->loss_capacity : (1 << 20);
   Plan pl;
   Layout L;
-  plan_arena(st, net->bwd_weights == 1, cap, L, pl, net->kernel_set == 0, tmp.N);
+  MlpPlan mp = mlp_plan(&tmp);
+  plan_arena(st, net->bwd_weights == 1, cap, L, pl, net->kernel_set == 0, tmp.N, mp);
   // step table, prefix, chunk map and segment table live in the arena too
   tmp.L = L; tmp.loss_cap = cap; tmp.arena = nullptr;
   tmp.labels_dev = (int32_t*)tmp.f(L.labels);
@@ -2306,7 +2442,8 @@ int64_t pb_plan_summary(const pb_net_desc* net, char* buf, int64_t cap) {
   take_settings(&tmp, net);
   const int lcap = net->loss_capacity > 0 ? net->loss_capacity : (1 << 20);
   Plan pl;
-  plan_arena(st, net->bwd_weights == 1, lcap, tmp.L, pl, net->kernel_set == 0, tmp.N);
+  MlpPlan mp = mlp_plan(&tmp);
+  plan_arena(st, net->bwd_weights == 1, lcap, tmp.L, pl, net->kernel_set == 0, tmp.N, mp);
   tmp.loss_cap = lcap;
   std::vector<std::pair<int, StepDesc>> steps;
   tmp.plan = &pl;
@@ -2383,7 +2520,6 @@ int init_common(pb_ctx** out, const pb_net_desc* net, const int32_t* delays, flo
   c->st = st; c->S = (int)st.size();
   c->mitigation = net->mitigation; c->lr = lr; c->m = momentum;
   take_settings(c, net);
-  c->lwp_w = net->lwp_form == 1;
   c->sequential = sequential;
   c->sc_scale = net->sc_scale > 0.f ? net->sc_scale : 1.0;
   c->lwp_scale = net->lwp_scale > 0.f ? net->lwp_scale : 1.0;
@@ -2424,7 +2560,8 @@ int init_common(pb_ctx** out, const pb_net_desc* net, const int32_t* delays, flo
   }
 
   Plan pl;
-  plan_arena(st, net->bwd_weights == 1, c->loss_cap, c->L, pl, net->kernel_set == 0, c->N);
+  c->mlp = mlp_plan(c);
+  plan_arena(st, net->bwd_weights == 1, c->loss_cap, c->L, pl, net->kernel_set == 0, c->N, c->mlp);
   c->labels_dev = (int32_t*)c->f(c->L.labels);
   c->globals_dev = (Globals*)c->f(c->L.globals);
   c->zero_dev = (int32_t*)c->f(c->L.zero);
@@ -2456,6 +2593,8 @@ int init_common(pb_ctx** out, const pb_net_desc* net, const int32_t* delays, flo
   int n_cu = 0, cur_dev = 0;
   INIT_TRY(hipGetDevice(&cur_dev));
   INIT_TRY(hipDeviceGetAttribute(&n_cu, hipDeviceAttributeMultiprocessorCount, cur_dev));
+  c->dev = cur_dev;
+  if (c->mlp.on && (c->mlp.grid > n_cu || cur_dev >= MAX_STATIC_DEVS)) c->mlp.on = false;
   const bool can_fuse = !c->sequential && n_ph_all >= 2 && n_ph_all <= MAX_SYNC_PHASES;
   if (c->tune.one_launch > 0 && !can_fuse) {
     pb_destroy(c);
@@ -2557,6 +2696,39 @@ int init_common(pb_ctx** out, const pb_net_desc* net, const int32_t* delays, flo
     const int32_t head[2] = {0, c->tune.spin_limit > 0 ? c->tune.spin_limit : (1 << 16)};   // error word, wait bound
     INIT_TRY(hipMemcpyAsync(c->sync_dev, head, sizeof head, hipMemcpyHostToDevice, c->stream));
   }
+  std::vector<MlpRec> mlp_recs;
+  if (c->mlp.on) {
+    for (int s = 0; s < c->S; ++s) {
+      const Stage& a = c->st[s];
+      StepDesc u = blank(K_UPDATE, s, 0);
+      set_update_coeffs(c, a, &u);
+      MlpRec r;
+      memset(&r, 0, sizeof r);
+      r.stage = s; r.n_wg = c->mlp.wgs[s];
+      r.K = a.K; r.C = a.C; r.D = a.D;
+      r.relu = a.pre_relu; r.bias = a.has_bias; r.lwp_w = c->lwp_w;
+      r.t_f = s; r.t_b = 2 * (c->S - 1) - s;
+      r.fa = u.fa; r.fb = u.fb; r.flrT = u.flrT; r.flr = u.flr; r.fm = u.fm;
+      r.w = c->f(c->L.w + a.off + a.o_w); r.v = c->f(c->L.v + a.off + a.o_w);
+      r.what = c->f(c->L.what[s] + a.o_w); r.what_stride = a.padded;
+      if (a.has_bias) { r.b = c->f(c->L.w + a.off + a.o_b); r.vb = c->f(c->L.v + a.off + a.o_b); r.hb = c->f(c->L.what[s] + a.o_b); }
+      r.xring = c->f(c->L.sb[s].xring);
+      r.xbox = (uint64_t*)c->f(c->mlp.xbox[s]);
+      if (s + 1 < c->S) {
+        r.parts = c->mlp.wgs[s + 1];
+        r.yring = c->f(c->L.sb[s + 1].xring);
+        r.ybox = (uint64_t*)c->f(c->mlp.xbox[s + 1]);
+        r.dybox = (uint64_t*)c->f(c->mlp.dybox[s]);
+        r.gradbox = c->f(c->L.sb[s].gradbox);
+      }
+      if (s > 0) r.dxbox = (uint64_t*)c->f(c->mlp.dybox[s - 1]);
+      for (int i = 0; i < r.n_wg; ++i) {
+        r.me = i; r.r0 = i * MLP_WAVES * c->mlp.rw;
+        mlp_recs.push_back(r);
+      }
+    }
+    INIT_TRY(hipMemcpyAsync(c->f(c->mlp.recs), mlp_recs.data(), sizeof(MlpRec) * mlp_recs.size(), hipMemcpyHostToDevice, c->stream));
+  }
   for (auto& tb : c->tables)
     INIT_TRY(hipMemcpyAsync(c->f(tb.first), tb.second.data(), sizeof(int32_t) * tb.second.size(), hipMemcpyHostToDevice, c->stream));
   INIT_TRY(hipStreamSynchronize(c->stream));
@@ -2569,6 +2741,7 @@ int init_common(pb_ctx** out, const pb_net_desc* net, const int32_t* delays, flo
     for (hipEvent_t& e : c->slot_done) INIT_TRY(hipEventCreateWithFlags(&e, hipEventDisableTiming));
   }
 #undef INIT_TRY
+  if (c->mlp.on && mlp_enter(c) != PB_OK) { pb_destroy(c); return PB_E_HIP; }
   *out = c;
   return PB_OK;
 }
@@ -2637,6 +2810,11 @@ int pb_run_resident(pb_ctx* c, const float* samples_dev, const int32_t* labels_d
     g.t_base = 0; g.idx_base = (int)ib; g.n_pool = n_pool; g.pool = samples_dev; g.pool_labels = labels_dev;
     launch_set_globals(c->globals_dev, g, c->stream);
     c->pool = samples_dev; c->pool_labels = labels_dev; c->n_pool = n_pool; c->idx_base = (int)ib;
+  }
+  if (c->mlp.on && c->launch_mode == 0) {
+    for (int64_t j = 0; j < n_ticks; j += MLP_LAUNCH_TICKS)
+      if (int rc = run_mlp(c, (int)std::min<int64_t>(MLP_LAUNCH_TICKS, n_ticks - j), nullptr, 0)) return rc;
+    return PB_OK;
   }
   for (int64_t j = 0; j < n_ticks; ++j) {
     int rc = run_one_tick(c, nullptr, 0);
@@ -2750,6 +2928,7 @@ int pb_sync(pb_ctx* c) {
 void pb_destroy(pb_ctx* c) {
   if (!c) return;
   (void)hipStreamSynchronize(c->stream);
+  mlp_leave(c);
   for (auto& e : c->evs) { (void)hipEventDestroy(e.a); (void)hipEventDestroy(e.b); }
   for (auto& e : c->ev_pool) { (void)hipEventDestroy(e.a); (void)hipEventDestroy(e.b); }
   for (hipEvent_t e : c->slot_done) if (e) (void)hipEventDestroy(e);
