@@ -12,6 +12,9 @@ constexpr int UPD_CHUNK = 1024;   // stages are padded to this many floats
 constexpr int UPD_TILE = 8192;    // floats per workgroup of an update step (8 float4 per thread and array in flight)
 constexpr float GN_EPS = 1e-5f;
 constexpr int GNB_WAVE_CH = 4;    // channels per wavefront in the one-wavefront-per-channel form of K_GNB_REDUCE
+constexpr int GNB_WAVE_HW = 256;  // ... whose maps have at most this many pixels
+constexpr int GAP_WAVE_CH = 4;    // channels per wavefront in the one-wavefront-per-channel form of K_GAP_FWD (at most 64 pixels)
+constexpr int FC_BX = 16;         // inputs per workgroup of K_FC_BWD_X
 
 // A tensor that lives in a ring of `depth` slots.  At tick t the slot in use
 // is (t - lag) mod depth: lag 0 = the slot of the sample handled now, lag D =
@@ -49,7 +52,7 @@ enum StepKind : int32_t {
   // A dense layer on one sample is a matrix-vector product (networks tiled for throughput, input length a multiple
   // of 4): nothing for the matrix cores, a stream of the weight matrix.
   K_FC_FWD = 18,     // y = W x + b: a wavefront per output, four outputs per workgroup
-  K_FC_BWD_X = 19,   // dx = W^T dy: 64 inputs per workgroup, the outputs dealt out to 16 groups of 16 lanes
+  K_FC_BWD_X = 19,   // dx = W^T dy: FC_BX inputs per workgroup, the outputs dealt out to groups of lanes
   K_FC_BWD_W = 20    // gW = dy x^T: 4096 consecutive weights per workgroup
 };
 
@@ -89,6 +92,8 @@ struct GemmCfg {
   int32_t sw, shw;         // channel's map, whose rows are sw floats and whose channels are shw floats apart
   int32_t ck, cpad, sh;    // dense form of a k x k layer (ck = k, its padding, rows of the source map): the reduction or the
                            // columns run over (channel, tap), see pb_mm.h
+  int32_t dc;              // 1: 3x3 layer with its weights straight from memory (pb_conv.h): wave tile mi x ni, CC channels per chunk,
+                           // sw vectors per patch row, channel planes of the patch shw floats apart; 2: 1x1 layer on a small map
   int32_t a_req;           // requests per thread that the A block of a full chunk takes (the kernel built for latency keeps
                            // nine of them in flight when there are more than six, six otherwise)
 };
@@ -96,6 +101,8 @@ struct GemmCfg {
 // Dense matrix-product form of a 1x1 layer (GemmCfg::mm)
 constexpr int MM_QC = 32;            // reduction entries per chunk
 constexpr int MM_LDK = MM_QC + 4;    // row stride of an operand stored [row][reduction]: 4 * odd, 16 rows on distinct banks
+
+constexpr int DC_VU = 6;             // direct 3x3 form: 16-byte requests per thread and chunk of the patch
 
 // LDS floats of one chunk (both operands); the step needs twice that
 __host__ __device__ constexpr int mm_chunk_floats(int mode, int MT, int NT) {
@@ -124,8 +131,12 @@ enum StepFlags : int32_t {
   F_BF16_OUT = 16384, // the step's output crosses a stage boundary in bf16 mode: round it to bf16 (nearest even)
   F_LWP_W = 32768,    // update: weight-difference form of the prediction, w_hat = w' + T (w' - w); flrT then holds T
   F_NT = 65536,       // K_UPDATE, in a kernel built for non-temporal output stores: this step uses them too
-  F_WGRAD = 131072    // K_UPDATE of a 3x3 layer on a 2x2 or 4x4 map: the weight gradient is not read from memory but
+  F_WGRAD = 131072,   // K_UPDATE of a 3x3 layer on a 2x2 or 4x4 map: the weight gradient is not read from memory but
                       // computed inside the step from the layer's saved input (x) and output gradient (dy)
+  F_UPD_W = 262144,   // K_GEMM backward weights: the tile's gradient stays in registers and the step updates the weights itself
+                      // (w, v in place, what), a phase after the step that reads them for the data gradient
+  F_WHAT_PERM = 524288 // direct 3x3 form: the predicted weights are stored as the forward pass loads them,
+                      // [row / 16][channel / 4][channel % 4][row % 16][tap]
 };
 
 struct StepDesc {
@@ -156,7 +167,7 @@ struct StepDesc {
   int32_t sig_idx, nwait;
   int32_t wait_idx[3], wait_n[3];
   int32_t grain;            // > 0: streaming form of an elementwise step, floats per workgroup (K_COPY, K_GNB_APPLY);
-                            // K_GNB_REDUCE: 1 = one wavefront per channel
+                            // K_GNB_REDUCE, K_GAP_FWD: 1 = one wavefront per channel
   GemmCfg g;     // main operand set of a K_GEMM step
   GemmCfg gp;    // projection of the skip tensor accumulated into the same tile (forward only)
   TRef x;        // op input (forward) / saved input (backward)

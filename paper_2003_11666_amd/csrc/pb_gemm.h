@@ -749,13 +749,15 @@ __device__ __forceinline__ void step_gemm_t(const LDesc& d, int tile_, int t, lf
 
 }  // namespace pb
 #include "pb_mm.h"
+#include "pb_conv.h"
 namespace pb {
 
 template <bool NTK>
-__device__ __forceinline__ void step_gemm(const LDesc& d, int tile, int t, lfloat* smem) {
+__device__ __forceinline__ void step_gemm(const LDesc& d, int tile, int t, lfloat* smem, bool live) {
   // the number of column subtiles per wave (1, 2 or 4) is a compile-time
   // constant so that the accumulators stay in fixed registers
-  if (!NTK && UNI(d.g.mm)) { step_mm(d, tile, t, smem); return; }   // (planned only for networks tiled for throughput)
+  if (!NTK && UNI(d.g.mm)) { step_mm(d, tile, t, smem, live); return; }   // (planned only for networks tiled for throughput)
+  if (!NTK && UNI(d.g.dc)) { step_dc(d, tile, t, smem, live); return; }
   const int gm = UNI(d.g.gm), ni = UNI(d.g.ni);
   if (gm == 1) {
     if (ni == 1) step_gemm_t<1, 1, NTK, (NTK ? 9 : 6)>(d, tile, t, smem);

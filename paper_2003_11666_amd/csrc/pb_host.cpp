@@ -342,7 +342,8 @@ void plan_arena(const std::vector<Stage>& st, bool stash, int loss_cap, Layout& 
   L.sb.assign(S, StageBufs());
   if (!stash && update_size == 1 && use_aring)
     for (int s = 0; s < S; ++s)
-      if (fusew_shape(st[s])) L.sb[s].w2 = pl.alloc(st[s].padded);
+      // (not where the GroupNorm backward updates the scale and shift in place: the read-back takes a stage from one copy)
+      if (fusew_shape(st[s]) && !st[s].pre_gn) L.sb[s].w2 = pl.alloc(st[s].padded);
   L.what.assign(S, 0);
   // Weight stashing (the backward pass uses the forward's predicted weights, Eq. sgdpb_weight_stash):
   // the version the forward pass of a sample read has to survive until its backward pass, De + 2 slots.
@@ -423,6 +424,7 @@ struct pb_ctx {
   MlpPlan mlp;                   // on: ticks run in the kernel that keeps a perceptron's parameters in registers
   bool mlp_messages = false;     // the tick before ran there: gradients between stages lie in its messages
   bool waits() const { return fuse_from >= 0 || mlp.on; }   // launches hold workgroups that wait for each other
+  std::vector<char> perm_what;   // per stage: the layer's predicted weights are stored in the lane order of its forward tiles
   std::vector<char> pp_active;   // per stage: the update alternates between two copies of the master parameters
   int fuse_from = -1;          // >= 0: the phases from this one on share one launch, dependencies through completion
                                // counters (0: one launch per tick)
@@ -681,6 +683,20 @@ bool fit_gemm(GemmCfg& g, int C, int H, int W, int K, int OH, int OW, int k, int
 // MFMA loop, whose cost per MFMA falls with the number of column subtiles a
 // wave keeps (one A fetch and one offset fetch per k-step whatever their number).
 double est_tile_us(const GemmCfg& g, int k) {
+  if (g.dc == 2)   // 1x1 layer on a small map: the weights' way from memory, or the MFMAs
+    return 4.0 + std::max(2.2 * (g.Q / 16 / g.wk) * 4.0 * g.mi * g.ni * 32.0 / 2400.0, g.MT * (double)g.Q * 4.0 / 25e3);
+  if (g.dc) {
+    // direct 3x3 form: MFMAs of the busiest wave with two workgroups sharing the matrix pipes; per chunk a barrier and the
+    // stores of the patch; never less than the weights' way from the L2
+    double mf, a_us = 0;
+    if (g.gm == 3) {
+      mf = cdiv(cdiv(g.rows_c * g.pw, 16), g.wk) * 36.0 * g.mi;
+    } else {
+      mf = g.CC / 4 / g.wk * 9.0 * g.mi * g.ni;
+      a_us = g.MT * g.CC * 36.0 / 50e3;
+    }
+    return 4.0 + g.n_chunks * (0.8 + std::max(2.2 * mf * 32.0 / 2400.0, a_us));
+  }
   if (g.mm) {
     // dense form: per chunk of 32 reduction entries 8 mi ni MFMAs per wave, two workgroups sharing the matrix pipes,
     // and never less than the round trip of the next chunk's requests
@@ -763,6 +779,131 @@ bool make_mm(const pb_ctx* c, int mode, int C, int H, int W, int K, int OH, int 
   g.tiles = g.parts * g.tpp;
   *out = g;
   return true;
+}
+
+// Direct 3x3 form (pb_conv.h) of a layer with padding 1 and stride 1 or 2 in a network tiled for throughput.  Tiles are
+// wm x wn x wk waves (wk: split of the reduction) of mi x ni subtiles; of the arrangements whose estimated tile time
+// stays within the budget the one with the least total work, else the shortest (as for the patch-based tiles).
+//   forward           M = cout, N = output pixels, reduction over cin
+//   backward data     M = cin,  N = input pixels (stride 2: the gradient's pixels), reduction over cout
+//   backward weights  M = cout, N = 9 cin (a wave: 16 channels), reduction over output rows padded to a multiple of 4 pixels
+// One arrangement (the reduction not split over workgroups); false if the shape rules or LDS do not allow it.
+bool fit_dc(const pb_ctx* c, int mode, int C, int H, int W, int K, int OH, int OW, int k, int stride, int pad, int mi, int ni,
+            int wm, int wn, GemmCfg* out) {
+  if (g_tile_budget_us <= 0 || c->kernel_set != 0 || (c->tune.dense_1x1 != 0 && c->tune.dense_1x1 != 1)) return false;
+  if (k != 3 || pad != 1 || (stride != 1 && stride != 2) || OH != (H - 1) / stride + 1 || OW != (W - 1) / stride + 1) return false;
+  const int M = mode == 2 ? C : K, R = mode == 2 ? K : C;
+  if (M % 16 || R % 4 || (mode == 3 && C % 16)) return false;
+  if ((int64_t)K * C * 9 >= ((int64_t)1 << 30) || (int64_t)std::max(C, K) * std::max(H * W, OH * OW) >= ((int64_t)1 << 30)) return false;
+  if ((int64_t)H * W >= (1 << 20)) return false;     // (index divisions in the kernel are exact below 2^21)
+  const bool s2 = mode == 2 && stride == 2;
+  const int SW = mode == 2 ? OW : W;                 // source of the patch
+  const int PW = (mode == 1 || s2) ? OW : W, PH = (mode == 1 || s2) ? OH : H;
+  GemmCfg g;
+  memset(&g, 0, sizeof g);
+  g.gm = mode; g.dc = 1; g.M = M; g.Q = mode == 3 ? OH * OW : R * 9; g.ps = stride; g.nsub = 1;
+  g.mi = mi; g.ni = ni; g.wm = wm; g.wn = wn; g.wk = 4 / (wm * wn);
+  g.MT = 16 * mi * wm;
+  if (M % g.MT || (s2 && mi == 4)) return false;     // (stride 2: four accumulator sets)
+  g.sw = cdiv(SW, 4); g.Wp = 4 * g.sw + 8;
+  if (mode != 3) {
+    g.N = PH * PW; g.NT = 16 * ni * wn; g.tiles_n = cdiv(g.N, g.NT);
+    if (wn > 1 && g.NT / 2 >= g.N) return false;
+    const int rows = tile_rows(g.NT, PW, PH), unit = 4 * (4 / mi) * g.wk;
+    g.PR = s2 ? rows + 1 : mode == 2 ? rows + 2 : (rows - 1) * stride + 3;
+    g.shw = g.PR * g.Wp;
+    while (g.shw % 32 != 16) g.shw += 4;             // the planes of two lane groups on different banks
+    if (R % unit) return false;
+    for (int cc = unit; cc <= R && cc <= 64; cc += unit)
+      if (R % cc == 0 && cc * g.PR * g.sw <= DC_VU * BLK && 2 * cc * g.shw <= LDS_FLOATS) g.CC = cc;
+    if (!g.CC) return false;
+    g.n_chunks = R / g.CC;
+  } else {
+    const int CT = 16 * wn;
+    if (C % CT) return false;
+    g.N = 9 * C; g.NT = 9 * CT; g.tiles_n = C / CT; g.CC = CT;
+    g.pw = (OW + 3) / 4 * 4;
+    for (int r = 1; r <= OH; ++r) {
+      const int pr = (r - 1) * stride + 3;
+      if (CT * pr * g.sw <= DC_VU * BLK && 2 * CT * pr * g.Wp + 64 <= LDS_FLOATS) g.rows_c = r;
+    }
+    if (!g.rows_c) return false;
+    g.rows_c = cdiv(OH, cdiv(OH, g.rows_c));         // even out the chunks
+    g.PR = (g.rows_c - 1) * stride + 3;
+    g.shw = g.PR * g.Wp;
+    g.n_chunks = cdiv(OH, g.rows_c);
+  }
+  g.QC = g.QCpad = mode == 3 ? g.rows_c * g.pw : 9 * g.CC;
+  g.tpp = (M / g.MT) * g.tiles_n;
+  g.parts = 1; g.cpp = g.n_chunks; g.tiles = g.tpp;
+  *out = g;
+  return true;
+}
+
+bool make_dc(const pb_ctx* c, int mode, int C, int H, int W, int K, int OH, int OW, int k, int stride, int pad, int max_parts,
+             GemmCfg* out) {
+  bool have = false, best_within = false;
+  double best_work = 0, best_tile = 0;
+  static const int shapes[4][2] = {{4, 2}, {2, 2}, {2, 1}, {1, 1}}, wshapes[2][2] = {{2, 1}, {1, 1}};
+  for (int si = 0; si < (mode == 3 ? 2 : 4); ++si)
+    for (int wm = 1; wm <= 4; wm *= 2)
+      for (int wn = 1; wm * wn <= 4; wn *= 2) {
+        const int* sh = (mode == 3 ? wshapes : shapes)[si];
+        GemmCfg g;
+        if (!fit_dc(c, mode, C, H, W, K, OH, OW, k, stride, pad, sh[0], sh[1], wm, wn, &g)) continue;
+        double tt = est_tile_us(g, 3);
+        for (int want = 2; want <= max_parts && want <= g.n_chunks && tt > (mode == 3 ? 20.0 : 12.0); want *= 2) {
+          g.cpp = cdiv(g.n_chunks, want);
+          g.parts = cdiv(g.n_chunks, g.cpp);
+          GemmCfg one = g;
+          one.n_chunks = g.cpp;
+          tt = est_tile_us(one, 3);
+        }
+        g.tiles = g.parts * g.tpp;
+        const double work = tt * g.tiles;
+        // (a small tile costs little here, a long one the end of its phase: never more than 45 us)
+        const bool within = tt <= std::min(45.0, g_tile_budget_us * g_budget_scale[mode]);
+        const bool better = !have ? true : within != best_within ? within : within ? (work < best_work || (work == best_work && tt < best_tile)) : tt < best_tile;
+        if (better) { have = true; best_within = within; best_work = work; best_tile = tt; *out = g; }
+      }
+  return have;
+}
+
+// Direct form of a 1x1 layer (stride 1, or 2 on even maps) whose product has fewer than 64 columns -- where the dense
+// form's tiles of 64 columns are mostly empty or do not fit at all: forward (mode 1) and backward data (mode 2).
+bool fit_d1(const pb_ctx* c, int mode, int C, int H, int W, int K, int OH, int OW, int k, int stride, int pad, int mi, int wm, GemmCfg* out) {
+  if (g_tile_budget_us <= 0 || c->kernel_set != 0 || (c->tune.dense_1x1 != 0 && c->tune.dense_1x1 != 1)) return false;
+  if (k != 1 || pad != 0 || OH * OW >= 64 || !((stride == 1 && H == OH && W == OW) || (stride == 2 && H == 2 * OH && W == 2 * OW))) return false;
+  if ((int64_t)K * C >= ((int64_t)1 << 30)) return false;
+  GemmCfg g;
+  memset(&g, 0, sizeof g);
+  g.gm = mode; g.dc = 2; g.M = mode == 1 ? K : C; g.N = OH * OW; g.Q = mode == 1 ? C : K; g.ps = stride; g.nsub = 1;
+  g.mi = mi; g.ni = g.N > 16 ? 4 : 1;
+  g.wm = wm; g.wn = 1; g.wk = 4 / wm;
+  g.MT = 16 * mi * wm; g.NT = 16 * g.ni;
+  const int ub = mi * g.ni == 1 ? 4 : mi * g.ni == 4 ? 2 : 1;
+  if (g.M % g.MT || g.Q % (16 * ub * g.wk)) return false;
+  g.tiles_n = cdiv(g.N, g.NT);
+  g.tpp = g.tiles = g.M / g.MT * g.tiles_n;
+  g.QC = g.QCpad = g.Q; g.n_chunks = g.cpp = g.parts = 1;
+  *out = g;
+  return true;
+}
+
+bool make_d1(const pb_ctx* c, int mode, int C, int H, int W, int K, int OH, int OW, int k, int stride, int pad, GemmCfg* out) {
+  bool have = false, best_within = false;
+  double best_work = 0, best_tile = 0;
+  for (int mi = 4; mi >= 1; mi -= 3)
+    for (int wm = 1; wm <= 4; wm *= 2) {
+      GemmCfg g;
+      if (!fit_d1(c, mode, C, H, W, K, OH, OW, k, stride, pad, mi, wm, &g)) continue;
+      const double tt = est_tile_us(g, 1), work = tt * g.tiles;
+      const bool within = tt <= std::min(20.0, g_tile_budget_us * g_budget_scale[mode]);
+      if (!have || (within != best_within ? within : within ? work < best_work : tt < best_tile)) {
+        have = true; best_within = within; best_work = work; best_tile = tt; *out = g;
+      }
+    }
+  return have;
 }
 
 // Choose the wave arrangement and the chunking of one operand set.  `like` !=
@@ -979,7 +1120,8 @@ void gn_stats_wave(StepDesc& d) {
 // One wavefront per channel for a K_GNB_REDUCE step over a small map.
 void wave_reduce(StepDesc& d) {
   // (a gradient routed back through a max-pool costs a window search per element: small maps only)
-  if (g_tile_budget_us <= 0 || !(d.flags & (F_DU_BUF | F_DU_POOL)) || d.H * d.W > ((d.flags & F_DU_POOL) ? 64 : 1024)) return;
+  // (larger maps: a workgroup per channel with 16-byte loads; a wavefront's rounds over a 32x32 map took 56 us)
+  if (g_tile_budget_us <= 0 || d.H * d.W > ((d.flags & F_DU_POOL) ? 64 : GNB_WAVE_HW)) return;
   d.grain = 1;
   d.ntiles = cdiv(d.C, GNB_WAVE_CH * (BLK / 64));
 }
@@ -1085,14 +1227,17 @@ void compile_steps_once(pb_ctx* c, std::vector<std::pair<int, StepDesc>>& out) {
   // over the two GEMM phases of a tick.
   {
     // (1x1 layers run as dense matrix products at about twice the rate of the patch-based tiles: counted half)
-    double macs = 0;
+    // (so do 3x3 layers in the direct form, which counts in the budget only: what is tiled for throughput stays the same)
+    double macs = 0, direct = 0;
     const bool dense = c->kernel_set == 0 && c->tune.dense_1x1 >= 0;
     for (const Stage& a : c->st) {
       macs += (double)a.K * a.OH * a.OW * a.C * a.k * a.k * (dense && a.k == 1 && a.K % 64 == 0 && a.C % 64 == 0 ? 0.5 : 1.0);
+      if (dense && c->tune.dense_1x1 != 2 && a.is_conv && a.k == 3 && a.pad == 1 && a.stride <= 2 && a.K % 16 == 0 && a.C % 16 == 0)
+        direct += (double)a.K * a.OH * a.OW * a.C * 9;
       if (a.proj) macs += (double)a.K * a.OH * a.OW * a.sC * (dense && a.K % 64 == 0 && a.sC % 64 == 0 ? 0.5 : 1.0);
     }
     const double tick_us = 6.0 * macs / 50e6;
-    g_tile_budget_us = tick_us >= 10.0 ? std::max(16.0, 0.65 * tick_us) : 0.0;
+    g_tile_budget_us = tick_us >= 10.0 ? std::max(16.0, 0.65 * (tick_us - 3.0 * direct / 50e6)) : 0.0;
     if (c->tune.tile_budget_us > 0.f) g_tile_budget_us = c->tune.tile_budget_us;
     else if (c->tune.tile_budget_us < 0.f) g_tile_budget_us = 0.0;
     // A compute unit has 160 KB of LDS and holds two workgroups: a tile may use up to 76 KB.  Planning with all of it
@@ -1105,6 +1250,8 @@ void compile_steps_once(pb_ctx* c, std::vector<std::pair<int, StepDesc>>& out) {
   std::vector<int> bwd0(S, 0);   // per stage: phase its backward chain starts in
   // stages whose weight gradient is computed inside the update step (see F_WGRAD): the phase the
   // gradient's operands are complete in, and the operands
+  std::vector<std::vector<std::pair<int64_t, int64_t>>> upd(S);   // per stage: parameter ranges that other steps than K_UPDATE update
+  c->perm_what.assign(S, 0);
   struct FusedW { int phase = -1; TRef x, dy; int64_t pp = 0; };
   std::vector<FusedW> fusedw(S);
   c->pp_active.assign(S, 0);
@@ -1135,6 +1282,19 @@ void compile_steps_once(pb_ctx* c, std::vector<std::pair<int, StepDesc>>& out) {
       d.pmask = mask; d.pdepth = wdepth; d.plag = a.De; d.pstride = (int)a.padded;
     };
     float* gr = c->f(b.gparts >= 0 ? b.gparts : L.g + a.off);
+    // Weight gradients whose tiles hold whole sums (reduction not split over workgroups) update their weights themselves:
+    // they run a phase after the data gradient, which reads the weights they overwrite.  (Not with a GroupNorm behind the
+    // layer: the phase after its backward GEMMs holds nothing else, and VGG-11 took 104 us instead of 94.)
+    auto fuse_update = [&](StepDesc& d, int64_t o, int64_t n) {
+      if (g_tile_budget_us <= 0 || c->N != 1 || a.post_gn || d.kind != K_GEMM || !(d.g.mm || d.g.dc) || d.g.parts != 1 || n % 4 || o % 4) return false;
+      d.flags |= F_UPD_W | F_ALWAYS;
+      set_update_coeffs(c, a, &d);
+      d.w = wb + o; d.v = c->f(L.v + a.off + o); d.what = c->f(L.what[s] + o);
+      d.pmask = PF_WHAT; d.pdepth = wdepth; d.plag = -1; d.pstride = (int)a.padded;
+      upd[s].push_back({o, o + n});
+      return true;
+    };
+    bool perm_what = false;   // the layer's predicted weights are stored in the order its forward tiles load them
     const bool seq = c->sequential;
     const int t_f = seq ? 0 : s, t_b = seq ? 0 : 2 * (S - 1) - s;
     const int ML = seq ? 0 : -1;                       // lag of the mailbox slot a producer writes (next tick's, or this tick's)
@@ -1211,6 +1371,7 @@ void compile_steps_once(pb_ctx* c, std::vector<std::pair<int, StepDesc>>& out) {
       d.x = x_f; d.st = ring(c, b.prest, D + 1, b.st_stride, 0);
       d.y = ring(c, b.pooled, D + 1, a.C, 0);
       d.ntiles = a.Cin;
+      if (g_tile_budget_us > 0 && a.Hin * a.Win <= 64) { d.grain = 1; d.ntiles = cdiv(a.Cin, GAP_WAVE_CH * (BLK / 64)); }
       out.push_back({ph++, d});
     }
     {
@@ -1256,8 +1417,9 @@ void compile_steps_once(pb_ctx* c, std::vector<std::pair<int, StepDesc>>& out) {
             e.y = ring(c, b.projy, 1, a.out_elems(), 0);
             e.ntiles = cdiv((int64_t)a.K * a.OH * a.OW, BLK);
             GemmCfg ge, gd;
-            const bool dense = arena_aligned16(c, e.w) && ref_vec4(c, e.x) &&
-                               make_mm(c, 1, e.C, e.H, e.W, e.K, e.OH, e.OW, 1, e.stride, 0, 1, &gd);
+            const bool dense = make_d1(c, 1, e.C, e.H, e.W, e.K, e.OH, e.OW, 1, e.stride, 0, &gd) ||
+                               (arena_aligned16(c, e.w) && ref_vec4(c, e.x) &&
+                                make_mm(c, 1, e.C, e.H, e.W, e.K, e.OH, e.OW, 1, e.stride, 0, 1, &gd));
             if (dense || make_gemm(1, e.C, e.H, e.W, e.K, e.OH, e.OW, 1, e.stride, 0, nullptr, &ge, true)) {
               if (dense) ge = gd;
               e.kind = K_GEMM; e.g = ge; e.ntiles = ge.tiles;
@@ -1298,6 +1460,20 @@ void compile_steps_once(pb_ctx* c, std::vector<std::pair<int, StepDesc>>& out) {
                             zsplit ? FWD_PARTS : 1);
         if (ok && (d.flags & F_PROJ)) ok = make_gemm(1, d.sC, d.sH, d.sW, d.K, d.OH, d.OW, 1, d.sstride, 0, &g, &gp, true);
         GemmCfg gd;
+        if (plain_src && !(d.flags & F_PROJ) &&
+            make_dc(c, 1, a.C, a.H, a.W, a.K, a.OH, a.OW, a.k, a.stride, a.pad, zsplit ? FWD_PARTS : 1, &gd)) {
+          d.kind = K_GEMM; d.g = gd; d.gp = gp; d.ntiles = gd.tiles;
+          if (gd.parts > 1) { d.gw = c->f(b.zparts); d.gparts = gd.parts; d.gpstride = (int)a.z_elems(); fwd_parts = gd.parts; }
+          // (with weight stashing the backward pass reads the predicted weights too, in their natural order)
+          GemmCfg gw;
+          perm_what = !c->stash && c->N == 1 && !a.post_gn && plain_src && a.C % 16 == 0 && !fusew_shape(a) &&
+                      make_dc(c, 3, a.C, a.H, a.W, a.K, a.OH, a.OW, a.k, a.stride, a.pad, b.gparts >= 0 ? GRAD_PARTS : 1, &gw) && gw.parts == 1;
+          if (perm_what) { d.flags |= F_WHAT_PERM; c->perm_what[s] = 1; }
+        } else
+        if (plain_src && !(d.flags & F_PROJ) && make_d1(c, 1, a.C, a.H, a.W, a.K, a.OH, a.OW, a.k, a.stride, a.pad, &gd)) {
+          d.H = a.H; d.W = a.W; d.OH = a.OH; d.OW = a.OW;
+          d.kind = K_GEMM; d.g = gd; d.gp = gp; d.ntiles = gd.tiles;
+        } else
         if (ok && plain_src && !(d.flags & F_PROJ) && arena_aligned16(c, d.w) &&
             ref_vec4(c, d.x) && make_mm(c, 1, a.C, a.H, a.W, a.K, a.OH, a.OW, a.k, a.stride, a.pad, 1, &gd)) {
           d.kind = K_GEMM; d.g = gd; d.gp = gp; d.ntiles = gd.tiles;
@@ -1427,14 +1603,18 @@ void compile_steps_once(pb_ctx* c, std::vector<std::pair<int, StepDesc>>& out) {
           out.push_back({pb, e});
         }
         GemmCfg gd;
-        const bool dense = !(d.flags & (F_PRE_AFFINE | F_PRE_RELU)) && ref_vec4(c, d.x) && ref_vec4(c, d.dy) &&
-                           make_mm(c, 3, a.C, a.H, a.W, a.K, a.OH, a.OW, a.k, a.stride, a.pad, b.gparts >= 0 ? GRAD_PARTS : 1, &gd);
+        const bool dense = (!(d.flags & (F_PRE_AFFINE | F_PRE_RELU)) &&
+                            make_dc(c, 3, a.C, a.H, a.W, a.K, a.OH, a.OW, a.k, a.stride, a.pad, b.gparts >= 0 ? GRAD_PARTS : 1, &gd)) ||
+                           (!(d.flags & (F_PRE_AFFINE | F_PRE_RELU)) && ref_vec4(c, d.x) && ref_vec4(c, d.dy) &&
+                           make_mm(c, 3, a.C, a.H, a.W, a.K, a.OH, a.OW, a.k, a.stride, a.pad, b.gparts >= 0 ? GRAD_PARTS : 1, &gd));
         if (dense) g = gd;
         d.kind = K_GEMM; d.g = g; d.ntiles = g.tiles; d.flags &= ~F_BIAS;
         d.gparts = g.parts; d.gpstride = (int)a.padded;
         if (!dense) gemm_tables(c, g, d.C, d.H, d.W, d.K, d.OH, d.OW, d.k, d.stride, &d.tq, &d.tn);
       }
-      if (!fuse_w) out.push_back({pb, d});
+      const bool upd_w = !fuse_w && fuse_update(d, a.o_w, a.n_w);
+      if (upd_w && perm_what) d.flags |= F_WHAT_PERM;
+      if (!fuse_w) out.push_back({upd_w ? pb + 1 : pb, d});
     }
     if (s > 0) {   // data gradient of the main layer
       StepDesc d = blank(K_CONV_BWD_X, s, t_b);
@@ -1462,7 +1642,7 @@ void compile_steps_once(pb_ctx* c, std::vector<std::pair<int, StepDesc>>& out) {
                            ref_vec4(c, d.dy) && ref_vec4(c, d.dx);
       if (fc_layer(c, d, d.w) && !(d.flags & (F_MASK_X | F_ADD_SKG)) && ref_vec4(c, d.dx)) {
         d.kind = K_FC_BWD_X;
-        d.ntiles = cdiv(d.C, 64);
+        d.ntiles = cdiv(d.C, FC_BX);
       } else
       if (dot_bwd) {
         // 64 input channels per workgroup; the output channels in as many parts as the gradient's consumer can
@@ -1476,8 +1656,12 @@ void compile_steps_once(pb_ctx* c, std::vector<std::pair<int, StepDesc>>& out) {
       if (c->kernel_set == 0 && make_gemm(2, d.C, d.H, d.W, d.K, d.OH, d.OW, d.k, d.stride, d.pad, nullptr, &g, true, 16, flat,
                                           dxsplit ? FWD_PARTS : 1)) {
         GemmCfg gd;
-        const bool dense = arena_aligned16(c, d.w) && ref_vec4(c, d.dy) &&
-                           make_mm(c, 2, a.C, a.H, a.W, a.K, a.OH, a.OW, a.k, a.stride, a.pad, 1, &gd);
+        const bool dense = ((a.stride == 1 || !(d.flags & (F_MASK_X | F_ADD_SKG))) &&
+                            make_dc(c, 2, a.C, a.H, a.W, a.K, a.OH, a.OW, a.k, a.stride, a.pad, dxsplit ? FWD_PARTS : 1, &gd)) ||
+                           ((a.stride == 1 || (!(d.flags & (F_MASK_X | F_ADD_SKG)) && ref_vec4(c, d.dx))) &&
+                            make_d1(c, 2, a.C, a.H, a.W, a.K, a.OH, a.OW, a.k, a.stride, a.pad, &gd)) ||
+                           (arena_aligned16(c, d.w) && ref_vec4(c, d.dy) &&
+                            make_mm(c, 2, a.C, a.H, a.W, a.K, a.OH, a.OW, a.k, a.stride, a.pad, 1, &gd));
         if (dense) g = gd;
         d.kind = K_GEMM; d.g = g; d.ntiles = g.tiles;
         if (g.parts > 1) { d.gw = c->f(L.sb[s - 1].dxparts); d.gparts = g.parts; d.gpstride = (int)a.in_elems(); }
@@ -1508,7 +1692,8 @@ void compile_steps_once(pb_ctx* c, std::vector<std::pair<int, StepDesc>>& out) {
           d.gparts = g.parts; d.gpstride = (int)a.padded;
           if (!dense) gemm_tables(c, g, d.C, d.H, d.W, d.K, d.OH, d.OW, 1, d.stride, &d.tq, &d.tn);
         }
-        out.push_back({pb, d});
+        const bool upd_w = fuse_update(d, a.o_wp, a.n_wp);
+        out.push_back({upd_w ? pb + 1 : pb, d});
         StepDesc e = blank(K_CONV_BWD_X, s, t_b);
         e.C = a.sC; e.H = a.sH; e.W = a.sW; e.K = a.K; e.OH = a.OH; e.OW = a.OW;
         e.k = 1; e.stride = a.sstride; e.pad = 0;
@@ -1521,8 +1706,9 @@ void compile_steps_once(pb_ctx* c, std::vector<std::pair<int, StepDesc>>& out) {
         GemmCfg g2;
         if (c->kernel_set == 0 && make_gemm(2, e.C, e.H, e.W, e.K, e.OH, e.OW, 1, e.stride, 0, nullptr, &g2, true)) {
           GemmCfg gd;
-          const bool dense = arena_aligned16(c, e.w) && ref_vec4(c, e.dy) && ref_vec4(c, e.dx) && ta.in_elems() % 2 == 0 &&
-                             make_mm(c, 2, e.C, e.H, e.W, e.K, e.OH, e.OW, 1, e.stride, 0, 1, &gd);
+          const bool dense = (ref_vec4(c, e.dx) && make_d1(c, 2, e.C, e.H, e.W, e.K, e.OH, e.OW, 1, e.stride, 0, &gd)) ||
+                             (arena_aligned16(c, e.w) && ref_vec4(c, e.dy) && ref_vec4(c, e.dx) && ta.in_elems() % 2 == 0 &&
+                              make_mm(c, 2, e.C, e.H, e.W, e.K, e.OH, e.OW, 1, e.stride, 0, 1, &gd));
           if (dense) g2 = gd;
           e.kind = K_GEMM; e.g = g2; e.ntiles = g2.tiles;
           if (!dense) gemm_tables(c, g2, e.C, e.H, e.W, e.K, e.OH, e.OW, 1, e.stride, &e.tq, &e.tn);
@@ -1648,6 +1834,7 @@ void compile_steps_once(pb_ctx* c, std::vector<std::pair<int, StepDesc>>& out) {
       const StepDesc& e = pr.second;
       if (e.stage != s) continue;
       if (e.kind == K_GN_BWD && (e.flags & F_UPD_GN)) { gn_fused = true; continue; }
+      if (e.kind == K_GEMM && (e.flags & F_UPD_W)) continue;
       const bool writes_grad = (e.kind == K_GEMM && e.g.gm == 3) || e.kind == K_CONV_BWD_W || e.kind == K_BIAS_GRAD ||
                                e.kind == K_GNB_REDUCE || e.kind == K_GN_BWD || e.kind == K_HEAD;
       if (writes_grad) last_grad_phase = std::max(last_grad_phase, pr.first);
@@ -1677,8 +1864,23 @@ void compile_steps_once(pb_ctx* c, std::vector<std::pair<int, StepDesc>>& out) {
       d.what0 = c->f(L.what[s]);
     }
     d.n = (int)(gn_fused ? a.o_gamma : a.padded);      // o_gamma is a multiple of 4
-    d.ntiles = (int)cdiv(d.n, UPD_TILE);
-    if (d.n > 0) out.push_back({last_grad_phase + 1, d});
+    // what other steps update is left out: a step per remaining range
+    const int64_t end = d.n, real = gn_fused ? a.o_gamma : a.n_gn ? a.o_beta + a.n_gn : a.n_head;
+    std::sort(upd[s].begin(), upd[s].end());
+    upd[s].push_back({end, end});
+    int64_t lo = 0;
+    for (auto& r : upd[s]) {
+      if (r.first > lo && lo < real) {
+        StepDesc e = d;
+        e.n = (int)(r.first - lo);
+        if (lo > 0) e.flags &= ~F_WGRAD;
+        e.w += lo; e.v += lo; e.gw += lo; e.wp += lo; e.b += lo; e.what += lo;
+        if (e.gacc) { e.gacc += lo; e.what0 += lo; }
+        e.ntiles = (int)cdiv(e.n, UPD_TILE);
+        out.push_back({last_grad_phase + 1, e});
+      }
+      lo = std::max(lo, r.second);
+    }
     c->pp_active[s] = d.ppstride > 0;
   }
   // Networks tiled for latency run the kernel instantiation whose bulk outputs leave the L2
@@ -1691,7 +1893,7 @@ void compile_steps_once(pb_ctx* c, std::vector<std::pair<int, StepDesc>>& out) {
   // (forward and backward-data GEMMs split over their reduction, several column tiles per workgroup and
   // flattened 1x1 layers exist only in the other instantiation)
   for (auto& pr : out)
-    if (pr.second.kind == K_GEMM && ((pr.second.g.gm != 3 && pr.second.g.parts > 1) || pr.second.g.nsub > 1 || pr.second.g.win > 0 || pr.second.g.mm ||
+    if (pr.second.kind == K_GEMM && ((pr.second.g.gm != 3 && pr.second.g.parts > 1) || pr.second.g.nsub > 1 || pr.second.g.win > 0 || pr.second.g.mm || pr.second.g.dc ||
                                     pr.second.gp.nsub > 1 || pr.second.gp.win > 0)) c->nt_stores = false;
   for (auto& pr : out)
     if ((pr.second.kind == K_UPDATE && (pr.second.flags & F_WGRAD)) || pr.second.kind == K_DOT_FWD || pr.second.kind == K_DOT_BWD_X ||
@@ -1840,7 +2042,7 @@ int validate_steps(const pb_ctx* c, const std::vector<std::pair<int, StepDesc>>&
              ptr_ok(d.gamma, d.C) && ptr_ok(d.beta, d.C) && (!d.y.base || ref_ok(d.y, in));
         break;
       case K_GAP_FWD:
-        ok = ok && d.ntiles == d.C && ref_ok(d.x, in) && ref_ok(d.y, d.C) &&
+        ok = ok && d.ntiles == (d.grain == 1 ? cdiv(d.C, GAP_WAVE_CH * (BLK / 64)) : d.C) && (d.grain != 1 || d.H * d.W <= 64) && ref_ok(d.x, in) && ref_ok(d.y, d.C) &&
              (!(d.flags & F_PRE_AFFINE) || ref_ok(d.st, stn));
         break;
       case K_CONV_FWD:
@@ -1870,7 +2072,7 @@ int validate_steps(const pb_ctx* c, const std::vector<std::pair<int, StepDesc>>&
              ptr_ok(d.part, 3 * d.C) && ptr_ok(d.gamma, d.C);
         if (d.kind == K_GNB_REDUCE) {
           ok = ok && ptr_ok(d.ggamma, d.C) && ptr_ok(d.gbeta, d.C);
-          if (d.grain == 1) ok = ok && (d.flags & (F_DU_BUF | F_DU_POOL)) && d.ntiles == cdiv(d.C, GNB_WAVE_CH * (BLK / 64));
+          if (d.grain == 1) ok = ok && d.H * d.W <= GNB_WAVE_HW && d.ntiles == cdiv(d.C, GNB_WAVE_CH * (BLK / 64));
           else ok = ok && d.grain == 0 && d.ntiles == d.C;
           if (d.gparts > 1) {   // sums partial gradients: wave form with at most 64 values per channel, or the form that
                                 // stages a channel's pooled gradient in LDS
@@ -1961,8 +2163,8 @@ int validate_steps(const pb_ctx* c, const std::vector<std::pair<int, StepDesc>>&
              ref_ok(d.x, d.C) && ref_vec4(c, d.x) && ref_ok(d.y, d.K) && ptr_ok(d.w, (int64_t)d.K * d.C) && (!(d.flags & F_BIAS) || ptr_ok(d.b, d.K));
         break;
       case K_FC_BWD_X:
-        ok = ok && !c->nt_stores && fc_layer(c, d, d.w) && !(d.flags & ~(F_ALWAYS | F_BF16_OUT)) && d.ntiles == cdiv(d.C, 64) &&
-             (d.K + 3) / 4 * 4 + 16 * 64 <= LDS_FLOATS && ref_ok(d.dy, d.K) && ref_ok(d.dx, d.C) && ptr_ok(d.w, (int64_t)d.K * d.C);
+        ok = ok && !c->nt_stores && fc_layer(c, d, d.w) && !(d.flags & ~(F_ALWAYS | F_BF16_OUT)) && d.ntiles == cdiv(d.C, FC_BX) &&
+             (d.K + 3) / 4 * 4 + 64 * FC_BX <= LDS_FLOATS && ref_ok(d.dy, d.K) && ref_ok(d.dx, d.C) && ptr_ok(d.w, (int64_t)d.K * d.C);
         break;
       case K_FC_BWD_W:
         ok = ok && !c->nt_stores && fc_layer(c, d, d.gw) && !(d.flags & ~F_ALWAYS) && d.ntiles == cdiv((int64_t)d.K * d.C, 4096) &&
@@ -2060,7 +2262,26 @@ int validate_steps(const pb_ctx* c, const std::vector<std::pair<int, StepDesc>>&
           else o = o && ref_vec4(c, d.x) && ref_vec4(c, d.dy);
           return o;
         };
-        if (d.g.mm) {
+        if (d.g.dc == 2) {
+          GemmCfg want;
+          ok = ok && !c->nt_stores && d.ntiles == d.g.tiles && d.gp.gm == 0 && !(d.flags & (F_PROJ | F_PRE_AFFINE | F_PRE_RELU)) && d.g.gm != 3 &&
+               fit_d1(c, d.g.gm, d.C, d.H, d.W, d.K, d.OH, d.OW, d.k, d.stride, d.pad, d.g.mi, d.g.wm, &want) && memcmp(&want, &d.g, sizeof want) == 0;
+          if (d.g.gm == 2 && d.stride == 2) ok = ok && !(d.flags & (F_MASK_X | F_ADD_SKG)) && ref_vec4(c, d.dx) && d.W % 2 == 0;
+        } else if (d.g.dc) {
+          // exactly what the planner makes of the step's geometry; vectors at the end of a row of no multiple of 4 floats
+          // reach up to 3 floats past their tensor
+          GemmCfg want;
+          ok = ok && !c->nt_stores && d.ntiles == d.g.tiles && d.gp.gm == 0 && !(d.flags & (F_PROJ | F_PRE_AFFINE | F_PRE_RELU)) &&
+               fit_dc(c, d.g.gm, d.C, d.H, d.W, d.K, d.OH, d.OW, d.k, d.stride, d.pad, d.g.mi, d.g.ni, d.g.wm, d.g.wn, &want);
+          want.parts = d.g.parts; want.cpp = d.g.cpp; want.tiles = d.g.parts * want.tpp;
+          ok = ok && memcmp(&want, &d.g, sizeof want) == 0 && d.g.parts >= 1 && (int64_t)d.g.parts * d.g.cpp >= d.g.n_chunks &&
+               (int64_t)(d.g.parts - 1) * d.g.cpp < d.g.n_chunks;
+          if (d.flags & F_WHAT_PERM) ok = ok && c->perm_what[d.stage] && !c->stash && (d.g.gm == 1 || (d.g.gm == 3 && (d.flags & F_UPD_W))) && d.C % 4 == 0 && d.K % 16 == 0;
+          else if (d.g.gm == 1 || (d.flags & F_UPD_W)) ok = ok && (!c->perm_what[d.stage] || d.k != 3);
+          const TRef& pt = d.g.gm == 2 ? d.dy : d.x;
+          ok = ok && pt.base + (int64_t)pt.depth * pt.stride + 4 <= hi && (d.g.gm != 3 || d.dy.base + (int64_t)d.dy.depth * d.dy.stride + 4 <= hi);
+          if (d.g.gm == 2 && d.stride == 2) ok = ok && !(d.flags & (F_MASK_X | F_ADD_SKG)) && ref_vec4(c, d.dx);
+        } else if (d.g.mm) {
           ok = ok && d.ntiles == d.g.tiles && mm_ok(d.g) && d.gp.gm == 0;
         } else {
         ok = ok && (!d.g.avec || a_aligned(c, d, false)) && (!(d.flags & F_PROJ) || !d.gp.avec || a_aligned(c, d, true));
@@ -2098,6 +2319,9 @@ int validate_steps(const pb_ctx* c, const std::vector<std::pair<int, StepDesc>>&
           ok = ok && ref_ok(d.dy, outn) && ref_ok(d.dx, in) && ptr_ok(d.w, wn_) &&
                (!(d.flags & F_MASK_X) || ref_ok(d.x, in)) && (!(d.flags & F_ADD_SKG) || ref_ok(d.skg, in));
         } else {
+          if (d.flags & F_UPD_W)
+            ok = ok && (d.g.mm || d.g.dc) && d.g.parts == 1 && d.upd_n <= 1 && d.pmask == PF_WHAT && d.plag == -1 && (d.flags & F_ALWAYS) &&
+                 ptr_ok(d.w, wn_) && ptr_ok(d.v, wn_) && d.what && ptr_ok(d.what + (int64_t)(d.pdepth - 1) * d.pstride, wn_);
           ok = ok && ref_ok(d.x, in) && ref_ok(d.dy, outn) && ptr_ok(d.gw, wn_) &&
                (!(d.flags & F_PRE_AFFINE) || ref_ok(d.st, stn)) && !(d.flags & F_BIAS);
           // a split reduction writes partial gradients gpstride floats apart
@@ -2460,7 +2684,13 @@ int64_t pb_plan_summary(const pb_net_desc* net, char* buf, int64_t cap) {
     o += line;
     if (d.kind == K_GEMM) {
       const GemmCfg& g = d.g;
-      if (g.mm)
+      if (g.dc == 2)
+        snprintf(line, sizeof line, " | gm%d M%d N%d Q%d small waves %dx1x%d mi%d ni%d tile %dx%d est %.1f", g.gm, g.M, g.N, g.Q, g.wm, g.wk, g.mi, g.ni,
+                 g.MT, g.NT, est_tile_us(g, 1));
+      else if (g.dc)
+        snprintf(line, sizeof line, " | gm%d M%d N%d Q%d direct waves %dx%dx%d mi%d ni%d tile %dx%d chunks %d/%d CC%d PR%d Wp%d plane%d rows%d est %.1f", g.gm, g.M, g.N, g.Q,
+                 g.wm, g.wn, g.wk, g.mi, g.ni, g.MT, g.NT, g.n_chunks, g.parts, g.CC, g.PR, g.Wp, g.shw, g.rows_c, est_tile_us(g, 3));
+      else if (g.mm)
         snprintf(line, sizeof line, " | gm%d M%d N%d Q%d dense mi%d ni%d tile %dx%d chunks %d/%d QC%d lds %d", g.gm, g.M, g.N, g.Q, g.mi, g.ni,
                  g.MT, g.NT, g.n_chunks, g.parts, g.QC, 2 * mm_chunk_floats(g.gm, g.MT, g.NT));
       else
@@ -2688,8 +2918,19 @@ int init_common(pb_ctx** out, const pb_net_desc* net, const int32_t* delays, flo
   memset(&g0, 0, sizeof g0);
   g0.n_pool = 1;
   INIT_TRY(hipMemcpyAsync(c->f(c->L.w), w.data(), sizeof(float) * c->L.P, hipMemcpyHostToDevice, c->stream));
-  for (int s = 0; s < c->S; ++s)     // slot 0 of every stage's ring of predicted weights: v = 0, so w_hat = w
-    INIT_TRY(hipMemcpyAsync(c->f(c->L.what[s]), w.data() + st[s].off, sizeof(float) * st[s].padded, hipMemcpyHostToDevice, c->stream));
+  std::vector<std::vector<float>> perm(c->S);
+  for (int s = 0; s < c->S; ++s) {   // slot 0 of every stage's ring of predicted weights: v = 0, so w_hat = w
+    const float* src = w.data() + st[s].off;
+    if (c->perm_what[s]) {
+      const int C = st[s].C, K = st[s].K;
+      perm[s].assign(src, src + st[s].padded);
+      for (int k = 0; k < K; ++k)
+        for (int ci = 0; ci < C; ++ci)
+          memcpy(&perm[s][(((size_t)(k / 16) * (C / 4) + ci / 4) * 64 + ci % 4 * 16 + k % 16) * 9], src + ((size_t)k * C + ci) * 9, 9 * sizeof(float));
+      src = perm[s].data();
+    }
+    INIT_TRY(hipMemcpyAsync(c->f(c->L.what[s]), src, sizeof(float) * st[s].padded, hipMemcpyHostToDevice, c->stream));
+  }
   INIT_TRY(hipMemcpyAsync(c->recs_dev, recs.data(), sizeof(StepDesc) * recs.size(), hipMemcpyHostToDevice, c->stream));
   INIT_TRY(hipMemcpyAsync(c->globals_dev, &g0, sizeof g0, hipMemcpyHostToDevice, c->stream));
   {

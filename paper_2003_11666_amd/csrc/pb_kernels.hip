@@ -320,7 +320,31 @@ __device__ __forceinline__ void step_gn_stats_wave(const LDesc& d, int t, lfloat
 }
 
 // pooled[c] = mean_hw relu(sc*x+sh)
+// grain = 1 (small maps): a wavefront per channel, GAP_WAVE_CH channels per wavefront with their loads in flight together.
 __device__ __forceinline__ void step_gap_fwd(const LDesc& d, int tile, int t, lfloat* red) {
+  if (UNI(d.grain) == 1) {
+    const int lane = threadIdx.x & 63, c0 = (tile * (BLK / 64) + UNI((int)(threadIdx.x >> 6))) * GAP_WAVE_CH;
+    const int C = UNI(d.C), G = UNI(d.G), HW = UNI(d.H) * UNI(d.W);
+    const bool aff = UNI(d.flags) & F_PRE_AFFINE, rl = UNI(d.flags) & F_PRE_RELU;
+    const gfloat* x = at(d.x, t);
+    const gfloat* st = aff ? (const gfloat*)at(d.st, t) : x;
+    float v[GAP_WAVE_CH], sc[GAP_WAVE_CH], sh[GAP_WAVE_CH];
+#pragma unroll
+    for (int q = 0; q < GAP_WAVE_CH; ++q) {
+      const int c = c0 + q < C ? c0 + q : C - 1;
+      v[q] = x[(size_t)c * HW + (lane < HW ? lane : 0)];
+      sc[q] = aff ? st[2 * G + c] : 1.f;
+      sh[q] = aff ? st[2 * G + C + c] : 0.f;
+    }
+#pragma unroll
+    for (int q = 0; q < GAP_WAVE_CH; ++q) {
+      float r = fmaf(sc[q], v[q], sh[q]);
+      if (rl) r = fmaxf(r, 0.f);
+      r = wave_sum(lane < HW ? r : 0.f);
+      if (lane == 0 && c0 + q < C) at(d.y, t)[c0 + q] = r / (float)HW;
+    }
+    return;
+  }
   const int c = tile, HW = d.H * d.W;
   const gfloat* xp = at(d.x, t) + (size_t)c * HW;
   const bool aff = d.flags & F_PRE_AFFINE, rl = d.flags & F_PRE_RELU;
@@ -526,7 +550,7 @@ __device__ __forceinline__ void step_gnb_reduce_wave(const LDesc& d, int tile, i
   const gfloat* st = at(d.st, t);
   const gfloat* x = at(d.x, t);
   const gfloat* dy = at(d.dy, t);
-  const bool rl = UNI(d.flags) & F_GN_RELU, pooled = UNI(d.flags) & F_DU_POOL;
+  const bool rl = UNI(d.flags) & F_GN_RELU, pooled = UNI(d.flags) & F_DU_POOL, gap = UNI(d.flags) & F_DU_GAP;
   constexpr int RU = 4;
   // The incoming gradient was left as partial sums by a backward-data GEMM split over its
   // reduction (at most 64 values per channel): add them up in order, write the gradient for
@@ -562,7 +586,7 @@ __device__ __forceinline__ void step_gnb_reduce_wave(const LDesc& d, int tile, i
 #pragma unroll
       for (int u = 0; u < RU; ++u) {
         const int i = lane + u * 64;
-        if (i < HW) { xv[q][u] = x[(size_t)c * HW + i]; if (!pooled) dv[q][u] = dy[(size_t)c * HW + i]; }
+        if (i < HW) { xv[q][u] = x[(size_t)c * HW + i]; if (!pooled) dv[q][u] = gap ? dy[c] / (float)HW : dy[(size_t)c * HW + i]; }
       }
       mean[q] = st[g]; rstd[q] = st[G + g]; sc[q] = st[2 * G + c]; sh[q] = st[2 * G + C + c];
       gm[q] = GP(d.gamma)[c];
@@ -598,14 +622,6 @@ __device__ __forceinline__ void step_gnb_reduce_wave(const LDesc& d, int tile, i
         sg = fmaf(du, (xv[q][u] - mean[q]) * rstd[q], sg);
         sb += du;
       }
-    }
-    for (int i = lane + RU * 64; i < HW; i += 64) {
-      const float x1 = x[(size_t)c * HW + i];
-      const float yv = fmaf(sc[q], x1, sh[q]);
-      float du = pooled ? gn_du(d, dy, x + (size_t)c * HW, sc[q], sh[q], c, i, HW) : dy[(size_t)c * HW + i];
-      if (rl && !(yv > 0.f)) du = 0.f;
-      sg = fmaf(du, (x1 - mean[q]) * rstd[q], sg);
-      sb += du;
     }
     sg = wave_sum(sg);
     sb = wave_sum(sb);
@@ -1499,11 +1515,12 @@ __device__ __forceinline__ void step_fc_fwd(const LDesc& d, int tile, int t) {
   }
 }
 
-// Backward data, dx[c] = sum_k w[k][c] dy[k]: a workgroup takes 64 inputs c (16 lanes x 4) and deals the outputs
-// k out to its 16 groups of 16 lanes, group g taking k = g, g + 16, ...; the 16 partial sums of an input are
-// added in the order of the groups.  LDS: dy[K] | part[16][64].
+// Backward data, dx[c] = sum_k w[k][c] dy[k]: a workgroup takes FC_BX inputs c (4 lanes x 4) and deals the outputs
+// k out to its 64 groups of 4 lanes, group g taking k = g, g + 64, ...; the partial sums of an input are added in the
+// order of the groups.  A step of its own in its launch, so latency is what counts: 16 inputs make 128 workgroups of a
+// 2048 x 1000 layer (64 made 32, whose 64 rounds of loads took 13 us).  LDS: dy[K] | part[64][FC_BX].
 __device__ __forceinline__ void step_fc_bwd_x(const LDesc& d, int tile, int t, lfloat* smem) {
-  const int tid = threadIdx.x, l = tid & 15, g = tid >> 4;
+  const int tid = threadIdx.x, l = tid & 3, g = tid >> 2;
   const int C = UNI(d.C), K = UNI(d.K);
   const int Kp = (K + 3) & ~3;
   lfloat* dyl = smem;
@@ -1511,32 +1528,34 @@ __device__ __forceinline__ void step_fc_bwd_x(const LDesc& d, int tile, int t, l
   const gfloat* dy = at(d.dy, t);
   for (int i = tid; i < K; i += BLK) dyl[i] = dy[i];
   __syncthreads();
-  const int c = tile * 64 + 4 * l;
+  const int c = tile * FC_BX + 4 * l;
   v4f acc = (v4f){0.f, 0.f, 0.f, 0.f};
   if (c < C) {
     const gfloat* w = GP(d.w) + c;
-    int k = g;
-    for (; k + 48 < K; k += 64) {
-      const v4f a0 = *(const gv4*)(w + (size_t)k * C), a1 = *(const gv4*)(w + (size_t)(k + 16) * C);
-      const v4f a2 = *(const gv4*)(w + (size_t)(k + 32) * C), a3 = *(const gv4*)(w + (size_t)(k + 48) * C);
-      const float e0 = dyl[k], e1 = dyl[k + 16], e2 = dyl[k + 32], e3 = dyl[k + 48];
+    constexpr int U = 8;
+    for (int k0 = g; k0 < K; k0 += 64 * U) {
+      v4f a[U];
 #pragma unroll
-      for (int j = 0; j < 4; ++j) acc[j] = fmaf(a3[j], e3, fmaf(a2[j], e2, fmaf(a1[j], e1, fmaf(a0[j], e0, acc[j]))));
-    }
-    for (; k < K; k += 16) {
-      const v4f a0 = *(const gv4*)(w + (size_t)k * C);
-      const float e0 = dyl[k];
+      for (int u = 0; u < U; ++u) {
+        const int k = k0 + 64 * u;
+        a[u] = *(const gv4*)(w + (size_t)(k < K ? k : g) * C);
+      }
 #pragma unroll
-      for (int j = 0; j < 4; ++j) acc[j] = fmaf(a0[j], e0, acc[j]);
+      for (int u = 0; u < U; ++u) {
+        const int k = k0 + 64 * u;
+        const float e = k < K ? dyl[k] : 0.f;
+#pragma unroll
+        for (int j = 0; j < 4; ++j) acc[j] = fmaf(a[u][j], e, acc[j]);
+      }
     }
   }
-  *(lv4*)(part + g * 64 + 4 * l) = acc;
+  *(lv4*)(part + g * FC_BX + 4 * l) = acc;
   __syncthreads();
-  if (tid < 64 && tile * 64 + tid < C) {
+  if (tid < FC_BX && tile * FC_BX + tid < C) {
     float s = 0.f;
-#pragma unroll
-    for (int q = 0; q < 16; ++q) s += part[q * 64 + tid];
-    at(d.dx, t)[tile * 64 + tid] = rbf_if(UNI(d.flags) & F_BF16_OUT, s);
+#pragma unroll 16
+    for (int q = 0; q < 64; ++q) s += part[q * FC_BX + tid];
+    at(d.dx, t)[tile * FC_BX + tid] = rbf_if(UNI(d.flags) & F_BF16_OUT, s);
   }
 }
 
@@ -2353,7 +2372,7 @@ k_phase(const StepDesc* __restrict__ recs, const Globals* __restrict__ G, int k,
     case K_CONV_BWD_X: step_conv_bwd_x(d, tile, t); break;
     case K_CONV_BWD_W: step_conv_bwd_w(d, tile, t); break;
     case K_COPY: step_copy(d, tile, t, NT); break;
-    case K_GEMM: step_gemm<NT>(d, tile, t, smem); break;
+    case K_GEMM: step_gemm<NT>(d, tile, t, smem, live); break;
     case K_BIAS_GRAD: step_bias_grad(d, tile, t); break;
     case K_INGEST: step_ingest(d, tile, t, G, k, sample_override, label_override); break;
     case K_UPDATE: step_update(d, tile, t, smem, NT); break;

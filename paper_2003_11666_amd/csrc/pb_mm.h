@@ -34,7 +34,7 @@
 namespace pb {
 
 template <int MODE, int MI, int NI>
-__device__ __forceinline__ void step_mm_t(const LDesc& d, int tile_, int t, lfloat* smem) {
+__device__ __forceinline__ void step_mm_t(const LDesc& d, int tile_, int t, lfloat* smem, bool live) {
   int tile = tile_;
   asm volatile("" : "+s"(tile));
   constexpr int MT = 32 * MI, NT = 32 * NI;
@@ -58,7 +58,8 @@ __device__ __forceinline__ void step_mm_t(const LDesc& d, int tile_, int t, lflo
   const int m0 = tm * MT, n0 = tn * NT;
   const int n_chunks = UNI(d.g.n_chunks);
   const int ch0 = MODE == 3 ? qpart * UNI(d.g.cpp) : 0;
-  const int ch_end = (MODE == 3 && ch0 + UNI(d.g.cpp) < n_chunks) ? ch0 + UNI(d.g.cpp) : n_chunks;
+  // (live: false before the layer's first gradient, when a step that updates the weights only carries them over)
+  const int ch_end = (MODE == 3 && !live) ? ch0 : (MODE == 3 && ch0 + UNI(d.g.cpp) < n_chunks) ? ch0 + UNI(d.g.cpp) : n_chunks;
 
   // operands in memory: Ag has lda floats per row, Bg ldb
   const gfloat* Ag = MODE == 3 ? (const gfloat*)at(d.dy, t) : GP(d.w);
@@ -308,6 +309,38 @@ __device__ __forceinline__ void step_mm_t(const LDesc& d, int tile_, int t, lflo
   const gfloat* xm = (MODE == 2 && (flags & F_MASK_X)) ? (const gfloat*)at(d.x, te) : nullptr;
   const gfloat* skg = (MODE == 2 && (flags & F_ADD_SKG)) ? (const gfloat*)at(d.skg, te) : nullptr;
   const bool round = MODE != 3 && (flags & F_BF16_OUT);
+  if (MODE == 3 && (flags & F_UPD_W)) {
+    // the update of the tile's weights, a row subtile's operands requested together: no gradient in memory
+    const float fa = UNIF(d.fa), fb = UNIF(d.fb), lrT = UNIF(d.flrT), lr = UNIF(d.flr), fm = UNIF(d.fm);
+    const bool wform = flags & F_LWP_W;
+    gfloat* wp = GP((float*)d.w);
+    gfloat* vp = GP(d.v);
+    gfloat* hp = GP(d.what);
+#pragma unroll
+    for (int i = 0; i < MI; ++i) {
+      const unsigned o0 = (unsigned)(m0 + wr * 16 * MI + 16 * i + 4 * kq) * (unsigned)N + (unsigned)(n0 + wc * 16 * NI + li);
+      float w[NI][4], v[NI][4];
+#pragma unroll
+      for (int j = 0; j < NI; ++j)
+#pragma unroll
+        for (int r = 0; r < 4; ++r) {
+          const unsigned o = o0 + (unsigned)(r * N + 16 * j);
+          w[j][r] = wp[o];
+          v[j][r] = vp[o];
+        }
+#pragma unroll
+      for (int j = 0; j < NI; ++j)
+#pragma unroll
+        for (int r = 0; r < 4; ++r) {
+          const unsigned o = o0 + (unsigned)(r * N + 16 * j);
+          const float g = acc[i][j][r], v2 = fmaf(fm, v[j][r], g), w2 = fmaf(-lr, fmaf(fa, v2, fb * g), w[j][r]);
+          vp[o] = v2;
+          wp[o] = w2;
+          hp[o] = wform ? fmaf(lrT, w2 - w[j][r], w2) : fmaf(-lrT, v2, w2);
+        }
+    }
+    return;
+  }
   // every operand of the epilogue is requested before the first one is used (the registers of the
   // contraction's operands are free by now): one memory round trip for the whole tile
   float add[MI][NI][4], msk[MI][NI][4];
@@ -375,22 +408,22 @@ __device__ __forceinline__ void step_mm_t(const LDesc& d, int tile_, int t, lflo
   }
 }
 
-__device__ __forceinline__ void step_mm(const LDesc& d, int tile, int t, lfloat* smem) {
+__device__ __forceinline__ void step_mm(const LDesc& d, int tile, int t, lfloat* smem, bool live) {
   // forward and backward data: tiles of 128 x 128, 64 x 128 (layers of 64 channels) or 128 x 64 (maps of at most 64 pixels)
   const int gm = UNI(d.g.gm), mi = UNI(d.g.mi), ni = UNI(d.g.ni);
   if (gm == 1) {
-    if (mi == 4 && ni == 4) step_mm_t<1, 4, 4>(d, tile, t, smem);
-    else if (mi == 4) step_mm_t<1, 4, 2>(d, tile, t, smem);
-    else step_mm_t<1, 2, 4>(d, tile, t, smem);
+    if (mi == 4 && ni == 4) step_mm_t<1, 4, 4>(d, tile, t, smem, live);
+    else if (mi == 4) step_mm_t<1, 4, 2>(d, tile, t, smem, live);
+    else step_mm_t<1, 2, 4>(d, tile, t, smem, live);
   } else if (gm == 2) {
-    if (mi == 4 && ni == 4) step_mm_t<2, 4, 4>(d, tile, t, smem);
-    else if (mi == 4) step_mm_t<2, 4, 2>(d, tile, t, smem);
-    else step_mm_t<2, 2, 4>(d, tile, t, smem);
+    if (mi == 4 && ni == 4) step_mm_t<2, 4, 4>(d, tile, t, smem, live);
+    else if (mi == 4) step_mm_t<2, 4, 2>(d, tile, t, smem, live);
+    else step_mm_t<2, 2, 4>(d, tile, t, smem, live);
   } else {
-    if (mi == 4 && ni == 4) step_mm_t<3, 4, 4>(d, tile, t, smem);
-    else if (mi == 4) step_mm_t<3, 4, 2>(d, tile, t, smem);
-    else if (ni == 4) step_mm_t<3, 2, 4>(d, tile, t, smem);
-    else step_mm_t<3, 2, 2>(d, tile, t, smem);
+    if (mi == 4 && ni == 4) step_mm_t<3, 4, 4>(d, tile, t, smem, live);
+    else if (mi == 4) step_mm_t<3, 4, 2>(d, tile, t, smem, live);
+    else if (ni == 4) step_mm_t<3, 2, 4>(d, tile, t, smem, live);
+    else step_mm_t<3, 2, 2>(d, tile, t, smem, live);
   }
 }
 

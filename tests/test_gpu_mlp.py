@@ -38,6 +38,7 @@ def test_perceptron_follows_the_oracle(dims, form):
             b.tick(xs[t % len(ys)], ys[t % len(ys)])
         at += n
     assert _close(a.read_weights(), orc.read_weights()) and _close(a.loss_history(), orc.loss_history())
+    assert _close(a.read_velocity(), orc.read_velocity(), 1e-3)
     for k in ("read_weights", "read_velocity", "loss_history"):
         assert np.array_equal(getattr(a, k)(), getattr(b, k)())
     # single-step launches of the phase kernel take over and hand back
