@@ -2685,7 +2685,7 @@ int64_t pb_plan_summary(const pb_net_desc* net, char* buf, int64_t cap) {
     if (d.kind == K_GEMM) {
       const GemmCfg& g = d.g;
       if (g.dc == 2)
-        snprintf(line, sizeof line, " | gm%d M%d N%d Q%d small waves %dx1x%d mi%d ni%d tile %dx%d est %.1f", g.gm, g.M, g.N, g.Q, g.wm, g.wk, g.mi, g.ni,
+        snprintf(line, sizeof line, " | gm%d M%d N%d Q%d dense small waves %dx1x%d mi%d ni%d tile %dx%d est %.1f", g.gm, g.M, g.N, g.Q, g.wm, g.wk, g.mi, g.ni,
                  g.MT, g.NT, est_tile_us(g, 1));
       else if (g.dc)
         snprintf(line, sizeof line, " | gm%d M%d N%d Q%d direct waves %dx%dx%d mi%d ni%d tile %dx%d chunks %d/%d CC%d PR%d Wp%d plane%d rows%d est %.1f", g.gm, g.M, g.N, g.Q,
