@@ -1126,6 +1126,14 @@ void wave_reduce(StepDesc& d) {
   d.ntiles = cdiv(d.C, GNB_WAVE_CH * (BLK / 64));
 }
 
+// Whether a K_GNB_REDUCE step writes the gradient it routes back through a max-pool: the forms that search every window
+// once, with the channel's map, its pooled gradient and the windows' first maxima in LDS (16-bit positions).
+bool route_fits(const StepDesc& d) {
+  const int64_t phw = (int64_t)d.PH * d.PW;
+  return (d.flags & F_DU_POOL) && d.grain == 0 && (int64_t)d.H * d.W + phw + (phw + 1) / 2 <= LDS_FLOATS;
+}
+bool route_pool(const pb_ctx* c, const StepDesc& d) { return c->kernel_set == 0 && route_fits(d); }
+
 // Compile the network into the step table.  Every step carries the phase it
 // may run in: steps of one stage's forward (or backward) chain depend on each
 // other and get consecutive phases; different stages and the two passes of
@@ -1548,9 +1556,14 @@ void compile_steps_once(pb_ctx* c, std::vector<std::pair<int, StepDesc>>& out) {
         d.ntiles = a.K;
         StepDesc e = d;
         wave_reduce(d);
+        e.dx = ring(c, b.dz, 1, a.z_elems(), 0);
+        if (route_pool(c, d)) {   // the routed gradient passes through the output buffer of the elementwise step
+          d.dx = e.dx;
+          e.dy = e.dx;
+          e.flags ^= F_DU_POOL | F_DU_BUF;
+        }
         out.push_back({pb++, d});
         e.kind = K_GNB_APPLY;
-        e.dx = ring(c, b.dz, 1, a.z_elems(), 0);
         e.ntiles = cdiv(a.z_elems(), BLK);
         stream_apply(c, e);
         out.push_back({pb++, e});
@@ -1931,7 +1944,8 @@ void order_steps(std::vector<std::pair<int, StepDesc>>& tagged, bool one_launch 
         // (routing the gradient back through a max-pool costs a window search per element: about 2 us per
         // 256 of them when the channel fits LDS, 7 us from global memory)
         const bool in_lds = (int64_t)d.H * d.W + (int64_t)d.PH * d.PW <= LDS_FLOATS;
-        us = 4.0 + (d.grain == 1 ? 1.0 : (double)d.H * d.W / BLK * ((d.flags & F_DU_POOL) ? (in_lds ? 2.0 : 7.0) : 0.05));
+        // (0.3 us where every window is searched once)
+        us = 4.0 + (d.grain == 1 ? 1.0 : (double)d.H * d.W / BLK * ((d.flags & F_DU_POOL) ? (d.dx.base ? 0.3 : in_lds ? 2.0 : 7.0) : 0.05));
       } else if (d.kind == K_DOT_FWD || d.kind == K_DOT_BWD_X) {
         us = 8.0;
       } else if (d.kind == K_UPDATE) {
@@ -2071,7 +2085,7 @@ int validate_steps(const pb_ctx* c, const std::vector<std::pair<int, StepDesc>>&
         ok = ok && d.G > 0 && d.C % d.G == 0 && ref_ok(d.x, in) && ref_ok(d.st, stn) && ref_ok(d.dy, dyn) &&
              ptr_ok(d.part, 3 * d.C) && ptr_ok(d.gamma, d.C);
         if (d.kind == K_GNB_REDUCE) {
-          ok = ok && ptr_ok(d.ggamma, d.C) && ptr_ok(d.gbeta, d.C);
+          ok = ok && ptr_ok(d.ggamma, d.C) && ptr_ok(d.gbeta, d.C) && (!d.dx.base || (route_fits(d) && ref_ok(d.dx, in)));
           if (d.grain == 1) ok = ok && d.H * d.W <= GNB_WAVE_HW && d.ntiles == cdiv(d.C, GNB_WAVE_CH * (BLK / 64));
           else ok = ok && d.grain == 0 && d.ntiles == d.C;
           if (d.gparts > 1) {   // sums partial gradients: wave form with at most 64 values per channel, or the form that

@@ -23,6 +23,7 @@ typedef __attribute__((address_space(1))) float gfloat;
 typedef __attribute__((address_space(1))) int32_t gint;
 typedef __attribute__((address_space(3))) float lfloat;
 typedef __attribute__((address_space(3))) int lint;
+typedef __attribute__((address_space(3))) unsigned short lushort;
 
 __device__ __forceinline__ gfloat* GP(float* p) { return (gfloat*)p; }
 __device__ __forceinline__ const gfloat* GP(const float* p) { return (const gfloat*)p; }
@@ -462,12 +463,60 @@ __device__ __forceinline__ void step_ce(const LDesc& d, int tile, int t, lfloat*
 // (row-major scan, strict >) sits at (h,w).
 // PK > 0: window size known at compile time (the nine reads of a 3x3 window are then
 // requested together instead of one by one)
-template <int PK, class PZ, class PD>   // pointers to the channel's map and to its pooled gradient: global memory or LDS
-__device__ __forceinline__ float pool_routed_k(const LDesc& d, PZ zc, float sc, float sh,
-                                               int h, int w, PD dyc) {
-  // window geometry in scalar registers; divisions by the pooling stride through a reciprocal
+// First maximum of pooling window (ph, pw): its position in the channel's map.
+template <int PK, class PZ>   // pointer to the channel's map: global memory or LDS
+__device__ __forceinline__ int pool_argmax_k(const LDesc& d, PZ zc, float sc, float sh, int ph, int pw) {
   const int pk = PK > 0 ? PK : UNI(d.pk);
-  const int ps = UNI(d.ps), pp = UNI(d.pp), H = UNI(d.H), W = UNI(d.W), PH = UNI(d.PH), PW = UNI(d.PW);
+  const int ps = UNI(d.ps), pp = UNI(d.pp), H = UNI(d.H), W = UNI(d.W);
+  float best = -1.f;
+  int bi = -1;
+  const int ih0 = ph * ps - pp, iw0 = pw * ps - pp;
+  if (PK > 0) {
+    float zv[PK > 0 ? PK * PK : 1];
+#pragma unroll
+    for (int kh = 0; kh < PK; ++kh)
+#pragma unroll
+      for (int kw = 0; kw < PK; ++kw) {
+        const int ih = ih0 + kh, iw = iw0 + kw;
+        const bool in = ih >= 0 && ih < H && iw >= 0 && iw < W;
+        zv[kh * PK + kw] = zc[in ? ih * W + iw : 0];
+      }
+#pragma unroll
+    for (int kh = 0; kh < PK; ++kh)
+#pragma unroll
+      for (int kw = 0; kw < PK; ++kw) {
+        const int ih = ih0 + kh, iw = iw0 + kw;
+        const bool in = ih >= 0 && ih < H && iw >= 0 && iw < W;
+        const float v = fmaxf(fmaf(sc, zv[kh * PK + kw], sh), 0.f);
+        if (in && v > best) { best = v; bi = ih * W + iw; }
+      }
+  } else {
+    for (int kh = 0; kh < pk; ++kh) {
+      const int ih = ih0 + kh;
+      if (ih < 0 || ih >= H) continue;
+      for (int kw = 0; kw < pk; ++kw) {
+        const int iw = iw0 + kw;
+        if (iw < 0 || iw >= W) continue;
+        const float v = fmaxf(fmaf(sc, zc[ih * W + iw], sh), 0.f);
+        if (v > best) { best = v; bi = ih * W + iw; }
+      }
+    }
+  }
+  return bi;
+}
+
+template <class PZ>
+__device__ __forceinline__ int pool_argmax(const LDesc& d, PZ zc, float sc, float sh, int ph, int pw) {
+  if (UNI(d.pk) == 3) return pool_argmax_k<3>(d, zc, sc, sh, ph, pw);
+  if (UNI(d.pk) == 2) return pool_argmax_k<2>(d, zc, sc, sh, ph, pw);
+  return pool_argmax_k<0>(d, zc, sc, sh, ph, pw);
+}
+
+// Sum of the windows' gradients dyc over the windows whose first maximum, argmax(ph, pw), is element (h, w).
+template <class AM, class PD>
+__device__ __forceinline__ float pool_sum(const LDesc& d, AM argmax, int h, int w, PD dyc) {
+  // window geometry in scalar registers; divisions by the pooling stride through a reciprocal
+  const int pk = UNI(d.pk), ps = UNI(d.ps), pp = UNI(d.pp), W = UNI(d.W), PH = UNI(d.PH), PW = UNI(d.PW);
   const float ips = frcp(ps);
   float sum = 0.f;
   int ph_lo = h + pp - pk + 1;
@@ -479,51 +528,14 @@ __device__ __forceinline__ float pool_routed_k(const LDesc& d, PZ zc, float sc, 
   int pw_hi = fdiv(w + pp, ips);
   if (pw_hi >= PW) pw_hi = PW - 1;
   for (int ph = ph_lo; ph <= ph_hi; ++ph)
-    for (int pw = pw_lo; pw <= pw_hi; ++pw) {
-      float best = -1.f;
-      int bi = -1;
-      const int ih0 = ph * ps - pp, iw0 = pw * ps - pp;
-      if (PK > 0) {
-        float zv[PK > 0 ? PK * PK : 1];
-#pragma unroll
-        for (int kh = 0; kh < PK; ++kh)
-#pragma unroll
-          for (int kw = 0; kw < PK; ++kw) {
-            const int ih = ih0 + kh, iw = iw0 + kw;
-            const bool in = ih >= 0 && ih < H && iw >= 0 && iw < W;
-            zv[kh * PK + kw] = zc[in ? ih * W + iw : 0];
-          }
-#pragma unroll
-        for (int kh = 0; kh < PK; ++kh)
-#pragma unroll
-          for (int kw = 0; kw < PK; ++kw) {
-            const int ih = ih0 + kh, iw = iw0 + kw;
-            const bool in = ih >= 0 && ih < H && iw >= 0 && iw < W;
-            const float v = fmaxf(fmaf(sc, zv[kh * PK + kw], sh), 0.f);
-            if (in && v > best) { best = v; bi = ih * W + iw; }
-          }
-      } else {
-        for (int kh = 0; kh < pk; ++kh) {
-          const int ih = ih0 + kh;
-          if (ih < 0 || ih >= H) continue;
-          for (int kw = 0; kw < pk; ++kw) {
-            const int iw = iw0 + kw;
-            if (iw < 0 || iw >= W) continue;
-            const float v = fmaxf(fmaf(sc, zc[ih * W + iw], sh), 0.f);
-            if (v > best) { best = v; bi = ih * W + iw; }
-          }
-        }
-      }
-      if (bi == h * W + w) sum += dyc[ph * PW + pw];
-    }
+    for (int pw = pw_lo; pw <= pw_hi; ++pw)
+      if (argmax(ph, pw) == h * W + w) sum += dyc[ph * PW + pw];
   return sum;
 }
 
 template <class PZ, class PD>
 __device__ __forceinline__ float pool_routed(const LDesc& d, PZ zc, float sc, float sh, int h, int w, PD dyc) {
-  if (UNI(d.pk) == 3) return pool_routed_k<3>(d, zc, sc, sh, h, w, dyc);
-  if (UNI(d.pk) == 2) return pool_routed_k<2>(d, zc, sc, sh, h, w, dyc);
-  return pool_routed_k<0>(d, zc, sc, sh, h, w, dyc);
+  return pool_sum(d, [&](int ph, int pw) { return pool_argmax(d, zc, sc, sh, ph, pw); }, h, w, dyc);
 }
 
 __device__ __forceinline__ float gn_du(const LDesc& d, const gfloat* dy, const gfloat* xc, float sc,
@@ -674,13 +686,16 @@ __device__ __forceinline__ void step_gnb_reduce(const LDesc& d, int tile, int t,
         }
     }
   } else if ((d.flags & F_DU_POOL) && HW + UNI(d.PH) * UNI(d.PW) <= LDS_FLOATS) {
-    // gradient routed back through a max-pool: every element looks at up to four pooling
-    // windows of nine inputs.  The channel's map and its pooled gradient are fetched once,
-    // with coalesced loads, and the window searches read LDS.
+    // gradient routed back through a max-pool.  The channel's map and its pooled gradient are fetched once, with
+    // coalesced loads; every window is searched once, its first maximum noted in LDS, and an element asks the up to
+    // four windows that hold it.  The routed gradient goes to memory where the elementwise pass (d.dx, its output
+    // buffer) takes it as a plain one.  Searching the windows of every element, in both passes: 64 maps of 112x112 took
+    // 153 us here and 3136 workgroups of 6.6 us there; now 224 workgroups follow.
     const int PHW = UNI(d.PH) * UNI(d.PW), W = UNI(d.W);
     lfloat* zs = smem;
     lfloat* ds = smem + HW;
     const gfloat* dyc = dy + (size_t)c * PHW;
+    const bool routed = d.dx.base != nullptr;
     if ((HW & 3) == 0) {
       for (int i = threadIdx.x * 4; i < HW; i += 4 * BLK) *(lv4*)(zs + i) = *(const gv4*)(xc + i);
     } else {
@@ -694,21 +709,37 @@ __device__ __forceinline__ void step_gnb_reduce(const LDesc& d, int tile, int t,
       for (int i = threadIdx.x; i < PHW; i += BLK) {
         const float sv = sum_parts<float, 8>(part + i, (size_t)UNI(d.gpstride), gparts);
         ds[i] = sv;
-        ((gfloat*)dyc)[i] = sv;
+        if (!routed) ((gfloat*)dyc)[i] = sv;
       }
     } else {
       for (int i = threadIdx.x; i < PHW; i += BLK) ds[i] = dyc[i];
     }
     __syncthreads();
     const float iw = frcp(W);
-    for (int i = threadIdx.x; i < HW; i += BLK) {
-      const float xv = zs[i];
-      const float yv = fmaf(sc, xv, sh);
-      const int h = fdiv(i, iw), w = i - h * W;
-      float du = pool_routed(d, (const lfloat*)zs, sc, sh, h, w, (const lfloat*)ds);
-      if (rl && !(yv > 0.f)) du = 0.f;
-      sg = fmaf(du, (xv - mean) * rstd, sg);
-      sb += du;
+    auto each = [&](auto argmax) {
+      for (int i = threadIdx.x; i < HW; i += BLK) {
+        const float xv = zs[i];
+        const float yv = fmaf(sc, xv, sh);
+        const int h = fdiv(i, iw), w = i - h * W;
+        float du = pool_sum(d, argmax, h, w, (const lfloat*)ds);
+        if (rl && !(yv > 0.f)) du = 0.f;
+        if (routed) at(d.dx, t)[(size_t)c * HW + i] = du;
+        sg = fmaf(du, (xv - mean) * rstd, sg);
+        sb += du;
+      }
+    };
+    if (routed) {
+      const int PW = UNI(d.PW);
+      const float ipw = frcp(PW);
+      lushort* am = (lushort*)(ds + PHW);
+      for (int p = threadIdx.x; p < PHW; p += BLK) {
+        const int ph = fdiv(p, ipw);
+        am[p] = (unsigned short)pool_argmax(d, (const lfloat*)zs, sc, sh, ph, p - ph * PW);
+      }
+      __syncthreads();
+      each([&](int ph, int pw) { return (int)am[ph * PW + pw]; });
+    } else {
+      each([&](int ph, int pw) { return pool_argmax(d, (const lfloat*)zs, sc, sh, ph, pw); });
     }
   } else {
     for (int i = threadIdx.x; i < HW; i += BLK) {
