@@ -1948,6 +1948,8 @@ void order_steps(std::vector<std::pair<int, StepDesc>>& tagged, bool one_launch 
         us = 4.0 + (d.grain == 1 ? 1.0 : (double)d.H * d.W / BLK * ((d.flags & F_DU_POOL) ? (d.dx.base ? 0.3 : in_lds ? 2.0 : 7.0) : 0.05));
       } else if (d.kind == K_DOT_FWD || d.kind == K_DOT_BWD_X) {
         us = 8.0;
+      } else if (d.kind == K_FC_BWD_X) {
+        us = 8.0;
       } else if (d.kind == K_UPDATE) {
         us = 15.0;
       } else if (d.kind == K_POST_FWD || d.kind == K_GNB_APPLY) {
@@ -1984,16 +1986,20 @@ void order_steps(std::vector<std::pair<int, StepDesc>>& tagged, bool one_launch 
   // 100 us: the update steps go last.  Beside the tiles they stream parameters at a fraction of the bandwidth and
   // lengthen every tile's memory round trips; after them they have the chip to themselves (measured: wide 178 ->
   // 170 us per tick, VGG-11 96 -> 93).  In a long phase (ResNet-50's GEMM launches) they stay in the order of
-  // cost, where they fill slots that would otherwise wait for bandwidth nobody uses (1 094 us against 1 112).
+  // cost, where they fill slots that would otherwise wait for bandwidth nobody uses (1 094 us against 1 112), and so do
+  // a few of them (fewer than a quarter of the slots: small parameters, sums of split reductions), which take no
+  // bandwidth to speak of and at the end only prolong the phase (ResNet-50's third launch: 603 -> 591 us per tick).
   std::vector<char> upd_last;
   if (g_tile_budget_us > 0) {
     std::vector<double> gemm_us;
+    std::vector<int> updates;
     for (auto& p : tagged) {
-      if ((int)gemm_us.size() <= p.first) gemm_us.resize(p.first + 1, 0.0);
+      if ((int)gemm_us.size() <= p.first) { gemm_us.resize(p.first + 1, 0.0); updates.resize(p.first + 1, 0); }
       const int k = p.second.kind;
+      if (k == K_UPDATE) updates[p.first] += p.second.ntiles;
       if (k == K_GEMM || k == K_DOT_FWD || k == K_DOT_BWD_X) gemm_us[p.first] += step_cost(p.second) * 1e-3 * p.second.ntiles / 512.0;
     }
-    for (double u : gemm_us) upd_last.push_back(u > 0.0 && u < 100.0);   // (a phase without tiles: in the order of cost)
+    for (size_t i = 0; i < gemm_us.size(); ++i) upd_last.push_back(gemm_us[i] > 0.0 && gemm_us[i] < 100.0 && updates[i] >= 128);   // (a phase without tiles: in the order of cost)
   }
   std::stable_sort(tagged.begin(), tagged.end(),
                    [&](const std::pair<int, StepDesc>& x, const std::pair<int, StepDesc>& y) {
