@@ -13,6 +13,7 @@ constexpr int UPD_TILE = 8192;    // floats per workgroup of an update step (8 f
 constexpr float GN_EPS = 1e-5f;
 constexpr int GNB_WAVE_CH = 4;    // channels per wavefront in the one-wavefront-per-channel form of K_GNB_REDUCE
 constexpr int GNB_WAVE_HW = 256;  // ... whose maps have at most this many pixels
+constexpr int GNB_WAVE4_HW = 1020; // ... or at most this many, with 16-byte requests (grain 2)
 constexpr int GAP_WAVE_CH = 4;    // channels per wavefront in the one-wavefront-per-channel form of K_GAP_FWD (at most 64 pixels)
 constexpr int FC_BX = 16;         // inputs per workgroup of K_FC_BWD_X
 
@@ -167,7 +168,7 @@ struct StepDesc {
   int32_t sig_idx, nwait;
   int32_t wait_idx[3], wait_n[3];
   int32_t grain;            // > 0: streaming form of an elementwise step, floats per workgroup (K_COPY, K_GNB_APPLY);
-                            // K_GNB_REDUCE, K_GAP_FWD: 1 = one wavefront per channel
+                            // K_GNB_REDUCE, K_GAP_FWD: 1 = one wavefront per channel; K_GNB_REDUCE: 2 = the same, 16-byte requests
   GemmCfg g;     // main operand set of a K_GEMM step
   GemmCfg gp;    // projection of the skip tensor accumulated into the same tile (forward only)
   TRef x;        // op input (forward) / saved input (backward)

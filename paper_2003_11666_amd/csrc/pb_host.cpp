@@ -1126,6 +1126,12 @@ void wave_reduce(StepDesc& d) {
   d.ntiles = cdiv(d.C, GNB_WAVE_CH * (BLK / 64));
 }
 
+// The same with 16-byte requests, for maps beyond that (see step_gnb_reduce_wave4).
+bool wave4_fits(const pb_ctx* c, const StepDesc& d) {
+  const int HW = d.H * d.W;
+  return g_tile_budget_us > 0 && (d.flags & F_DU_BUF) && HW > GNB_WAVE_HW && HW <= GNB_WAVE4_HW && HW % 4 == 0 && ref_vec4(c, d.x) && ref_vec4(c, d.dy);
+}
+
 // Whether a K_GNB_REDUCE step writes the gradient it routes back through a max-pool: the forms that search every window
 // once, with the channel's map, its pooled gradient and the windows' first maxima in LDS (16-bit positions).
 bool route_fits(const StepDesc& d) {
@@ -1779,6 +1785,7 @@ void compile_steps_once(pb_ctx* c, std::vector<std::pair<int, StepDesc>>& out) {
         d.ntiles = a.Cin;
         const StepDesc d_plain = d;
         wave_reduce(d);
+        if (d.grain == 0 && wave4_fits(c, d)) { d.grain = 2; d.ntiles = cdiv(d.C, BLK / 64); }
         out.push_back({pb++, d});
         if (s > 0) {
           StepDesc e = d_plain;
@@ -1945,7 +1952,7 @@ void order_steps(std::vector<std::pair<int, StepDesc>>& tagged, bool one_launch 
         // 256 of them when the channel fits LDS, 7 us from global memory)
         const bool in_lds = (int64_t)d.H * d.W + (int64_t)d.PH * d.PW <= LDS_FLOATS;
         // (0.3 us where every window is searched once)
-        us = 4.0 + (d.grain == 1 ? 1.0 : (double)d.H * d.W / BLK * ((d.flags & F_DU_POOL) ? (d.dx.base ? 0.3 : in_lds ? 2.0 : 7.0) : 0.05));
+        us = 4.0 + (d.grain > 0 ? 1.0 : (double)d.H * d.W / BLK * ((d.flags & F_DU_POOL) ? (d.dx.base ? 0.3 : in_lds ? 2.0 : 7.0) : 0.05));
       } else if (d.kind == K_DOT_FWD || d.kind == K_DOT_BWD_X) {
         us = 8.0;
       } else if (d.kind == K_FC_BWD_X) {
@@ -2093,6 +2100,7 @@ int validate_steps(const pb_ctx* c, const std::vector<std::pair<int, StepDesc>>&
         if (d.kind == K_GNB_REDUCE) {
           ok = ok && ptr_ok(d.ggamma, d.C) && ptr_ok(d.gbeta, d.C) && (!d.dx.base || (route_fits(d) && ref_ok(d.dx, in)));
           if (d.grain == 1) ok = ok && d.H * d.W <= GNB_WAVE_HW && d.ntiles == cdiv(d.C, GNB_WAVE_CH * (BLK / 64));
+          else if (d.grain == 2) ok = ok && wave4_fits(c, d) && d.gparts <= 1 && d.ntiles == cdiv(d.C, BLK / 64);
           else ok = ok && d.grain == 0 && d.ntiles == d.C;
           if (d.gparts > 1) {   // sums partial gradients: wave form with at most 64 values per channel, or the form that
                                 // stages a channel's pooled gradient in LDS

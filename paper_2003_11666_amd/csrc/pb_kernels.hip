@@ -647,7 +647,51 @@ __device__ __forceinline__ void step_gnb_reduce_wave(const LDesc& d, int tile, i
   }
 }
 
+// Maps of more than 256 and fewer than 1024 pixels (a multiple of 4) with a plain gradient buffer: one wavefront per
+// channel, the channel in four 16-byte requests per lane and operand, no barrier.  Bound by the memory round trip: a
+// workgroup per channel holds a slot for 3.7 us with one request per lane (ResNet-50, 2816 channels of 28x28: 590 -> 581 us
+// per tick).  At 1024 pixels that request fills every lane and the workgroup is the better form (wide: 125 against 127 us).
+__device__ __forceinline__ void step_gnb_reduce_wave4(const LDesc& d, int tile, int t) {
+  const int lane = threadIdx.x & 63, c = tile * (BLK / 64) + UNI((int)(threadIdx.x >> 6));
+  const int C = UNI(d.C), G = UNI(d.G), HW = UNI(d.H) * UNI(d.W);
+  if (c >= C) return;
+  const gfloat* st = at(d.st, t);
+  const gfloat* x = at(d.x, t) + (size_t)c * HW;
+  const gfloat* dy = at(d.dy, t) + (size_t)c * HW;
+  constexpr int RU = (GNB_WAVE4_HW + 255) / 256;
+  v4f xv[RU], dv[RU];
+#pragma unroll
+  for (int u = 0; u < RU; ++u) {
+    const int i = 4 * (lane + 64 * u);
+    xv[u] = (v4f){0.f, 0.f, 0.f, 0.f}; dv[u] = xv[u];
+    if (i < HW) { xv[u] = *(const gv4*)(x + i); dv[u] = *(const gv4*)(dy + i); }
+  }
+  const int g = UNI(fdiv(c, frcp(UNI(fdiv(C, frcp(G))))));
+  const float mean = st[g], rstd = st[G + g], sc = st[2 * G + c], sh = st[2 * G + C + c], gm = GP(d.gamma)[c];
+  const bool rl = UNI(d.flags) & F_GN_RELU;
+  float sg = 0.f, sb = 0.f;
+#pragma unroll
+  for (int u = 0; u < RU; ++u)     // (elements beyond the map: a gradient of zero)
+#pragma unroll
+    for (int e = 0; e < 4; ++e) {
+      const float du = (rl && !(fmaf(sc, xv[u][e], sh) > 0.f)) ? 0.f : dv[u][e];
+      const float xh = (xv[u][e] - mean) * rstd;
+      sg = fmaf(du, 4 * (lane + 64 * u) < HW ? xh : 0.f, sg);
+      sb += du;
+    }
+  sg = wave_sum(sg);
+  sb = wave_sum(sb);
+  if (lane == 0) {
+    GP(d.ggamma)[c] = sg;
+    GP(d.gbeta)[c] = sb;
+    GP(d.part)[c] = gm * sb;
+    GP(d.part)[C + c] = gm * sg;
+    GP(d.part)[2 * C + c] = gm;
+  }
+}
+
 __device__ __forceinline__ void step_gnb_reduce(const LDesc& d, int tile, int t, lfloat* red, lfloat* smem, const bool nt) {
+  if (!nt && UNI(d.grain) == 2) { step_gnb_reduce_wave4(d, tile, t); return; }
   if (UNI(d.grain) == 1) { step_gnb_reduce_wave(d, tile, t, smem, nt); return; }
   const int c = tile, HW = UNI(d.H) * UNI(d.W), cpg = UNI(fdiv(UNI(d.C), frcp(UNI(d.G)))), g = UNI(fdiv(c, frcp(cpg)));
   const gfloat* st = at(d.st, t);
@@ -1326,18 +1370,25 @@ __device__ __forceinline__ void step_update(const LDesc& d, int tile, int t, lfl
   // backward-weights GEMM): add the other parts, in order
   const int gparts = UNI(d.gparts);
   if (gparts > 1) {
+    // (two parts requested together: with 14 of them a workgroup took 17 us, a memory round trip each)
     const int ps4 = UNI(d.gpstride) >> 2;
-    for (int p = 1; p < gparts; ++p) {
-      v4f pv[UU];
+    for (int p = 1; p < gparts; p += 2) {
+      const bool two = p + 1 < gparts;
+      v4f pv[2][UU];
 #pragma unroll
-      for (int u = 0; u < UU; ++u) {
-        const int i = i0 + u * BLK;
-        pv[u] = (v4f){0.f, 0.f, 0.f, 0.f};
-        if (i < n4) pv[u] = gp[(size_t)p * ps4 + i];
-      }
+      for (int h = 0; h < 2; ++h)
+#pragma unroll
+        for (int u = 0; u < UU; ++u) {
+          const int i = i0 + u * BLK;
+          pv[h][u] = (v4f){0.f, 0.f, 0.f, 0.f};
+          if (i < n4 && (h == 0 || two)) pv[h][u] = gp[(size_t)(p + h) * ps4 + i];
+        }
 #pragma unroll
       for (int u = 0; u < UU; ++u)
-        if (i0 + u * BLK < n4) gv[u] += pv[u];
+        if (i0 + u * BLK < n4) {
+          gv[u] += pv[0][u];
+          if (two) gv[u] += pv[1][u];
+        }
     }
   }
   gv4* vo = (gv4*)(float*)d.b;
