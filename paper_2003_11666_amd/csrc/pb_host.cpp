@@ -913,10 +913,15 @@ bool make_d1(const pb_ctx* c, int mode, int C, int H, int W, int K, int OH, int 
 //   Latency policy (small networks): at least g_tile_target tiles per step, rows
 //   first.  Throughput policy (g_tile_budget_us > 0): of all arrangements whose
 //   estimated tile duration stays within the budget, the one with the least total
-//   work (tiles x duration); if none does, the one with the shortest tile.
+//   work (tiles x duration); if none does, the one with the shortest tile.  Work below
+//   small_work microseconds (256: half a microsecond of the chip's 512 places) counts
+//   alike there and the shortest tile wins: the first layer of a network with post-layer
+//   norms shares its phase with elementwise steps and is the longest workgroup in it
+//   (VGG-11: 8 tiles of 14 us -> 32 tiles, 86 -> 82.6 us per tick).  In the full forward
+//   phase of a network with pre-layer norms more tiles only cost (wide: 125.2 -> 126.4).
 bool make_gemm(int mode, int C, int H, int W, int K, int OH, int OW, int k, int s, int pad,
                const GemmCfg* like, GemmCfg* out, bool allow_vec = false, int max_sub = 16, bool flat = false,
-               int max_parts = 1) {
+               int max_parts = 1, double small_work = 0.0) {
   const int target = (mode == 1) ? g_tile_target : g_tile_target_bwd;
   GemmCfg g;
   memset(&g, 0, sizeof g);
@@ -989,7 +994,8 @@ bool make_gemm(int mode, int C, int H, int W, int K, int OH, int OW, int k, int 
           bool better;
           if (!have) better = true;
           else if (within != best_within) better = within;
-          else if (within) better = work < best_work || (work == best_work && tt < best_tile);
+          else if (within) better = std::max(work, small_work) < std::max(best_work, small_work) ||
+                                    (std::max(work, small_work) == std::max(best_work, small_work) && tt < best_tile);
           else better = tt < best_tile;
           if (better) { have = true; bestg = e; best_work = work; best_tile = tt; best_within = within; }
         }
@@ -1471,7 +1477,7 @@ void compile_steps_once(pb_ctx* c, std::vector<std::pair<int, StepDesc>>& out) {
         const bool zsplit = a.post_gn && b.zparts >= 0 && !c->bf16 && g_tile_budget_us > 0 && !(d.flags & (F_SKIP | F_PROJ)) &&
                             (a.K / a.G) * a.OH * a.OW % 4 == 0 && (int64_t)(a.K / a.G) * a.OH * a.OW <= 32768 && a.K / a.G <= BLK;
         bool ok = make_gemm(1, d.C, d.H, d.W, d.K, d.OH, d.OW, d.k, d.stride, d.pad, nullptr, &g, plain_src, (d.flags & F_PROJ) ? 1 : 16, flat,
-                            zsplit ? FWD_PARTS : 1);
+                            zsplit ? FWD_PARTS : 1, a.post_gn ? 256.0 : 0.0);
         if (ok && (d.flags & F_PROJ)) ok = make_gemm(1, d.sC, d.sH, d.sW, d.K, d.OH, d.OW, 1, d.sstride, 0, &g, &gp, true);
         GemmCfg gd;
         if (plain_src && !(d.flags & F_PROJ) &&
@@ -1962,6 +1968,9 @@ void order_steps(std::vector<std::pair<int, StepDesc>>& tagged, bool one_launch 
       } else if (d.kind == K_POST_FWD || d.kind == K_GNB_APPLY) {
         us = (d.flags & (F_POOL | F_DU_POOL)) ? 8.0 : 5.0;
       }
+      // partial sums of a split reduction, added up first: 10-12 us where the plain step takes 4-5 (VGG-11's first launch
+      // ended 4 us late with 80 workgroups that started last)
+      if (d.gparts > 1 && (d.kind == K_GNB_REDUCE || d.kind == K_GN_STATS || d.kind == K_GN_BWD)) us += 7.0;
       return (int64_t)(us * 1000.0);
     }
     if (d.kind == K_GEMM) {
