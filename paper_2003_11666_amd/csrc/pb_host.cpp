@@ -1922,7 +1922,7 @@ void compile_steps_once(pb_ctx* c, std::vector<std::pair<int, StepDesc>>& out) {
     if (pr.second.kind == K_GEMM && ((pr.second.g.gm != 3 && pr.second.g.parts > 1) || pr.second.g.nsub > 1 || pr.second.g.win > 0 || pr.second.g.mm || pr.second.g.dc ||
                                     pr.second.gp.nsub > 1 || pr.second.gp.win > 0)) c->nt_stores = false;
   for (auto& pr : out)
-    if ((pr.second.kind == K_UPDATE && (pr.second.flags & F_WGRAD)) || pr.second.kind == K_DOT_FWD || pr.second.kind == K_DOT_BWD_X ||
+    if ((pr.second.kind == K_UPDATE && (pr.second.flags & F_WGRAD)) || (pr.second.kind == K_GNB_REDUCE && pr.second.grain == 2) || pr.second.kind == K_DOT_FWD || pr.second.kind == K_DOT_BWD_X ||
         pr.second.kind == K_FC_FWD || pr.second.kind == K_FC_BWD_X || pr.second.kind == K_FC_BWD_W)
       c->nt_stores = false;
   if (c->nt_stores) {
@@ -2109,7 +2109,7 @@ int validate_steps(const pb_ctx* c, const std::vector<std::pair<int, StepDesc>>&
         if (d.kind == K_GNB_REDUCE) {
           ok = ok && ptr_ok(d.ggamma, d.C) && ptr_ok(d.gbeta, d.C) && (!d.dx.base || (route_fits(d) && ref_ok(d.dx, in)));
           if (d.grain == 1) ok = ok && d.H * d.W <= GNB_WAVE_HW && d.ntiles == cdiv(d.C, GNB_WAVE_CH * (BLK / 64));
-          else if (d.grain == 2) ok = ok && wave4_fits(c, d) && d.gparts <= 1 && d.ntiles == cdiv(d.C, BLK / 64);
+          else if (d.grain == 2) ok = ok && !c->nt_stores && wave4_fits(c, d) && d.gparts <= 1 && d.ntiles == cdiv(d.C, BLK / 64);
           else ok = ok && d.grain == 0 && d.ntiles == d.C;
           if (d.gparts > 1) {   // sums partial gradients: wave form with at most 64 values per channel, or the form that
                                 // stages a channel's pooled gradient in LDS
