@@ -8,6 +8,7 @@
 
 #include <algorithm>
 #include <atomic>
+#include <exception>
 #include <mutex>
 #include <string>
 #include <thread>
@@ -2449,6 +2450,8 @@ int stage_runs(pb_ctx* c, const Run* runs, int n_runs, bool* ok) {
   return PB_OK;
 }
 
+constexpr int MAX_READ_THREADS = 6;   // host threads that unpack a large read-back, the caller's among them
+
 // Parameters (or velocities) of every stage from the padded arena layout into the caller's packed array.
 int64_t copy_params_out(pb_ctx* c, int64_t arena_off, float* dst, int64_t cap) {
   if (!dst) return c->n_params;
@@ -2538,11 +2541,16 @@ int64_t copy_params_out(pb_ctx* c, int64_t arena_off, float* dst, int64_t cap) {
       if (ch + pb_ctx::RING_CHUNKS < n_ch && !enqueue(ch + pb_ctx::RING_CHUNKS)) { bad = 1; return; }
     }
   };
-  const int n_thr = std::max(1, std::min({n_ch, 6, (int)std::thread::hardware_concurrency()}));
-  std::vector<std::thread> pool;
-  for (int i = 1; i < n_thr; ++i) pool.emplace_back(work);
+  const int n_thr = std::max(1, std::min({n_ch, MAX_READ_THREADS, (int)std::thread::hardware_concurrency()}));
+  std::thread pool[MAX_READ_THREADS];
+  try {
+    for (int i = 1; i < n_thr; ++i) pool[i] = std::thread(work);
+  } catch (const std::exception&) {
+    // (the system refused one: the chunks are dealt out among those there are, this thread alone if need be)
+  }
   work();
-  for (std::thread& t : pool) t.join();
+  for (std::thread& t : pool)
+    if (t.joinable()) t.join();
   if (bad) { (void)hipStreamSynchronize(c->stream); return fail(PB_E_HIP, "device to host copy failed"); }
   if (int rc = check_device_error(c)) return rc;
   return n;

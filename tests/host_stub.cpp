@@ -1,0 +1,82 @@
+// A HIP runtime of host memory and launchers that compute nothing, for CPU tests of the host runtime (pb_host.cpp):
+// "device" memory is the process's own, copies are copies, launches are counted.  What a test wants to happen (a refused
+// thread, a smaller GPU) and what it wants to know is in `stub`, read and written through stub_get / stub_set.
+#include <dlfcn.h>
+#include <pthread.h>
+#include <stdlib.h>
+#include <string.h>
+
+#include <atomic>
+#include <string>
+
+#include "pb_device.h"
+#include "pb_mlp.h"
+
+namespace {
+struct Stub {
+  std::atomic<long> cus{256}, threads_refused{0};
+  std::atomic<long> mlp_launches{0}, mlp_ticks_max{0}, fused_launches{0}, plain_launches{0}, waits{0}, device_syncs{0};
+} stub;
+std::atomic<long>* field(const char* name) {
+  const std::string n = name;
+  return n == "cus" ? &stub.cus : n == "threads_refused" ? &stub.threads_refused : n == "mlp_launches" ? &stub.mlp_launches
+       : n == "mlp_ticks_max" ? &stub.mlp_ticks_max : n == "fused_launches" ? &stub.fused_launches
+       : n == "plain_launches" ? &stub.plain_launches : n == "waits" ? &stub.waits : n == "device_syncs" ? &stub.device_syncs : nullptr;
+}
+}  // namespace
+
+extern "C" {
+long stub_get(const char* name) { return field(name)->load(); }
+void stub_set(const char* name, long v) { field(name)->store(v); }
+
+int pthread_create(pthread_t* t, const pthread_attr_t* a, void* (*f)(void*), void* arg) {
+  if (stub.threads_refused > 0) { --stub.threads_refused; return EAGAIN; }
+  static auto real = (int (*)(pthread_t*, const pthread_attr_t*, void* (*)(void*), void*))dlsym(RTLD_NEXT, "pthread_create");
+  return real(t, a, f, arg);
+}
+
+hipError_t hipGetDevice(int* d) { *d = 0; return hipSuccess; }
+hipError_t hipSetDevice(int) { return hipSuccess; }
+hipError_t hipDeviceGetAttribute(int* v, hipDeviceAttribute_t, int) { *v = (int)stub.cus; return hipSuccess; }
+hipError_t hipDeviceSynchronize() { ++stub.device_syncs; return hipSuccess; }
+hipError_t hipMalloc(void** p, size_t n) { *p = aligned_alloc(256, (n + 255) / 256 * 256); return *p ? hipSuccess : hipErrorOutOfMemory; }
+hipError_t hipFree(void* p) { free(p); return hipSuccess; }
+hipError_t hipHostMalloc(void** p, size_t n, unsigned) { return hipMalloc(p, n); }
+hipError_t hipHostFree(void* p) { free(p); return hipSuccess; }
+hipError_t hipMemcpy(void* d, const void* s, size_t n, hipMemcpyKind) { memcpy(d, s, n); return hipSuccess; }
+hipError_t hipMemcpyAsync(void* d, const void* s, size_t n, hipMemcpyKind, hipStream_t) { memcpy(d, s, n); return hipSuccess; }
+hipError_t hipMemsetAsync(void* d, int v, size_t n, hipStream_t) { memset(d, v, n); return hipSuccess; }
+hipError_t hipStreamSynchronize(hipStream_t) { return hipSuccess; }
+hipError_t hipStreamWaitEvent(hipStream_t, hipEvent_t, unsigned) { ++stub.waits; return hipSuccess; }
+hipError_t hipEventCreate(hipEvent_t* e) { *e = (hipEvent_t)&stub; return hipSuccess; }
+hipError_t hipEventCreateWithFlags(hipEvent_t* e, unsigned) { return hipEventCreate(e); }
+hipError_t hipEventDestroy(hipEvent_t) { return hipSuccess; }
+hipError_t hipEventRecord(hipEvent_t, hipStream_t) { return hipSuccess; }
+hipError_t hipEventSynchronize(hipEvent_t) { return hipSuccess; }
+hipError_t hipEventElapsedTime(float* ms, hipEvent_t, hipEvent_t) { *ms = 0; return hipSuccess; }
+hipError_t hipGetLastError() { return hipSuccess; }
+const char* hipGetErrorString(hipError_t) { return "stub"; }
+}
+
+namespace pb {
+void launch_mlp(const MlpArgs& a, int, int, int, bool, hipStream_t) {
+  ++stub.mlp_launches;
+  if (a.n_ticks > stub.mlp_ticks_max) stub.mlp_ticks_max = a.n_ticks;
+}
+void launch_mlp_flush(const MlpRec*, int, int, int, hipStream_t) {}
+void launch_phase(const StepDesc*, int, const Globals*, int, const float*, int, bool, hipStream_t, int32_t* sync, uint32_t) {
+  ++(sync ? stub.fused_launches : stub.plain_launches);
+}
+void launch_copy_out(float* dst, const float* src, int64_t n, const int32_t* err, int32_t* err_out, hipStream_t) {
+  memcpy(dst, src, sizeof(float) * n);
+  if (err) *err_out = *err;
+}
+void launch_fill_zero(void* p, size_t bytes, hipStream_t) { memset(p, 0, bytes); }
+void launch_set_globals(Globals* g, Globals v, hipStream_t) { *g = v; }
+void launch_update_flat(float*, float*, const float*, float*, int64_t, float, float, float, float, float, hipStream_t) {}
+hipError_t static_arena(void** p, int* dev) {
+  static void* a = aligned_alloc(256, STATIC_ARENA_BYTES);
+  *p = a; *dev = 0;
+  return hipSuccess;
+}
+}  // namespace pb
