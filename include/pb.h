@@ -35,7 +35,7 @@ enum {
   PB_OK = 0,
   PB_E_INVALID = -1,      /* bad descriptor / argument                     */
   PB_E_UNSUPPORTED = -2,  /* valid request the GPU path does not implement  */
-  PB_E_NOMEM = -3,        /* arena too small or device allocation failed    */
+  PB_E_NOMEM = -3,        /* arena too small, device or host memory ran out */
   PB_E_HIP = -4           /* a HIP runtime call failed                      */
 };
 

@@ -9,6 +9,7 @@
 #include <algorithm>
 #include <atomic>
 #include <exception>
+#include <memory>
 #include <mutex>
 #include <string>
 #include <thread>
@@ -22,7 +23,7 @@ using namespace pb;
 
 namespace {
 
-thread_local std::string g_err;
+thread_local char g_err[512];   // (fixed: reporting a failure must not need memory)
 
 // contexts built by pb_init_static share one static device array per GPU: one at a time
 constexpr int MAX_STATIC_DEVS = 64;
@@ -30,13 +31,22 @@ bool g_static_busy[MAX_STATIC_DEVS] = {};
 int g_static_dev = -1;   // device of the pb_init_static call in progress
 
 int fail(int code, const char* fmt, ...) {
-  char buf[512];
   va_list ap;
   va_start(ap, fmt);
-  vsnprintf(buf, sizeof buf, fmt, ap);
+  vsnprintf(g_err, sizeof g_err, fmt, ap);
   va_end(ap);
-  g_err = buf;
   return code;
+}
+
+// Body of a C entry: no exception (host memory that ran out, in practice) leaves it.
+template <class R, class F>
+R guarded(R on_error, F&& body) {
+  try {
+    return body();
+  } catch (const std::exception& e) {
+    fail(PB_E_NOMEM, "out of host memory (%s)", e.what());
+  }
+  return on_error;
 }
 
 #define HIP_TRY(expr)                                                                    \
@@ -2564,8 +2574,14 @@ struct ScopedEv {
     if (!c->ev_pool.empty()) { e = c->ev_pool.back(); c->ev_pool.pop_back(); }
     else { if (hipEventCreate(&e.a) != hipSuccess || hipEventCreate(&e.b) != hipSuccess) return; }
     e.cls = cls;
+    try {
+      c->evs.push_back(e);
+    } catch (const std::exception&) {   // (out of host memory: this launch is not recorded)
+      (void)hipEventDestroy(e.a);
+      (void)hipEventDestroy(e.b);
+      return;
+    }
     (void)hipEventRecord(e.a, c->stream);
-    c->evs.push_back(e);
     idx = (int)c->evs.size() - 1;
   }
   ~ScopedEv() { if (idx >= 0) (void)hipEventRecord(c->evs[idx].b, c->stream); }
@@ -2670,14 +2686,7 @@ int run_one_tick(pb_ctx* c, const float* staging, int label) {
   return PB_OK;
 }
 
-}  // namespace
-
-// =============================================================== the C ABI
-extern "C" {
-
-const char* pb_last_error(void) { return g_err.c_str(); }
-
-size_t pb_arena_bytes(const pb_net_desc* net, const int32_t* delays) {
+size_t arena_bytes(const pb_net_desc* net, const int32_t* delays) {
   std::vector<Stage> st;
   bool sequential = false;
   if (parse_net(net, st) != PB_OK || check_delays(st, delays, &sequential) != PB_OK) return 0;
@@ -2703,7 +2712,7 @@ size_t pb_arena_bytes(const pb_net_desc* net, const int32_t* delays) {
   return (size_t)pl.total * sizeof(float) + 256;
 }
 
-int64_t pb_plan_summary(const pb_net_desc* net, char* buf, int64_t cap) {
+int64_t plan_summary(const pb_net_desc* net, char* buf, int64_t cap) {
   std::vector<Stage> st;
   if (parse_net(net, st) != PB_OK) return PB_E_INVALID;
   pb_ctx tmp;
@@ -2770,6 +2779,21 @@ int64_t pb_plan_summary(const pb_net_desc* net, char* buf, int64_t cap) {
   return (int64_t)o.size() + 1;
 }
 
+}  // namespace
+
+// =============================================================== the C ABI
+extern "C" {
+
+const char* pb_last_error(void) { return g_err; }
+
+size_t pb_arena_bytes(const pb_net_desc* net, const int32_t* delays) {
+  return guarded((size_t)0, [&] { return arena_bytes(net, delays); });
+}
+
+int64_t pb_plan_summary(const pb_net_desc* net, char* buf, int64_t cap) {
+  return guarded((int64_t)PB_E_NOMEM, [&] { return plan_summary(net, buf, cap); });
+}
+
 }  // extern "C"
 
 namespace {
@@ -2788,10 +2812,22 @@ int init_common(pb_ctx** out, const pb_net_desc* net, const int32_t* delays, flo
   if (rc != PB_OK) return rc;
   if (!(momentum >= 0.f && momentum <= 1.f)) return fail(PB_E_INVALID, "momentum must be in [0,1]");
   if (!(lr >= 0.f)) return fail(PB_E_INVALID, "learning rate must be >= 0");
-  const size_t need = pb_arena_bytes(net, delays);
+  const size_t need = arena_bytes(net, delays);
   if (!need) return PB_E_INVALID;
+  if (static_arena && need > base_bytes)
+    return fail(PB_E_NOMEM, "this network needs %zu bytes of device memory, the library's static arena holds %zu: use pb_init",
+                need, base_bytes);
+  if (!static_arena && base && base_bytes < need) return fail(PB_E_NOMEM, "arena has %zu bytes, %zu needed", base_bytes, need);
+  if (!static_arena && base && (uintptr_t)base % 256) return fail(PB_E_INVALID, "arena must be 256-byte aligned");
 
-  pb_ctx* c = new pb_ctx();
+  // (sources of asynchronous copies outlive the context's destruction, which waits for the stream)
+  std::vector<float> w;
+  std::vector<std::vector<float>> perm;
+  std::vector<StepDesc> recs;
+  std::vector<MlpRec> mlp_recs;
+  Globals g0;
+  std::unique_ptr<pb_ctx, void (*)(pb_ctx*)> own(new pb_ctx(), pb_destroy);   // (destroyed on every way out but the last)
+  pb_ctx* c = own.get();
   c->st = st; c->S = (int)st.size();
   c->mitigation = net->mitigation; c->lr = lr; c->m = momentum;
   take_settings(c, net);
@@ -2802,28 +2838,16 @@ int init_common(pb_ctx** out, const pb_net_desc* net, const int32_t* delays, flo
   c->stream = (hipStream_t)net->stream;
   for (const Stage& a : st) c->n_params += a.n_params;
   if (static_arena) {
-    if (need > base_bytes) {
-      delete c;
-      return fail(PB_E_NOMEM, "this network needs %zu bytes of device memory, the library's static arena holds %zu: use pb_init",
-                  need, base_bytes);
-    }
     c->static_dev = g_static_dev;
-  } else if (base) {
-    if (base_bytes < need) { delete c; return fail(PB_E_NOMEM, "arena has %zu bytes, %zu needed", base_bytes, need); }
-    if ((uintptr_t)base % 256) { delete c; return fail(PB_E_INVALID, "arena must be 256-byte aligned"); }
-  } else {
-    if (hipMalloc(&base, need) != hipSuccess) { delete c; return fail(PB_E_NOMEM, "hipMalloc of %zu bytes failed", need); }
+  } else if (!base) {
+    if (hipMalloc(&base, need) != hipSuccess) return fail(PB_E_NOMEM, "hipMalloc of %zu bytes failed", need);
     c->own_arena = true;
   }
   c->arena = (float*)base;
 #define INIT_TRY(expr)                                                                  \
   do {                                                                                  \
     hipError_t e_ = (expr);                                                             \
-    if (e_ != hipSuccess) {                                                             \
-      fail(PB_E_HIP, "%s failed: %s", #expr, hipGetErrorString(e_));                    \
-      pb_destroy(c);                                                                    \
-      return PB_E_HIP;                                                                  \
-    }                                                                                   \
+    if (e_ != hipSuccess) return fail(PB_E_HIP, "%s failed: %s", #expr, hipGetErrorString(e_)); \
   } while (0)
   if (static_arena) {
     // the array keeps the previous context's contents: everything must start at zero (a fill kernel,
@@ -2845,7 +2869,7 @@ int init_common(pb_ctx** out, const pb_net_desc* net, const int32_t* delays, flo
   std::vector<std::pair<int, StepDesc>> tagged;
   c->plan = &pl;
   compile_steps(c, tagged);
-  if (validate_steps(c, tagged, pl.total) != PB_OK) { pb_destroy(c); return PB_E_INVALID; }
+  if (validate_steps(c, tagged, pl.total) != PB_OK) return PB_E_INVALID;
   int n_ph_all = 0;
   for (auto& p : tagged) n_ph_all = std::max(n_ph_all, p.first + 1);
   // Phases sharing a launch: pipelined form only (in the sample-indexed form steps of different stages depend on
@@ -2872,7 +2896,6 @@ int init_common(pb_ctx** out, const pb_net_desc* net, const int32_t* delays, flo
   if (c->mlp.on && (c->mlp.grid > n_cu || cur_dev >= MAX_STATIC_DEVS)) c->mlp.on = false;
   const bool can_fuse = !c->sequential && n_ph_all >= 2 && n_ph_all <= MAX_SYNC_PHASES;
   if (c->tune.one_launch > 0 && !can_fuse) {
-    pb_destroy(c);
     return fail(PB_E_UNSUPPORTED, "one launch per tick needs the pipelined form and 2..%d phases (this network has %d)", MAX_SYNC_PHASES, n_ph_all);
   }
   c->fuse_from = -1;
@@ -2885,7 +2908,6 @@ int init_common(pb_ctx** out, const pb_net_desc* net, const int32_t* delays, flo
   }
   if (c->fuse_from < 0 && c->tune.tail_merge > 0) {
     if (c->sequential || c->tune.tail_merge > n_ph_all - 2 || n_ph_all - c->tune.tail_merge > MAX_SYNC_PHASES) {
-      pb_destroy(c);
       return fail(PB_E_UNSUPPORTED, "tail_merge %d: needs the pipelined form, at least two phases from there on and at most %d (this network has %d phases)",
                   c->tune.tail_merge, MAX_SYNC_PHASES, n_ph_all);
     }
@@ -2931,7 +2953,6 @@ int init_common(pb_ctx** out, const pb_net_desc* net, const int32_t* delays, flo
   for (auto& p : tagged) n_ph = std::max(n_ph, p.first + 1);
   c->phases.assign(n_ph, Phase());
   c->rec_first.assign(n_steps, 0);
-  std::vector<StepDesc> recs;
   for (int i = 0, cur = -1, acc = 0; i < n_steps; ++i) {
     const int ph = tagged[i].first;
     if (ph != cur) { cur = ph; acc = 0; c->phases[ph].first = i; }
@@ -2954,16 +2975,15 @@ int init_common(pb_ctx** out, const pb_net_desc* net, const int32_t* delays, flo
     c->phases.resize(c->fuse_from + 1);
   }
   const int64_t o_recs = pl.alloc((int64_t)recs.size() * sizeof(StepDesc) / 4 + 64);
-  if ((size_t)pl.total * sizeof(float) > need) { pb_destroy(c); return fail(PB_E_NOMEM, "internal: arena plan mismatch"); }
+  if ((size_t)pl.total * sizeof(float) > need) return fail(PB_E_NOMEM, "internal: arena plan mismatch");
   c->recs_dev = (StepDesc*)c->f(o_recs);
 
-  std::vector<float> w(c->L.P, 0.f);
+  w.assign(c->L.P, 0.f);
   init_weights_host(st, seed, w);
-  Globals g0;
   memset(&g0, 0, sizeof g0);
   g0.n_pool = 1;
   INIT_TRY(hipMemcpyAsync(c->f(c->L.w), w.data(), sizeof(float) * c->L.P, hipMemcpyHostToDevice, c->stream));
-  std::vector<std::vector<float>> perm(c->S);
+  perm.resize(c->S);
   for (int s = 0; s < c->S; ++s) {   // slot 0 of every stage's ring of predicted weights: v = 0, so w_hat = w
     const float* src = w.data() + st[s].off;
     if (c->perm_what[s]) {
@@ -2982,7 +3002,6 @@ int init_common(pb_ctx** out, const pb_net_desc* net, const int32_t* delays, flo
     const int32_t head[2] = {0, c->tune.spin_limit > 0 ? c->tune.spin_limit : (1 << 16)};   // error word, wait bound
     INIT_TRY(hipMemcpyAsync(c->sync_dev, head, sizeof head, hipMemcpyHostToDevice, c->stream));
   }
-  std::vector<MlpRec> mlp_recs;
   if (c->mlp.on) {
     for (int s = 0; s < c->S; ++s) {
       const Stage& a = c->st[s];
@@ -3027,8 +3046,8 @@ int init_common(pb_ctx** out, const pb_net_desc* net, const int32_t* delays, flo
     for (hipEvent_t& e : c->slot_done) INIT_TRY(hipEventCreateWithFlags(&e, hipEventDisableTiming));
   }
 #undef INIT_TRY
-  if (c->mlp.on && mlp_enter(c) != PB_OK) { pb_destroy(c); return PB_E_HIP; }
-  *out = c;
+  if (c->mlp.on && mlp_enter(c) != PB_OK) return PB_E_HIP;
+  *out = own.release();
   return PB_OK;
 }
 
@@ -3039,7 +3058,7 @@ extern "C" {
 int pb_init(pb_ctx** out, const pb_net_desc* net, const int32_t* delays, float lr, float momentum,
             uint64_t seed) {
   if (!net) return fail(PB_E_INVALID, "empty network");
-  return init_common(out, net, delays, lr, momentum, seed, net->device_arena, net->arena_bytes, false);
+  return guarded((int)PB_E_NOMEM, [&] { return init_common(out, net, delays, lr, momentum, seed, net->device_arena, net->arena_bytes, false); });
 }
 
 size_t pb_static_arena_bytes(void) { return STATIC_ARENA_BYTES; }
@@ -3056,7 +3075,7 @@ int pb_init_static(pb_ctx** out, const pb_net_desc* net, const int32_t* delays, 
   if (g_static_busy[dev])
     return fail(PB_E_UNSUPPORTED, "the static arena of device %d is held by another context: destroy it first", dev);
   g_static_dev = dev;
-  const int rc = init_common(out, net, delays, lr, momentum, seed, base, STATIC_ARENA_BYTES, true);
+  const int rc = guarded((int)PB_E_NOMEM, [&] { return init_common(out, net, delays, lr, momentum, seed, base, STATIC_ARENA_BYTES, true); });
   if (rc == PB_OK) g_static_busy[dev] = true;
   return rc;
 }
@@ -3111,12 +3130,12 @@ int pb_run_resident(pb_ctx* c, const float* samples_dev, const int32_t* labels_d
 
 int64_t pb_read_weights(pb_ctx* c, float* dst, int64_t cap) {
   if (!c) return fail(PB_E_INVALID, "NULL context");
-  return copy_params_out(c, c->L.w, dst, cap);
+  return guarded((int64_t)PB_E_NOMEM, [&] { return copy_params_out(c, c->L.w, dst, cap); });
 }
 
 int64_t pb_read_velocity(pb_ctx* c, float* dst, int64_t cap) {
   if (!c) return fail(PB_E_INVALID, "NULL context");
-  return copy_params_out(c, c->L.v, dst, cap);
+  return guarded((int64_t)PB_E_NOMEM, [&] { return copy_params_out(c, c->L.v, dst, cap); });
 }
 
 int64_t pb_loss_history(pb_ctx* c, float* dst, int64_t cap) {
@@ -3155,11 +3174,14 @@ int pb_set_launch_mode(pb_ctx* c, int32_t mode) {
 
 int pb_profile_begin(pb_ctx* c, int32_t max_events) {
   if (!c || max_events <= 0) return fail(PB_E_INVALID, "bad argument");
-  for (auto& e : c->evs) c->ev_pool.push_back(e);
-  c->evs.clear();
-  c->profiling = true;
-  c->max_events = max_events;
-  return PB_OK;
+  return guarded((int)PB_E_NOMEM, [&] {
+    c->ev_pool.reserve(c->ev_pool.size() + c->evs.size());
+    for (auto& e : c->evs) c->ev_pool.push_back(e);
+    c->evs.clear();
+    c->profiling = true;
+    c->max_events = max_events;
+    return (int)PB_OK;
+  });
 }
 
 int pb_profile_end(pb_ctx* c, int32_t which, int64_t* n_launches, double* total_ms) {

@@ -20,3 +20,25 @@ for refused in (0, 1, 2, 100):
     assert np.array_equal(e.read_weights(), want), refused
 e.close()
 """)
+
+
+def test_host_memory_that_runs_out_is_an_error_code(lib):
+    """A descriptor that asks for more host memory than the process may have: PB_E_NOMEM from every entry that plans a
+    network, and the library goes on working."""
+    host_stub.run(lib, """
+import ctypes as C, resource
+net = mlp(5, 7, 4)
+desc, keep = B.marshal_net(net)
+desc.n_stages = 2 ** 31 - 1
+have = int(open('/proc/self/statm').read().split()[0]) * resource.getpagesize()
+resource.setrlimit(resource.RLIMIT_AS, (have + (4 << 30),) * 2)
+ctx = C.c_void_p()
+assert lib.pb_arena_bytes(C.byref(desc), None) == 0
+for init in (lib.pb_init, lib.pb_init_static):
+    assert init(C.byref(ctx), C.byref(desc), None, 0.1, 0.9, 1) == -3 and not ctx
+    assert b'host memory' in lib.pb_last_error()
+assert lib.pb_plan_summary(C.byref(desc), None, 0) == -3
+e = engine(net)
+assert e.read_weights().size == 5 * 7 + 7 + 7 * 4 + 4
+e.close()
+""")
