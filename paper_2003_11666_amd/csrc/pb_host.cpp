@@ -2504,7 +2504,8 @@ int64_t copy_params_out(pb_ctx* c, int64_t arena_off, float* dst, int64_t cap) {
       (void)hipGetLastError();
       c->ring_host = nullptr;
     } else {
-      for (hipEvent_t& e : c->ring_done) HIP_TRY(hipEventCreateWithFlags(&e, hipEventDisableTiming));
+      for (hipEvent_t& e : c->ring_done)
+        if (!e) HIP_TRY(hipEventCreateWithFlags(&e, hipEventDisableTiming));
     }
   }
   if (!c->ring_host) {
@@ -3042,8 +3043,13 @@ int init_common(pb_ctx** out, const pb_net_desc* net, const int32_t* delays, flo
     c->slot_bytes = (bytes + 255) / 256 * 256;
     c->n_slots = (int)std::min<size_t>(64, std::max<size_t>(8, ((size_t)1 << 20) / c->slot_bytes)) / pb_ctx::SLOT_GROUPS * pb_ctx::SLOT_GROUPS;
     c->stage_bytes = std::min<size_t>((size_t)2 << 20, (size_t)(c->L.P + 64) * sizeof(float));
-    INIT_TRY(hipHostMalloc((void**)&c->pinned, c->slot_bytes * c->n_slots + c->stage_bytes, hipHostMallocDefault));
-    for (hipEvent_t& e : c->slot_done) INIT_TRY(hipEventCreateWithFlags(&e, hipEventDisableTiming));
+    // (no pinned memory to be had: samples and read-backs go through pageable memory, as in a context that must not allocate)
+    if (hipHostMalloc((void**)&c->pinned, c->slot_bytes * c->n_slots + c->stage_bytes, hipHostMallocDefault) != hipSuccess) {
+      (void)hipGetLastError();
+      c->pinned = nullptr;
+    } else {
+      for (hipEvent_t& e : c->slot_done) INIT_TRY(hipEventCreateWithFlags(&e, hipEventDisableTiming));
+    }
   }
 #undef INIT_TRY
   if (c->mlp.on && mlp_enter(c) != PB_OK) return PB_E_HIP;

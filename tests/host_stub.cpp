@@ -14,12 +14,12 @@
 
 namespace {
 struct Stub {
-  std::atomic<long> cus{256}, threads_refused{0};
+  std::atomic<long> cus{256}, threads_refused{0}, pinned_refused{0};
   std::atomic<long> mlp_launches{0}, mlp_ticks_max{0}, fused_launches{0}, plain_launches{0}, waits{0}, device_syncs{0};
 } stub;
 std::atomic<long>* field(const char* name) {
   const std::string n = name;
-  return n == "cus" ? &stub.cus : n == "threads_refused" ? &stub.threads_refused : n == "mlp_launches" ? &stub.mlp_launches
+  return n == "cus" ? &stub.cus : n == "threads_refused" ? &stub.threads_refused : n == "pinned_refused" ? &stub.pinned_refused : n == "mlp_launches" ? &stub.mlp_launches
        : n == "mlp_ticks_max" ? &stub.mlp_ticks_max : n == "fused_launches" ? &stub.fused_launches
        : n == "plain_launches" ? &stub.plain_launches : n == "waits" ? &stub.waits : n == "device_syncs" ? &stub.device_syncs : nullptr;
 }
@@ -41,7 +41,7 @@ hipError_t hipDeviceGetAttribute(int* v, hipDeviceAttribute_t, int) { *v = (int)
 hipError_t hipDeviceSynchronize() { ++stub.device_syncs; return hipSuccess; }
 hipError_t hipMalloc(void** p, size_t n) { *p = aligned_alloc(256, (n + 255) / 256 * 256); return *p ? hipSuccess : hipErrorOutOfMemory; }
 hipError_t hipFree(void* p) { free(p); return hipSuccess; }
-hipError_t hipHostMalloc(void** p, size_t n, unsigned) { return hipMalloc(p, n); }
+hipError_t hipHostMalloc(void** p, size_t n, unsigned) { return stub.pinned_refused ? hipErrorOutOfMemory : hipMalloc(p, n); }
 hipError_t hipHostFree(void* p) { free(p); return hipSuccess; }
 hipError_t hipMemcpy(void* d, const void* s, size_t n, hipMemcpyKind) { memcpy(d, s, n); return hipSuccess; }
 hipError_t hipMemcpyAsync(void* d, const void* s, size_t n, hipMemcpyKind, hipStream_t) { memcpy(d, s, n); return hipSuccess; }

@@ -42,3 +42,19 @@ e = engine(net)
 assert e.read_weights().size == 5 * 7 + 7 + 7 * 4 + 4
 e.close()
 """)
+
+
+def test_contexts_work_where_no_memory_can_be_pinned(lib):
+    host_stub.run(lib, """
+from oracle import pb_oracle as O
+for at_init in (1, 0):                     # refused from the start, or only when a large read-back asks for its ring
+    for net in (mlp(5, 7, 4), mlp(2048, 600, 12)):
+        put('pinned_refused', at_init)
+        e = engine(net)
+        put('pinned_refused', 1)
+        for t in range(9):
+            e.tick(np.zeros(net['in_c'], np.float32), 0)
+        assert np.array_equal(e.read_weights(), O.PBOracle(net).read_weights().astype(np.float32))
+        assert e.loss_history().size == 9 - 2 + 1
+        e.close()
+""")
