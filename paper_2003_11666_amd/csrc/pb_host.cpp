@@ -331,7 +331,7 @@ struct MlpPlan {
   int64_t recs = -1, lbox = -1;      // arena offsets
   std::vector<int64_t> xbox, dybox;  // per stage: messages with its input, with the gradient of its output
 };
-constexpr int MLP_CUS = 256;         // compute units of the GPU the plan is made for
+constexpr int MLP_CUS = 256;         // compute units of the GPU the plan is made for (a context on a smaller one checks again)
 
 int what_depth(const Stage& a, bool stash) { return stash ? a.De + 2 : a.De - a.D + 2; }
 
@@ -435,6 +435,7 @@ struct pb_ctx {
   MlpPlan mlp;                   // on: ticks run in the kernel that keeps a perceptron's parameters in registers
   bool mlp_messages = false;     // the tick before ran there: gradients between stages lie in its messages
   bool waits() const { return fuse_from >= 0 || mlp.on; }   // launches hold workgroups that wait for each other
+  int wait_shares = 0;           // ... and take this many of a GPU's WAIT_SHARES equal parts
   std::vector<char> perm_what;   // per stage: the layer's predicted weights are stored in the lane order of its forward tiles
   std::vector<char> pp_active;   // per stage: the update alternates between two copies of the master parameters
   int fuse_from = -1;          // >= 0: the phases from this one on share one launch, dependencies through completion
@@ -2588,40 +2589,64 @@ struct ScopedEv {
   ~ScopedEv() { if (idx >= 0) (void)hipEventRecord(c->evs[idx].b, c->stream); }
 };
 
-// Launches of k_mlp wait for each other's workgroups, so the workgroups of one launch must all get a compute unit.  One
-// launch never has more than the GPU has; launches of several contexts (on different streams) could, together, and are
-// then put one behind the other with an event.
-struct MlpDevice {
+// Launches of k_mlp, and phase launches that hold several phases, have workgroups that wait for others of the same launch.
+// One such launch never has more workgroups than the GPU holds at once, but launches of several contexts (on different
+// streams) could, together: each would hold a part of the compute units and wait for the rest.  So every context that
+// makes such launches is entered here with its share of the GPU's compute units, in eighths (the XCDs take a launch's
+// workgroups in turn, so that an eighth is the same number of compute units on each of them): a workgroup of k_mlp takes a
+// whole compute unit, two of a phase launch share one.  Contexts whose shares add up to more than the GPU put their
+// waiting launches one behind the other, with an event.  (k_mlp workgroups that find places of phase workgroups in
+// their way wait only until that launch has ended: the phase workgroups always fit beside them.)
+constexpr int WAIT_SHARES = 8;
+struct WaitDevice {
   std::mutex mu;
   std::vector<pb_ctx*> live;
   bool crowded = false;
   pb_ctx* last = nullptr;        // crowded: context of the latest launch, which ev follows
   hipEvent_t ev = nullptr;
 };
-MlpDevice g_mlp_dev[MAX_STATIC_DEVS];
+WaitDevice g_wait_dev[MAX_STATIC_DEVS];
 
-int mlp_enter(pb_ctx* c) {
-  MlpDevice& d = g_mlp_dev[c->dev];
+int shares_of(int64_t cus, int n_cu) { return (int)std::min<int64_t>(WAIT_SHARES, (WAIT_SHARES * cus + n_cu - 1) / std::max(1, n_cu)); }
+
+int wait_enter(pb_ctx* c, int shares) {
+  WaitDevice& d = g_wait_dev[c->dev];
   std::lock_guard<std::mutex> lock(d.mu);
-  d.live.push_back(c);
-  int wgs = 0;
-  for (pb_ctx* o : d.live) wgs += o->mlp.grid;
-  if (wgs > MLP_CUS && !d.crowded) {
+  int total = shares;
+  for (pb_ctx* o : d.live) total += o->wait_shares;
+  if (total > WAIT_SHARES && !d.crowded) {
     if (!d.ev) HIP_TRY(hipEventCreateWithFlags(&d.ev, hipEventDisableTiming));
     HIP_TRY(hipDeviceSynchronize());   // (launches made so far have no event behind them)
     d.crowded = true;
     d.last = nullptr;
   }
+  d.live.push_back(c);
+  c->wait_shares = shares;
   return PB_OK;
 }
 
-void mlp_leave(pb_ctx* c) {
-  if (!c->mlp.on) return;
-  MlpDevice& d = g_mlp_dev[c->dev];
+void wait_leave(pb_ctx* c) {   // (the context's stream has been synchronised)
+  if (!c->wait_shares) return;
+  WaitDevice& d = g_wait_dev[c->dev];
   std::lock_guard<std::mutex> lock(d.mu);
   d.live.erase(std::remove(d.live.begin(), d.live.end(), c), d.live.end());
-  if (d.last == c) d.last = nullptr;   // (its stream has been synchronised)
-  if (d.live.size() <= 1) d.crowded = false;
+  if (d.last == c) d.last = nullptr;
+  int total = 0;
+  for (pb_ctx* o : d.live) total += o->wait_shares;
+  d.crowded = total > WAIT_SHARES;
+}
+
+// Makes one launch whose workgroups wait for each other.
+template <class F>
+int waiting_launch(pb_ctx* c, F&& launch) {
+  if (!c->wait_shares) { launch(); return PB_OK; }
+  WaitDevice& d = g_wait_dev[c->dev];
+  std::lock_guard<std::mutex> lock(d.mu);
+  if (d.crowded && d.last && d.last != c) HIP_TRY(hipStreamWaitEvent(c->stream, d.ev, 0));
+  launch();
+  HIP_TRY(hipGetLastError());
+  if (d.crowded) { HIP_TRY(hipEventRecord(d.ev, c->stream)); d.last = c; }
+  return PB_OK;
 }
 
 // n ticks in the kernel that keeps a perceptron's parameters in registers.  staging: one tick's sample (n = 1), or
@@ -2638,17 +2663,11 @@ int run_mlp(pb_ctx* c, int n, const float* staging, int label) {
   a.labels = c->labels_dev;
   a.sync = c->sync_dev;
   a.lbox = (uint64_t*)c->f(c->mlp.lbox);
-  MlpDevice& d = g_mlp_dev[c->dev];
-  {
-    std::lock_guard<std::mutex> lock(d.mu);
-    if (d.crowded && d.last && d.last != c) HIP_TRY(hipStreamWaitEvent(c->stream, d.ev, 0));
-    {
-      ScopedEv ev(c, 0);
-      launch_mlp(a, c->mlp.grid, c->mlp.nq, c->mlp.rw, c->lwp_w, c->stream);
-    }
-    HIP_TRY(hipGetLastError());
-    if (d.crowded) { HIP_TRY(hipEventRecord(d.ev, c->stream)); d.last = c; }
-  }
+  const int rc = waiting_launch(c, [&] {
+    ScopedEv ev(c, 0);
+    launch_mlp(a, c->mlp.grid, c->mlp.nq, c->mlp.rw, c->lwp_w, c->stream);
+  });
+  if (rc != PB_OK) return rc;
   c->ticks += n;
   c->mlp_messages = true;
   return PB_OK;
@@ -2664,12 +2683,14 @@ int run_one_tick(pb_ctx* c, const float* staging, int label) {
   }
   const int k = (int)c->ticks;   // t_base stays 0 on this path
   if (c->launch_mode == 0) {
-    bool counted = false;
     for (const Phase& p : c->phases) {
-      ScopedEv ev(c, 0);
-      if (p.fused && !counted) { ++c->fused_ticks; counted = true; }
-      launch_phase(c->recs_dev + c->rec_first[p.first], p.tiles, c->globals_dev, k, staging, label, c->nt_stores, c->stream,
-                   p.fused ? c->sync_dev : nullptr, p.fused ? c->fused_ticks : 0u);
+      auto launch = [&] {
+        ScopedEv ev(c, 0);
+        launch_phase(c->recs_dev + c->rec_first[p.first], p.tiles, c->globals_dev, k, staging, label, c->nt_stores, c->stream,
+                     p.fused ? c->sync_dev : nullptr, p.fused ? ++c->fused_ticks : 0u);
+      };
+      if (!p.fused) launch();
+      else if (int rc = waiting_launch(c, launch)) return rc;
     }
   } else {
     // one launch per step (same records, same arithmetic); event classes: 1 = update steps, 2 = ingest
@@ -3052,7 +3073,13 @@ int init_common(pb_ctx** out, const pb_net_desc* net, const int32_t* delays, flo
     }
   }
 #undef INIT_TRY
-  if (c->mlp.on && mlp_enter(c) != PB_OK) return PB_E_HIP;
+  if (c->waits() && cur_dev < MAX_STATIC_DEVS) {
+    int64_t cus = c->mlp.on ? c->mlp.grid : 0;
+    if (!c->mlp.on)
+      for (const Phase& p : c->phases)
+        if (p.fused) cus = (p.tiles + 1) / 2;   // (of more workgroups than the GPU holds, all of it)
+    if (wait_enter(c, shares_of(cus, n_cu)) != PB_OK) return PB_E_HIP;
+  }
   *out = own.release();
   return PB_OK;
 }
@@ -3242,7 +3269,7 @@ int pb_sync(pb_ctx* c) {
 void pb_destroy(pb_ctx* c) {
   if (!c) return;
   (void)hipStreamSynchronize(c->stream);
-  mlp_leave(c);
+  wait_leave(c);
   for (auto& e : c->evs) { (void)hipEventDestroy(e.a); (void)hipEventDestroy(e.b); }
   for (auto& e : c->ev_pool) { (void)hipEventDestroy(e.a); (void)hipEventDestroy(e.b); }
   for (hipEvent_t e : c->slot_done) if (e) (void)hipEventDestroy(e);

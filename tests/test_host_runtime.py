@@ -58,3 +58,27 @@ for at_init in (1, 0):                     # refused from the start, or only whe
         assert e.loss_history().size == 9 - 2 + 1
         e.close()
 """)
+
+
+def test_launches_that_do_not_fit_the_gpu_together_take_turns(lib):
+    """Contexts whose launches hold workgroups that wait for each other: launches of one wait for the other's (an event)
+    exactly when their workgroups might not all find a place on the GPU's compute units."""
+    host_stub.run(lib, """
+wide, small = mlp(1024, 1024, 1024, 1024, 1024, 100), mlp(64, 128, 128, 128, 10)     # 177 and 25 workgroups, one to a compute unit
+conv = W.config('small_resnet')                                                     # 248 workgroups, two to a compute unit
+for cus, nets, together in [(256, [wide, small], True), (256, [wide, wide], False), (256, [small] * 8, True), (256, [small] * 9, False),
+                            (64, [small, small], True), (64, [small] * 3, False), (256, [small, conv], True),
+                            (256, [wide, conv], False), (256, [conv] * 2, True), (256, [conv] * 3, False)]:
+    print(cus, [n['name'] for n in nets], together, flush=True)
+    put('cus', cus)
+    for name in ('mlp_launches', 'fused_launches', 'plain_launches', 'waits'):
+        put(name, 0)
+    engines = [engine(n) for n in nets]
+    for _ in range(2):
+        for n, e in zip(nets, engines):
+            e.tick(np.zeros(n['in_c'] * n['in_h'] * n['in_w'], np.float32), 0)
+    assert get('mlp_launches') + get('fused_launches') == 2 * len(nets) and get('plain_launches') == 0
+    assert get('waits') == (0 if together else 2 * len(nets) - 1), get('waits')
+    for e in engines:
+        e.close()
+""")
