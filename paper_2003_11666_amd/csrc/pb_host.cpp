@@ -1,10 +1,13 @@
 // Host runtime of the PB tick engine: descriptor validation, arena planning,
 // step-table compilation, the C ABI declared in include/pb.h.
+#include <errno.h>
+#include <fcntl.h>
 #include <math.h>
 #include <stdarg.h>
 #include <stdio.h>
 #include <stdlib.h>
 #include <string.h>
+#include <sys/stat.h>
 
 #include <algorithm>
 #include <atomic>
@@ -436,6 +439,8 @@ struct pb_ctx {
   bool mlp_messages = false;     // the tick before ran there: gradients between stages lie in its messages
   bool waits() const { return fuse_from >= 0 || mlp.on; }   // launches hold workgroups that wait for each other
   int wait_shares = 0;           // ... and take this many of a GPU's WAIT_SHARES equal parts
+  bool wait_busy = false;        // such launches have been made which no call has waited for yet: the shares are held
+  int64_t wait_retry = 0;        // the tick at which to ask for the shares again, after another process had them
   std::vector<char> perm_what;   // per stage: the layer's predicted weights are stored in the lane order of its forward tiles
   std::vector<char> pp_active;   // per stage: the update alternates between two copies of the master parameters
   int fuse_from = -1;          // >= 0: the phases from this one on share one launch, dependencies through completion
@@ -447,6 +452,7 @@ struct pb_ctx {
   Plan* plan = nullptr;                // arena allocator while the step table is compiled
   std::vector<std::pair<int64_t, std::vector<int32_t>>> tables;   // (arena offset, contents) of the GEMM offset tables
   std::vector<Phase> phases;
+  std::vector<Phase> plain_phases;     // fuse_from >= 0: the same steps, a launch per phase
   // device views
   StepDesc* recs_dev = nullptr;        // one descriptor copy per workgroup, in launch order
   Globals* globals_dev = nullptr;
@@ -2427,8 +2433,171 @@ void init_weights_host(const std::vector<Stage>& st, uint64_t seed, std::vector<
   }
 }
 
+// Launches of k_mlp, and phase launches that hold several phases, have workgroups that wait for others of the same launch.
+// One such launch never has more workgroups than the GPU holds at once, but launches of several contexts (on different
+// streams) could, together: each would hold a part of the compute units and wait for the rest.  So a context that makes
+// such launches has a share of the GPU's compute units, in eighths (the XCDs take a launch's workgroups in turn, so that an
+// eighth is the same number of compute units on each of them): a workgroup of k_mlp takes a whole compute unit, two of a
+// phase launch share one.  It is busy from its first launch until a call has waited for its stream.  Busy contexts whose
+// shares add up to more than the GPU put their waiting launches one behind the other, with an event.  (k_mlp workgroups
+// that find places of phase workgroups in their way wait only until that launch has ended: the phase workgroups always fit
+// beside them.)
+//
+// Other processes on the same GPU are kept apart by locks on the bytes of a file named after it, one per eighth, which the
+// system releases when a process ends, however it ends.  A process holds what its busy contexts need (taken and given back
+// in a microsecond); where that is not to be had a context's ticks run as plain phase launches, one per phase, which wait
+// for nobody, and it asks again 64 ticks later.
+constexpr int WAIT_SHARES = 8;
+struct WaitDevice {
+  std::mutex mu;
+  std::vector<pb_ctx*> busy;
+  size_t contexts = 0;           // that make waiting launches, busy or not
+  bool crowded = false;          // the busy ones do not fit the GPU together
+  pb_ctx* last = nullptr;        // crowded: context of the latest launch, which ev follows
+  hipEvent_t ev = nullptr;
+  int lock_fd = -2;              // file with the shares' locks (-2: not opened yet, -1: none to be had, other processes are not seen)
+  unsigned held = 0;             // bit per share this process has locked
+};
+WaitDevice g_wait_dev[MAX_STATIC_DEVS];
+
+int shares_of(int64_t cus, int n_cu) { return (int)std::min<int64_t>(WAIT_SHARES, (WAIT_SHARES * cus + n_cu - 1) / std::max(1, n_cu)); }
+
+// The file lives where every process of the machine (or container) can open it.  Nothing is ever written to it.
+int open_share_file(int dev) {
+  char id[64];
+  if (hipDeviceGetPCIBusId(id, sizeof id, dev) != hipSuccess) { (void)hipGetLastError(); return -1; }
+  for (const char* dir : {"/dev/shm", "/tmp"}) {
+    char path[128];
+    snprintf(path, sizeof path, "%s/pb-tick-%s", dir, id);
+    for (int tries = 0; tries < 2; ++tries) {
+      int fd = open(path, O_RDWR | O_CLOEXEC | O_NOFOLLOW);
+      if (fd >= 0) return fd;
+      fd = open(path, O_RDWR | O_CLOEXEC | O_NOFOLLOW | O_CREAT | O_EXCL, 0666);
+      if (fd >= 0) { (void)fchmod(fd, 0666); return fd; }   // (other users' processes, whatever this one's umask)
+    }
+  }
+  return -1;
+}
+
+// (locks of the open file, not of the process: a second copy of the library in the same process is kept apart as well)
+bool set_share_lock(int fd, short type, int first, int n) {
+  struct flock fl;
+  memset(&fl, 0, sizeof fl);
+  fl.l_type = type; fl.l_whence = SEEK_SET; fl.l_start = first; fl.l_len = n;
+  return fcntl(fd, F_OFD_SETLK, &fl) == 0 || (errno != EAGAIN && errno != EACCES);   // (a system without such locks sees nobody)
+}
+
+// Holds exactly the shares the busy contexts need (those of a crowded GPU take turns): false if others hold too many.
+bool claim_shares(WaitDevice& d) {
+  int most = 0, sum = 0;
+  for (pb_ctx* o : d.busy) { most = std::max(most, o->wait_shares); sum += o->wait_shares; }
+  const int want = sum > WAIT_SHARES ? most : sum;
+  if (d.lock_fd < 0) return true;
+  int have = __builtin_popcount(d.held);
+  const unsigned before = d.held;
+  // neighbouring shares in one call where that is possible, else one by one
+  for (int n = want - have, i = 0; n > 0 && i + n <= WAIT_SHARES; ++i) {
+    const unsigned run = ((1u << n) - 1u) << i;
+    if (!(d.held & run) && set_share_lock(d.lock_fd, F_WRLCK, i, n)) { d.held |= run; have = want; break; }
+  }
+  for (int i = 0; i < WAIT_SHARES && have < want; ++i)
+    if (!(d.held >> i & 1u) && set_share_lock(d.lock_fd, F_WRLCK, i, 1)) { d.held |= 1u << i; ++have; }
+  const bool ok = have >= want;
+  unsigned keep = before;
+  if (ok) {
+    keep = d.held;
+    for (int i = WAIT_SHARES - 1; i >= 0 && have > want; --i)
+      if (keep >> i & 1u) { keep &= ~(1u << i); --have; }
+  }
+  if (!keep && d.held) {
+    (void)set_share_lock(d.lock_fd, F_UNLCK, 0, WAIT_SHARES);
+  } else {
+    for (int i = 0; i < WAIT_SHARES; ++i)
+      if ((d.held & ~keep) >> i & 1u) (void)set_share_lock(d.lock_fd, F_UNLCK, i, 1);
+  }
+  d.held = keep;
+  return ok;
+}
+
+bool shares_fit(const WaitDevice& d) {
+  int sum = 0;
+  for (pb_ctx* o : d.busy) sum += o->wait_shares;
+  return sum <= WAIT_SHARES;
+}
+
+// Before a launch whose workgroups wait for each other: may it be made?
+bool wait_begin(pb_ctx* c) {
+  if (!c->wait_shares || c->wait_busy) return true;
+  if (c->ticks < c->wait_retry) return false;
+  WaitDevice& d = g_wait_dev[c->dev];
+  std::lock_guard<std::mutex> lock(d.mu);
+  d.busy.push_back(c);
+  bool ok = claim_shares(d);
+  if (ok && !d.crowded && !shares_fit(d)) {
+    // (launches made so far have no event behind them: this context's stream waits for them all, the others for it)
+    for (pb_ctx* o : d.busy)
+      if (o != c) ok = ok && hipEventRecord(d.ev, o->stream) == hipSuccess && hipStreamWaitEvent(c->stream, d.ev, 0) == hipSuccess;
+    ok = ok && hipEventRecord(d.ev, c->stream) == hipSuccess;
+    d.crowded = ok;
+    d.last = c;
+  }
+  c->wait_busy = ok;
+  if (ok) return true;
+  (void)hipGetLastError();
+  d.busy.pop_back();
+  (void)claim_shares(d);
+  c->wait_retry = c->ticks + 64;
+  return false;
+}
+
+// After the context's stream has been waited for.
+void wait_end(pb_ctx* c) {
+  if (!c->wait_busy) return;
+  WaitDevice& d = g_wait_dev[c->dev];
+  std::lock_guard<std::mutex> lock(d.mu);
+  d.busy.erase(std::remove(d.busy.begin(), d.busy.end(), c), d.busy.end());
+  if (d.last == c) d.last = nullptr;   // (and with it every launch before it has ended)
+  // (contexts left go on taking turns if another process has what they would need side by side)
+  const bool fit = shares_fit(d), claimed = claim_shares(d);
+  d.crowded = d.crowded && !(fit && claimed);
+  c->wait_busy = false;
+}
+
+int wait_enter(pb_ctx* c, int shares) {
+  WaitDevice& d = g_wait_dev[c->dev];
+  std::lock_guard<std::mutex> lock(d.mu);
+  if (!d.ev) HIP_TRY(hipEventCreateWithFlags(&d.ev, hipEventDisableTiming));
+  if (d.lock_fd == -2) d.lock_fd = open_share_file(c->dev);
+  d.busy.reserve(d.contexts + 1);   // (a tick needs no memory)
+  ++d.contexts;
+  c->wait_shares = shares;
+  return PB_OK;
+}
+
+void wait_leave(pb_ctx* c) {   // (the context's stream has been synchronised)
+  if (!c->wait_shares) return;
+  wait_end(c);
+  WaitDevice& d = g_wait_dev[c->dev];
+  std::lock_guard<std::mutex> lock(d.mu);
+  --d.contexts;
+}
+
+// Makes one launch whose workgroups wait for each other.
+template <class F>
+int waiting_launch(pb_ctx* c, F&& launch) {
+  if (!c->wait_shares) { launch(); return PB_OK; }
+  WaitDevice& d = g_wait_dev[c->dev];
+  std::lock_guard<std::mutex> lock(d.mu);
+  if (d.crowded && d.last && d.last != c) HIP_TRY(hipStreamWaitEvent(c->stream, d.ev, 0));
+  launch();
+  HIP_TRY(hipGetLastError());
+  if (d.crowded) { HIP_TRY(hipEventRecord(d.ev, c->stream)); d.last = c; }
+  return PB_OK;
+}
+
 // After the stream has been synchronised: did a dependency wait of a one-launch tick expire?
 int check_device_error(pb_ctx* c) {
+  wait_end(c);
   if (!c->waits()) return PB_OK;
   int32_t err = 0;
   if (hipMemcpy(&err, c->sync_dev + SYNC_ERR, sizeof err, hipMemcpyDeviceToHost) != hipSuccess)
@@ -2457,6 +2626,7 @@ int stage_runs(pb_ctx* c, const Run* runs, int n_runs, bool* ok) {
   }
   HIP_TRY(hipGetLastError());
   HIP_TRY(hipStreamSynchronize(c->stream));
+  wait_end(c);
   if (*err) return fail(PB_E_HIP, "a workgroup's wait for the steps it depends on expired (inside a launch): results are invalid");
   return PB_OK;
 }
@@ -2589,66 +2759,6 @@ struct ScopedEv {
   ~ScopedEv() { if (idx >= 0) (void)hipEventRecord(c->evs[idx].b, c->stream); }
 };
 
-// Launches of k_mlp, and phase launches that hold several phases, have workgroups that wait for others of the same launch.
-// One such launch never has more workgroups than the GPU holds at once, but launches of several contexts (on different
-// streams) could, together: each would hold a part of the compute units and wait for the rest.  So every context that
-// makes such launches is entered here with its share of the GPU's compute units, in eighths (the XCDs take a launch's
-// workgroups in turn, so that an eighth is the same number of compute units on each of them): a workgroup of k_mlp takes a
-// whole compute unit, two of a phase launch share one.  Contexts whose shares add up to more than the GPU put their
-// waiting launches one behind the other, with an event.  (k_mlp workgroups that find places of phase workgroups in
-// their way wait only until that launch has ended: the phase workgroups always fit beside them.)
-constexpr int WAIT_SHARES = 8;
-struct WaitDevice {
-  std::mutex mu;
-  std::vector<pb_ctx*> live;
-  bool crowded = false;
-  pb_ctx* last = nullptr;        // crowded: context of the latest launch, which ev follows
-  hipEvent_t ev = nullptr;
-};
-WaitDevice g_wait_dev[MAX_STATIC_DEVS];
-
-int shares_of(int64_t cus, int n_cu) { return (int)std::min<int64_t>(WAIT_SHARES, (WAIT_SHARES * cus + n_cu - 1) / std::max(1, n_cu)); }
-
-int wait_enter(pb_ctx* c, int shares) {
-  WaitDevice& d = g_wait_dev[c->dev];
-  std::lock_guard<std::mutex> lock(d.mu);
-  int total = shares;
-  for (pb_ctx* o : d.live) total += o->wait_shares;
-  if (total > WAIT_SHARES && !d.crowded) {
-    if (!d.ev) HIP_TRY(hipEventCreateWithFlags(&d.ev, hipEventDisableTiming));
-    HIP_TRY(hipDeviceSynchronize());   // (launches made so far have no event behind them)
-    d.crowded = true;
-    d.last = nullptr;
-  }
-  d.live.push_back(c);
-  c->wait_shares = shares;
-  return PB_OK;
-}
-
-void wait_leave(pb_ctx* c) {   // (the context's stream has been synchronised)
-  if (!c->wait_shares) return;
-  WaitDevice& d = g_wait_dev[c->dev];
-  std::lock_guard<std::mutex> lock(d.mu);
-  d.live.erase(std::remove(d.live.begin(), d.live.end(), c), d.live.end());
-  if (d.last == c) d.last = nullptr;
-  int total = 0;
-  for (pb_ctx* o : d.live) total += o->wait_shares;
-  d.crowded = total > WAIT_SHARES;
-}
-
-// Makes one launch whose workgroups wait for each other.
-template <class F>
-int waiting_launch(pb_ctx* c, F&& launch) {
-  if (!c->wait_shares) { launch(); return PB_OK; }
-  WaitDevice& d = g_wait_dev[c->dev];
-  std::lock_guard<std::mutex> lock(d.mu);
-  if (d.crowded && d.last && d.last != c) HIP_TRY(hipStreamWaitEvent(c->stream, d.ev, 0));
-  launch();
-  HIP_TRY(hipGetLastError());
-  if (d.crowded) { HIP_TRY(hipEventRecord(d.ev, c->stream)); d.last = c; }
-  return PB_OK;
-}
-
 // n ticks in the kernel that keeps a perceptron's parameters in registers.  staging: one tick's sample (n = 1), or
 // nullptr: samples from the resident pool.
 int run_mlp(pb_ctx* c, int n, const float* staging, int label) {
@@ -2674,7 +2784,7 @@ int run_mlp(pb_ctx* c, int n, const float* staging, int label) {
 }
 
 int run_one_tick(pb_ctx* c, const float* staging, int label) {
-  if (c->mlp.on && c->launch_mode == 0) return run_mlp(c, 1, staging, label);
+  if (c->mlp.on && c->launch_mode == 0 && wait_begin(c)) return run_mlp(c, 1, staging, label);
   // the kernels index every ring with a 32-bit tick counter
   if (c->ticks >= (int64_t)0x7fffff00) return fail(PB_E_UNSUPPORTED, "tick counter exhausted (2^31 ticks): start a new context");
   if (c->mlp_messages) {
@@ -2683,7 +2793,8 @@ int run_one_tick(pb_ctx* c, const float* staging, int label) {
   }
   const int k = (int)c->ticks;   // t_base stays 0 on this path
   if (c->launch_mode == 0) {
-    for (const Phase& p : c->phases) {
+    const bool plain = c->fuse_from >= 0 && (c->mlp.on || !wait_begin(c));
+    for (const Phase& p : plain ? c->plain_phases : c->phases) {
       auto launch = [&] {
         ScopedEv ev(c, 0);
         launch_phase(c->recs_dev + c->rec_first[p.first], p.tiles, c->globals_dev, k, staging, label, c->nt_stores, c->stream,
@@ -2989,6 +3100,7 @@ int init_common(pb_ctx** out, const pb_net_desc* net, const int32_t* delays, flo
     c->phases[ph].tiles = acc;
   }
   if (c->fuse_from >= 0) {
+    c->plain_phases = c->phases;
     // (launch mode 1 still walks the steps one by one, in this same order: phase by phase)
     Phase& m = c->phases[c->fuse_from];
     m.fused = true;
@@ -3150,8 +3262,11 @@ int pb_run_resident(pb_ctx* c, const float* samples_dev, const int32_t* labels_d
     c->pool = samples_dev; c->pool_labels = labels_dev; c->n_pool = n_pool; c->idx_base = (int)ib;
   }
   if (c->mlp.on && c->launch_mode == 0) {
-    for (int64_t j = 0; j < n_ticks; j += MLP_LAUNCH_TICKS)
-      if (int rc = run_mlp(c, (int)std::min<int64_t>(MLP_LAUNCH_TICKS, n_ticks - j), nullptr, 0)) return rc;
+    for (int64_t j = 0; j < n_ticks;) {
+      const int n = wait_begin(c) ? (int)std::min<int64_t>(MLP_LAUNCH_TICKS, n_ticks - j) : 0;
+      if (int rc = n ? run_mlp(c, n, nullptr, 0) : run_one_tick(c, nullptr, 0)) return rc;
+      j += std::max(1, n);
+    }
     return PB_OK;
   }
   for (int64_t j = 0; j < n_ticks; ++j) {
@@ -3221,6 +3336,7 @@ int pb_profile_end(pb_ctx* c, int32_t which, int64_t* n_launches, double* total_
   if (!c || !n_launches || !total_ms) return fail(PB_E_INVALID, "NULL argument");
   c->profiling = false;
   HIP_TRY(hipStreamSynchronize(c->stream));
+  wait_end(c);
   int64_t n = 0;
   double ms = 0;
   for (auto& e : c->evs) {

@@ -39,6 +39,12 @@ hipError_t hipGetDevice(int* d) { *d = 0; return hipSuccess; }
 hipError_t hipSetDevice(int) { return hipSuccess; }
 hipError_t hipDeviceGetAttribute(int* v, hipDeviceAttribute_t, int) { *v = (int)stub.cus; return hipSuccess; }
 hipError_t hipDeviceSynchronize() { ++stub.device_syncs; return hipSuccess; }
+hipError_t hipDeviceGetPCIBusId(char* id, int n, int) {
+  const char* name = getenv("STUB_GPU");
+  if (!name) return hipErrorInvalidValue;
+  strncpy(id, name, n);
+  return hipSuccess;
+}
 hipError_t hipMalloc(void** p, size_t n) { *p = aligned_alloc(256, (n + 255) / 256 * 256); return *p ? hipSuccess : hipErrorOutOfMemory; }
 hipError_t hipFree(void* p) { free(p); return hipSuccess; }
 hipError_t hipHostMalloc(void** p, size_t n, unsigned) { return stub.pinned_refused ? hipErrorOutOfMemory : hipMalloc(p, n); }

@@ -26,13 +26,16 @@ def load(path):
     return lib
 
 
+def prelude(path):
+    return ("import sys\nsys.path.insert(0, %r)\nimport numpy as np\nimport pb_workloads as W\nfrom tests import host_stub\n"
+            "from paper_2003_11666_amd import PBEngine, binding as B\nlib = host_stub.load(%r)\n"
+            "get, put = (lambda n: lib.stub_get(n.encode())), (lambda n, v: lib.stub_set(n.encode(), v))\n"
+            "def mlp(*dims): return W._net('p', W.mlp(dims), dims[0], 1, 1, dims[-1], 0.01, 0.9, 16, 5, 16)\n"
+            "def engine(net, **kw): return PBEngine(net, torch_arena=False, **kw)\n" % (ROOT, path))
+
+
 def run(path, body, **kw):
     """A program of its own (a fault of the library must not end the tests): prelude, then `body`."""
-    prelude = ("import sys\nsys.path.insert(0, %r)\nimport numpy as np\nimport pb_workloads as W\nfrom tests import host_stub\n"
-               "from paper_2003_11666_amd import PBEngine, binding as B\nlib = host_stub.load(%r)\n"
-               "get, put = (lambda n: lib.stub_get(n.encode())), (lambda n, v: lib.stub_set(n.encode(), v))\n"
-               "def mlp(*dims): return W._net('p', W.mlp(dims), dims[0], 1, 1, dims[-1], 0.01, 0.9, 16, 5, 16)\n"
-               "def engine(net, **kw): return PBEngine(net, torch_arena=False, **kw)\n" % (ROOT, path))
-    r = subprocess.run([sys.executable, "-c", prelude + body], capture_output=True, text=True, timeout=120, cwd=ROOT, **kw)
+    r = subprocess.run([sys.executable, "-c", prelude(path) + body], capture_output=True, text=True, timeout=120, cwd=ROOT, **kw)
     assert r.returncode == 0, f"exit status {r.returncode}\n{r.stdout}\n{r.stderr}"
     return r.stdout

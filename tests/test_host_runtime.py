@@ -1,4 +1,6 @@
 """The host runtime without a GPU: what it does when the system refuses something, and which launches it chooses."""
+import os
+
 import pytest
 
 from tests import host_stub
@@ -80,5 +82,61 @@ for cus, nets, together in [(256, [wide, small], True), (256, [wide, wide], Fals
     assert get('mlp_launches') + get('fused_launches') == 2 * len(nets) and get('plain_launches') == 0
     assert get('waits') == (0 if together else 2 * len(nets) - 1), get('waits')
     for e in engines:
+        e.sync()
+    put('waits', 0)                     # contexts whose work has been waited for take no room
+    for _ in range(3):
+        engines[0].tick(np.zeros(nets[0]['in_c'] * nets[0]['in_h'] * nets[0]['in_w'], np.float32), 0)
+    assert get('waits') == 0
+    for e in engines:
         e.close()
 """)
+
+
+def test_other_processes_on_the_gpu(lib):
+    """While another process has waiting launches under way, ticks that would not fit beside them run as plain phase
+    launches; when it has waited for its stream, is gone or was small enough, they don't.  An idle context holds nothing."""
+    gpu = f"test-{os.getpid()}"
+    other = host_stub.prelude(lib) + """
+net = {"wide": mlp(1024, 1024, 1024, 1024, 1024, 100), "small": mlp(64, 128, 128, 128, 10), "conv": W.config("small_resnet")}[sys.argv[1]]
+x = np.zeros(net['in_c'] * net['in_h'] * net['in_w'], np.float32)
+e = engine(net)
+for line in sys.stdin:
+    put('mlp_launches', 0), put('fused_launches', 0), put('plain_launches', 0)
+    if line == 'tick\\n': e.tick(x, 0)
+    if line == 'sync\\n': e.sync()
+    if line == 'die\\n': import os; os._exit(0)
+    print(get('mlp_launches'), get('fused_launches'), get('plain_launches'), flush=True)
+"""
+    try:
+        host_stub.run(lib, f"""
+import subprocess
+class Other:
+    def __init__(self, what):
+        self.p = subprocess.Popen([sys.executable, '-c', {other!r}, what], stdin=subprocess.PIPE, stdout=subprocess.PIPE, text=True)
+    def __call__(self, word):
+        self.p.stdin.write(word + chr(10)); self.p.stdin.flush()
+        return self.p.stdout.readline().split() if word != 'die' else self.p.wait()
+a, b, small, conv, conv2 = Other('wide'), Other('wide'), Other('small'), Other('conv'), Other('conv')
+mlp, fused = ['1', '0', '0'], ['0', '1', '0']
+def plain(o): r = o('tick'); return r[:2] == ['0', '0'] and int(r[2]) >= 2
+assert a('tick') == mlp                                  # six eighths
+assert plain(b) and plain(conv)                          # (four eighths)
+assert small('tick') == mlp and a('tick') == mlp
+a('sync')
+for _ in range(63): r = b('tick')                        # asked again 64 ticks after the refusal
+assert r[0] == '0' and b('tick') == mlp and plain(a)
+b('die')
+for _ in range(63): a('tick')
+assert a('tick') == mlp
+a('sync'), small('sync')
+for _ in range(64): conv('tick')
+assert conv('tick') == fused and conv2('tick') == fused and plain(small)
+conv('die')
+for _ in range(63): small('tick')
+assert small('tick') == mlp and a('tick')[0] == '0'
+for o in (a, small, conv2): o('die')
+""", env=dict(os.environ, STUB_GPU=gpu))
+    finally:
+        for d in ("/dev/shm", "/tmp"):
+            if os.path.exists(f"{d}/pb-tick-{gpu}"):
+                os.remove(f"{d}/pb-tick-{gpu}")
