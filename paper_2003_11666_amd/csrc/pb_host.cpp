@@ -3263,7 +3263,7 @@ int pb_run_resident(pb_ctx* c, const float* samples_dev, const int32_t* labels_d
   }
   if (c->mlp.on && c->launch_mode == 0) {
     for (int64_t j = 0; j < n_ticks;) {
-      const int n = wait_begin(c) ? (int)std::min<int64_t>(MLP_LAUNCH_TICKS, n_ticks - j) : 0;
+      const int n = wait_begin(c) ? (int)std::min<int64_t>(mlp_launch_ticks(c->mlp.nq), n_ticks - j) : 0;
       if (int rc = n ? run_mlp(c, n, nullptr, 0) : run_one_tick(c, nullptr, 0)) return rc;
       j += std::max(1, n);
     }

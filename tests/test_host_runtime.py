@@ -140,3 +140,18 @@ for o in (a, small, conv2): o('die')
         for d in ("/dev/shm", "/tmp"):
             if os.path.exists(f"{d}/pb-tick-{gpu}"):
                 os.remove(f"{d}/pb-tick-{gpu}")
+
+
+def test_a_launch_is_bounded_by_time(lib):
+    """A launch that may hold every compute unit ends after 5 ms, at the ticks' measured durations, whatever is asked for."""
+    host_stub.run(lib, """
+import ctypes as C
+pool, labels = np.zeros(4096, np.float32), np.zeros(4, np.int32)
+for dims, us in [((64, 128, 128, 128, 10), 3.1), ((256,) * 6 + (10,), 3.4), ((512,) * 6 + (100,), 5.6), ((1024,) * 5 + (1000,), 9.1)]:
+    put('mlp_ticks_max', 0), put('mlp_launches', 0)
+    e = engine(mlp(*dims))
+    assert lib.pb_run_resident(e.ctx, pool.ctypes.data, labels.ctypes.data, 4, 0, 5000) == 0 and e.ticks == 5000
+    n, most = get('mlp_launches'), get('mlp_ticks_max')
+    assert most * us <= 5000 and n == -(-5000 // most), (dims, n, most)
+    e.close()
+""")
