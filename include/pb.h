@@ -18,6 +18,24 @@
  * PB_E* code on failure; pb_last_error() then describes the failure.  No
  * function throws.  Unless said otherwise pointers are HOST pointers.  The
  * library is not thread-safe per context.
+ *
+ * Waiting launches.  Some networks run in launches whose workgroups wait for
+ * each other: perceptrons whose parameters fit the register files (a launch
+ * runs up to 3-5 ms of ticks and may hold every compute unit, closed to other
+ * streams meanwhile) and small networks whose tick is one launch.  Such a launch needs
+ * all of its workgroups resident at once.  The library keeps waiting launches
+ * of this process's contexts, and of other processes on the same GPU that use
+ * it, from holding parts of the GPU against each other: contexts of one
+ * process take turns; where another process has launches under way that no
+ * call has waited for yet, ticks run as plain launches, which wait for nobody
+ * (results are then those of another order of 32-bit sums in perceptrons, and the
+ * same bits elsewhere).  Processes see each other through a lock file named
+ * after the GPU in /dev/shm or /tmp, so not across containers that share
+ * neither; nor does the library know of other software whose kernels stay
+ * resident.  There, or where results must not depend on who else is at work,
+ * set pb_tuning.one_launch = -1.  A wait is bounded (4 s in perceptrons,
+ * pb_tuning.spin_limit elsewhere): on expiry the launch ends and the next
+ * synchronising call returns PB_E_HIP.
  */
 #ifndef PB_H_
 #define PB_H_
@@ -84,11 +102,13 @@ typedef struct {
   int32_t nt_stores;        /* kernel instantiation with non-temporal output stores: 1 on, -1 off, 0 by policy  */
   int32_t one_launch;       /* one kernel launch per tick -- the workgroups of a later phase wait inside the launch
                                for the stage's workgroups of the earlier phases --: 1 on, -1 off, 0 by policy
-                               (on where a tick has no more workgroups than the GPU has compute units)             */
+                               (on where a tick has no more workgroups than the GPU has compute units).  -1 also turns
+                               the register form of perceptrons off, as any other setting here does: no launch of the
+                               context then has workgroups that wait for each other (see "Waiting launches")        */
   int32_t tail_merge;       /* n > 0: the phases from phase n on share one launch in the same way (n = 0 with
                                one_launch = 1); 0 or -1: off (measured slower on every configuration); -2: the
                                longest run of last phases that hold steps of at most two stages                    */
-  int32_t spin_limit;       /* bound of such a wait, in polls (0 = default, 65536: a fraction of a second); when it expires the
+  int32_t spin_limit;       /* bound of such a wait, in polls of one memory round trip each (0 = default, 65536); when it expires the
                                step is skipped and the next synchronising call returns PB_E_HIP                    */
   int32_t dense_1x1;        /* 1x1 layers in throughput-tiled networks as dense matrix products with register tiles:
                                -1 off, 0 or 1 on where the shapes allow, 2 also forward and backward weights of k x k

@@ -434,6 +434,11 @@ struct pb_ctx {
   bool bf16 = false;   // bf16 activation mode: tensors that cross a stage boundary are rounded to bf16
   int N = 1;           // update size: samples per update
   pb_tuning tune = {0, 0, 0.f, 0, 0, 0, 0, 0, 0};
+  // a caller with a wish about the phase kernels' launches gets the phase kernels (one_launch -1: launches that never wait)
+  bool phase_settings() const {
+    return tune.tile_target || tune.tile_target_bwd || tune.tile_budget_us != 0.f || tune.nt_stores || tune.one_launch || tune.tail_merge ||
+           tune.spin_limit || tune.dense_1x1 || tune.gemm_lds_kb;
+  }
   int dev = 0;
   MlpPlan mlp;                   // on: ticks run in the kernel that keeps a perceptron's parameters in registers
   bool mlp_messages = false;     // the tick before ran there: gradients between stages lie in its messages
@@ -506,8 +511,7 @@ MlpPlan mlp_plan(const pb_ctx* c) {
   MlpPlan p;
   const std::vector<Stage>& st = c->st;
   const int S = (int)st.size();
-  pb_tuning none = {0, 0, 0.f, 0, 0, 0, 0, 0, 0};
-  if (c->kernel_set != 0 || c->bf16 || c->stash || c->N != 1 || c->sequential || memcmp(&c->tune, &none, sizeof none) != 0) return p;
+  if (c->kernel_set != 0 || c->bf16 || c->stash || c->N != 1 || c->sequential || c->phase_settings()) return p;
   if (S < 2 || S > MLP_MAX_STAGES) return p;
   int c_max = 0;
   for (int s = 0; s < S; ++s) {

@@ -155,3 +155,17 @@ for dims, us in [((64, 128, 128, 128, 10), 3.1), ((256,) * 6 + (10,), 3.4), ((51
     assert most * us <= 5000 and n == -(-5000 // most), (dims, n, most)
     e.close()
 """)
+
+
+def test_settings_that_choose_plain_launches(lib):
+    """one_launch = -1: no launch of the context has workgroups that wait, in perceptrons and small networks alike."""
+    host_stub.run(lib, """
+for net in (mlp(1024, 1024, 1024, 100), mlp(64, 128, 10), W.config('small_resnet')):
+    for tuning, plain in [(None, False), (dict(one_launch=-1), True)]:
+        put('plain_launches', 0), put('mlp_launches', 0), put('fused_launches', 0)
+        e = engine(net, tuning=tuning)
+        for _ in range(3):
+            e.tick(np.zeros(net['in_c'] * net['in_h'] * net['in_w'], np.float32), 0)
+        assert (get('mlp_launches') + get('fused_launches') == 0) == plain and (get('plain_launches') > 0) == plain
+        e.close()
+""")
