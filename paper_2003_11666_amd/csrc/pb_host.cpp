@@ -3030,7 +3030,15 @@ int init_common(pb_ctx** out, const pb_net_desc* net, const int32_t* delays, flo
   INIT_TRY(hipGetDevice(&cur_dev));
   INIT_TRY(hipDeviceGetAttribute(&n_cu, hipDeviceAttributeMultiprocessorCount, cur_dev));
   c->dev = cur_dev;
-  if (c->mlp.on && (c->mlp.grid > n_cu || cur_dev >= MAX_STATIC_DEVS)) c->mlp.on = false;
+  // (a stream that is kept to some of the compute units: a launch of k_mlp might never be resident as a whole)
+  uint32_t cu_mask[32] = {};
+  int stream_cus = 0;
+  if (hipExtStreamGetCUMask(c->stream, 32, cu_mask) == hipSuccess)
+    for (uint32_t m : cu_mask) stream_cus += __builtin_popcount(m);
+  else
+    (void)hipGetLastError();
+  const bool masked = stream_cus > 0 && stream_cus < n_cu;
+  if (c->mlp.on && (c->mlp.grid > n_cu || cur_dev >= MAX_STATIC_DEVS || masked)) c->mlp.on = false;
   const bool can_fuse = !c->sequential && n_ph_all >= 2 && n_ph_all <= MAX_SYNC_PHASES;
   if (c->tune.one_launch > 0 && !can_fuse) {
     return fail(PB_E_UNSUPPORTED, "one launch per tick needs the pipelined form and 2..%d phases (this network has %d)", MAX_SYNC_PHASES, n_ph_all);
@@ -3194,7 +3202,7 @@ int init_common(pb_ctx** out, const pb_net_desc* net, const int32_t* delays, flo
     if (!c->mlp.on)
       for (const Phase& p : c->phases)
         if (p.fused) cus = (p.tiles + 1) / 2;   // (of more workgroups than the GPU holds, all of it)
-    if (wait_enter(c, shares_of(cus, n_cu)) != PB_OK) return PB_E_HIP;
+    if (wait_enter(c, masked ? WAIT_SHARES : shares_of(cus, n_cu)) != PB_OK) return PB_E_HIP;
   }
   *out = own.release();
   return PB_OK;

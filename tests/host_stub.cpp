@@ -14,12 +14,12 @@
 
 namespace {
 struct Stub {
-  std::atomic<long> cus{256}, threads_refused{0}, pinned_refused{0};
+  std::atomic<long> cus{256}, threads_refused{0}, pinned_refused{0}, masked{0};
   std::atomic<long> mlp_launches{0}, mlp_ticks_max{0}, fused_launches{0}, plain_launches{0}, waits{0}, device_syncs{0};
 } stub;
 std::atomic<long>* field(const char* name) {
   const std::string n = name;
-  return n == "cus" ? &stub.cus : n == "threads_refused" ? &stub.threads_refused : n == "pinned_refused" ? &stub.pinned_refused : n == "mlp_launches" ? &stub.mlp_launches
+  return n == "cus" ? &stub.cus : n == "threads_refused" ? &stub.threads_refused : n == "pinned_refused" ? &stub.pinned_refused : n == "masked" ? &stub.masked : n == "mlp_launches" ? &stub.mlp_launches
        : n == "mlp_ticks_max" ? &stub.mlp_ticks_max : n == "fused_launches" ? &stub.fused_launches
        : n == "plain_launches" ? &stub.plain_launches : n == "waits" ? &stub.waits : n == "device_syncs" ? &stub.device_syncs : nullptr;
 }
@@ -38,6 +38,11 @@ int pthread_create(pthread_t* t, const pthread_attr_t* a, void* (*f)(void*), voi
 hipError_t hipGetDevice(int* d) { *d = 0; return hipSuccess; }
 hipError_t hipSetDevice(int) { return hipSuccess; }
 hipError_t hipDeviceGetAttribute(int* v, hipDeviceAttribute_t, int) { *v = (int)stub.cus; return hipSuccess; }
+hipError_t hipExtStreamGetCUMask(hipStream_t, uint32_t n, uint32_t* m) {
+  if (!stub.masked) return hipErrorInvalidValue;
+  for (uint32_t i = 0; i < n; ++i) m[i] = 32 * i < (uint32_t)stub.masked ? ~0u : 0u;
+  return hipSuccess;
+}
 hipError_t hipDeviceSynchronize() { ++stub.device_syncs; return hipSuccess; }
 hipError_t hipDeviceGetPCIBusId(char* id, int n, int) {
   const char* name = getenv("STUB_GPU");

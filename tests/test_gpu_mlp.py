@@ -72,3 +72,74 @@ def test_contexts_that_do_not_fit_the_gpu_together_take_turns():
     assert np.array_equal(a, b)
     for e in engines:
         e.close()
+
+
+def test_beside_a_network_that_runs_one_launch_per_tick():
+    """A perceptron of 177 workgroups and a convolution network whose ticks are one launch of 248, both with workgroups
+    that wait inside a launch, on two streams: the same bits as one after the other."""
+    import torch
+    from paper_2003_11666_amd import PBEngine
+    nets = [_net((1024,) * 5 + (100,), 1e-5), W.config("small_resnet")]
+    pools = [[torch.from_numpy(a).cuda() for a in W.sample_pool(n)] for n in nets]
+    streams = [torch.cuda.Stream() for _ in nets]
+    torch.cuda.synchronize()
+
+    def run(together):
+        engines = []
+        for n, s in zip(nets, streams):
+            with torch.cuda.stream(s):
+                engines.append(PBEngine(n))
+        out = []
+        for rounds in ([[0, 1]] * 40 if together else [[0]] * 40 + [[1]] * 40):
+            for i in rounds:
+                engines[i].run_resident(*pools[i], engines[i].ticks, 5)
+        for e in engines:
+            out += [e.read_weights(), e.read_velocity(), e.loss_history()]
+            e.close()
+        return out
+    for a, b in zip(run(True), run(False)):
+        assert np.isfinite(a).all() and np.array_equal(a, b)
+
+
+def test_beside_another_process():
+    """While another process has launches of a wide perceptron under way, this one's ticks run as plain phase launches;
+    afterwards they run in registers again.  The weights follow the oracle through both."""
+    import subprocess
+    import sys
+    import torch
+    from oracle import pb_oracle as O
+    from paper_2003_11666_amd import PBEngine
+    root = __file__.rsplit("/tests/", 1)[0]
+    other = subprocess.Popen([sys.executable, "-c", f"""
+import sys; sys.path.insert(0, {root!r})
+import torch, pb_workloads as W
+from tests.test_gpu_mlp import _net
+from paper_2003_11666_amd import PBEngine
+net = _net((1024,) * 5 + (100,), 1e-5)
+xs, ys = W.sample_pool(net)
+e = PBEngine(net)
+for t in range(3): e.tick(xs[t], ys[t])
+print('ready', flush=True)
+sys.stdin.readline()
+e.close()
+"""], stdin=subprocess.PIPE, stdout=subprocess.PIPE, text=True)
+    try:
+        assert other.stdout.readline() == "ready\n"
+        net = _net((1024,) * 5 + (100,), 1e-5)
+        xs, ys = W.sample_pool(net)
+        orc, e = O.PBOracle(net), PBEngine(net)
+
+        def launches_per_tick(n):
+            e.profile_begin()
+            for t in range(e.ticks, e.ticks + n):
+                orc.tick(xs[t % len(ys)], ys[t % len(ys)])
+                e.tick(xs[t % len(ys)], ys[t % len(ys)])
+            return e.profile_end(0)[0] / n
+        assert launches_per_tick(70) > 1           # (asked again in between: refused)
+        other.communicate("done\n", timeout=60)
+        launches_per_tick(64)
+        assert launches_per_tick(6) == 1
+        assert _close(e.read_weights(), orc.read_weights()) and _close(e.loss_history(), orc.loss_history())
+        e.close()
+    finally:
+        other.kill()

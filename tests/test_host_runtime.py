@@ -169,3 +169,16 @@ for net in (mlp(1024, 1024, 1024, 100), mlp(64, 128, 10), W.config('small_resnet
         assert (get('mlp_launches') + get('fused_launches') == 0) == plain and (get('plain_launches') > 0) == plain
         e.close()
 """)
+
+
+def test_streams_that_are_kept_to_some_compute_units(lib):
+    """A launch of the perceptron kernel needs all of its workgroups resident: not on a stream with a mask."""
+    host_stub.run(lib, """
+net = mlp(64, 128, 128, 128, 10)
+for masked, register_form in [(0, True), (256, True), (224, False), (32, False)]:
+    put('masked', masked), put('mlp_launches', 0)
+    e = engine(net)
+    e.tick(np.zeros(64, np.float32), 0)
+    assert (get('mlp_launches') == 1) == register_form, masked
+    e.close()
+""")
