@@ -30,8 +30,7 @@ thread_local char g_err[512];   // (fixed: reporting a failure must not need mem
 
 // contexts built by pb_init_static share one static device array per GPU: one at a time
 constexpr int MAX_STATIC_DEVS = 64;
-bool g_static_busy[MAX_STATIC_DEVS] = {};
-int g_static_dev = -1;   // device of the pb_init_static call in progress
+std::atomic<bool> g_static_busy[MAX_STATIC_DEVS] = {};
 
 int fail(int code, const char* fmt, ...) {
   va_list ap;
@@ -579,11 +578,12 @@ int pow2_floor(int x) { int p = 1; while (p * 2 <= x) p *= 2; return p; }
 
 // Tiling of one implicit-GEMM operand set.  mode 1 forward, 2 backward data,
 // 3 backward weights.
-int g_tile_target_bwd = 8; // ... of a backward step (a stage has two of them in the same phase)
-int g_tile_target = 8;     // latency policy: workgroups a step is split into at least, when its shape allows
-int g_gemm_lds = 15872;        // floats of LDS a GEMM tile is planned with (the kernel's array holds LDS_FLOATS)
-double g_tile_budget_us = 0;   // throughput policy (> 0): longest tile a step should have, microseconds (estimate)
-double g_budget_scale[4] = {1.0, 1.0, 1.0, 1.0};   // ... times this factor for the steps of a pass (index: GEMM mode), see compile_steps
+// (per thread: contexts may be planned side by side)
+thread_local int g_tile_target_bwd = 8; // ... of a backward step (a stage has two of them in the same phase)
+thread_local int g_tile_target = 8;     // latency policy: workgroups a step is split into at least, when its shape allows
+thread_local int g_gemm_lds = 15872;        // floats of LDS a GEMM tile is planned with (the kernel's array holds LDS_FLOATS)
+thread_local double g_tile_budget_us = 0;   // throughput policy (> 0): longest tile a step should have, microseconds (estimate)
+thread_local double g_budget_scale[4] = {1.0, 1.0, 1.0, 1.0};   // ... times this factor for the steps of a pass (index: GEMM mode), see compile_steps
 
 // Given the wave arrangement (wm, wn, wk, ni), choose the chunking of the
 // reduction that fits the LDS budget.  `fine`: search the channel count of a
@@ -2974,9 +2974,7 @@ int init_common(pb_ctx** out, const pb_net_desc* net, const int32_t* delays, flo
   c->loss_cap = net->loss_capacity > 0 ? net->loss_capacity : (1 << 20);
   c->stream = (hipStream_t)net->stream;
   for (const Stage& a : st) c->n_params += a.n_params;
-  if (static_arena) {
-    c->static_dev = g_static_dev;
-  } else if (!base) {
+  if (!static_arena && !base) {
     if (hipMalloc(&base, need) != hipSuccess) return fail(PB_E_NOMEM, "hipMalloc of %zu bytes failed", need);
     c->own_arena = true;
   }
@@ -3229,11 +3227,11 @@ int pb_init_static(pb_ctx** out, const pb_net_desc* net, const int32_t* delays, 
   const hipError_t e = static_arena(&base, &dev);
   if (e != hipSuccess) return fail(PB_E_HIP, "static arena: %s", hipGetErrorString(e));
   if (dev < 0 || dev >= MAX_STATIC_DEVS) return fail(PB_E_UNSUPPORTED, "device ordinal %d", dev);
-  if (g_static_busy[dev])
+  if (g_static_busy[dev].exchange(true))
     return fail(PB_E_UNSUPPORTED, "the static arena of device %d is held by another context: destroy it first", dev);
-  g_static_dev = dev;
   const int rc = guarded((int)PB_E_NOMEM, [&] { return init_common(out, net, delays, lr, momentum, seed, base, STATIC_ARENA_BYTES, true); });
-  if (rc == PB_OK) g_static_busy[dev] = true;
+  if (rc == PB_OK) (*out)->static_dev = dev;
+  else g_static_busy[dev] = false;
   return rc;
 }
 

@@ -182,3 +182,31 @@ for masked, register_form in [(0, True), (256, True), (224, False), (32, False)]
     assert (get('mlp_launches') == 1) == register_form, masked
     e.close()
 """)
+
+
+def test_networks_are_planned_side_by_side(lib):
+    """Threads that plan different networks at the same time get the plans they get alone; of threads that ask for the
+    library's own arena one gets it."""
+    host_stub.run(lib, """
+import threading
+nets = [W.config(n) for n in ('resnet20', 'vgg11', 'mlp', 'wide', 'tiny_vgg', 'resnet50_64')]
+alone = [B.plan_summary(n) for n in nets]
+bad = []
+def work(i):
+    for _ in range(10):
+        if B.plan_summary(nets[i]) != alone[i]: bad.append(nets[i]['name'])
+threads = [threading.Thread(target=work, args=(i,)) for i in range(len(nets))]
+[t.start() for t in threads]; [t.join() for t in threads]
+assert not bad, bad
+got = []
+def take():
+    try: got.append(PBEngine(W.config('tiny_mlp'), torch_arena=False, static_arena=True))
+    except B.PBError: pass
+import torch
+torch.cuda.current_stream = lambda: type('S', (), dict(cuda_stream=None))
+for _ in range(20):
+    threads = [threading.Thread(target=take) for _ in range(6)]
+    [t.start() for t in threads]; [t.join() for t in threads]
+    assert len(got) == 1
+    got.pop().close()
+""")
