@@ -1,5 +1,7 @@
 """Helpers that drive the HIP engine and the CPU oracle on the same seeded
 inputs and compare them tensor by tensor."""
+import json
+
 import numpy as np
 
 import pb_workloads as W
@@ -80,6 +82,49 @@ def perturbed_oracle(net, seed, mitigation, eps, gen_seed=12345, lr=None, bwd_we
         for k in p:
             p[k] = p[k] * (1.0 + eps * torch.randn(p[k].shape, generator=g, dtype=torch.float64))
     return orc
+
+
+_references = {}
+
+
+def reference(net, ticks, mitigation=3, bwd_weights=0, **okw):
+    """The oracle and its probes (see the head of this file) after each of `ticks`: per tick count the weights, the velocity
+    and the losses, with the bound of every tensor and of every loss.  Computed once per network and options."""
+    key = json.dumps([net, ticks, mitigation, bwd_weights, okw], sort_keys=True, default=float)
+    if key in _references:
+        return _references[key]
+    xs, ys = W.sample_pool(net)
+    slices = tensor_slices(net)
+    kw = dict(mitigation=mitigation, bwd_weights=bwd_weights, **okw)
+    orc, probes = O.PBOracle(net, **kw), [perturbed_oracle(net, 42, mitigation, e, 12345 + i, bwd_weights=bwd_weights, **okw)
+                                          for i, e in enumerate(PERTURB)]
+    for shift in (RELU_BAND, -RELU_BAND):
+        probes.append(O.PBOracle(net, **kw))
+        probes[-1].relu_shift = shift
+    out = {}
+    for t in range(max(ticks)):
+        for o in [orc] + probes:
+            o.tick(xs[t % len(ys)], ys[t % len(ys)])
+        if t + 1 in ticks:
+            r = dict(slices=slices, read_weights=orc.read_weights(), read_velocity=orc.read_velocity(), loss_history=np.asarray(orc.loss_history()))
+            for k, tol in (("read_weights", TOL), ("read_velocity", 10 * TOL)):
+                sens = np.max([per_tensor_errors(getattr(o, k)(), r[k], slices) for o in probes], axis=0)
+                r[k + "_bounds"] = np.maximum(tol, SENS_FACTOR * sens)
+            sens = np.max([np.abs(np.asarray(o.loss_history()) - r["loss_history"]) for o in probes], axis=0)
+            r["loss_bounds"] = np.maximum(1e-4 * np.maximum(1.0, np.abs(r["loss_history"])), SENS_FACTOR * sens)
+            out[t + 1] = r
+    _references[key] = out
+    return out
+
+
+def assert_tensors_follow(eng, ref):
+    """Every parameter tensor, its velocity and every loss within its own bound."""
+    for k in ("read_weights", "read_velocity"):
+        err = per_tensor_errors(getattr(eng, k)(), ref[k], ref["slices"])
+        bad = [(ref["slices"][i][:2], float(err[i]), float(ref[k + "_bounds"][i])) for i in np.nonzero(err > ref[k + "_bounds"])[0]]
+        assert not bad, f"{k}: {bad}"
+    d = np.abs(np.asarray(eng.loss_history(), np.float64) - ref["loss_history"])
+    assert (d <= ref["loss_bounds"]).all(), (np.nonzero(d > ref["loss_bounds"])[0], d.max())
 
 
 class _OracleAsEngine:

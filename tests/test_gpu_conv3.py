@@ -8,6 +8,7 @@ import numpy as np
 import pytest
 
 import pb_workloads as W
+from tests.parity_util import assert_tensors_follow, reference
 
 pytestmark = pytest.mark.gpu
 
@@ -28,18 +29,15 @@ def test_direct_tiles_follow_the_oracle(widths, hw, budget):
 
 
 def _follow(net, tuning, tol=1e-4, **kw):
-    from oracle import pb_oracle as O
     from paper_2003_11666_amd import PBEngine
     (xs, ys), S = W.sample_pool(net), len(net["stages"])
-    orc, eng = O.PBOracle(net, **kw), PBEngine(net, tuning=tuning, **kw)
-    for n in (2 * S + 4, 1):
-        for _ in range(n):
-            t = orc.t
-            orc.tick(xs[t % len(ys)], ys[t % len(ys)])
+    eng, ref = PBEngine(net, tuning=tuning, **kw), reference(net, (2 * S + 4, 2 * S + 5), **kw)
+    for n, want in ref.items():
+        for t in range(eng.ticks, n):
             eng.tick(xs[t % len(ys)], ys[t % len(ys)])
         for k in ("read_weights", "read_velocity", "loss_history"):
-            got, want = getattr(eng, k)(), np.asarray(getattr(orc, k)(), np.float64)
-            assert np.linalg.norm(got - want) < tol * np.linalg.norm(want), k
+            assert np.linalg.norm(getattr(eng, k)() - want[k]) < tol * np.linalg.norm(want[k]), k
+        assert_tensors_follow(eng, want)
     eng.close()
 
 
