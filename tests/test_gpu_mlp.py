@@ -6,12 +6,21 @@ import numpy as np
 import pytest
 
 import pb_workloads as W
+from tests.parity_util import per_tensor_errors, tensor_slices
 
 pytestmark = pytest.mark.gpu
 
 
 def _net(dims, lr=0.01):
     return W._net("perceptron", W.mlp(dims), dims[0], 1, 1, dims[-1], lr, 0.9, 16, 5, 16)
+
+
+def _tensors_close(eng, orc, net):
+    """Every weight matrix and bias, and its velocity, by itself."""
+    slices = tensor_slices(net)
+    for k, tol in (("read_weights", 2e-5), ("read_velocity", 1e-3)):
+        err = per_tensor_errors(getattr(eng, k)(), getattr(orc, k)(), slices)
+        assert err.max() <= tol, (k, slices[int(err.argmax())], err.max())
 
 
 def _close(a, b, tol=2e-5):
@@ -39,6 +48,7 @@ def test_perceptron_follows_the_oracle(dims, form):
         at += n
     assert _close(a.read_weights(), orc.read_weights()) and _close(a.loss_history(), orc.loss_history())
     assert _close(a.read_velocity(), orc.read_velocity(), 1e-3)
+    _tensors_close(a, orc, net)
     for k in ("read_weights", "read_velocity", "loss_history"):
         assert np.array_equal(getattr(a, k)(), getattr(b, k)())
     # single-step launches of the phase kernel take over and hand back
@@ -49,6 +59,7 @@ def test_perceptron_follows_the_oracle(dims, form):
             orc.tick(xs[t % len(ys)], ys[t % len(ys)])
         at += 5
         assert _close(a.read_weights(), orc.read_weights()) and _close(a.loss_history(), orc.loss_history())
+        _tensors_close(a, orc, net)
     a.close()
     b.close()
 
