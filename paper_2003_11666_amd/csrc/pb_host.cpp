@@ -1990,9 +1990,6 @@ void order_steps(std::vector<std::pair<int, StepDesc>>& tagged, bool one_launch 
       } else if (d.kind == K_POST_FWD || d.kind == K_GNB_APPLY) {
         us = (d.flags & (F_POOL | F_DU_POOL)) ? 8.0 : 5.0;
       }
-      // partial sums of a split reduction, added up first: 10-12 us where the plain step takes 4-5 (VGG-11's first launch
-      // ended 4 us late with 80 workgroups that started last)
-      if (d.gparts > 1 && (d.kind == K_GNB_REDUCE || d.kind == K_GN_STATS || d.kind == K_GN_BWD)) us += 7.0;
       return (int64_t)(us * 1000.0);
     }
     if (d.kind == K_GEMM) {
