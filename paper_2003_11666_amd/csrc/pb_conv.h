@@ -146,8 +146,10 @@ __device__ __forceinline__ void step_dc_t(const LDesc& d, int tile_, int t, lflo
   __syncthreads();
   p_commit(smem);
   __syncthreads();
-  // Forward, a chunk's sum is formed by itself and added to the total: shorter chains of additions halve the rounding error
-  // of a long reduction, and with it the number of ReLU decisions that come out otherwise than in exact arithmetic.
+  // Forward, a chunk's sum is formed by itself and added to the total.  Against float64, the gradients of 3x3 weights
+  // (which carry the forward pass's error) are 0-5 % nearer than with one chain (2.52e-7 and 2.66e-7 at 128 and 256
+  // channels, equal at 64); beside the patch-based tiles VGG-11, the wide network and ResNet-50 at 64 pixels stand at
+  // 0.90, 0.72 and 0.98 of the error.
   constexpr bool BLOCKED = MODE == 1;
   v4f tot[BLOCKED ? MI : 1][BLOCKED ? NI : 1];
   if (BLOCKED) {
@@ -158,6 +160,7 @@ __device__ __forceinline__ void step_dc_t(const LDesc& d, int tile_, int t, lflo
   }
   const int sb_fl = 4 * UB * wk * plane;
   int g = 0;
+  PB_TS(9);
   for (int ch = ch0; ch < ch_end; ++ch) {
     const lfloat* cur = smem + ((ch - ch0) & 1) * buf_fl;
     lfloat* nxt = smem + (((ch - ch0) & 1) ^ 1) * buf_fl;
@@ -245,6 +248,7 @@ __device__ __forceinline__ void step_dc_t(const LDesc& d, int tile_, int t, lflo
     }
     __syncthreads();
   }
+  PB_TS(10);
   if (BLOCKED) {
 #pragma unroll
     for (int i = 0; i < MI; ++i)
@@ -444,6 +448,7 @@ __device__ __forceinline__ void step_dcw_t(const LDesc& d, int tile_, int t, lfl
   __syncthreads();
   p_commit(smem);
   __syncthreads();                           // (a step that is not live yet contracts nothing)
+  PB_TS(9);
   for (int ch = ch0; ch < ch_end; ++ch) {
     const lfloat* cur = smem + ((ch - ch0) & 1) * buf_fl;
     lfloat* nxt = smem + (((ch - ch0) & 1) ^ 1) * buf_fl;
@@ -494,6 +499,7 @@ __device__ __forceinline__ void step_dcw_t(const LDesc& d, int tile_, int t, lfl
     if (more) p_commit(nxt);
     __syncthreads();
   }
+  PB_TS(10);
   // ---- the waves' shares of the reduction, in order
   if (wk > 1) {
     if (wk_id > 0) {

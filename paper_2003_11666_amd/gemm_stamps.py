@@ -11,7 +11,8 @@ the time the tile's MFMAs would take if the workgroup had a compute unit's four 
 compute unit (ideal / (duration / 2)), and for the second chunk of the reduction of wavefront 0 (steps
 with at least two chunks): storing the prefetched patch into LDS (with the wait for its loads), storing
 the A block (with what was not prefetched), the barrier, issuing the next chunk's requests, the MFMA
-loop; then the epilogue.
+loop; then the epilogue.  Direct 3x3 tiles (pb_conv.h) are listed after them with the time before the loop over the
+chunks, in it, and after it (the waves' sums, the outputs or the update of the weights).
 """
 from __future__ import annotations
 
@@ -46,6 +47,14 @@ def main():
             v = m.groups()
             plan[(int(v[0]), int(v[3]), int(v[4]))] = dict(N=int(v[5]), Q=int(v[6]), waves=v[7], tile=f"{v[9]}x{v[10]}x{v[11]}",
                                                            chunks=f"{v[12]}/{v[13]}", QC=int(v[14]))
+    direct = {}
+    for l in binding.plan_summary(net).splitlines():
+        m = re.match(r"stage\s+(\d+) phase (\d+) gemm\s+tiles\s+(\d+) .*\| gm(\d) M(\d+) N(\d+) Q(\d+) direct waves (\S+) mi(\d) ni(\d) "
+                     r"tile (\d+)x(\d+) chunks (\d+)/(\d+)", l)
+        if m:
+            v = m.groups()
+            direct[(int(v[0]), int(v[3]), int(v[4]))] = dict(N=int(v[5]), Q=int(v[6]), waves=f"{v[7]} {v[8]}x{v[9]}", tile=f"{v[10]}x{v[11]}",
+                                                             chunks=f"{v[12]}/{v[13]}")
     eng = binding.PBEngine(net, lr=net["lr"], momentum=net["momentum"], seed=W.WEIGHT_SEED)
     lib = binding.load_library()
     x, y = W.sample_pool(net)
@@ -81,7 +90,7 @@ def main():
                 other[int(r[i, 0])] += float(ts[:, 11].max() - ts[0, 0])
         print(f"launch {ph} (grid {grid}): microseconds; chunk columns are means over the step's workgroups")
         print("stage gm      M     N     Q tile      chunks   QC waves     n    dur  ideal   eff | patch     A  barr issue  mfma |  epi")
-        rows = []
+        rows, drows = [], []
         for k, v in agg.items():
             a = np.array(v)
 
@@ -92,6 +101,9 @@ def main():
             dur = float(np.mean(a[:, 11] - a[:, 0]))
             pl = plan.get(k)
             if pl is None:
+                if k in direct:
+                    pl = direct[k]
+                    drows.append((len(v) * dur, k, pl, len(v), dur, 2.0 * k[2] * pl["N"] * pl["Q"] / len(v) / (CU_GFLOPS * 1e3), dl(9, 0), dl(10, 9), dl(11, 10)))
                 continue
             ideal = 2.0 * k[2] * pl["N"] * pl["Q"] / len(v) / (CU_GFLOPS * 1e3)
             rows.append((len(v) * dur, k, pl, len(v), dur, ideal, ideal / (dur / 2),
@@ -103,6 +115,15 @@ def main():
             k, pl = q[1], q[2]
             print(f"{k[0]:5d} {k[1]:2d} {k[2]:6d} {pl['N']:5d} {pl['Q']:5d} {pl['tile']:9s} {pl['chunks']:>6s} {pl['QC']:4d} {pl['waves']:5s} "
                   f"{q[3]:5d} {q[4]:6.1f} {q[5]:6.1f} {100 * q[6]:5.0f}% | " + " ".join(f"{z:5.2f}" for z in q[7:12]) + f" | {q[12]:4.2f}")
+        if drows:
+            print("direct 3x3 tiles: stage gm M N Q tile chunks waves n dur ideal eff | before loop, loop, after; loop eff (ideal / (loop / 2))")
+            for q in sorted(drows, key=lambda q: -q[0]):
+                k, pl = q[1], q[2]
+                print(f"{k[0]:5d} {k[1]:2d} {k[2]:6d} {pl['N']:5d} {pl['Q']:5d} {pl['tile']:9s} {pl['chunks']:>6s} {pl['waves']:11s} {q[3]:5d} {q[4]:6.1f} {q[5]:6.1f} "
+                      f"{100 * q[5] / (q[4] / 2):5.0f}% | {q[6]:5.2f} {q[7]:5.2f} {q[8]:5.2f}  {100 * q[5] / (q[7] / 2):5.0f}%")
+            drows = [q for q in drows if q[7] == q[7]]
+            dt, di, lp = sum(q[0] for q in drows), sum(q[3] * q[5] for q in drows), sum(q[3] * q[7] for q in drows)
+            print(f"direct workgroups: {dt:.0f} workgroup-us, ideal {2 * di:.0f}: efficiency {200 * di / dt:.0f} %, in the loop {200 * di / lp:.0f} %")
         print(f"GEMM workgroups: {tot:.0f} workgroup-us ({tot / 512:.0f} us over 512 slots), ideal {tot_ideal:.0f}: "
               f"efficiency {100 * tot_ideal / max(tot, 1):.0f} %; other step kinds {sum(other.values()):.0f} workgroup-us")
 

@@ -7,7 +7,7 @@ import numpy as np
 import pb_workloads as W
 from oracle import pb_oracle as O
 
-TOL = 1e-5   # per-tick relative weight tolerance for fp32 (stated by the benchmark spec)
+TOL = 1e-5   # per-tick relative weight tolerance for fp32
 # The tolerance is taken PER TENSOR and is TOL unless one of three conditioning probes says that
 # this very tensor cannot be pinned that tightly at this tick.  The probes are three more runs of the
 # oracle on the same inputs:
