@@ -938,9 +938,11 @@ bool make_d1(const pb_ctx* c, int mode, int C, int H, int W, int K, int OH, int 
 //   work (tiles x duration); if none does, the one with the shortest tile.  Work below
 //   small_work microseconds (256: half a microsecond of the chip's 512 places) counts
 //   alike there and the shortest tile wins: the first layer of a network with post-layer
-//   norms shares its phase with elementwise steps and is the longest workgroup in it
-//   (VGG-11: 8 tiles of 14 us -> 32 tiles, 86 -> 82.6 us per tick).  In the full forward
-//   phase of a network with pre-layer norms more tiles only cost (wide: 125.2 -> 126.4).
+//   norms shares its phase with elementwise steps and is the longest workgroup in it.
+//   Measured, us per tick without and with: VGG-11 87.6 and 82.7; in three other VGG
+//   networks (32, 48 and 64 channels at 20-40 pixels) the plan is the same either way.
+//   In networks with pre-layer norms it makes little difference (0 there): seven basic
+//   ResNets -0.6 to +0.9 %, the wide one 125.7 without and 126.8 with.
 bool make_gemm(int mode, int C, int H, int W, int K, int OH, int OW, int k, int s, int pad,
                const GemmCfg* like, GemmCfg* out, bool allow_vec = false, int max_sub = 16, bool flat = false,
                int max_parts = 1, double small_work = 0.0) {
@@ -2023,7 +2025,9 @@ void order_steps(std::vector<std::pair<int, StepDesc>>& tagged, bool one_launch 
   // 170 us per tick, VGG-11 96 -> 93).  In a long phase (ResNet-50's GEMM launches) they stay in the order of
   // cost, where they fill slots that would otherwise wait for bandwidth nobody uses (1 094 us against 1 112), and so do
   // a few of them (fewer than a quarter of the slots: small parameters, sums of split reductions), which take no
-  // bandwidth to speak of and at the end only prolong the phase (ResNet-50's third launch: 603 -> 591 us per tick).
+  // bandwidth to speak of.  The line of 128 matters for one of 27 networks measured: ResNet-50 at 224 pixels 592 us per
+  // tick with all of them last, 582 with it; a basic network at 24 pixels 85.8 and 86.8, the others within 0.7 %.
+  // Never last at all: VGG-11 88.3 against 82.7, but a ResNet-50 at 64 pixels 222 against 228.
   std::vector<char> upd_last;
   if (g_tile_budget_us > 0) {
     std::vector<double> gemm_us;
@@ -3008,8 +3012,10 @@ int init_common(pb_ctx** out, const pb_net_desc* net, const int32_t* delays, flo
   // each other inside a tick).
   //  * One launch per tick.  By policy only where the tick's workgroups number no more than the compute units:
   //    then all of them are resident at once, no waiting workgroup can hold a producer's place, and the launch
-  //    boundary saved outweighs what the per-workgroup release and acquire cost (measured: a tick of 165
-  //    workgroups gains 7 %, one of 944 workgroups takes twice as long).
+  //    boundary saved outweighs what the per-workgroup release and acquire cost.  Measured, us per tick with a launch
+  //    per phase and with one, by workgroups: convolution networks of 42 19.0 and 13.4, 53 (four phases) 25.6 and
+  //    18.6, 101 21.2 and 15.6, 136 23.4 and 19.4, 143 17.5 and 17.6, 248 22.6 and 20.2; a perceptron of 165 in this
+  //    form 17.0 and 14.5; ResNet-20, 944 workgroups, 24 and 46.
   //  * The last phases in one launch.  A deep network's last phases hold the dependency chains of one or two
   //    stages only (the loss stage runs forward and backward in the same tick, the first stage's weight
   //    gradient is split and summed): a few hundred workgroups each, a launch each.  On request (tail_merge n)

@@ -649,8 +649,12 @@ __device__ __forceinline__ void step_gnb_reduce_wave(const LDesc& d, int tile, i
 
 // Maps of more than 256 and fewer than 1024 pixels (a multiple of 4) with a plain gradient buffer: one wavefront per
 // channel, the channel in four 16-byte requests per lane and operand, no barrier.  Bound by the memory round trip: a
-// workgroup per channel holds a slot for 3.7 us with one request per lane (ResNet-50, 2816 channels of 28x28: 590 -> 581 us
-// per tick).  At 1024 pixels that request fills every lane and the workgroup is the better form (wide: 125 against 127 us).
+// workgroup per channel holds a slot for 3.7 us with one request per lane.  Measured, us per tick with a workgroup per
+// channel and with a wavefront: ResNet-50 at 224 pixels (2816 channels of 28x28) 590.3 and 581.7; basic networks at 24, 28
+// and 40 pixels 87.3 and 86.8, 95.3 and 95.0, 133.8 and 134.3; a bottleneck network at 224 465.4 and 463.7.  At 1024 pixels,
+// where that request fills every lane, it depends: the wide network 125.7 and 128.1, but a basic one of 128 and 256 channels
+// 253.7 and 252.1 and bottleneck ones at 128 pixels 227.6 and 225.0, 118.1 and 116.9; the line stands below, where no
+// network loses more than 0.4 %.
 __device__ __forceinline__ void step_gnb_reduce_wave4(const LDesc& d, int tile, int t) {
   const int lane = threadIdx.x & 63, c = tile * (BLK / 64) + UNI((int)(threadIdx.x >> 6));
   const int C = UNI(d.C), G = UNI(d.G), HW = UNI(d.H) * UNI(d.W);
