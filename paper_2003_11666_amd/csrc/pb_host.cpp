@@ -8,6 +8,7 @@
 #include <stdlib.h>
 #include <string.h>
 #include <sys/stat.h>
+#include <unistd.h>
 
 #include <algorithm>
 #include <atomic>
@@ -2461,6 +2462,7 @@ struct WaitDevice {
   pb_ctx* last = nullptr;        // crowded: context of the latest launch, which ev follows
   hipEvent_t ev = nullptr;
   int lock_fd = -2;              // file with the shares' locks (-2: not opened yet, -1: none to be had, other processes are not seen)
+  pid_t owner = 0;               // the process that opened it (a forked child has the same open file, and its locks are not its own)
   unsigned held = 0;             // bit per share this process has locked
 };
 WaitDevice g_wait_dev[MAX_STATIC_DEVS];
@@ -2497,7 +2499,7 @@ bool claim_shares(WaitDevice& d) {
   int most = 0, sum = 0;
   for (pb_ctx* o : d.busy) { most = std::max(most, o->wait_shares); sum += o->wait_shares; }
   const int want = sum > WAIT_SHARES ? most : sum;
-  if (d.lock_fd < 0) return true;
+  if (d.lock_fd < 0 || d.owner != getpid()) return true;
   int have = __builtin_popcount(d.held);
   const unsigned before = d.held;
   // neighbouring shares in one call where that is possible, else one by one
@@ -2572,7 +2574,7 @@ int wait_enter(pb_ctx* c, int shares) {
   WaitDevice& d = g_wait_dev[c->dev];
   std::lock_guard<std::mutex> lock(d.mu);
   if (!d.ev) HIP_TRY(hipEventCreateWithFlags(&d.ev, hipEventDisableTiming));
-  if (d.lock_fd == -2) d.lock_fd = open_share_file(c->dev);
+  if (d.lock_fd == -2) { d.lock_fd = open_share_file(c->dev); d.owner = getpid(); }
   d.busy.reserve(d.contexts + 1);   // (a tick needs no memory)
   ++d.contexts;
   c->wait_shares = shares;

@@ -97,6 +97,7 @@ def test_other_processes_on_the_gpu(lib):
     launches; when it has waited for its stream, is gone or was small enough, they don't.  An idle context holds nothing."""
     gpu = f"test-{os.getpid()}"
     other = host_stub.prelude(lib) + """
+import os
 net = {"wide": mlp(1024, 1024, 1024, 1024, 1024, 100), "small": mlp(64, 128, 128, 128, 10), "conv": W.config("small_resnet")}[sys.argv[1]]
 x = np.zeros(net['in_c'] * net['in_h'] * net['in_w'], np.float32)
 e = engine(net)
@@ -104,7 +105,11 @@ for line in sys.stdin:
     put('mlp_launches', 0), put('fused_launches', 0), put('plain_launches', 0)
     if line == 'tick\\n': e.tick(x, 0)
     if line == 'sync\\n': e.sync()
-    if line == 'die\\n': import os; os._exit(0)
+    if line == 'die\\n': os._exit(0)
+    if line == 'fork\\n':                     # a child (a loader's worker, say) that cleans up what it inherited
+        pid = os.fork()
+        if pid == 0: e.sync(); os._exit(0)
+        os.waitpid(pid, 0)
     print(get('mlp_launches'), get('fused_launches'), get('plain_launches'), flush=True)
 """
     try:
@@ -122,6 +127,8 @@ def plain(o): r = o('tick'); return r[:2] == ['0', '0'] and int(r[2]) >= 2
 assert a('tick') == mlp                                  # six eighths
 assert plain(b) and plain(conv)                          # (four eighths)
 assert small('tick') == mlp and a('tick') == mlp
+a('fork')
+for _ in range(64): assert plain(b)
 a('sync')
 for _ in range(63): r = b('tick')                        # asked again 64 ticks after the refusal
 assert r[0] == '0' and b('tick') == mlp and plain(a)
