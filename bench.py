@@ -10,7 +10,7 @@ HBM before the timed region starts.  Prints ONE JSON line:
 
   value / ms_per_step   exactly --steps ticks of --config, host clock, synchronised on both sides
   steady_state          median of 5 windows of >= 1000 ticks (HIP events around each window, host clock beside)
-  roofline              the dominant kernel k_phase: algorithmic bytes per launch / mean launch duration
+  roofline              the dominant kernel (k_phase; k_mlp in the mlp configuration): algorithmic bytes per launch / mean launch duration
   all_configs           the other benchmark configurations measured the same way, oracle beside each
   update_standalone     the update arithmetic over 1 GiB arrays: the kernel's ceiling beyond every cache
   cpu_baseline          the float64 oracle on the host, one thread (primary) and all cores
@@ -26,12 +26,12 @@ ROOT = os.path.dirname(os.path.abspath(__file__))
 sys.path.insert(0, ROOT)
 
 HBM_PEAK_GBS = 8000.0      # MI355X published HBM3E bandwidth
-# Bytes that crossed the L2 / fabric boundary per algorithmic byte of a k_phase launch, from `rocprofv3 --pmc
-# FETCH_SIZE` and `--pmc WRITE_SIZE` runs of this script (each scaled by what the counter reads for a plain copy of
-# known size): profiles/k_phase_counters_all_configs.md.  A figure from those runs, made before the direct 3x3 tiles, the
-# updates inside weight-gradient tiles and the perceptron kernel, not a measurement of this run.
-KPHASE_TRAFFIC_PER_ALGORITHMIC_BYTE = {"resnet20": 2.59, "mlp": 1.76, "vgg11": 0.88, "wide": 1.26, "resnet50": 1.64}
-TRAFFIC_SOURCE = "profiles/k_phase_counters_all_configs.md (rocprofv3 --pmc FETCH_SIZE / WRITE_SIZE passes over this command on an earlier build; not measured by this run)"
+# Bytes that crossed the L2 / fabric boundary per algorithmic byte of a tick, from `rocprofv3 --pmc FETCH_SIZE` and
+# `--pmc WRITE_SIZE` runs of this script (each scaled by what the counter reads for a plain copy of known size):
+# profiles/k_phase_counters_all_configs.md.  Figures from those runs, not a measurement of this one.  (The mlp's are of
+# k_mlp, in launches of 688 ticks on average.)
+TRAFFIC_PER_ALGORITHMIC_BYTE = {"resnet20": 2.59, "mlp": 4.8, "vgg11": 0.88, "wide": 1.33, "resnet50": 1.71}
+TRAFFIC_SOURCE = "profiles/k_phase_counters_all_configs.md (rocprofv3 --pmc FETCH_SIZE / WRITE_SIZE passes over this command; not measured by this run)"
 UPDATE_TRAFFIC_PER_ALGORITHMIC_BYTE = 1.0   # profiles/k_update_flat_1GiB_arrays.md
 
 
@@ -43,6 +43,14 @@ def tick_algorithmic_bytes(net, n_params):
     import pb_workloads as W
     a = sum(c * h * w for (_, (c, h, w)) in W.stage_shapes(net)[:-1])
     return 36 * n_params + 6 * a * 4
+
+
+def register_form_bytes(net, n_params, ticks_per_launch):
+    """A tick of the kernel that keeps a perceptron's parameters in registers: its sample, every stage-boundary value and its
+    gradient written and read once as 8-byte messages, and its share of the launch's 16 B per parameter (w, v read, written)."""
+    import pb_workloads as W
+    a = sum(c * h * w for (_, (c, h, w)) in W.stage_shapes(net)[:-1])
+    return 4 * net["in_c"] * net["in_h"] * net["in_w"] + 4 * 8 * a + 16 * n_params / ticks_per_launch
 
 
 def oracle_rate(net, budget_s, threads):
@@ -122,11 +130,19 @@ def measure(name, steps, warmup, windows=5, window_ticks=1000, update_share=Fals
     launches = n_launch / 16
     tick_us = 1e3 * statistics.median(ev_ms) / window_ticks
     tick_bytes = tick_algorithmic_bytes(net, n_params)
+    in_registers = launches < 1               # several ticks a launch: a perceptron whose parameters stay in registers
+    if in_registers:
+        eng.profile_begin(window_ticks)
+        eng.run_resident(xd, yd, done, window_ticks)
+        n_launch, _ = eng.profile_end(0)
+        done += window_ticks
+        launches = n_launch / window_ticks
+        tick_bytes = register_form_bytes(net, n_params, window_ticks / n_launch)
     res = {"net": net, "S": S, "n_params": n_params, "warm": warm, "dt": dt, "ticks_per_s_cli": steps / dt,
            "steady": {"ticks_per_s": 1e6 / tick_us, "us_per_tick": tick_us, "windows": windows, "window_ticks": window_ticks,
                       "event_ms_per_window": [round(x, 3) for x in ev_ms],
                       "ticks_per_s_host_clock": 1e3 * window_ticks / statistics.median(wall_ms)},
-           "launches": launches, "tick_bytes": tick_bytes, "pool": len(ys)}
+           "launches": launches, "tick_bytes": tick_bytes, "pool": len(ys), "in_registers": in_registers}
     if update_share:
         # the update steps inside the tick, one launch per step: 24 B per parameter (w, v, g read; w, v, w_hat written)
         eng.set_launch_mode(1)
@@ -149,14 +165,15 @@ def measure(name, steps, warmup, windows=5, window_ticks=1000, update_share=Fals
 
 
 def roofline_of(r, name):
-    """k_phase of one configuration: algorithmic bytes per launch over the mean launch duration.  The
+    """The tick's kernel of one configuration: algorithmic bytes per launch over the mean launch duration.  The
     launches of a window run back to back on one stream, so the window's event time over its number
     of launches bounds the mean kernel duration from above (it holds the dispatch gaps too)."""
     per_launch = r["tick_bytes"] / r["launches"]
     launch_us = r["steady"]["us_per_tick"] / r["launches"]
     achieved = per_launch / (launch_us * 1e-6) / 1e9
-    ratio = KPHASE_TRAFFIC_PER_ALGORITHMIC_BYTE.get(name)
-    return {"kernel": "k_phase (every step of a tick: forward, backward and update of all stages)", "bound": "hbm",
+    ratio = TRAFFIC_PER_ALGORITHMIC_BYTE.get(name)
+    return {"kernel": "k_mlp (many ticks a launch, parameters in registers: bound by the messages' round trips, not by bytes)"
+                      if r["in_registers"] else "k_phase (every step of a tick: forward, backward and update of all stages)", "bound": "hbm",
             "achieved": achieved, "peak": HBM_PEAK_GBS, "unit": "GB/s", "frac": achieved / HBM_PEAK_GBS,
             "traffic": ratio * per_launch if ratio else None, "traffic_source": TRAFFIC_SOURCE if ratio else None,
             "avg_launch_us": launch_us, "launches_per_tick": r["launches"], "algorithmic_bytes_per_launch": per_launch}
@@ -217,7 +234,7 @@ def main():
                  "windows": f"{q['steady']['windows']} x {q['steady']['window_ticks']} ticks, median",
                  "launches_per_tick": q["launches"], "algorithmic_bytes_per_tick": q["tick_bytes"],
                  "tick_roofline_frac": q["tick_bytes"] / (q["steady"]["us_per_tick"] * 1e-6) / 1e9 / HBM_PEAK_GBS,
-                 "traffic_per_algorithmic_byte": KPHASE_TRAFFIC_PER_ALGORITHMIC_BYTE.get(name), "traffic_source": TRAFFIC_SOURCE,
+                 "traffic_per_algorithmic_byte": TRAFFIC_PER_ALGORITHMIC_BYTE.get(name), "traffic_source": TRAFFIC_SOURCE,
                  "avg_launch_us": rf["avg_launch_us"], "final_loss_mean_last_200": q["final_loss"],
                  "dtype": "f32 (activations rounded to bf16 at stage boundaries)" if q["net"].get("act_dtype") == "bf16" else "f32"}
             if "update_in_tick" in q:

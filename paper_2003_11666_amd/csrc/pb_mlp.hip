@@ -19,7 +19,7 @@
 // tick, are enough: a workgroup finishes tick t only after every workgroup of both neighbours has published tick t - 1,
 // i.e. has consumed what it was sent for tick t - 1.  (They publish in every tick, zeros while the pipeline fills.)
 // The waits need all workgroups resident: one per compute unit, never more than the GPU has, and the host keeps launches
-// of several contexts apart.  A wait is bounded by the clock (4 s); on expiry the error word is set and the grid drains.
+// of several contexts and processes apart (WaitDevice in pb_host.cpp).  A wait is bounded by the clock (4 s); on expiry the error word is set and the grid drains.
 #include "pb_device.h"
 #include "pb_mlp.h"
 #include "pb_wave.h"
