@@ -2494,11 +2494,24 @@ bool set_share_lock(int fd, short type, int first, int n) {
   return fcntl(fd, F_OFD_SETLK, &fl) == 0 || (errno != EAGAIN && errno != EACCES);   // (a system without such locks sees nobody)
 }
 
+// Shares of the launches that may run at the same time: of contexts on one stream, those of the largest.
+int shares_busy(const WaitDevice& d) {
+  int sum = 0;
+  for (size_t i = 0; i < d.busy.size(); ++i) {
+    bool largest = true;
+    for (size_t j = 0; j < d.busy.size(); ++j)
+      if (i != j && d.busy[j]->stream == d.busy[i]->stream)
+        largest = largest && (d.busy[j]->wait_shares < d.busy[i]->wait_shares || (d.busy[j]->wait_shares == d.busy[i]->wait_shares && i < j));
+    if (largest) sum += d.busy[i]->wait_shares;
+  }
+  return sum;
+}
+
 // Holds exactly the shares the busy contexts need (those of a crowded GPU take turns): false if others hold too many.
 bool claim_shares(WaitDevice& d) {
-  int most = 0, sum = 0;
-  for (pb_ctx* o : d.busy) { most = std::max(most, o->wait_shares); sum += o->wait_shares; }
-  const int want = sum > WAIT_SHARES ? most : sum;
+  int most = 0;
+  for (pb_ctx* o : d.busy) most = std::max(most, o->wait_shares);
+  const int sum = shares_busy(d), want = sum > WAIT_SHARES ? most : sum;
   if (d.lock_fd < 0 || d.owner != getpid()) return true;
   int have = __builtin_popcount(d.held);
   const unsigned before = d.held;
@@ -2526,12 +2539,6 @@ bool claim_shares(WaitDevice& d) {
   return ok;
 }
 
-bool shares_fit(const WaitDevice& d) {
-  int sum = 0;
-  for (pb_ctx* o : d.busy) sum += o->wait_shares;
-  return sum <= WAIT_SHARES;
-}
-
 // Before a launch whose workgroups wait for each other: may it be made?
 bool wait_begin(pb_ctx* c) {
   if (!c->wait_shares || c->wait_busy) return true;
@@ -2540,10 +2547,10 @@ bool wait_begin(pb_ctx* c) {
   std::lock_guard<std::mutex> lock(d.mu);
   d.busy.push_back(c);
   bool ok = claim_shares(d);
-  if (ok && !d.crowded && !shares_fit(d)) {
+  if (ok && !d.crowded && shares_busy(d) > WAIT_SHARES) {
     // (launches made so far have no event behind them: this context's stream waits for them all, the others for it)
     for (pb_ctx* o : d.busy)
-      if (o != c) ok = ok && hipEventRecord(d.ev, o->stream) == hipSuccess && hipStreamWaitEvent(c->stream, d.ev, 0) == hipSuccess;
+      if (o->stream != c->stream) ok = ok && hipEventRecord(d.ev, o->stream) == hipSuccess && hipStreamWaitEvent(c->stream, d.ev, 0) == hipSuccess;
     ok = ok && hipEventRecord(d.ev, c->stream) == hipSuccess;
     d.crowded = ok;
     d.last = c;
@@ -2565,7 +2572,7 @@ void wait_end(pb_ctx* c) {
   d.busy.erase(std::remove(d.busy.begin(), d.busy.end(), c), d.busy.end());
   if (d.last == c) d.last = nullptr;   // (and with it every launch before it has ended)
   // (contexts left go on taking turns if another process has what they would need side by side)
-  const bool fit = shares_fit(d), claimed = claim_shares(d);
+  const bool fit = shares_busy(d) <= WAIT_SHARES, claimed = claim_shares(d);
   d.crowded = d.crowded && !(fit && claimed);
   c->wait_busy = false;
 }
@@ -2595,7 +2602,7 @@ int waiting_launch(pb_ctx* c, F&& launch) {
   if (!c->wait_shares) { launch(); return PB_OK; }
   WaitDevice& d = g_wait_dev[c->dev];
   std::lock_guard<std::mutex> lock(d.mu);
-  if (d.crowded && d.last && d.last != c) HIP_TRY(hipStreamWaitEvent(c->stream, d.ev, 0));
+  if (d.crowded && d.last && d.last->stream != c->stream) HIP_TRY(hipStreamWaitEvent(c->stream, d.ev, 0));
   launch();
   HIP_TRY(hipGetLastError());
   if (d.crowded) { HIP_TRY(hipEventRecord(d.ev, c->stream)); d.last = c; }

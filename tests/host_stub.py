@@ -31,7 +31,16 @@ def prelude(path):
             "from paper_2003_11666_amd import PBEngine, binding as B\nlib = host_stub.load(%r)\n"
             "get, put = (lambda n: lib.stub_get(n.encode())), (lambda n, v: lib.stub_set(n.encode(), v))\n"
             "def mlp(*dims): return W._net('p', W.mlp(dims), dims[0], 1, 1, dims[-1], 0.01, 0.9, 16, 5, 16)\n"
-            "def engine(net, **kw): return PBEngine(net, torch_arena=False, **kw)\n" % (ROOT, path))
+            "marshal, streams = B.marshal_net, [0]\n"
+            "def engine(net, stream=None, **kw):          # (a stream of its own unless one is named)\n"
+            "    streams[0] += 1\n"
+            "    def on_stream(*a, **k):\n"
+            "        d, keep = marshal(*a, **k)\n"
+            "        d.stream = 16 * streams[0] if stream is None else stream\n"
+            "        return d, keep\n"
+            "    B.marshal_net = on_stream\n"
+            "    try: return PBEngine(net, torch_arena=False, **kw)\n"
+            "    finally: B.marshal_net = marshal\n" % (ROOT, path))
 
 
 def run(path, body, **kw):

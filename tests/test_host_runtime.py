@@ -89,6 +89,13 @@ for cus, nets, together in [(256, [wide, small], True), (256, [wide, wide], Fals
     assert get('waits') == 0
     for e in engines:
         e.close()
+    engines = [engine(n, stream=16) for n in nets]      # nor do launches on one stream wait for each other's events
+    for _ in range(2):
+        for n, e in zip(nets, engines):
+            e.tick(np.zeros(n['in_c'] * n['in_h'] * n['in_w'], np.float32), 0)
+    assert get('waits') == 0
+    for e in engines:
+        e.close()
 """)
 
 
