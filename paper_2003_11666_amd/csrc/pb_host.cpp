@@ -1851,6 +1851,8 @@ void compile_steps_once(pb_ctx* c, std::vector<std::pair<int, StepDesc>>& out) {
       const int st_ = pr.second.stage;
       pr.first = is_bwd(pr.second) ? baseB[st_] + (pr.first - bwd0[st_]) : baseF[st_] + pr.first;
     }
+    for (int s = 0; s < S; ++s)
+      if (fusedw[s].phase >= 0) fusedw[s].phase += baseB[s] - bwd0[s];
   }
   // 16-byte loads of the A operand need a 16-byte aligned operand (the arena is)
   for (auto& pr : out) {
