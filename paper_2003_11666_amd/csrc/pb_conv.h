@@ -501,6 +501,7 @@ __device__ __forceinline__ void step_dcw_t(const LDesc& d, int tile_, int t, lfl
   }
   PB_TS(10);
   // ---- the waves' shares of the reduction, in order
+  const int flags = UNI(d.flags), ch = c0 + wn_id * 16 + li;
   if (wk > 1) {
     if (wk_id > 0) {
 #pragma unroll
@@ -509,7 +510,8 @@ __device__ __forceinline__ void step_dcw_t(const LDesc& d, int tile_, int t, lfl
         for (int j = 0; j < 9; ++j) *(lv4*)(smem + (((wv - (wv >> lg(wk)) - 1) * MI * 9 + k * 9 + j) * 64 + lane) * 4) = acc[k][j];
     }
     __syncthreads();
-    if (wk_id != 0) return;
+  }
+  if (wk > 1 && wk_id == 0) {
     for (int w2 = 1; w2 < wk; ++w2) {
       const int ow = wv + w2;
 #pragma unroll
@@ -518,60 +520,47 @@ __device__ __forceinline__ void step_dcw_t(const LDesc& d, int tile_, int t, lfl
         for (int j = 0; j < 9; ++j) acc[k][j] += *(const lv4*)(smem + (((ow - (ow >> lg(wk)) - 1) * MI * 9 + k * 9 + j) * 64 + lane) * 4);
     }
   }
-  // ---- lane holds, for rows 4 kq + r and channel li, the nine taps: 36 contiguous bytes
-  const int flags = UNI(d.flags), ch = c0 + wn_id * 16 + li;
   if (flags & F_UPD_W) {
-    // the update of the tile's weights: no gradient in memory (8 bytes per weight and a launch's tail saved), and the
-    // parameters stream while other tiles contract
-    const float fa = UNIF(d.fa), fb = UNIF(d.fb), lrT = UNIF(d.flrT), lr = UNIF(d.flr), fm = UNIF(d.fm);
-    const bool wform = flags & F_LWP_W, perm = flags & F_WHAT_PERM;
-    gfloat* wp = GP((float*)d.w);
-    gfloat* vp = GP(d.v);
-    gfloat* hp = GP(d.what);
+    // the update of the tile's weights: no gradient in memory (8 bytes per weight and a launch's tail saved).  The tile lies
+    // behind the waves' shares: 2304 MI floats for all four waves' shares and sums together, 4 more per row.
+    const int pitch = 9 * CT + 4, MT = UNI(d.g.MT), mt0 = tm * MT;
+    lfloat* T = smem + (wk > 1 ? (4 - (4 >> lg(wk))) * MI * 9 * 256 : 0);
+    const bool perm = flags & F_WHAT_PERM;
+    tile_update<4>(d, T, pitch, MT, 9 * CT / 4, (unsigned)(mt0 * C + c0) * 9u, 9u * (unsigned)C, perm, [&]() {
+      if (wk_id != 0) return;
 #pragma unroll
-    for (int k = 0; k < MI; ++k) {
-      float w[4][9], v[4][9];
+      for (int k = 0; k < MI; ++k)
 #pragma unroll
-      for (int r = 0; r < 4; ++r) {
-        const unsigned o = (unsigned)((m0 + k * 16 + 4 * kq + r) * C + ch) * 9u;
-        const v4f w0 = *(const gv4u*)(wp + o), w1 = *(const gv4u*)(wp + o + 4), v0 = *(const gv4u*)(vp + o), v1 = *(const gv4u*)(vp + o + 4);
+        for (int r = 0; r < 4; ++r) {
+          lfloat* q = T + ((wm_id * MI + k) * 16 + 4 * kq + r) * pitch + (wn_id * 16 + li) * 9;
 #pragma unroll
-        for (int e = 0; e < 4; ++e) { w[r][e] = w0[e]; w[r][4 + e] = w1[e]; v[r][e] = v0[e]; v[r][4 + e] = v1[e]; }
-        w[r][8] = wp[o + 8];
-        v[r][8] = vp[o + 8];
-      }
-      v4f h[9];                            // the 36 predicted weights, rows outermost
-#pragma unroll
-      for (int r = 0; r < 4; ++r)
-#pragma unroll
-        for (int e = 0; e < 9; ++e) {
-          const float g = acc[k][e][r], w_old = w[r][e];
-          v[r][e] = fmaf(fm, v[r][e], g);
-          w[r][e] = fmaf(-lr, fmaf(fa, v[r][e], fb * g), w_old);
-          h[(9 * r + e) >> 2][(9 * r + e) & 3] = wform ? fmaf(lrT, w[r][e] - w_old, w[r][e]) : fmaf(-lrT, v[r][e], w[r][e]);
+          for (int e = 0; e < 9; ++e) q[e] = acc[k][e][r];
         }
+    });
+    if (perm) {
+      // the predicted weights in the order of the forward tiles' lanes: 16 threads per block of 16 rows x 4 channels
+      __syncthreads();
+      const int nb = (MT >> 4) * (CT >> 2), tl = tid & 15;
+      int off[9][4];
 #pragma unroll
-      for (int r = 0; r < 4; ++r) {
-        const unsigned o = (unsigned)((m0 + k * 16 + 4 * kq + r) * C + ch) * 9u;
-        *(gv4u*)(wp + o) = (v4f){w[r][0], w[r][1], w[r][2], w[r][3]};
-        *(gv4u*)(wp + o + 4) = (v4f){w[r][4], w[r][5], w[r][6], w[r][7]};
-        wp[o + 8] = w[r][8];
-        *(gv4u*)(vp + o) = (v4f){v[r][0], v[r][1], v[r][2], v[r][3]};
-        *(gv4u*)(vp + o + 4) = (v4f){v[r][4], v[r][5], v[r][6], v[r][7]};
-        vp[o + 8] = v[r][8];
-        if (!perm) {
+      for (int i = 0; i < 9; ++i)
 #pragma unroll
-          for (int e = 0; e < 9; ++e) hp[o + e] = h[(9 * r + e) >> 2][(9 * r + e) & 3];
+        for (int e = 0; e < 4; ++e) {
+          const int x = 4 * (tl + 16 * i) + e, s = fdiv(x, 1.f / 9.f), row = s & 15;
+          off[i][e] = row * pitch + (s >> 4) * 9 + x - 9 * s;
         }
-      }
-      if (perm) {
-        gfloat* q = hp + (size_t)((unsigned)(((m0 >> 4) + k) * (C >> 2) + (ch >> 2)) * 64u + (unsigned)((ch & 3) * 16 + 4 * kq)) * 9u;
+      for (int b = tid >> 4; b < nb; b += 16) {
+        const int rt = b >> (2 + lg(wn)), c4 = b & (4 * wn - 1);
+        const lfloat* p = T + 16 * rt * pitch + 36 * c4;
+        gfloat* q = GP(d.what) + (size_t)((unsigned)(((mt0 >> 4) + rt) * (C >> 2) + (c0 >> 2) + c4) * 576u) + 4 * tl;
 #pragma unroll
-        for (int e = 0; e < 9; ++e) *(gv4*)(q + 4 * e) = h[e];
+        for (int i = 0; i < 9; ++i) *(gv4*)(q + 64 * i) = (v4f){p[off[i][0]], p[off[i][1]], p[off[i][2]], p[off[i][3]]};
       }
     }
     return;
   }
+  if (wk_id != 0) return;
+  // ---- lane holds, for rows 4 kq + r and channel li, the nine taps: 36 contiguous bytes
   gfloat* out = GP(d.gw) + (size_t)qpart * (size_t)UNI(d.gpstride);
 #pragma unroll
   for (int k = 0; k < MI; ++k)

@@ -748,6 +748,7 @@ __device__ __forceinline__ void step_gemm_t(const LDesc& d, int tile_, int t, lf
 }
 
 }  // namespace pb
+#include "pb_update.h"
 #include "pb_mm.h"
 #include "pb_conv.h"
 namespace pb {

@@ -310,35 +310,16 @@ __device__ __forceinline__ void step_mm_t(const LDesc& d, int tile_, int t, lflo
   const gfloat* skg = (MODE == 2 && (flags & F_ADD_SKG)) ? (const gfloat*)at(d.skg, te) : nullptr;
   const bool round = MODE != 3 && (flags & F_BF16_OUT);
   if (MODE == 3 && (flags & F_UPD_W)) {
-    // the update of the tile's weights, a row subtile's operands requested together: no gradient in memory
-    const float fa = UNIF(d.fa), fb = UNIF(d.fb), lrT = UNIF(d.flrT), lr = UNIF(d.flr), fm = UNIF(d.fm);
-    const bool wform = flags & F_LWP_W;
-    gfloat* wp = GP((float*)d.w);
-    gfloat* vp = GP(d.v);
-    gfloat* hp = GP(d.what);
+    // the update of the tile's weights: no gradient in memory
+    constexpr int pitch = NT + 4;
+    tile_update<4>(d, smem, pitch, MT, NT / 4, (unsigned)m0 * (unsigned)N + (unsigned)n0, (unsigned)N, false, [&]() {
 #pragma unroll
-    for (int i = 0; i < MI; ++i) {
-      const unsigned o0 = (unsigned)(m0 + wr * 16 * MI + 16 * i + 4 * kq) * (unsigned)N + (unsigned)(n0 + wc * 16 * NI + li);
-      float w[NI][4], v[NI][4];
+      for (int i = 0; i < MI; ++i)
 #pragma unroll
-      for (int j = 0; j < NI; ++j)
+        for (int j = 0; j < NI; ++j)
 #pragma unroll
-        for (int r = 0; r < 4; ++r) {
-          const unsigned o = o0 + (unsigned)(r * N + 16 * j);
-          w[j][r] = wp[o];
-          v[j][r] = vp[o];
-        }
-#pragma unroll
-      for (int j = 0; j < NI; ++j)
-#pragma unroll
-        for (int r = 0; r < 4; ++r) {
-          const unsigned o = o0 + (unsigned)(r * N + 16 * j);
-          const float g = acc[i][j][r], v2 = fmaf(fm, v[j][r], g), w2 = fmaf(-lr, fmaf(fa, v2, fb * g), w[j][r]);
-          vp[o] = v2;
-          wp[o] = w2;
-          hp[o] = wform ? fmaf(lrT, w2 - w[j][r], w2) : fmaf(-lrT, v2, w2);
-        }
-    }
+          for (int r = 0; r < 4; ++r) smem[(wr * 16 * MI + 16 * i + 4 * kq + r) * pitch + wc * 16 * NI + 16 * j + li] = acc[i][j][r];
+    });
     return;
   }
   // every operand of the epilogue is requested before the first one is used (the registers of the
