@@ -30,9 +30,6 @@
 
 namespace pb {
 
-typedef float v4u __attribute__((ext_vector_type(4), aligned(4)));
-typedef __attribute__((address_space(1))) v4u gv4u;
-
 // acc += a[tap] * window, see above.  MODE 1 forward, 2 backward data.
 template <int MODE, bool S2, int MI, int NI>
 __device__ __forceinline__ void step_dc_t(const LDesc& d, int tile_, int t, lfloat* smem) {

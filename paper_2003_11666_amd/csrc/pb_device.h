@@ -101,14 +101,12 @@ struct GemmCfg {
 
 // Dense matrix-product form of a 1x1 layer (GemmCfg::mm)
 constexpr int MM_QC = 32;            // reduction entries per chunk
-constexpr int MM_LDK = MM_QC + 4;    // row stride of an operand stored [row][reduction]: 4 * odd, 16 rows on distinct banks
 
 constexpr int DC_VU = 6;             // direct 3x3 form: 16-byte requests per thread and chunk of the patch
 
-// LDS floats of one chunk (both operands); the step needs twice that
-__host__ __device__ constexpr int mm_chunk_floats(int mode, int MT, int NT) {
-  return (mode == 2 ? MM_QC * (MT + 4) : MT * MM_LDK) + (mode == 3 ? NT * MM_LDK : MM_QC * (NT + 4));
-}
+// LDS floats of one chunk of a dense tile: three bf16 pieces of both operands; two chunks where they fit
+__host__ __device__ constexpr int mm_chunk_floats(int MT, int NT) { return 3 * (MT + NT) * MM_QC / 2; }
+__host__ __device__ constexpr int mm_buffers(int MT, int NT) { return 2 * mm_chunk_floats(MT, NT) <= LDS_FLOATS ? 2 : 1; }
 
 // Pointer fields of a step that point into slot 0 of the stage's ring of predicted-weight versions;
 // k_phase moves them to the slot of the tick before the step runs.

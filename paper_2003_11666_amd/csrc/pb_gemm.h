@@ -26,6 +26,8 @@ namespace pb {
 template <int V> struct IConst { static constexpr int value = V; };
 typedef float v4f __attribute__((ext_vector_type(4)));
 typedef __attribute__((address_space(1))) v4f gv4;
+typedef float v4u __attribute__((ext_vector_type(4), aligned(4)));   // a vector at any float
+typedef __attribute__((address_space(1))) v4u gv4u;
 typedef int v4i __attribute__((ext_vector_type(4)));
 typedef __attribute__((address_space(3))) v4i lvi4;
 typedef float v2f __attribute__((ext_vector_type(2)));
@@ -749,6 +751,7 @@ __device__ __forceinline__ void step_gemm_t(const LDesc& d, int tile_, int t, lf
 
 }  // namespace pb
 #include "pb_update.h"
+#include "pb_split.h"
 #include "pb_mm.h"
 #include "pb_conv.h"
 namespace pb {

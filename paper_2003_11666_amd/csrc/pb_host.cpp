@@ -780,13 +780,13 @@ bool make_mm(const pb_ctx* c, int mode, int C, int H, int W, int K, int OH, int 
   if (k == 1 && stride == 1) { g.pw = P; g.sw = HW; g.sh = 1; g.shw = HW; }          // the map as one row
   else if (mode == 2 && k > 1) { g.pw = W; g.sw = OW; g.sh = OH; g.shw = P; }          // pixel space: the input map; source: dY
   else { g.pw = OW; g.sw = W; g.sh = H; g.shw = HW; }                                  // pixel space: the output map; source: the input
-  g.gather = k > 1 ? 1 : mode == 2 ? (P % 4 != 0) : (stride == 2 || P % 4 != 0);
+  g.gather = k > 1 || (mode != 2 && stride == 2);
   g.mi = M % 128 == 0 ? 4 : 2;
   g.ni = mode == 3 ? (N % 128 == 0 ? 4 : 2) : (N > 64 ? 4 : 2);
   if (mode != 3 && g.mi == 2 && g.ni == 2) return false;   // (no 64 x 64 tiles for these two passes)
   g.wm = 2; g.wn = 2; g.wk = 1; g.nsub = 1;
   g.MT = 32 * g.mi; g.NT = 32 * g.ni;
-  if (2 * mm_chunk_floats(mode, g.MT, g.NT) > LDS_FLOATS) return false;
+  static_assert(mm_chunk_floats(128, 128) <= LDS_FLOATS && 128 * 132 <= LDS_FLOATS, "a chunk, or the gradients of a tile, in LDS");
   g.tiles_n = cdiv(N, g.NT);
   g.tpp = (M / g.MT) * g.tiles_n;
   g.QC = g.QCpad = MM_QC; g.n_chunks = cdiv(Q, MM_QC);
@@ -2323,6 +2323,9 @@ int validate_steps(const pb_ctx* c, const std::vector<std::pair<int, StepDesc>>&
             o = o && ref_vec4(c, d.dy) &&
                 (g.ps == 1 || (!(d.flags & (F_MASK_X | F_ADD_SKG)) && ref_vec4(c, d.dx) && (d.H * d.W) % 2 == 0 && d.W % 2 == 0));
           else o = o && ref_vec4(c, d.x) && ref_vec4(c, d.dy);
+          // vectors at the end of a row of no multiple of 4 pixels reach up to 3 floats past their tensor
+          auto tail_ok = [&](const TRef& r) { return r.base + (int64_t)r.depth * r.stride + 4 <= hi; };
+          if (d.OH * d.OW % 4) o = o && (g.gm == 2 || tail_ok(d.x)) && (g.gm == 1 || tail_ok(d.dy));
           return o;
         };
         if (d.g.dc == 2) {
@@ -2895,7 +2898,7 @@ int64_t plan_summary(const pb_net_desc* net, char* buf, int64_t cap) {
                  g.wm, g.wn, g.wk, g.mi, g.ni, g.MT, g.NT, g.n_chunks, g.parts, g.CC, g.PR, g.Wp, g.shw, g.rows_c, est_tile_us(g, 3));
       else if (g.mm)
         snprintf(line, sizeof line, " | gm%d M%d N%d Q%d dense mi%d ni%d tile %dx%d chunks %d/%d QC%d lds %d", g.gm, g.M, g.N, g.Q, g.mi, g.ni,
-                 g.MT, g.NT, g.n_chunks, g.parts, g.QC, 2 * mm_chunk_floats(g.gm, g.MT, g.NT));
+                 g.MT, g.NT, g.n_chunks, g.parts, g.QC, mm_buffers(g.MT, g.NT) * mm_chunk_floats(g.MT, g.NT));
       else
       snprintf(line, sizeof line, " | gm%d M%d N%d Q%d waves %dx%dx%d ni%d tile %dx%d x%d chunks %d/%d QC%d CC%d PR%d Wp%d lds %d",
                g.gm, g.M, g.N, g.Q, g.wm, g.wn, g.wk, g.ni, g.MT, g.NT, g.nsub, g.n_chunks, g.parts, g.QC, g.CC, g.PR, g.Wp,
