@@ -54,9 +54,11 @@ enum StepKind : int32_t {
   // of 4): nothing for the matrix cores, a stream of the weight matrix.
   K_FC_FWD = 18,     // y = W x + b: a wavefront per output, four outputs per workgroup
   K_FC_BWD_X = 19,   // dx = W^T dy: FC_BX inputs per workgroup, the outputs dealt out to groups of lanes
-  K_FC_BWD_W = 20    // gW = dy x^T: 4096 consecutive weights per workgroup
+  K_FC_BWD_W = 20,   // gW = dy x^T: 4096 consecutive weights per workgroup
+  K_NATURAL = 21     // read-back of a layer stored in the order of F_W_PERM (w) in its own order (gw): NAT_TILE floats per workgroup
 };
 
+constexpr int NAT_TILE = 8192;
 constexpr int LDS_FLOATS = 19456;   // 76 KB of LDS per workgroup (a compute unit has 160 KB and holds two workgroups); the
                                     // planner gives GEMM tiles all of it or 62 KB (pb_tuning.gemm_lds_kb)
 
@@ -94,7 +96,8 @@ struct GemmCfg {
   int32_t ck, cpad, sh;    // dense form of a k x k layer (ck = k, its padding, rows of the source map): the reduction or the
                            // columns run over (channel, tap), see pb_mm.h
   int32_t dc;              // 1: 3x3 layer with its weights straight from memory (pb_conv.h): wave tile mi x ni, CC channels per chunk,
-                           // sw vectors per patch row, channel planes of the patch shw floats apart; 2: 1x1 layer on a small map
+                           // sw vectors per patch row, channel planes of the patch shw floats apart; 2: 1x1 layer on a small map;
+                           // 3: forward or backward data of a 3x3 layer on the bf16 pipes (octets of the patch shw pixels apart)
   int32_t a_req;           // requests per thread that the A block of a full chunk takes (the kernel built for latency keeps
                            // nine of them in flight when there are more than six, six otherwise)
 };
@@ -103,6 +106,7 @@ struct GemmCfg {
 constexpr int MM_QC = 32;            // reduction entries per chunk
 
 constexpr int DC_VU = 6;             // direct 3x3 form: 16-byte requests per thread and chunk of the patch
+constexpr int DS_VU = 2;             // ... split products: groups of four such requests, in one pass over the patch
 
 // LDS floats of one chunk of a dense tile: three bf16 pieces of both operands; two chunks where they fit
 __host__ __device__ constexpr int mm_chunk_floats(int MT, int NT) { return 3 * (MT + NT) * MM_QC / 2; }
@@ -134,8 +138,11 @@ enum StepFlags : int32_t {
                       // computed inside the step from the layer's saved input (x) and output gradient (dy)
   F_UPD_W = 262144,   // K_GEMM backward weights: the tile's gradient stays in registers and the step updates the weights itself
                       // (w, v in place, what), a phase after the step that reads them for the data gradient
-  F_WHAT_PERM = 524288 // direct 3x3 form: the predicted weights are stored as the forward pass loads them,
+  F_WHAT_PERM = 524288 // direct 3x3 form: the predicted weights are stored as the forward pass loads them; a multiple of 32
+                      // channels: [row / 16][channel / 32][tap][channel / 16 % 2][channel % 4][row % 16][channel / 4 % 4], else
                       // [row / 16][channel / 4][channel % 4][row % 16][tap]
+  , F_W_PERM = 1048576 // ... weights and velocities as the backward-data tiles load the weights, K and C multiples of 32:
+                      // [C / 16][K / 32][tap][K / 16 % 2][K % 4][C % 16][K / 4 % 4] (pb_read_weights sees the natural order)
 };
 
 struct StepDesc {

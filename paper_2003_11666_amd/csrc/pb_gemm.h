@@ -28,6 +28,13 @@ typedef float v4f __attribute__((ext_vector_type(4)));
 typedef __attribute__((address_space(1))) v4f gv4;
 typedef float v4u __attribute__((ext_vector_type(4), aligned(4)));   // a vector at any float
 typedef __attribute__((address_space(1))) v4u gv4u;
+typedef float v3f __attribute__((ext_vector_type(3)));
+typedef float v3u __attribute__((ext_vector_type(3), aligned(4)));
+typedef __attribute__((address_space(1))) v3u gv3u;
+typedef __attribute__((address_space(1))) unsigned char gbyte;
+// A copy the compiler cannot look through: what is derived from it is worked out where it is used (a few instructions) instead
+// of being hoisted out of the loops around and kept in registers.
+__device__ __forceinline__ unsigned here(unsigned x) { asm volatile("" : "+v"(x)); return x; }
 typedef int v4i __attribute__((ext_vector_type(4)));
 typedef __attribute__((address_space(3))) v4i lvi4;
 typedef float v2f __attribute__((ext_vector_type(2)));

@@ -268,6 +268,7 @@ struct StageBufs {
 struct Layout {
   int64_t P = 0;                      // padded parameter count
   int64_t w = 0, v = 0, g = 0;
+  int64_t nat = -1;                   // [P]: parameters in their own order for a read-back, where a layer may store them otherwise
   int64_t gacc = -1;                  // update size above one: gradients added up since each stage's latest update
   std::vector<int64_t> what;          // per stage: ring [De - D + 2][padded] of predicted-weight versions
   std::vector<StageBufs> sb;
@@ -287,6 +288,11 @@ constexpr int FWD_PARTS = 8;
 constexpr int THIN_MAX_PIXELS = 64;
 bool fwd_split_candidate(const Stage& a) {
   return a.is_conv && a.post_gn && !a.add && (int64_t)a.OH * a.OW <= THIN_MAX_PIXELS && (int64_t)a.C * a.k * a.k >= 2048;
+}
+// 3x3 layers whose weights and velocities may be stored in the order of their backward-data tiles' lanes (F_W_PERM)
+bool perm_w_shape(const Stage& a) {
+  return a.is_conv && a.k == 3 && a.pad == 1 && a.pre_gn && !a.post_gn && a.C % 32 == 0 && a.K % 32 == 0 && a.o_w % 4 == 0 &&
+         (int64_t)a.C * a.K < (1 << 21);   // (an index division of the read-back)
 }
 bool split_candidate(const Stage& a) { return a.is_conv && (int64_t)a.OH * a.OW >= 256 && a.padded <= 65536; }
 
@@ -350,6 +356,8 @@ void plan_arena(const std::vector<Stage>& st, bool stash, int loss_cap, Layout& 
   // stage's update.  Without weight prediction the forward copy simply equals the master weights.
   L.w = pl.alloc(L.P); L.v = pl.alloc(L.P); L.g = pl.alloc(L.P);
   if (update_size > 1) L.gacc = pl.alloc(L.P);
+  for (const Stage& a : st)
+    if (L.nat < 0 && update_size == 1 && !stash && perm_w_shape(a)) L.nat = pl.alloc(L.P);
   // Exception: a stage whose update computes the weight gradient itself needs nothing but the layer's two maps, which
   // are complete a phase before the stage's backward-data step has read the weights.  With a second copy of the
   // stage's master parameters (the update of tick t reads copy t mod 2 and writes the other) it runs beside that step.
@@ -447,6 +455,7 @@ struct pb_ctx {
   bool wait_busy = false;        // such launches have been made which no call has waited for yet: the shares are held
   int64_t wait_retry = 0;        // the tick at which to ask for the shares again, after another process had them
   std::vector<char> perm_what;   // per stage: the layer's predicted weights are stored in the lane order of its forward tiles
+  std::vector<char> perm_w;      // ... its weights and velocities in that of its backward-data tiles
   std::vector<char> pp_active;   // per stage: the update alternates between two copies of the master parameters
   int fuse_from = -1;          // >= 0: the phases from this one on share one launch, dependencies through completion
                                // counters (0: one launch per tick)
@@ -460,6 +469,8 @@ struct pb_ctx {
   std::vector<Phase> plain_phases;     // fuse_from >= 0: the same steps, a launch per phase
   // device views
   StepDesc* recs_dev = nullptr;        // one descriptor copy per workgroup, in launch order
+  int64_t nat_first = 0;               // behind them the workgroups that put parameters into their own order for a read-back:
+  int nat_tiles = 0;                   // this many for the weights, as many for the velocities
   Globals* globals_dev = nullptr;
   int32_t* zero_dev = nullptr;
   int32_t* labels_dev = nullptr;
@@ -711,20 +722,26 @@ double est_tile_us(const GemmCfg& g, int k) {
   if (g.dc) {
     // direct 3x3 form: MFMAs of the busiest wave with two workgroups sharing the matrix pipes; per chunk a barrier and the
     // stores of the patch; never less than the weights' way from the L2
-    double mf, a_us = 0;
     if (g.gm == 3) {
-      mf = cdiv(cdiv(g.rows_c * g.pw, 16), g.wk) * 36.0 * g.mi;
-    } else {
-      mf = g.CC / 4 / g.wk * 9.0 * g.mi * g.ni;
-      a_us = g.MT * g.CC * 36.0 / 50e3;
+      // split products: blocks of 32 pixels, 54 MFMAs of 16 cycles per row subtile
+      const double mf = cdiv(cdiv(g.rows_c * (g.pw / 8), 4), g.wk) * 54.0 * g.mi;
+      return 6.0 + g.n_chunks * (1.0 + 3.5 * mf * 16.0 / 2400.0);
     }
+    if (g.dc == 3) {
+      // split products: blocks of 32 channels, 54 MFMAs of 16 cycles per pair of subtiles and beside them, per tap, 44 vector
+      // instructions per row subtile that split weights; two workgroups share a compute unit
+      const double blk = 2.0 * 9.0 * std::max(g.mi * g.ni * 96.0, (g.mi * 44.0 + 25.0) * 4.0) * 1.15 / 2400.0 + 0.3;
+      const int passes = cdiv(g.CC / 4 * g.PR * g.sw, DS_VU * BLK);
+      return 9.0 + g.n_chunks * (passes + g.CC / 32 / g.wk * blk);
+    }
+    const double mf = g.CC / 4 / g.wk * 9.0 * g.mi * g.ni, a_us = g.MT * g.CC * 36.0 / 50e3;
     return 4.0 + g.n_chunks * (0.8 + std::max(2.2 * mf * 32.0 / 2400.0, a_us));
   }
   if (g.mm) {
-    // dense form: per chunk of 32 reduction entries 8 mi ni MFMAs per wave, two workgroups sharing the matrix pipes,
+    // dense form: per chunk of 32 reduction entries 6 mi ni MFMAs per wave, two workgroups sharing the matrix pipes,
     // and never less than the round trip of the next chunk's requests
-    const double t_mfma = 2.0 * 8.0 * g.mi * g.ni * 32.0 / 2400.0;
-    return 5.0 + g.n_chunks * std::max(2.2, t_mfma);
+    const double t_mfma = 2.5 * 6.0 * g.mi * g.ni * 16.0 / 2400.0;
+    return 5.0 + g.n_chunks * std::max(1.2, t_mfma);
   }
   const int kk = k * k;
   const double a_fl = g.gm == 2 ? (double)((g.QCpad + kk - 1) / kk + 1) * g.MT * kk : (double)g.MT * g.QCpad;
@@ -811,8 +828,9 @@ bool make_mm(const pb_ctx* c, int mode, int C, int H, int W, int K, int OH, int 
 //   backward data     M = cin,  N = input pixels (stride 2: the gradient's pixels), reduction over cout
 //   backward weights  M = cout, N = 9 cin (a wave: 16 channels), reduction over output rows padded to a multiple of 4 pixels
 // One arrangement (the reduction not split over workgroups); false if the shape rules or LDS do not allow it.
+// split (forward and backward data): on the bf16 pipes, the largest chunk of at most cc channels; else on the fp32 pipes
 bool fit_dc(const pb_ctx* c, int mode, int C, int H, int W, int K, int OH, int OW, int k, int stride, int pad, int mi, int ni,
-            int wm, int wn, GemmCfg* out) {
+            int wm, int wn, bool split, int cc, GemmCfg* out) {
   if (g_tile_budget_us <= 0 || c->kernel_set != 0 || (c->tune.dense_1x1 != 0 && c->tune.dense_1x1 != 1)) return false;
   if (k != 3 || pad != 1 || (stride != 1 && stride != 2) || OH != (H - 1) / stride + 1 || OW != (W - 1) / stride + 1) return false;
   const int M = mode == 2 ? C : K, R = mode == 2 ? K : C;
@@ -824,36 +842,41 @@ bool fit_dc(const pb_ctx* c, int mode, int C, int H, int W, int K, int OH, int O
   const int PW = (mode == 1 || s2) ? OW : W, PH = (mode == 1 || s2) ? OH : H;
   GemmCfg g;
   memset(&g, 0, sizeof g);
-  g.gm = mode; g.dc = 1; g.M = M; g.Q = mode == 3 ? OH * OW : R * 9; g.ps = stride; g.nsub = 1;
+  g.gm = mode; g.dc = split && mode != 3 ? 3 : 1; g.M = M; g.Q = mode == 3 ? OH * OW : R * 9; g.ps = stride; g.nsub = 1;
   g.mi = mi; g.ni = ni; g.wm = wm; g.wn = wn; g.wk = 4 / (wm * wn);
   g.MT = 16 * mi * wm;
   if (M % g.MT || (s2 && mi == 4)) return false;     // (stride 2: four accumulator sets)
-  g.sw = cdiv(SW, 4); g.Wp = 4 * g.sw + 8;
+  if (g.dc == 3 && (mi > 2 || (ni > 2 && mi < 2) || (s2 && mi > 1))) return false;
+  g.sw = cdiv(SW, 4);
   if (mode != 3) {
     g.N = PH * PW; g.NT = 16 * ni * wn; g.tiles_n = cdiv(g.N, g.NT);
     if (wn > 1 && g.NT / 2 >= g.N) return false;
-    const int rows = tile_rows(g.NT, PW, PH), unit = 4 * (4 / mi) * g.wk;
+    const int rows = tile_rows(g.NT, PW, PH), unit = split ? 32 * g.wk : 4 * (4 / mi) * g.wk;
     g.PR = s2 ? rows + 1 : mode == 2 ? rows + 2 : (rows - 1) * stride + 3;
+    g.Wp = split ? SW + (s2 ? 1 : 2) : 4 * g.sw + 8;
     g.shw = g.PR * g.Wp;
-    while (g.shw % 32 != 16) g.shw += 4;             // the planes of two lane groups on different banks
+    if (!split) while (g.shw % 32 != 16) g.shw += 4; // the planes of two lane groups on different banks
     if (R % unit) return false;
-    for (int cc = unit; cc <= R && cc <= 64; cc += unit)
-      if (R % cc == 0 && cc * g.PR * g.sw <= DC_VU * BLK && 2 * cc * g.shw <= LDS_FLOATS) g.CC = cc;
+    for (int q = unit; q <= R && q <= cc; q += unit)
+      if (R % q == 0 && (split ? 3 * (q / 2 * g.shw + 4) <= LDS_FLOATS
+                               : q * g.PR * g.sw <= DC_VU * BLK && 2 * q * g.shw <= LDS_FLOATS)) g.CC = q;
     if (!g.CC) return false;
     g.n_chunks = R / g.CC;
   } else {
-    const int CT = 16 * wn;
+    const int CT = 16 * wn, noc = cdiv(OW, 8);
     if (C % CT) return false;
     g.N = 9 * C; g.NT = 9 * CT; g.tiles_n = C / CT; g.CC = CT;
-    g.pw = (OW + 3) / 4 * 4;
+    g.pw = 8 * noc;                                  // pixels of a row in the reduction
+    g.Wp = 4 * stride * (noc + 1);                   // floats of a patch row of a piece
+    auto plane = [&](int pr) { return pr * g.Wp % 8 ? pr * g.Wp : pr * g.Wp + 4; };   // 16 channels on different banks
     for (int r = 1; r <= OH; ++r) {
       const int pr = (r - 1) * stride + 3;
-      if (CT * pr * g.sw <= DC_VU * BLK && 2 * CT * pr * g.Wp + 64 <= LDS_FLOATS) g.rows_c = r;
+      if (CT * pr * g.sw <= DC_VU * BLK && 6 * CT * pr * g.Wp + 16 <= LDS_FLOATS) g.rows_c = r;
     }
     if (!g.rows_c) return false;
     g.rows_c = cdiv(OH, cdiv(OH, g.rows_c));         // even out the chunks
     g.PR = (g.rows_c - 1) * stride + 3;
-    g.shw = g.PR * g.Wp;
+    g.shw = 6 * CT * plane(g.PR) + 16 <= LDS_FLOATS ? plane(g.PR) : g.PR * g.Wp;
     g.n_chunks = cdiv(OH, g.rows_c);
   }
   g.QC = g.QCpad = mode == 3 ? g.rows_c * g.pw : 9 * g.CC;
@@ -863,17 +886,29 @@ bool fit_dc(const pb_ctx* c, int mode, int C, int H, int W, int K, int OH, int O
   return true;
 }
 
+// lanes: the weights lie in the order of the tile's lanes if it runs on the bf16 pipes (tiles of 2 x 4 subtiles have no
+// registers for the other order's requests)
 bool make_dc(const pb_ctx* c, int mode, int C, int H, int W, int K, int OH, int OW, int k, int stride, int pad, int max_parts,
-             GemmCfg* out) {
+             bool lanes, GemmCfg* out) {
   bool have = false, best_within = false;
   double best_work = 0, best_tile = 0;
-  static const int shapes[4][2] = {{4, 2}, {2, 2}, {2, 1}, {1, 1}}, wshapes[2][2] = {{2, 1}, {1, 1}};
-  for (int si = 0; si < (mode == 3 ? 2 : 4); ++si)
+  static const int shapes[4][2] = {{4, 2}, {2, 2}, {2, 1}, {1, 1}}, sshapes[5][2] = {{2, 4}, {2, 2}, {2, 1}, {1, 2}, {1, 1}},
+                   wshapes[2][2] = {{2, 1}, {1, 1}};
+  const int R = mode == 2 ? K : C;
+  // a reduction over a multiple of 32 channels runs on the bf16 pipes, chunks of 32 channels per wave and more; else on the
+  // fp32 pipes, the largest chunk of up to 64 channels.  So do maps of fewer than 16 pixels, whose tiles stream weights and
+  // little else: those of the fp32 pipes keep more of them in flight (512 channels on 2x2 maps: loops of 18-20 us there,
+  // 26-31 here; 256 channels on 4x4 maps: 15-18 there, 9-12 here)
+  const int px = mode == 2 && stride == 1 ? H * W : OH * OW;       // columns of the product
+  for (int split = mode != 3 && R % 32 == 0 && px >= 16; split >= 0 && !have; --split)
+  for (int si = 0; si < (mode == 3 ? 2 : split ? 5 : 4); ++si)
     for (int wm = 1; wm <= 4; wm *= 2)
-      for (int wn = 1; wm * wn <= 4; wn *= 2) {
-        const int* sh = (mode == 3 ? wshapes : shapes)[si];
+      for (int wn = 1; wm * wn <= 4; wn *= 2)
+        for (int cc = split ? 32 : 64; cc <= (split ? 512 : 64); cc *= 2) {
+        const int* sh = (mode == 3 ? wshapes : split ? sshapes : shapes)[si];
         GemmCfg g;
-        if (!fit_dc(c, mode, C, H, W, K, OH, OW, k, stride, pad, sh[0], sh[1], wm, wn, &g)) continue;
+        if (split && sh[1] == 4 && !lanes) continue;
+        if (!fit_dc(c, mode, C, H, W, K, OH, OW, k, stride, pad, sh[0], sh[1], wm, wn, split, cc, &g) || (split && 2 * g.CC <= cc)) continue;
         double tt = est_tile_us(g, 3);
         for (int want = 2; want <= max_parts && want <= g.n_chunks && tt > (mode == 3 ? 20.0 : 12.0); want *= 2) {
           g.cpp = cdiv(g.n_chunks, want);
@@ -1297,6 +1332,7 @@ void compile_steps_once(pb_ctx* c, std::vector<std::pair<int, StepDesc>>& out) {
   // gradient's operands are complete in, and the operands
   std::vector<std::vector<std::pair<int64_t, int64_t>>> upd(S);   // per stage: parameter ranges that other steps than K_UPDATE update
   c->perm_what.assign(S, 0);
+  c->perm_w.assign(S, 0);
   struct FusedW { int phase = -1; TRef x, dy; int64_t pp = 0; };
   std::vector<FusedW> fusedw(S);
   c->pp_active.assign(S, 0);
@@ -1502,17 +1538,17 @@ void compile_steps_once(pb_ctx* c, std::vector<std::pair<int, StepDesc>>& out) {
         const bool zsplit = a.post_gn && b.zparts >= 0 && !c->bf16 && g_tile_budget_us > 0 && !(d.flags & (F_SKIP | F_PROJ)) &&
                             (a.K / a.G) * a.OH * a.OW % 4 == 0 && (int64_t)(a.K / a.G) * a.OH * a.OW <= 32768 && a.K / a.G <= BLK;
         bool ok = make_gemm(1, d.C, d.H, d.W, d.K, d.OH, d.OW, d.k, d.stride, d.pad, nullptr, &g, plain_src, (d.flags & F_PROJ) ? 1 : 16, flat,
-                            zsplit ? FWD_PARTS : 1, a.post_gn ? 256.0 : 0.0);
+                            zsplit ? FWD_PARTS : 1, 256.0);
         if (ok && (d.flags & F_PROJ)) ok = make_gemm(1, d.sC, d.sH, d.sW, d.K, d.OH, d.OW, 1, d.sstride, 0, &g, &gp, true);
-        GemmCfg gd;
+        GemmCfg gd, gw;
+        // (with weight stashing the backward pass reads the predicted weights too, in their natural order)
+        const bool lanes = !c->stash && c->N == 1 && !a.post_gn && plain_src && a.C % 16 == 0 && !fusew_shape(a) &&
+                           make_dc(c, 3, a.C, a.H, a.W, a.K, a.OH, a.OW, a.k, a.stride, a.pad, b.gparts >= 0 ? GRAD_PARTS : 1, false, &gw) && gw.parts == 1;
         if (plain_src && !(d.flags & F_PROJ) &&
-            make_dc(c, 1, a.C, a.H, a.W, a.K, a.OH, a.OW, a.k, a.stride, a.pad, zsplit ? FWD_PARTS : 1, &gd)) {
+            make_dc(c, 1, a.C, a.H, a.W, a.K, a.OH, a.OW, a.k, a.stride, a.pad, zsplit ? FWD_PARTS : 1, lanes, &gd)) {
           d.kind = K_GEMM; d.g = gd; d.gp = gp; d.ntiles = gd.tiles;
           if (gd.parts > 1) { d.gw = c->f(b.zparts); d.gparts = gd.parts; d.gpstride = (int)a.z_elems(); fwd_parts = gd.parts; }
-          // (with weight stashing the backward pass reads the predicted weights too, in their natural order)
-          GemmCfg gw;
-          perm_what = !c->stash && c->N == 1 && !a.post_gn && plain_src && a.C % 16 == 0 && !fusew_shape(a) &&
-                      make_dc(c, 3, a.C, a.H, a.W, a.K, a.OH, a.OW, a.k, a.stride, a.pad, b.gparts >= 0 ? GRAD_PARTS : 1, &gw) && gw.parts == 1;
+          perm_what = lanes && (gd.dc == 3) == (a.C % 32 == 0);   // (the order goes with the number of channels)
           if (perm_what) { d.flags |= F_WHAT_PERM; c->perm_what[s] = 1; }
         } else
         if (plain_src && !(d.flags & F_PROJ) && make_d1(c, 1, a.C, a.H, a.W, a.K, a.OH, a.OW, a.k, a.stride, a.pad, &gd)) {
@@ -1654,7 +1690,7 @@ void compile_steps_once(pb_ctx* c, std::vector<std::pair<int, StepDesc>>& out) {
         }
         GemmCfg gd;
         const bool dense = (!(d.flags & (F_PRE_AFFINE | F_PRE_RELU)) &&
-                            make_dc(c, 3, a.C, a.H, a.W, a.K, a.OH, a.OW, a.k, a.stride, a.pad, b.gparts >= 0 ? GRAD_PARTS : 1, &gd)) ||
+                            make_dc(c, 3, a.C, a.H, a.W, a.K, a.OH, a.OW, a.k, a.stride, a.pad, b.gparts >= 0 ? GRAD_PARTS : 1, false, &gd)) ||
                            (!(d.flags & (F_PRE_AFFINE | F_PRE_RELU)) && ref_vec4(c, d.x) && ref_vec4(c, d.dy) &&
                            make_mm(c, 3, a.C, a.H, a.W, a.K, a.OH, a.OW, a.k, a.stride, a.pad, b.gparts >= 0 ? GRAD_PARTS : 1, &gd));
         if (dense) g = gd;
@@ -1664,6 +1700,12 @@ void compile_steps_once(pb_ctx* c, std::vector<std::pair<int, StepDesc>>& out) {
       }
       const bool upd_w = !fuse_w && fuse_update(d, a.o_w, a.n_w);
       if (upd_w && perm_what) d.flags |= F_WHAT_PERM;
+      GemmCfg gb;
+      if (upd_w && perm_what && s > 0 && L.nat >= 0 && perm_w_shape(a) && d.g.dc && b.w2 < 0 &&
+          make_dc(c, 2, a.C, a.H, a.W, a.K, a.OH, a.OW, a.k, a.stride, a.pad, 1, true, &gb) && gb.dc == 3) {
+        d.flags |= F_W_PERM;
+        c->perm_w[s] = 1;
+      }
       if (!fuse_w) out.push_back({upd_w ? pb + 1 : pb, d});
     }
     if (s > 0) {   // data gradient of the main layer
@@ -1707,12 +1749,13 @@ void compile_steps_once(pb_ctx* c, std::vector<std::pair<int, StepDesc>>& out) {
                                           dxsplit ? FWD_PARTS : 1)) {
         GemmCfg gd;
         const bool dense = ((a.stride == 1 || !(d.flags & (F_MASK_X | F_ADD_SKG))) &&
-                            make_dc(c, 2, a.C, a.H, a.W, a.K, a.OH, a.OW, a.k, a.stride, a.pad, dxsplit ? FWD_PARTS : 1, &gd)) ||
+                            make_dc(c, 2, a.C, a.H, a.W, a.K, a.OH, a.OW, a.k, a.stride, a.pad, dxsplit ? FWD_PARTS : 1, c->perm_w[s], &gd)) ||
                            ((a.stride == 1 || (!(d.flags & (F_MASK_X | F_ADD_SKG)) && ref_vec4(c, d.dx))) &&
                             make_d1(c, 2, a.C, a.H, a.W, a.K, a.OH, a.OW, a.k, a.stride, a.pad, &gd)) ||
                            (arena_aligned16(c, d.w) && ref_vec4(c, d.dy) &&
                             make_mm(c, 2, a.C, a.H, a.W, a.K, a.OH, a.OW, a.k, a.stride, a.pad, 1, &gd));
         if (dense) g = gd;
+        if (c->perm_w[s]) d.flags |= F_W_PERM;
         d.kind = K_GEMM; d.g = g; d.ntiles = g.tiles;
         if (g.parts > 1) { d.gw = c->f(L.sb[s - 1].dxparts); d.gparts = g.parts; d.gpstride = (int)a.in_elems(); }
         if (!dense) gemm_tables(c, g, d.C, d.H, d.W, d.K, d.OH, d.OW, d.k, d.stride, &d.tq, &d.tn);
@@ -2338,12 +2381,16 @@ int validate_steps(const pb_ctx* c, const std::vector<std::pair<int, StepDesc>>&
           // reach up to 3 floats past their tensor
           GemmCfg want;
           ok = ok && !c->nt_stores && d.ntiles == d.g.tiles && d.gp.gm == 0 && !(d.flags & (F_PROJ | F_PRE_AFFINE | F_PRE_RELU)) &&
-               fit_dc(c, d.g.gm, d.C, d.H, d.W, d.K, d.OH, d.OW, d.k, d.stride, d.pad, d.g.mi, d.g.ni, d.g.wm, d.g.wn, &want);
+               fit_dc(c, d.g.gm, d.C, d.H, d.W, d.K, d.OH, d.OW, d.k, d.stride, d.pad, d.g.mi, d.g.ni, d.g.wm, d.g.wn, d.g.dc == 3, d.g.CC, &want);
           want.parts = d.g.parts; want.cpp = d.g.cpp; want.tiles = d.g.parts * want.tpp;
           ok = ok && memcmp(&want, &d.g, sizeof want) == 0 && d.g.parts >= 1 && (int64_t)d.g.parts * d.g.cpp >= d.g.n_chunks &&
                (int64_t)(d.g.parts - 1) * d.g.cpp < d.g.n_chunks;
-          if (d.flags & F_WHAT_PERM) ok = ok && c->perm_what[d.stage] && !c->stash && (d.g.gm == 1 || (d.g.gm == 3 && (d.flags & F_UPD_W))) && d.C % 4 == 0 && d.K % 16 == 0;
+          if (d.flags & F_WHAT_PERM) ok = ok && c->perm_what[d.stage] && !c->stash && (d.g.gm == 1 || (d.g.gm == 3 && (d.flags & F_UPD_W))) && (d.g.gm == 3 || (d.g.dc == 3) == (d.C % 32 == 0)) && d.K % 16 == 0;
           else if (d.g.gm == 1 || (d.flags & F_UPD_W)) ok = ok && (!c->perm_what[d.stage] || d.k != 3);
+          if (d.flags & F_W_PERM)
+            ok = ok && c->perm_w[d.stage] && c->L.nat >= 0 && d.K % 32 == 0 && d.C % 32 == 0 && (d.g.gm == 2 ? d.g.dc == 3 && d.pmask == 0 : d.g.gm == 3 && (d.flags & F_UPD_W));
+          else if (d.g.gm == 2 || (d.flags & F_UPD_W)) ok = ok && !c->perm_w[d.stage];
+          ok = ok && (d.g.dc != 3 || d.g.ni < 4 || (d.flags & (d.g.gm == 1 ? F_WHAT_PERM : F_W_PERM)));
           const TRef& pt = d.g.gm == 2 ? d.dy : d.x;
           ok = ok && pt.base + (int64_t)pt.depth * pt.stride + 4 <= hi && (d.g.gm != 3 || d.dy.base + (int64_t)d.dy.depth * d.dy.stride + 4 <= hi);
           if (d.g.gm == 2 && d.stride == 2) ok = ok && !(d.flags & (F_MASK_X | F_ADD_SKG)) && ref_vec4(c, d.dx);
@@ -2675,6 +2722,15 @@ int64_t copy_params_out(pb_ctx* c, int64_t arena_off, float* dst, int64_t cap) {
     put(0, a.n_head);
     if (a.n_gn) put(a.o_gamma, 2 * a.n_gn);
   }
+  // layers that store them in another order: the whole block by way of a copy on the device
+  if (c->nat_tiles > 0) {
+    for (size_t i = 0; i < runs.size(); ++i)
+      HIP_TRY(hipMemcpyAsync(c->f(c->L.nat + run_at[i]), runs[i].src, sizeof(float) * runs[i].n, hipMemcpyDeviceToDevice, c->stream));
+    launch_phase(c->recs_dev + c->nat_first + (arena_off == c->L.w ? 0 : c->nat_tiles), c->nat_tiles, c->globals_dev, 0, nullptr, 0, false, c->stream);
+    HIP_TRY(hipGetLastError());
+    runs.assign(1, Run{c->f(c->L.nat), P});
+    run_at.assign(1, 0);
+  }
   // pieces inside [lo, hi) of the padded layout, of which src holds the floats from lo on
   auto unpack = [&](const float* src, int64_t lo, int64_t hi) {
     size_t i = std::lower_bound(pieces.begin(), pieces.end(), lo, [](const Piece& p, int64_t v) { return p.off + p.n <= v; }) - pieces.begin();
@@ -2838,6 +2894,8 @@ int run_one_tick(pb_ctx* c, const float* staging, int label) {
   return PB_OK;
 }
 
+int nat_tiles(const pb_ctx* c, int s) { return c->perm_w[s] ? (int)cdiv(c->st[s].n_w, NAT_TILE) : 0; }
+
 size_t arena_bytes(const pb_net_desc* net, const int32_t* delays) {
   std::vector<Stage> st;
   bool sequential = false;
@@ -2860,6 +2918,7 @@ size_t arena_bytes(const pb_net_desc* net, const int32_t* delays) {
   if (validate_steps(&tmp, steps, pl.total) != PB_OK) return 0;
   int64_t total_tiles = 0;
   for (auto& pr : steps) total_tiles += pr.second.ntiles;
+  for (int s = 0; s < tmp.S; ++s) total_tiles += 2 * nat_tiles(&tmp, s);
   pl.alloc(total_tiles * (int64_t)sizeof(StepDesc) / 4 + 64);
   return (size_t)pl.total * sizeof(float) + 256;
 }
@@ -2894,8 +2953,8 @@ int64_t plan_summary(const pb_net_desc* net, char* buf, int64_t cap) {
         snprintf(line, sizeof line, " | gm%d M%d N%d Q%d dense small waves %dx1x%d mi%d ni%d tile %dx%d est %.1f", g.gm, g.M, g.N, g.Q, g.wm, g.wk, g.mi, g.ni,
                  g.MT, g.NT, est_tile_us(g, 1));
       else if (g.dc)
-        snprintf(line, sizeof line, " | gm%d M%d N%d Q%d direct waves %dx%dx%d mi%d ni%d tile %dx%d chunks %d/%d CC%d PR%d Wp%d plane%d rows%d est %.1f", g.gm, g.M, g.N, g.Q,
-                 g.wm, g.wn, g.wk, g.mi, g.ni, g.MT, g.NT, g.n_chunks, g.parts, g.CC, g.PR, g.Wp, g.shw, g.rows_c, est_tile_us(g, 3));
+        snprintf(line, sizeof line, " | gm%d M%d N%d Q%d direct waves %dx%dx%d mi%d ni%d tile %dx%d chunks %d/%d CC%d PR%d Wp%d plane%d rows%d est %.1f%s", g.gm, g.M, g.N, g.Q,
+                 g.wm, g.wn, g.wk, g.mi, g.ni, g.MT, g.NT, g.n_chunks, g.parts, g.CC, g.PR, g.Wp, g.shw, g.rows_c, est_tile_us(g, 3), g.dc == 3 ? " split" : "");
       else if (g.mm)
         snprintf(line, sizeof line, " | gm%d M%d N%d Q%d dense mi%d ni%d tile %dx%d chunks %d/%d QC%d lds %d", g.gm, g.M, g.N, g.Q, g.mi, g.ni,
                  g.MT, g.NT, g.n_chunks, g.parts, g.QC, mm_buffers(g.MT, g.NT) * mm_chunk_floats(g.MT, g.NT));
@@ -3135,6 +3194,19 @@ int init_common(pb_ctx** out, const pb_net_desc* net, const int32_t* delays, flo
     m.tiles = (int)(recs.size() - (size_t)c->rec_first[m.first]);
     c->phases.resize(c->fuse_from + 1);
   }
+  c->nat_first = (int64_t)recs.size();
+  for (int v = 0; v < 2; ++v)
+    for (int s = 0; s < c->S; ++s) {
+      if (!c->perm_w[s]) continue;
+      StepDesc d;
+      memset(&d, 0, sizeof d);
+      d.kind = K_NATURAL; d.flags = F_ALWAYS; d.stage = s; d.sig_idx = -1;
+      d.K = st[s].K; d.C = st[s].C; d.ntiles = nat_tiles(c, s);
+      d.w = c->f((v ? c->L.v : c->L.w) + st[s].off + st[s].o_w);
+      d.gw = c->f(c->L.nat + st[s].off + st[s].o_w);
+      for (d.tile = 0; d.tile < d.ntiles; ++d.tile) recs.push_back(d);
+    }
+  c->nat_tiles = (int)((int64_t)recs.size() - c->nat_first) / 2;
   const int64_t o_recs = pl.alloc((int64_t)recs.size() * sizeof(StepDesc) / 4 + 64);
   if ((size_t)pl.total * sizeof(float) > need) return fail(PB_E_NOMEM, "internal: arena plan mismatch");
   c->recs_dev = (StepDesc*)c->f(o_recs);
@@ -3143,7 +3215,6 @@ int init_common(pb_ctx** out, const pb_net_desc* net, const int32_t* delays, flo
   init_weights_host(st, seed, w);
   memset(&g0, 0, sizeof g0);
   g0.n_pool = 1;
-  INIT_TRY(hipMemcpyAsync(c->f(c->L.w), w.data(), sizeof(float) * c->L.P, hipMemcpyHostToDevice, c->stream));
   perm.resize(c->S);
   for (int s = 0; s < c->S; ++s) {   // slot 0 of every stage's ring of predicted weights: v = 0, so w_hat = w
     const float* src = w.data() + st[s].off;
@@ -3152,11 +3223,26 @@ int init_common(pb_ctx** out, const pb_net_desc* net, const int32_t* delays, flo
       perm[s].assign(src, src + st[s].padded);
       for (int k = 0; k < K; ++k)
         for (int ci = 0; ci < C; ++ci)
-          memcpy(&perm[s][(((size_t)(k / 16) * (C / 4) + ci / 4) * 64 + ci % 4 * 16 + k % 16) * 9], src + ((size_t)k * C + ci) * 9, 9 * sizeof(float));
+          if (C % 32 == 0)
+            for (int tap = 0; tap < 9; ++tap)
+              perm[s][((((size_t)(k / 16) * (C / 32) + ci / 32) * 9 + tap) * 2 + ci / 16 % 2) * 256 + (ci % 4 * 16 + k % 16) * 4 + ci / 4 % 4] = src[((size_t)k * C + ci) * 9 + tap];
+          else
+            memcpy(&perm[s][(((size_t)(k / 16) * (C / 4) + ci / 4) * 64 + ci % 4 * 16 + k % 16) * 9], src + ((size_t)k * C + ci) * 9, 9 * sizeof(float));
       src = perm[s].data();
     }
     INIT_TRY(hipMemcpyAsync(c->f(c->L.what[s]), src, sizeof(float) * st[s].padded, hipMemcpyHostToDevice, c->stream));
   }
+  for (int s = 0; s < c->S; ++s)
+    if (c->perm_w[s]) {
+      const int C = st[s].C, K = st[s].K;
+      const std::vector<float> nat(w.begin() + st[s].off, w.begin() + st[s].off + (int64_t)K * C * 9);
+      float* to = w.data() + st[s].off;
+      for (int k = 0; k < K; ++k)
+        for (int ci = 0; ci < C; ++ci)
+          for (int tap = 0; tap < 9; ++tap)
+            to[(((((size_t)(ci / 16) * (K / 32) + k / 32) * 9 + tap) * 2 + k / 16 % 2) * 4 + k % 4) * 64 + ci % 16 * 4 + k / 4 % 4] = nat[((size_t)k * C + ci) * 9 + tap];
+    }
+  INIT_TRY(hipMemcpyAsync(c->f(c->L.w), w.data(), sizeof(float) * c->L.P, hipMemcpyHostToDevice, c->stream));
   INIT_TRY(hipMemcpyAsync(c->recs_dev, recs.data(), sizeof(StepDesc) * recs.size(), hipMemcpyHostToDevice, c->stream));
   INIT_TRY(hipMemcpyAsync(c->globals_dev, &g0, sizeof g0, hipMemcpyHostToDevice, c->stream));
   {

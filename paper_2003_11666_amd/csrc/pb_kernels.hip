@@ -2352,6 +2352,20 @@ __device__ __forceinline__ void step_head(const LDesc& d, int t, lfloat* red, lf
   }
 }
 
+// 3x3 weights (or velocities) from the order of F_W_PERM to their own, for a read-back: 4 of every 16 bytes requested are used,
+// the rest of a line by the same workgroup.
+__device__ __forceinline__ void step_natural(const LDesc& d, int tile) {
+  const int C = UNI(d.C), K = UNI(d.K), n = K * C * 9;
+  const float ic = frcp(C);
+  const gfloat* src = GP(d.w);
+  gfloat* dst = GP(d.gw);
+  for (int i = tile * NAT_TILE + (int)threadIdx.x; i < n && i < (tile + 1) * NAT_TILE; i += BLK) {
+    const int kc = (int)((unsigned)i / 9u), tap = i - 9 * kc, k = fdiv(kc, ic), c = kc - k * C;
+    dst[i] = src[(((((c >> 4) * (K >> 5) + (k >> 5)) * 9 + tap) * 2 + ((k >> 4) & 1)) * 4 + (k & 3)) * 64 + (c & 15) * 4 + ((k >> 2) & 3)];
+  }
+}
+
+
 // ------------------------------------------------------------------ kernels
 // One workgroup = one tile of one step.  recs[] holds, per workgroup of the
 // phase, a full copy of its step descriptor with the tile index filled in, so
@@ -2470,6 +2484,7 @@ k_phase(const StepDesc* __restrict__ recs, const Globals* __restrict__ G, int k,
     case K_FC_FWD: if (!NT) step_fc_fwd(d, tile, t); break;
     case K_FC_BWD_X: if (!NT) step_fc_bwd_x(d, tile, t, smem); break;
     case K_FC_BWD_W: if (!NT) step_fc_bwd_w(d, tile, t); break;
+    case K_NATURAL: if (!NT) step_natural(d, tile); break;
     default: break;
   }
   }

@@ -72,4 +72,69 @@ __device__ __forceinline__ void tile_update(const LDesc& d, lfloat* T, int pitch
   }
 }
 
+// The same for a 3x3 layer whose weights and velocities lie in the order of the lanes of its backward-data tiles (F_W_PERM,
+// see pb_device.h): runs of 64 lanes x 4 weights for 16 output channels, 16 input channels and one tap.  A wavefront takes
+// every fourth run of the tile of 16 kgs rows x 16 2^lcg channels; the predicted weights stay in LDS.
+template <int U, class F>
+__device__ __forceinline__ void tile_update_lanes(const LDesc& d, lfloat* T, int pitch, int kgs, int lcg, int mt0, int c0, F stage) {
+  const float fa = UNIF(d.fa), fb = UNIF(d.fb), lrT = UNIF(d.flrT), lr = UNIF(d.flr), fm = UNIF(d.fm);
+  const bool wform = UNI(d.flags) & F_LWP_W;
+  gfloat* wp = GP((float*)d.w);
+  gfloat* vp = GP(d.v);
+  const int lane = threadIdx.x & 63, wv = UNI((int)threadIdx.x >> 6), kb = UNI(d.K) >> 5;
+  const int np = (9 * kgs) << lcg;
+  lfloat* Tl = T + (lane >> 4) * pitch + (lane & 15) * 9;
+  v4f w[2][U], v[2][U];
+  auto run_of = [&](int p, int& lds) {
+    const int g = UNI(fdiv(p, 1.f / 9.f)), tap = p - 9 * g, kg = g >> lcg, cg = g & ((1 << lcg) - 1), k = mt0 + 16 * kg;
+    lds = 16 * kg * pitch + 144 * cg + tap;
+    return (size_t)(((((c0 >> 4) + cg) * kb + (k >> 5)) * 9 + tap) * 2 + ((k >> 4) & 1)) * 256;
+  };
+  auto issue = [&](auto B, int i0) {
+    constexpr int b = decltype(B)::value;
+    const unsigned lb = here(16u * (unsigned)lane);
+#pragma unroll
+    for (int u = 0; u < U; ++u) {
+      const int p = 4 * (i0 + u) + wv;
+      int lds;
+      const size_t o = run_of(p < np ? p : np - 1, lds);
+      w[b][u] = *(const gv4*)((const gbyte*)(wp + o) + lb);
+      v[b][u] = *(const gv4*)((const gbyte*)(vp + o) + lb);
+    }
+  };
+  auto apply = [&](auto B, int i0) {
+    constexpr int b = decltype(B)::value;
+    const unsigned lb = here(16u * (unsigned)lane);
+#pragma unroll
+    for (int u = 0; u < U; ++u) {
+      const int p = 4 * (i0 + u) + wv;
+      if (p >= np) continue;
+      int lds;
+      const size_t o = run_of(p, lds);
+      v4f v2, w2;
+#pragma unroll
+      for (int e = 0; e < 4; ++e) {
+        lfloat* q = Tl + lds + 4 * e * pitch;
+        const float g = *q;
+        v2[e] = fmaf(fm, v[b][u][e], g);
+        w2[e] = fmaf(-lr, fmaf(fa, v2[e], fb * g), w[b][u][e]);
+        *q = wform ? fmaf(lrT, w2[e] - w[b][u][e], w2[e]) : fmaf(-lrT, v2[e], w2[e]);
+      }
+      *(gv4*)((gbyte*)(vp + o) + lb) = v2;
+      *(gv4*)((gbyte*)(wp + o) + lb) = w2;
+    }
+  };
+  const int n = (np + 3) >> 2;
+  issue(IConst<0>(), 0);
+  stage();
+  __syncthreads();
+  for (int i = 0; i < n; i += 2 * U) {
+    if (i + U < n) issue(IConst<1>(), i + U);
+    apply(IConst<0>(), i);
+    if (i + U >= n) break;
+    if (i + 2 * U < n) issue(IConst<0>(), i + 2 * U);
+    apply(IConst<1>(), i + U);
+  }
+}
+
 }  // namespace pb
