@@ -143,6 +143,7 @@ enum StepFlags : int32_t {
                       // [row / 16][channel / 4][channel % 4][row % 16][tap]
   , F_W_PERM = 1048576 // ... weights and velocities as the backward-data tiles load the weights, K and C multiples of 32:
                       // [C / 16][K / 32][tap][K / 16 % 2][K % 4][C % 16][K / 4 % 4] (pb_read_weights sees the natural order)
+  , F_UPD_GEN = 2097152 // K_GN_BWD that updates scale and shift: at an update size above one or with weight stashing
 };
 
 struct StepDesc {

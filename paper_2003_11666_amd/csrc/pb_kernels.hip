@@ -904,26 +904,34 @@ __device__ __forceinline__ void step_gnb_apply(const LDesc& d, int tile, int t) 
   at(d.dx, t)[o] = rbf_if(d.flags & F_BF16_OUT, r);
 }
 
-// The same update for one parameter (GroupNorm scale or shift updated by the
-// step that produced its gradient): w, v at index i in place, w_hat into the other copy.
-// (the same with the parameter and its velocity already in registers)
-__device__ __forceinline__ void update_loaded(const LDesc& d, int i, float g, float vv, float wv) {
-  const float w_old = wv;
-  vv = fmaf(UNIF(d.fm), vv, g);
-  wv = fmaf(-UNIF(d.flr), fmaf(UNIF(d.fa), vv, UNIF(d.fb) * g), wv);
-  GP((float*)d.b)[i] = vv;
-  GP((float*)d.w)[i] = wv;
-  if (d.what) GP(d.what)[i] = (UNI(d.flags) & F_LWP_W) ? fmaf(UNIF(d.flrT), wv - w_old, wv) : fmaf(-UNIF(d.flrT), vv, wv);
+// The update of one parameter (GroupNorm scale or shift) by the step that produced its gradient: w, v at index i in place,
+// w_hat into the next tick's version.  UpdOld: what the update reads, requested ahead of the gradient.  With an update size
+// above one the gradients are added up across ticks as step_update_acc does.
+struct UpdOld { float v, w, acc, what; };
+__device__ __forceinline__ UpdOld update_fetch(const LDesc& d, int t, int i, bool general) {
+  UpdOld o = {GP(d.v)[i], GP(d.w)[i], 0.f, 0.f};
+  if (general && UNI(d.upd_n) > 1) {
+    o.acc = GP(d.gacc)[i];
+    o.what = GP(d.what0)[(size_t)(t % UNI(d.pdepth)) * (size_t)UNI(d.pstride) + (size_t)i];
+  }
+  return o;
 }
-
-__device__ __forceinline__ void update_one(const LDesc& d, int i, float g) {
-  float vv = GP(d.v)[i], wv = GP(d.w)[i];
-  const float w_old = wv;
-  vv = fmaf(UNIF(d.fm), vv, g);
-  wv = fmaf(-UNIF(d.flr), fmaf(UNIF(d.fa), vv, UNIF(d.fb) * g), wv);
+__device__ __forceinline__ void update_one(const LDesc& d, int t, int i, float g, UpdOld o, bool general) {
+  gfloat* what = GP(d.what);
+  const int N = general ? UNI(d.upd_n) : 1;
+  // (with weight stashing the step's ring fields address the version its backward pass reads)
+  if (general && !(UNI(d.pmask) & PF_WHAT)) what = GP((float*)d.what0) + (size_t)((t + 1) % UNI(d.pdepth)) * (size_t)UNI(d.pstride);
+  if (N > 1) {
+    const int j = t - UNI(d.upd_t0), pos = j >= 0 ? j % N : -1;
+    if (pos > 0) g += o.acc;
+    if (pos >= 0 && pos != N - 1) GP(d.gacc)[i] = g;
+    if (pos != N - 1) { what[i] = o.what; return; }
+    g *= 1.0f / (float)N;
+  }
+  const float vv = fmaf(UNIF(d.fm), o.v, g), wv = fmaf(-UNIF(d.flr), fmaf(UNIF(d.fa), vv, UNIF(d.fb) * g), o.w);
   GP((float*)d.b)[i] = vv;
   GP((float*)d.w)[i] = wv;
-  if (d.what) GP(d.what)[i] = (UNI(d.flags) & F_LWP_W) ? fmaf(UNIF(d.flrT), wv - w_old, wv) : fmaf(-UNIF(d.flrT), vv, wv);
+  what[i] = (UNI(d.flags) & F_LWP_W) ? fmaf(UNIF(d.flrT), wv - o.w, wv) : fmaf(-UNIF(d.flrT), vv, wv);
 }
 
 // Limit of the one-workgroup GroupNorm backward: elements of a group (they
@@ -940,9 +948,15 @@ __device__ __forceinline__ void step_gn_bwd(const LDesc& d, int tile, int t, boo
   const int tid = threadIdx.x;
   const int C = UNI(d.C), G = UNI(d.G), HW = UNI(d.H) * UNI(d.W), flags = UNI(d.flags);
   const int g = tile, cpg = UNI(fdiv(C, frcp(G))), n = cpg * HW, ns = n >> 2, HW4 = HW >> 2;
+  const bool gen = flags & F_UPD_GEN;
   if (!live) {
     // no gradient has reached this stage yet: carry scale and shift over to the other forward copy
-    if ((flags & F_UPD_GN) && tid < cpg) { update_one(d, g * cpg + tid, 0.f); update_one(d, C + g * cpg + tid, 0.f); }
+    if ((flags & F_UPD_GN) && tid < cpg) {
+      const int i = g * cpg + tid;
+      const UpdOld o0 = update_fetch(d, t, i, gen), o1 = update_fetch(d, t, C + i, gen);
+      update_one(d, t, i, 0.f, o0, gen);
+      update_one(d, t, C + i, 0.f, o1, gen);
+    }
     return;
   }
   const bool rl = flags & F_GN_RELU, gapd = flags & F_DU_GAP, has_skg = flags & F_ADD_SKG;
@@ -977,10 +991,10 @@ __device__ __forceinline__ void step_gn_bwd(const LDesc& d, int tile, int t, boo
   // master values and velocities are requested here, with the step's other reads, not after the sums (a memory round
   // trip in the middle of the step, with the whole workgroup waiting at the next barrier).
   const bool upd_pre = (flags & F_UPD_GN) && 4 * cpg <= BLK;
-  float uv0 = 0.f, uw0 = 0.f, uv1 = 0.f, uw1 = 0.f;
+  UpdOld old0 = {0.f, 0.f, 0.f, 0.f}, old1 = old0;
   if (upd_pre && tid < 4 * cpg && (tid & 3) == 0) {
-    const int i0 = g * cpg + (tid >> 2), i1 = C + i0;
-    uv0 = GP(d.v)[i0]; uw0 = GP(d.w)[i0]; uv1 = GP(d.v)[i1]; uw1 = GP(d.w)[i1];
+    old0 = update_fetch(d, t, g * cpg + (tid >> 2), gen);
+    old1 = update_fetch(d, t, C + g * cpg + (tid >> 2), gen);
   }
   if (!nt && UNI(d.gparts) > 1 && !gapd) {
     // the gradient was left as partial sums by a backward-data GEMM split over its reduction
@@ -1042,8 +1056,11 @@ __device__ __forceinline__ void step_gn_bwd(const LDesc& d, int tile, int t, boo
     if (p == 0) {
       GP(d.ggamma)[g * cpg + c] = sg; GP(d.gbeta)[g * cpg + c] = sb;
       cs2[c] = sb; cs2[cpg + c] = sg;
-      if (upd_pre) { update_loaded(d, g * cpg + c, sg, uv0, uw0); update_loaded(d, C + g * cpg + c, sb, uv1, uw1); }
-      else if (flags & F_UPD_GN) { update_one(d, g * cpg + c, sg); update_one(d, C + g * cpg + c, sb); }
+      if (flags & F_UPD_GN) {
+        if (!upd_pre) { old0 = update_fetch(d, t, g * cpg + c, gen); old1 = update_fetch(d, t, C + g * cpg + c, gen); }
+        if (gen) { update_one(d, t, g * cpg + c, sg, old0, true); update_one(d, t, C + g * cpg + c, sb, old1, true); }
+        else { update_one(d, t, g * cpg + c, sg, old0, false); update_one(d, t, C + g * cpg + c, sb, old1, false); }
+      }
     }
   }
   __syncthreads();
@@ -1221,11 +1238,10 @@ __device__ __forceinline__ void step_ingest(const LDesc& d, int tile, int t, con
 // other (d.what), so the update may run beside forward work of the same tick
 // as soon as the stage's gradients are complete.  Master weights and velocity
 // (read d.w, d.v; written d.wp, d.b) are updated in place.
-// Update size N above one (the paper's setting is one; this path is not tuned): the gradients of N
+// Update size N above one (the paper's setting is one): the gradients of N
 // consecutive samples are added up in d.gacc and one update with their mean is applied after the
 // backward pass of the last of them.  On every other tick the parameters stand still and the
 // predicted weights are carried over from the slot of this tick to the slot of the next one.
-// Two vectors per thread at a time: the step shares its kernel with steps that need every register.
 __device__ __forceinline__ void step_update_acc(const LDesc& d, int tile, int t) {
   const int N = UNI(d.upd_n);
   const int n4 = UNI(d.n) >> 2;
@@ -1242,29 +1258,49 @@ __device__ __forceinline__ void step_update_acc(const LDesc& d, int tile, int t)
   const gv4* hs = (const gv4*)(d.what0 + (size_t)(t % UNI(d.pdepth)) * (size_t)UNI(d.pstride));
   const float inv = 1.0f / (float)N;
   const int lo = tile * (UPD_TILE / 4), hi = (n4 < lo + UPD_TILE / 4) ? n4 : lo + UPD_TILE / 4;
-#pragma unroll 2
-  for (int i = lo + (int)threadIdx.x; i < hi; i += BLK) {
-    if (pos < 0) { if (ho) ho[i] = hs[i]; continue; }
-    v4f g = gp[i];
-    for (int p = 1; p < gparts; ++p) g += gp[(size_t)p * ps4 + i];
-    if (pos > 0) g += ap[i];
-    if (pos != N - 1) {
-      ap[i] = g;
-      if (ho) ho[i] = hs[i];
-      continue;
-    }
-    const v4f v0 = vp[i], w0 = wp[i];
-    v4f v2, w2, h;
+  // four vectors per thread and array at a time, requested together: one after the other they took a memory round trip each
+  constexpr int U = 4;
+  const bool first = pos == 0, apply = pos == N - 1;
+  for (int base = lo + (int)threadIdx.x; base < hi; base += U * BLK) {
+    v4f g[U], acc[U], x[U], y[U];                       // x, y: velocity and weight, or x the predicted weight that stands
 #pragma unroll
-    for (int e = 0; e < 4; ++e) {
-      const float ge = g[e] * inv;
-      v2[e] = fmaf(m, v0[e], ge);
-      w2[e] = fmaf(-lr, fmaf(a, v2[e], b * ge), w0[e]);
-      h[e] = wform ? fmaf(lrT, w2[e] - w0[e], w2[e]) : fmaf(-lrT, v2[e], w2[e]);
+    for (int u = 0; u < U; ++u) {
+      const int i = base + u * BLK < hi ? base + u * BLK : hi - 1;
+      if (pos >= 0) g[u] = gp[i];
+      if (pos > 0) acc[u] = ap[i];
+      if (apply) { x[u] = vp[i]; y[u] = wp[i]; }
+      else if (ho) x[u] = hs[i];
     }
-    vp[i] = v2;
-    wp[i] = w2;
-    if (ho) ho[i] = h;
+    if (pos >= 0)
+      for (int p = 1; p < gparts; ++p) {
+        v4f q[U];
+#pragma unroll
+        for (int u = 0; u < U; ++u) q[u] = gp[(size_t)p * ps4 + (base + u * BLK < hi ? base + u * BLK : hi - 1)];
+#pragma unroll
+        for (int u = 0; u < U; ++u) g[u] += q[u];
+      }
+#pragma unroll
+    for (int u = 0; u < U; ++u) {
+      const int i = base + u * BLK;
+      if (i >= hi) continue;
+      if (pos >= 0 && !first) g[u] += acc[u];
+      if (!apply) {
+        if (pos >= 0) ap[i] = g[u];
+        if (ho) ho[i] = x[u];
+        continue;
+      }
+      v4f v2, w2, h;
+#pragma unroll
+      for (int e = 0; e < 4; ++e) {
+        const float ge = g[u][e] * inv;
+        v2[e] = fmaf(m, x[u][e], ge);
+        w2[e] = fmaf(-lr, fmaf(a, v2[e], b * ge), y[u][e]);
+        h[e] = wform ? fmaf(lrT, w2[e] - y[u][e], w2[e]) : fmaf(-lrT, v2[e], w2[e]);
+      }
+      vp[i] = v2;
+      wp[i] = w2;
+      if (ho) ho[i] = h;
+    }
   }
 }
 
