@@ -13,8 +13,8 @@ constexpr int MLP_MAX_C = 1024;          // inputs of a stage: 16 per lane
 constexpr int MLP_MAX_K = 1024;          // classes (logits in LDS)
 constexpr int MLP_DYB = 4096;            // LDS floats for the partial gradients of a workgroup's rows
 // Ticks one launch runs at most: a launch may hold every compute unit, which are closed to other streams meanwhile, so it
-// is bounded by time.  Measured per tick: 2.9-3.3 us up to 256 inputs per stage (nq 2 and 4), 5.5 us at 512 (nq 8),
-// 4.7-9.0 us at 1024 (nq 16), i.e. 3-5 ms a launch; the way from one launch to the next costs 8 us.
+// is bounded by time.  Measured per tick: 2.1-2.3 us up to 256 inputs per stage (nq 2 and 4), 2.9 us at 512 (nq 8),
+// 4.1-6.5 us at 1024 (nq 16), i.e. 1.5-3.3 ms a launch; the way from one launch to the next costs 8 us.
 constexpr int mlp_launch_ticks(int nq) { return nq <= 4 ? 1024 : 512; }
 constexpr int mlp_hist_slots(int nq) { return nq >= 16 ? 12 : 24; }   // input history of a stage in LDS (its delay + 2)
 

@@ -7,8 +7,11 @@
 // velocities of such a network fit the register files: 512 KB per compute unit.  Here a workgroup owns 8 RW consecutive
 // rows of one stage for the whole launch, wavefront w the rows w RW .. w RW + RW - 1, lane l the columns l, l + 64, ...;
 // parameters are read when the launch starts and written when it ends, and between the ticks only activations and
-// gradients move: a few KB.  Measured: 1000 ticks of 64-128-128-128-10 15.3 -> 3.1 ms; 256 ticks of 1024-1024-1024-1024-1024-100
-// with the read-back of 34 MB 28.3 -> 3.2 ms; 16 ticks of the small one fed by the host, one launch each, 0.48 -> 0.19 ms.
+// gradients move: a few KB.  Measured: 1000 ticks of 64-128-128-128-10 15.3 -> 2.1 ms; 256 ticks of 1024-1024-1024-1024-1024-100
+// with the read-back of 34 MB 28.3 -> 3.0 ms; 16 ticks of the small one fed by the host, one launch each, 0.48 -> 0.19 ms.
+// A small tick is a chain of dependent instructions between two messages (a hop takes 0.35-0.5 us of its 2.1): no division
+// by a run-time value in it, labels in LDS, the softmax in registers, the loss after the messages, and only wavefronts that
+// take messages wait for them (with all that inside the chain the 1000 ticks took 3.1 ms).
 //
 // A tick of a workgroup: take the stage's input (from all workgroups of the previous stage) and the gradient of its own
 // rows (one partial value from every workgroup of the next stage, added in order), forward rows out, backward columns out,
@@ -24,11 +27,16 @@
 #include "pb_mlp.h"
 #include "pb_wave.h"
 
+#include <type_traits>
+
 namespace pb {
 
 typedef __attribute__((address_space(1))) float gfloat;
 typedef __attribute__((address_space(1))) uint64_t gmsg;
 typedef __attribute__((address_space(1))) int32_t gint;
+typedef __attribute__((address_space(1))) unsigned char gbyte;
+// an opaque copy: what is derived from it is worked out where it is used instead of being kept in registers
+__device__ __forceinline__ unsigned here(unsigned x) { asm volatile("" : "+v"(x)); return x; }
 #define MLP_UNI(x) __builtin_amdgcn_readfirstlane(x)
 
 __device__ __forceinline__ uint64_t msg_load(const gmsg* p) {
@@ -67,6 +75,7 @@ __global__ void __launch_bounds__(MLP_BLK) __attribute__((amdgpu_waves_per_eu(2,
   __shared__ float red[MLP_WAVES * CP];     // gradient of the input, one partial sum per wavefront
   __shared__ float dyb[MLP_DYB];            // partial gradients [part][row]
   __shared__ float lg[MLP_MAX_K];
+  __shared__ int lab[mlp_launch_ticks(NQ)];
   __shared__ int stop;
   const MlpRec P = A.recs[blockIdx.x];
   const int tid = threadIdx.x, lane = tid & 63, wv = MLP_UNI(tid >> 6);
@@ -110,7 +119,10 @@ __global__ void __launch_bounds__(MLP_BLK) __attribute__((amdgpu_waves_per_eu(2,
       if (c < CP) hist[sl * CP + c] = (tt >= 0 && c < C) ? ((const gfloat*)P.xring)[(size_t)sl * C + c] : 0.f;
     }
   }
-  auto sample_of = [&](int t) { return (const gfloat*)(A.sample ? A.sample : A.pool + (size_t)(((int64_t)A.idx_base + t) % A.n_pool) * C); };
+  // (pool items, ring slots and the like are counted up from tick to tick: a division by a run-time value is some forty
+  // dependent instructions, with 64 bits far more)
+  int item = A.sample ? 0 : (int)(((int64_t)A.idx_base + t0) % A.n_pool);
+  auto sample_of = [&](int it) { return (const gfloat*)(A.sample ? A.sample : A.pool + (size_t)it * C); };
   float xs[XU];
   auto fetch_input = [&](const gfloat* src) {
 #pragma unroll
@@ -119,16 +131,20 @@ __global__ void __launch_bounds__(MLP_BLK) __attribute__((amdgpu_waves_per_eu(2,
       xs[u] = c < C ? src[c] : 0.f;
     }
   };
-  fetch_input(first ? sample_of(t0) : (const gfloat*)P.xring + (size_t)(t0 % depth) * C);
-  // labels of the samples that entered before this launch (the ring's slot is overwritten when the launch ends)
-  int old_label[MLP_MAX_STAGES];
+  fetch_input(first ? sample_of(item) : (const gfloat*)P.xring + (size_t)(t0 % depth) * C);
+  // the launch's labels into LDS: in the last stage, whose tick is the longest, a request and its index arithmetic would stand
+  // between the logits and their gradient.  Samples that entered before this launch have theirs in the label ring (whose
+  // slots are overwritten when the launch ends).
+  int loss_at = 0;
   if (last) {
-#pragma unroll
-    for (int j = 0; j < MLP_MAX_STAGES; ++j) {
-      const int sm = t0 - (S - 1) + j;
-      old_label[j] = (j < S - 1 && sm >= 0) ? ((const gint*)A.labels)[sm % S] : 0;
+    const int j0 = t0 - (S - 1);
+    loss_at = j0 > 0 ? j0 % A.loss_cap : 0;
+    for (int i = tid; i < n; i += MLP_BLK) {
+      const int j = j0 + i;
+      lab[i] = j >= t0 ? ((const gint*)A.pool_labels)[((int64_t)A.idx_base + j) % A.n_pool] : j >= 0 ? ((const gint*)A.labels)[j % S] : 0;
     }
   }
+  int yslot = last ? 0 : (t0 + 1) % D;
   if (tid == 0) stop = 0;
   __syncthreads();
 
@@ -139,37 +155,47 @@ __global__ void __launch_bounds__(MLP_BLK) __attribute__((amdgpu_waves_per_eu(2,
     const uint32_t tag = (uint32_t)t + 1u;
     const bool live_f = t >= P.t_f, live_b = t >= P.t_b;
     float* hx = hist + slot * CP;
-    // ---- the tick's input and the gradient of the workgroup's rows
-    {
+    float sm = 0.f, lmx = 0.f;
+    // ---- the tick's input and the gradient of the workgroup's rows.  NU: messages per thread the latter take.  (Where one is
+    // enough the bookkeeping of up to eight -- guards, addresses, checks -- was half of the time between two ticks.)
+    auto take = [&](auto NU_) {
+      constexpr int NU = decltype(NU_)::value;
       const bool plain_dy = it == 0 && A.dy_plain;
       const bool poll_x = !first && it > 0;
       const int nd = (last || (it == 0 && (!live_b || plain_dy))) ? 0 : parts * R;
-      const gmsg* xm_p = (const gmsg*)P.xbox + (size_t)par * C;
-      const gmsg* dm_p = (const gmsg*)P.dybox + (size_t)par * parts * K;
-      uint64_t xm[XU], dm[DU];
+      const gbyte* xb = (const gbyte*)P.xbox + (size_t)(par * C) * 8;
+      const gbyte* db = (const gbyte*)P.dybox + (size_t)(par * parts * K) * 8;
+      const unsigned tl = here((unsigned)tid);
+      unsigned xof[XU], dof[NU];
+#pragma unroll
+      for (int u = 0; u < XU; ++u) {
+        const unsigned c = tl + u * MLP_BLK;
+        xof[u] = c < (unsigned)C ? 8u * c : 0u;
+      }
+#pragma unroll
+      for (int u = 0; u < NU; ++u) {
+        const unsigned i = tl + u * MLP_BLK, q = i / R, row = (unsigned)r0 + i % R;
+        dof[u] = (i < (unsigned)nd && row < (unsigned)K) ? 8u * (q * (unsigned)K + row) : 0u;
+      }
+      uint64_t xm[XU], dm[NU];
       MlpWait wait;
-      for (;;) {
+      // (only wavefronts that take something: with few columns the first ones do, which have no messages of their own on
+      // their way -- a wait for a load is one for the stores before it, too)
+      while ((poll_x && wv * 64 < C) || wv * 64 < nd) {
         bool ok = true;
         if (poll_x) {
 #pragma unroll
-          for (int u = 0; u < XU; ++u) {
-            const int c = tid + u * MLP_BLK;
-            xm[u] = msg_load(xm_p + (c < C ? c : 0));
-          }
+          for (int u = 0; u < XU; ++u) xm[u] = msg_load((const gmsg*)(xb + xof[u]));
         }
 #pragma unroll
-        for (int u = 0; u < DU; ++u) {
-          if (u * MLP_BLK < nd) {
-            const int i = tid + u * MLP_BLK, p = i / R, row = r0 + i % R;
-            dm[u] = msg_load(dm_p + ((i < nd && row < K) ? (size_t)p * K + row : 0));
-          }
-        }
+        for (int u = 0; u < NU; ++u)
+          if (u * MLP_BLK < nd) dm[u] = msg_load((const gmsg*)(db + dof[u]));
         if (poll_x) {
 #pragma unroll
           for (int u = 0; u < XU; ++u) ok = ok && msg_tag(xm[u]) == tag;
         }
 #pragma unroll
-        for (int u = 0; u < DU; ++u)
+        for (int u = 0; u < NU; ++u)
           if (u * MLP_BLK < nd) ok = ok && msg_tag(dm[u]) == tag;
         if (__ballot(!ok) == 0) break;
         if (wait.expired(A.sync)) { stop = 1; break; }
@@ -181,7 +207,7 @@ __global__ void __launch_bounds__(MLP_BLK) __attribute__((amdgpu_waves_per_eu(2,
         if (first && P.me == 0 && c < C) ((gfloat*)P.xring)[(size_t)slot * C + c] = xs[u];
       }
 #pragma unroll
-      for (int u = 0; u < DU; ++u) {
+      for (int u = 0; u < NU; ++u) {
         const int i = tid + u * MLP_BLK;
         if (u * MLP_BLK < nd && i < nd) dyb[i] = r0 + i % R < K ? msg_value(dm[u]) : 0.f;
       }
@@ -190,7 +216,9 @@ __global__ void __launch_bounds__(MLP_BLK) __attribute__((amdgpu_waves_per_eu(2,
         const float g = (plain_dy && live_b && row < K) ? ((const gfloat*)P.gradbox)[(size_t)par * K + row] : 0.f;
         for (int p = 0; p < parts; ++p) dyb[p * R + tid] = p == 0 ? g : 0.f;
       }
-    }
+    };
+    if (parts * R <= MLP_BLK) take(std::integral_constant<int, 1>());
+    else take(std::integral_constant<int, DU>());
     __syncthreads();
     if (stop) { ok_all = false; break; }
     float xn[NQ], xo[NQ];
@@ -205,8 +233,8 @@ __global__ void __launch_bounds__(MLP_BLK) __attribute__((amdgpu_waves_per_eu(2,
     if (!last) {
 #pragma unroll
       for (int i = 0; i < RW; ++i) {
-        float a = 0.f;
-        for (int p = lane; p < parts; p += 64) a += dyb[p * R + wv * RW + i];
+        float a = lane < parts ? dyb[lane * R + wv * RW + i] : 0.f;
+        for (int p = lane + 64; p < parts; p += 64) a += dyb[p * R + wv * RW + i];
         dy[i] = wave_sum(a);
       }
     }
@@ -231,7 +259,7 @@ __global__ void __launch_bounds__(MLP_BLK) __attribute__((amdgpu_waves_per_eu(2,
     if (!last) {
       if (mine) {
         msg_store((gmsg*)P.ybox + (size_t)(par ^ 1) * K + row0 + lane, ysel, tag + 1u);
-        if (live_f) ((gfloat*)P.yring)[(size_t)((t + 1) % D) * K + row0 + lane] = ysel;
+        if (live_f) ((gfloat*)P.yring)[(size_t)yslot * K + row0 + lane] = ysel;
       }
     } else {
       if (P.n_wg == 1) {
@@ -251,22 +279,26 @@ __global__ void __launch_bounds__(MLP_BLK) __attribute__((amdgpu_waves_per_eu(2,
 #pragma unroll
       for (int i = 0; i < RW; ++i) dy[i] = 0.f;
       if (live_f) {
-        // softmax cross-entropy, by every wavefront for itself
-        const int j = t - (S - 1);
-        int label = 0;
-        if (j >= t0) label = ((const gint*)A.pool_labels)[((int64_t)A.idx_base + j) % A.n_pool];
-#pragma unroll
-        for (int q = 0; q < MLP_MAX_STAGES; ++q) label = (j < t0 && q == it) ? old_label[q] : label;
-        float mx = -3.0e38f;
-        for (int k = lane; k < K; k += 64) mx = fmaxf(mx, lg[k]);
-        mx = wave_max(mx);
-        float sm = 0.f;
-        for (int k = lane; k < K; k += 64) sm += expf(lg[k] - mx);
+        // softmax cross-entropy, by every wavefront for itself; up to 64 classes stay in a register
+        const int label = lab[it];
+        float mx = -3.0e38f, l0 = -3.0e38f;
+        if (lane < K) l0 = lg[lane];
+        mx = l0;
+        for (int k = lane + 64; k < K; k += 64) mx = fmaxf(mx, lg[k]);
+        mx = wave_max_dpp(mx);
+        const float e0 = lane < K ? expf(l0 - mx) : 0.f;
+        sm = e0;
+        for (int k = lane + 64; k < K; k += 64) sm += expf(lg[k] - mx);
         sm = wave_sum(sm);
-        if (P.me == 0 && tid == 0) A.loss[j % A.loss_cap] = logf(sm) + mx - lg[label];
+        lmx = mx;
 #pragma unroll
-        for (int i = 0; i < RW; ++i)
-          if (row0 + i < K) dy[i] = expf(lg[row0 + i] - mx) / sm - (row0 + i == label ? 1.f : 0.f);
+        for (int i = 0; i < RW; ++i) {
+          const int r = row0 + i;
+          if (r < K) {
+            const float e = r < 64 ? __int_as_float(__builtin_amdgcn_readlane(__float_as_int(e0), MLP_UNI(r))) : expf(lg[r] - mx);
+            dy[i] = e / sm - (r == label ? 1.f : 0.f);
+          }
+        }
       }
     }
     // ---- gradient of the input: this workgroup's rows' share of every column
@@ -277,12 +309,16 @@ __global__ void __launch_bounds__(MLP_BLK) __attribute__((amdgpu_waves_per_eu(2,
       for (int i = 0; i < RW; ++i) a = fmaf(w[i][q], dy[i], a);
       if (!first) red[wv * CP + lane + 64 * q] = a;
     }
-    if (first && it + 1 < n) fetch_input(sample_of(t + 1));
+    if (first && it + 1 < n) {
+      if (!A.sample) item = item + 1 == A.n_pool ? 0 : item + 1;
+      fetch_input(sample_of(item));
+    }
     __syncthreads();
     if (!first) {
 #pragma unroll
       for (int u = 0; u < XU; ++u) {
-        const int c = tid + u * MLP_BLK;
+        // (with up to 256 columns the other half of the workgroup sends)
+        const int c = (tid ^ (MLP_BLK / 2)) + u * MLP_BLK;
         if (c < C) {
           float a = 0.f;
 #pragma unroll
@@ -292,6 +328,13 @@ __global__ void __launch_bounds__(MLP_BLK) __attribute__((amdgpu_waves_per_eu(2,
         }
       }
     }
+    if (last) {
+      if (live_f) {
+        if (P.me == 0 && tid == MLP_BLK - 64) ((gfloat*)A.loss)[loss_at] = logf(sm) + lmx - lg[lab[it]];
+        loss_at = loss_at + 1 == A.loss_cap ? 0 : loss_at + 1;
+      }
+    }
+    yslot = yslot + 1 == D ? 0 : yslot + 1;
     // ---- update (Eqs. gscv, gscw, lwp_v_form / lwp_w_form) while the messages are on their way
 #pragma unroll
     for (int i = 0; i < RW; ++i) {

@@ -32,6 +32,21 @@ __device__ __forceinline__ float row_sum(float v) {
   return v;
 }
 
+// Maximum over the wavefront, returned to every lane, without LDS: lanes without a source keep their own value.
+template <int CTRL, int ROW_MASK>
+__device__ __forceinline__ float dpp_or_self(float v) {
+  return __int_as_float(__builtin_amdgcn_update_dpp(__float_as_int(v), __float_as_int(v), CTRL, ROW_MASK, 0xF, false));
+}
+__device__ __forceinline__ float wave_max_dpp(float v) {
+  v = fmaxf(v, dpp_or_self<0xB1, 0xF>(v));
+  v = fmaxf(v, dpp_or_self<0x4E, 0xF>(v));
+  v = fmaxf(v, dpp_or_self<0x141, 0xF>(v));
+  v = fmaxf(v, dpp_or_self<0x140, 0xF>(v));
+  v = fmaxf(v, dpp_or_self<0x142, 0xA>(v));
+  v = fmaxf(v, dpp_or_self<0x143, 0xC>(v));
+  return __int_as_float(__builtin_amdgcn_readlane(__float_as_int(v), 63));
+}
+
 __device__ __forceinline__ float wave_max(float v) {
 #pragma unroll
   for (int o = 32; o > 0; o >>= 1) v = fmaxf(v, __shfl_xor(v, o, 64));

@@ -64,6 +64,13 @@ def test_perceptron_follows_the_oracle(dims, form):
     b.close()
 
 
+@pytest.mark.parametrize("dims", [(40, 24, 63), (40, 24, 64), (40, 24, 65), (30, 256, 520, 64), (30, 1024, 129)])
+def test_classes_around_a_wavefront_and_messages_around_a_workgroup(dims):
+    """Up to 64 classes the softmax keeps a lane's exponential, the other logits it reads again; up to 512 partial gradients
+    a thread takes one message, above that up to eight."""
+    test_perceptron_follows_the_oracle(dims, "v")
+
+
 def test_contexts_that_do_not_fit_the_gpu_together_take_turns():
     """Two contexts of 177 workgroups on two streams: launches of one wait for the other's."""
     import torch
