@@ -1188,6 +1188,7 @@ void wave_reduce(StepDesc& d) {
   // (a gradient routed back through a max-pool costs a window search per element: small maps only)
   // (larger maps: a workgroup per channel with 16-byte loads; a wavefront's rounds over a 32x32 map took 56 us)
   if (g_tile_budget_us <= 0 || d.H * d.W > ((d.flags & F_DU_POOL) ? 64 : GNB_WAVE_HW)) return;
+  if ((d.flags & F_DU_POOL) && d.PH * d.PW > 64) return;
   d.grain = 1;
   d.ntiles = cdiv(d.C, GNB_WAVE_CH * (BLK / 64));
 }
@@ -2181,13 +2182,13 @@ int validate_steps(const pb_ctx* c, const std::vector<std::pair<int, StepDesc>>&
              ptr_ok(d.part, 3 * d.C) && ptr_ok(d.gamma, d.C);
         if (d.kind == K_GNB_REDUCE) {
           ok = ok && ptr_ok(d.ggamma, d.C) && ptr_ok(d.gbeta, d.C) && (!d.dx.base || (route_fits(d) && ref_ok(d.dx, in)));
-          if (d.grain == 1) ok = ok && d.H * d.W <= GNB_WAVE_HW && d.ntiles == cdiv(d.C, GNB_WAVE_CH * (BLK / 64));
+          if (d.grain == 1) ok = ok && d.H * d.W <= GNB_WAVE_HW && (!(d.flags & F_DU_POOL) || (d.H * d.W <= 64 && dyn <= 64 * (int64_t)d.C)) && d.ntiles == cdiv(d.C, GNB_WAVE_CH * (BLK / 64));
           else if (d.grain == 2) ok = ok && !c->nt_stores && wave4_fits(c, d) && d.gparts <= 1 && d.ntiles == cdiv(d.C, BLK / 64);
           else ok = ok && d.grain == 0 && d.ntiles == d.C;
           if (d.gparts > 1) {   // sums partial gradients: wave form with at most 64 values per channel, or the form that
                                 // stages a channel's pooled gradient in LDS
             ok = ok && d.gparts <= FWD_PARTS && d.gpstride >= dyn && ptr_ok(d.gw, (int64_t)(d.gparts - 1) * d.gpstride + dyn);
-            if (d.grain == 1) ok = ok && dyn / d.C <= 64;
+            if (d.grain == 1) ok = ok && dyn / d.C <= 64 && (d.flags & (F_DU_BUF | F_DU_POOL));
             else ok = ok && (d.flags & F_DU_POOL) && (int64_t)d.H * d.W + (int64_t)d.PH * d.PW <= LDS_FLOATS;
           }
         } else {

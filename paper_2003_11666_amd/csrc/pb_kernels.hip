@@ -564,27 +564,8 @@ __device__ __forceinline__ void step_gnb_reduce_wave(const LDesc& d, int tile, i
   const gfloat* dy = at(d.dy, t);
   const bool rl = UNI(d.flags) & F_GN_RELU, pooled = UNI(d.flags) & F_DU_POOL, gap = UNI(d.flags) & F_DU_GAP;
   constexpr int RU = 4;
-  // The incoming gradient was left as partial sums by a backward-data GEMM split over its
-  // reduction (at most 64 values per channel): add them up in order, write the gradient for
-  // the elementwise pass that reads it in a later launch, and keep it in LDS for this step.
   const int gparts = nt ? 1 : UNI(d.gparts);   // (only in the instantiation for networks tiled for throughput)
-  lfloat* ls = smem + UNI((int)(threadIdx.x >> 6)) * (GNB_WAVE_CH * 64);
-  if (gparts > 1) {
-    const int n_dy = pooled ? UNI(d.PH) * UNI(d.PW) : HW;
-    const gfloat* part = GP(d.gw);
-    const size_t ps = (size_t)UNI(d.gpstride);
-#pragma unroll
-    for (int q = 0; q < GNB_WAVE_CH; ++q) {
-      const int c = c0 + q;
-      if (c < C && lane < n_dy) {
-        const size_t o = (size_t)c * n_dy + lane;
-        const float s = sum_parts<float, 8>(part + o, ps, gparts);
-        ((gfloat*)dy)[o] = s;
-        ls[q * 64 + lane] = s;
-      }
-    }
-    __builtin_amdgcn_wave_barrier();
-  }
+  const bool staged = pooled || gparts > 1;    // (at most 64 gradient values per channel; pooled, at most 64 pixels)
   float xv[GNB_WAVE_CH][RU], dv[GNB_WAVE_CH][RU], mean[GNB_WAVE_CH], rstd[GNB_WAVE_CH], sc[GNB_WAVE_CH], sh[GNB_WAVE_CH],
       gm[GNB_WAVE_CH];
 #pragma unroll
@@ -598,27 +579,55 @@ __device__ __forceinline__ void step_gnb_reduce_wave(const LDesc& d, int tile, i
 #pragma unroll
       for (int u = 0; u < RU; ++u) {
         const int i = lane + u * 64;
-        if (i < HW) { xv[q][u] = x[(size_t)c * HW + i]; if (!pooled) dv[q][u] = gap ? dy[c] / (float)HW : dy[(size_t)c * HW + i]; }
+        if (i < HW) { xv[q][u] = x[(size_t)c * HW + i]; if (!staged) dv[q][u] = gap ? dy[c] / (float)HW : dy[(size_t)c * HW + i]; }
       }
       mean[q] = st[g]; rstd[q] = st[G + g]; sc[q] = st[2 * G + c]; sh[q] = st[2 * G + C + c];
       gm[q] = GP(d.gamma)[c];
-      if (pooled) {   // gradient routed back through the max-pool (needs the channel's scale and shift)
-#pragma unroll
-        for (int u = 0; u < RU; ++u) {
-          const int i = lane + u * 64;
-          if (i < HW && gparts <= 1) dv[q][u] = gn_du(d, dy, x + (size_t)c * HW, sc[q], sh[q], c, i, HW);
-        }
-      }
     }
   }
-  if (gparts > 1) {   // (maps of at most 64 pixels: u = 0 only) the summed gradient from LDS
-    const int W = UNI(d.W), h = fdiv(lane, frcp(W)), w = lane - h * W;
+  // The incoming gradient is left as partial sums by a backward-data GEMM split over its reduction: they are added up in
+  // order, the sum is written for the elementwise pass that reads it in a later launch, and kept in LDS for this step.  A
+  // pooled gradient goes by LDS too, and so does the map whose windows are searched: from memory the four channels' sums and
+  // searches were a chain of some ten round trips, the end of a launch of VGG-11 (81.5 us per tick that way, 77.9 this way).
+  if (staged) {
+    lfloat* ls = smem + UNI((int)(threadIdx.x >> 6)) * (2 * GNB_WAVE_CH * 64);
+    lfloat* lx = ls + GNB_WAVE_CH * 64;
+    const int n_dy = pooled ? UNI(d.PH) * UNI(d.PW) : HW;
+    const gfloat* part = gparts > 1 ? (const gfloat*)GP(d.gw) : dy;
+    const size_t ps = gparts > 1 ? (size_t)UNI(d.gpstride) : 0;
+    const unsigned at0 = (unsigned)(lane < n_dy ? lane : 0);
+    float s[GNB_WAVE_CH];
+    constexpr int PB = 4;                      // parts of all channels in flight
+    for (int p0 = 0; p0 < gparts || p0 == 0; p0 += PB) {
+      float v[PB][GNB_WAVE_CH];
+#pragma unroll
+      for (int p = 0; p < PB; ++p)
+        if (p0 + p == 0 || p0 + p < gparts) {
+#pragma unroll
+          for (int q = 0; q < GNB_WAVE_CH; ++q) {
+            const int c = c0 + q < C ? c0 + q : C - 1;
+            v[p][q] = (part + (size_t)(p0 + p) * ps + (size_t)c * n_dy)[at0];
+          }
+        }
+#pragma unroll
+      for (int p = 0; p < PB; ++p)
+        if (p0 + p == 0 || p0 + p < gparts) {
+#pragma unroll
+          for (int q = 0; q < GNB_WAVE_CH; ++q) s[q] = p0 + p == 0 ? v[p][q] : s[q] + v[p][q];
+        }
+    }
 #pragma unroll
     for (int q = 0; q < GNB_WAVE_CH; ++q) {
-      const int c = c0 + q;
-      if (c < C && lane < HW)
-        dv[q][0] = pooled ? pool_routed(d, x + (size_t)c * HW, sc[q], sh[q], h, w, (const lfloat*)(ls + q * 64)) : ls[q * 64 + lane];
+      if (gparts > 1 && c0 + q < C && lane < n_dy) ((gfloat*)dy)[(size_t)(c0 + q) * n_dy + lane] = s[q];
+      ls[q * 64 + lane] = s[q];
+      lx[q * 64 + lane] = xv[q][0];
     }
+    __builtin_amdgcn_wave_barrier();
+    const int W = UNI(d.W), h = fdiv(lane, frcp(W)), w = lane - h * W;
+#pragma unroll
+    for (int q = 0; q < GNB_WAVE_CH; ++q)
+      if (c0 + q < C && lane < HW)
+        dv[q][0] = pooled ? pool_routed(d, (const lfloat*)(lx + q * 64), sc[q], sh[q], h, w, (const lfloat*)(ls + q * 64)) : ls[q * 64 + lane];
   }
 #pragma unroll
   for (int q = 0; q < GNB_WAVE_CH; ++q) {

@@ -33,3 +33,12 @@ def test_pool_backward_follows_the_oracle(net, tuning):
         assert np.linalg.norm(getattr(eng, k)() - ref[k]) < (2e-3 if net["in_h"] > 100 else 2e-4) * np.linalg.norm(ref[k]), k
     assert_tensors_follow(eng, ref)
     eng.close()
+
+
+@pytest.mark.parametrize("widths,pools,hw", [((8, 24, 256), (0, 1), 14), ((32, 40, 512), (0, 1), 14), ((64, 128, 72, 256), (1, 2), 16),
+                                             ((16, 16, 1024), (1,), 8), ((32, 40, 512, 20), (0, 1, 2), 15)], ids=str)
+def test_pooled_gradients_of_small_maps(widths, pools, hw):
+    """A wavefront takes four channels of up to 64 pixels: channels that do not fill the wavefronts, maps of 1 to 64 pixels,
+    pooled gradients left in up to four parts by the next stage."""
+    net = W._net("pools", W.vgg(widths, pools, 4, n_classes=5, in_hw=hw), 3, hw, hw, 5, 1e-3, 0.9, 8, 3, 8)
+    test_pool_backward_follows_the_oracle(net, dict(tile_budget_us=6.0))
