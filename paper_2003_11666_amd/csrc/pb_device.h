@@ -34,7 +34,7 @@ enum StepKind : int32_t {
   K_GAP_FWD = 1,     // mean over H*W of relu(affine(x))
   K_CONV_FWD = 2,    // convolution / linear forward with fused input transform and skip add
   K_POST_FWD = 3,    // relu(affine(z)) [+ max-pool]
-  K_CE = 4,          // softmax cross-entropy + dlogits
+  K_CE = 4,          // softmax cross-entropy + dlogits (gb: also written there, the bias gradient of a dense layer)
   K_GNB_REDUCE = 5,  // GroupNorm backward: per-channel sums (dgamma, dbeta)
   K_GNB_APPLY = 6,   // GroupNorm backward: elementwise dx
   K_CONV_BWD_X = 7,  // backward data
@@ -54,7 +54,7 @@ enum StepKind : int32_t {
   // of 4): nothing for the matrix cores, a stream of the weight matrix.
   K_FC_FWD = 18,     // y = W x + b: a wavefront per output, four outputs per workgroup
   K_FC_BWD_X = 19,   // dx = W^T dy: FC_BX inputs per workgroup, the outputs dealt out to groups of lanes
-  K_FC_BWD_W = 20,   // gW = dy x^T: 4096 consecutive weights per workgroup
+  K_FC_BWD_W = 20,   // gW = dy x^T: 4096 consecutive weights per workgroup (F_UPD_W: their update)
   K_NATURAL = 21     // read-back of a layer stored in the order of F_W_PERM (w) in its own order (gw): NAT_TILE floats per workgroup
 };
 
@@ -144,6 +144,7 @@ enum StepFlags : int32_t {
   , F_W_PERM = 1048576 // ... weights and velocities as the backward-data tiles load the weights, K and C multiples of 32:
                       // [C / 16][K / 32][tap][K / 16 % 2][K % 4][C % 16][K / 4 % 4] (pb_read_weights sees the natural order)
   , F_UPD_GEN = 2097152 // K_GN_BWD that updates scale and shift: at an update size above one or with weight stashing
+  , F_CE_DY = 4194304  // K_FC_BWD_X: dy holds the logits; the step works out their gradient itself (beside K_CE, not behind it)
 };
 
 struct StepDesc {

@@ -1367,8 +1367,9 @@ void compile_steps_once(pb_ctx* c, std::vector<std::pair<int, StepDesc>>& out) {
     // Weight gradients whose tiles hold whole sums (reduction not split over workgroups) update their weights themselves:
     // they run a phase after the data gradient, which reads the weights they overwrite.  (Not with a GroupNorm behind the
     // layer: the phase after its backward GEMMs holds nothing else, and VGG-11 took 104 us instead of 94.)
+    bool fc_upd = false;   // the weights of the dense layer in front of the loss are updated by its weight-gradient step
     auto fuse_update = [&](StepDesc& d, int64_t o, int64_t n) {
-      if (g_tile_budget_us <= 0 || c->N != 1 || a.post_gn || d.kind != K_GEMM || !(d.g.mm || d.g.dc) || d.g.parts != 1 || n % 4 || o % 4) return false;
+      if (g_tile_budget_us <= 0 || c->N != 1 || a.post_gn || (d.kind == K_GEMM ? !(d.g.mm || d.g.dc) || d.g.parts != 1 : d.kind != K_FC_BWD_W || !fc_upd) || n % 4 || o % 4) return false;
       d.flags |= F_UPD_W | F_ALWAYS;
       set_update_coeffs(c, a, &d);
       d.w = wb + o; d.v = c->f(L.v + a.off + o); d.what = c->f(L.what[s] + o);
@@ -1588,6 +1589,7 @@ void compile_steps_once(pb_ctx* c, std::vector<std::pair<int, StepDesc>>& out) {
       if (c->bf16) e.flags |= F_BF16_OUT;
       out.push_back({ph++, e});
     }
+    int ce_at = -1;
     if (a.ce) {
       StepDesc d = blank(K_CE, s, t_f);
       d.n = a.K; d.n_stages = NS; d.loss_cap = c->loss_cap;
@@ -1596,9 +1598,11 @@ void compile_steps_once(pb_ctx* c, std::vector<std::pair<int, StepDesc>>& out) {
       d.loss_log = c->f(L.loss);
       d.labels = c->labels_dev;
       d.ntiles = 1;
+      ce_at = (int)out.size();
       out.push_back({ph++, d});
     }
     // ----------------------------------------------------------- backward
+    int wgrad_at = -1;
     int pb = (s == S - 1) ? ph : 0;
     bwd0[s] = pb;
     const TRef dy_src = (s == S - 1) ? ring(c, b.dlogits, 1, a.K, 0)
@@ -1672,7 +1676,13 @@ void compile_steps_once(pb_ctx* c, std::vector<std::pair<int, StepDesc>>& out) {
       if (fuse_w) {
         fusedw[s].phase = pb; fusedw[s].x = d.x; fusedw[s].dy = d.dy; fusedw[s].pp = pp_stride > 0 ? pp_stride : 0;
       } else if (fc_w) {
-        if (a.has_bias) {
+        // the dense layer in front of the loss: its bias gradient is the logits' gradient, which K_CE writes twice, and the step
+        // updates the weights itself, a phase behind backward data, which reads them.  Measured without and with this (and with
+        // F_CE_DY below), head 2048 x 1000: ResNet-50 at 224 pixels 490 and 477 us per tick, its stages at 64 pixels 228 and 220.
+        // At update sizes above one the gradient is needed in memory.
+        fc_upd = ce_at >= 0 && !a.add && !a.post_gn && c->N == 1;
+        if (a.has_bias && fc_upd) out[ce_at].second.gb = gr + a.o_b;
+        else if (a.has_bias) {
           StepDesc e = blank(K_BIAS_GRAD, s, t_b);
           e.K = a.K; e.OH = a.OH; e.OW = a.OW; e.dy = dz_src; e.gb = gr + a.o_b;
           e.ntiles = cdiv(a.K, BLK / 64);
@@ -1707,6 +1717,8 @@ void compile_steps_once(pb_ctx* c, std::vector<std::pair<int, StepDesc>>& out) {
         d.flags |= F_W_PERM;
         c->perm_w[s] = 1;
       }
+      fc_upd = fc_upd && upd_w;
+      wgrad_at = (int)out.size();
       if (!fuse_w) out.push_back({upd_w ? pb + 1 : pb, d});
     }
     if (s > 0) {   // data gradient of the main layer
@@ -1736,6 +1748,12 @@ void compile_steps_once(pb_ctx* c, std::vector<std::pair<int, StepDesc>>& out) {
       if (fc_layer(c, d, d.w) && !(d.flags & (F_MASK_X | F_ADD_SKG)) && ref_vec4(c, d.dx)) {
         d.kind = K_FC_BWD_X;
         d.ntiles = cdiv(d.C, FC_BX);
+        if (fc_upd && d.dy.base == dy_src.base) {   // in the phase of K_CE, from the logits
+          d.flags |= F_CE_DY;
+          d.dy = ring(c, b.logits, 1, a.K, 0);
+          d.labels = c->labels_dev; d.n_stages = NS;
+          out[wgrad_at].first = pb--;
+        }
       } else
       if (dot_bwd) {
         // 64 input channels per workgroup; the output channels in as many parts as the gradient's consumer can
@@ -1935,9 +1953,9 @@ void compile_steps_once(pb_ctx* c, std::vector<std::pair<int, StepDesc>>& out) {
       const StepDesc& e = pr.second;
       if (e.stage != s) continue;
       if (e.kind == K_GN_BWD && (e.flags & F_UPD_GN)) { gn_fused = true; continue; }
-      if (e.kind == K_GEMM && (e.flags & F_UPD_W)) continue;
+      if (e.flags & F_UPD_W) continue;
       const bool writes_grad = (e.kind == K_GEMM && e.g.gm == 3) || e.kind == K_CONV_BWD_W || e.kind == K_BIAS_GRAD ||
-                               e.kind == K_GNB_REDUCE || e.kind == K_GN_BWD || e.kind == K_HEAD;
+                               e.kind == K_GNB_REDUCE || e.kind == K_GN_BWD || e.kind == K_HEAD || (e.kind == K_CE && e.gb);
       if (writes_grad) last_grad_phase = std::max(last_grad_phase, pr.first);
       if (e.kind == K_GEMM && e.g.gm == 3) gparts = std::max(gparts, e.g.parts);
     }
@@ -2172,7 +2190,7 @@ int validate_steps(const pb_ctx* c, const std::vector<std::pair<int, StepDesc>>&
              ref_ok(d.y, (d.flags & F_POOL) ? (int64_t)d.C * d.PH * d.PW : in);
         break;
       case K_CE:
-        ok = ok && d.n > 0 && ref_ok(d.x, d.n) && ref_ok(d.dx, d.n) && ptr_ok(d.loss_log, d.loss_cap) &&
+        ok = ok && d.n > 0 && ref_ok(d.x, d.n) && ref_ok(d.dx, d.n) && (!d.gb || ptr_ok(d.gb, d.n)) && ptr_ok(d.loss_log, d.loss_cap) &&
              ptr_ok((const float*)d.labels, d.n_stages);
         break;
       case K_GNB_REDUCE:
@@ -2277,12 +2295,16 @@ int validate_steps(const pb_ctx* c, const std::vector<std::pair<int, StepDesc>>&
              ref_ok(d.x, d.C) && ref_vec4(c, d.x) && ref_ok(d.y, d.K) && ptr_ok(d.w, (int64_t)d.K * d.C) && (!(d.flags & F_BIAS) || ptr_ok(d.b, d.K));
         break;
       case K_FC_BWD_X:
-        ok = ok && !c->nt_stores && fc_layer(c, d, d.w) && !(d.flags & ~(F_ALWAYS | F_BF16_OUT)) && d.ntiles == cdiv(d.C, FC_BX) &&
+        ok = ok && !c->nt_stores && fc_layer(c, d, d.w) && !(d.flags & ~(F_ALWAYS | F_BF16_OUT | F_CE_DY)) && d.ntiles == cdiv(d.C, FC_BX) &&
+             (!(d.flags & F_CE_DY) || (d.n_stages > 0 && ptr_ok((const float*)d.labels, d.n_stages))) &&
              (d.K + 3) / 4 * 4 + 64 * FC_BX <= LDS_FLOATS && ref_ok(d.dy, d.K) && ref_ok(d.dx, d.C) && ptr_ok(d.w, (int64_t)d.K * d.C);
         break;
       case K_FC_BWD_W:
-        ok = ok && !c->nt_stores && fc_layer(c, d, d.gw) && !(d.flags & ~F_ALWAYS) && d.ntiles == cdiv((int64_t)d.K * d.C, 4096) &&
+        ok = ok && !c->nt_stores && fc_layer(c, d, d.gw) && !(d.flags & ~(F_ALWAYS | F_UPD_W | F_LWP_W)) && d.ntiles == cdiv((int64_t)d.K * d.C, 4096) &&
              ref_ok(d.x, d.C) && ref_vec4(c, d.x) && ref_ok(d.dy, d.K) && ptr_ok(d.gw, (int64_t)d.K * d.C);
+        if (d.flags & F_UPD_W)
+          ok = ok && (d.flags & F_ALWAYS) && ptr_ok(d.w, (int64_t)d.K * d.C) && ptr_ok(d.v, (int64_t)d.K * d.C) && d.pmask == PF_WHAT &&
+               d.pdepth > 0 && d.plag == -1 && ptr_ok(d.what, (int64_t)(d.pdepth - 1) * d.pstride + (int64_t)d.K * d.C);
         break;
       case K_DOT_FWD: {
         const int R = d.H == 4 ? 4 : 8;

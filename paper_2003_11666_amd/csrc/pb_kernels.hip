@@ -451,8 +451,9 @@ __device__ __forceinline__ void step_ce(const LDesc& d, int tile, int t, lfloat*
   for (int i = threadIdx.x; i < n; i += BLK) s += expf(z[i] - mx);
   s = block_sum(s, red);
   for (int i = threadIdx.x; i < n; i += BLK) {
-    float p = expf(z[i] - mx) / s;
-    dz[i] = p - (i == label ? 1.f : 0.f);
+    const float p = expf(z[i] - mx) / s, e = p - (i == label ? 1.f : 0.f);
+    dz[i] = e;
+    if (d.gb) GP(d.gb)[i] = e;
   }
   if (threadIdx.x == 0) GP(d.loss_log)[sample % d.loss_cap] = logf(s) + mx - z[label];
 }
@@ -1650,27 +1651,50 @@ __device__ __forceinline__ void step_fc_fwd(const LDesc& d, int tile, int t) {
 // k out to its 64 groups of 4 lanes, group g taking k = g, g + 64, ...; the partial sums of an input are added in the
 // order of the groups.  A step of its own in its launch, so latency is what counts: 16 inputs make 128 workgroups of a
 // 2048 x 1000 layer (64 made 32, whose 64 rounds of loads took 13 us).  LDS: dy[K] | part[64][FC_BX].
-__device__ __forceinline__ void step_fc_bwd_x(const LDesc& d, int tile, int t, lfloat* smem) {
+// F_CE_DY: every workgroup works out the gradient of the logits from the logits, in the order of K_CE (the same bits), while
+// its first weights are on their way: a phase less than waiting for K_CE's single workgroup.
+__device__ __forceinline__ void step_fc_bwd_x(const LDesc& d, int tile, int t, lfloat* smem, lfloat* red) {
   const int tid = threadIdx.x, l = tid & 3, g = tid >> 2;
   const int C = UNI(d.C), K = UNI(d.K);
   const int Kp = (K + 3) & ~3;
   lfloat* dyl = smem;
   lfloat* part = smem + Kp;
   const gfloat* dy = at(d.dy, t);
-  for (int i = tid; i < K; i += BLK) dyl[i] = dy[i];
-  __syncthreads();
   const int c = tile * FC_BX + 4 * l;
+  constexpr int U = 8;
+  v4f a[U];
+  const gfloat* w = GP(d.w) + (c < C ? c : 0);
+  auto fetch = [&](int k0) {
+#pragma unroll
+    for (int u = 0; u < U; ++u) {
+      const int k = k0 + 64 * u;
+      a[u] = *(const gv4*)(w + (size_t)(k < K ? k : 0) * C);
+    }
+  };
+  for (int i = tid; i < K; i += BLK) dyl[i] = dy[i];
+  int label = -1;
+  if (UNI(d.flags) & F_CE_DY) label = ((const gint*)d.labels)[(t - (UNI(d.n_stages) - 1)) % UNI(d.n_stages)];
+  fetch(g);
+  if (UNI(d.flags) & F_CE_DY) {   // (a thread reads and writes its own entries only)
+    float mx = -3.0e38f;
+#pragma unroll 1
+    for (int i = tid; i < K; i += BLK) mx = fmaxf(mx, dyl[i]);
+    mx = block_max(mx, red);
+    float s = 0.f;
+#pragma unroll 1
+    for (int i = tid; i < K; i += BLK) s += expf(dyl[i] - mx);
+    s = block_sum(s, red);
+#pragma unroll 1
+    for (int i = tid; i < K; i += BLK) {
+      const float p = expf(dyl[i] - mx) / s;
+      dyl[i] = p - (i == label ? 1.f : 0.f);
+    }
+  }
+  __syncthreads();
   v4f acc = (v4f){0.f, 0.f, 0.f, 0.f};
   if (c < C) {
-    const gfloat* w = GP(d.w) + c;
-    constexpr int U = 8;
     for (int k0 = g; k0 < K; k0 += 64 * U) {
-      v4f a[U];
-#pragma unroll
-      for (int u = 0; u < U; ++u) {
-        const int k = k0 + 64 * u;
-        a[u] = *(const gv4*)(w + (size_t)(k < K ? k : g) * C);
-      }
+      if (k0 > g) fetch(k0);
 #pragma unroll
       for (int u = 0; u < U; ++u) {
         const int k = k0 + 64 * u;
@@ -1691,21 +1715,54 @@ __device__ __forceinline__ void step_fc_bwd_x(const LDesc& d, int tile, int t, l
 }
 
 // Backward weights, gW[k][c] = dy[k] x[c] (an outer product): 4096 consecutive weights per workgroup.
-__device__ __forceinline__ void step_fc_bwd_w(const LDesc& d, int tile, int t) {
-  const int C = UNI(d.C);
-  const int64_t n = (int64_t)UNI(d.K) * C;
+// F_UPD_W: the workgroup updates its weights instead of writing their gradient (the arithmetic of step_update, the same
+// bits): 20 bytes per weight in one launch instead of 28 in two.
+__device__ __forceinline__ void step_fc_bwd_w(const LDesc& d, int tile, int t, bool live) {
+  const int C = UNI(d.C), flags = UNI(d.flags), n = UNI(d.K) * C, e0 = tile * 4096 + 4 * (int)threadIdx.x;
   const gfloat* x = at(d.x, t);
   const gfloat* dy = at(d.dy, t);
-  gfloat* gw = GP(d.gw);
+  v4f g[4];
+  float s[4];
 #pragma unroll
   for (int j = 0; j < 4; ++j) {
-    const int e = tile * 4096 + j * 1024 + 4 * (int)threadIdx.x;
-    if (e < n) {
-      const int k = e / C, c = e - k * C;
-      const v4f xv = *(const gv4*)(x + c);
-      const float s = dy[k];
-      *(gv4*)(gw + e) = (v4f){s * xv[0], s * xv[1], s * xv[2], s * xv[3]};
+    const int e = e0 + j * 1024, ec = e < n ? e : 0, k = ec / C;
+    g[j] = *(const gv4*)(x + (ec - k * C));
+    s[j] = dy[k];
+  }
+  if (!(flags & F_UPD_W)) {
+    gfloat* gw = GP(d.gw);
+#pragma unroll
+    for (int j = 0; j < 4; ++j)
+      if (e0 + j * 1024 < n) *(gv4*)(gw + e0 + j * 1024) = g[j] * s[j];
+    return;
+  }
+  const float a = UNIF(d.fa), b = UNIF(d.fb), lrT = UNIF(d.flrT), lr = UNIF(d.flr), m = UNIF(d.fm);
+  const bool wform = flags & F_LWP_W;
+  gfloat* wp = GP((float*)d.w);
+  gfloat* vp = GP((float*)d.v);
+  gfloat* hp = GP(d.what);
+  v4f vv[4], wv[4];
+#pragma unroll
+  for (int j = 0; j < 4; ++j) {
+    const int e = e0 + j * 1024, ec = e < n ? e : 0;
+    vv[j] = *(const gv4*)(vp + ec);
+    wv[j] = *(const gv4*)(wp + ec);
+  }
+#pragma unroll
+  for (int j = 0; j < 4; ++j) {
+    const int e = e0 + j * 1024;
+    if (e >= n) continue;
+    v4f v2, w2, p;
+#pragma unroll
+    for (int q = 0; q < 4; ++q) {
+      const float gr = live ? g[j][q] * s[j] : 0.f;   // (before the layer's first gradient the weights are carried over)
+      v2[q] = fmaf(m, vv[j][q], gr);
+      w2[q] = fmaf(-lr, fmaf(a, v2[q], b * gr), wv[j][q]);
+      p[q] = wform ? fmaf(lrT, w2[q] - wv[j][q], w2[q]) : fmaf(-lrT, v2[q], w2[q]);
     }
+    *(gv4*)(vp + e) = v2;
+    *(gv4*)(wp + e) = w2;
+    *(gv4*)(hp + e) = p;
   }
 }
 
@@ -2527,8 +2584,8 @@ k_phase(const StepDesc* __restrict__ recs, const Globals* __restrict__ G, int k,
     case K_DOT_FWD: if (!NT) step_dot_fwd(d, tile, t, smem); break;
     case K_DOT_BWD_X: if (!NT) step_dot_bwd_x(d, tile, t, smem); break;
     case K_FC_FWD: if (!NT) step_fc_fwd(d, tile, t); break;
-    case K_FC_BWD_X: if (!NT) step_fc_bwd_x(d, tile, t, smem); break;
-    case K_FC_BWD_W: if (!NT) step_fc_bwd_w(d, tile, t); break;
+    case K_FC_BWD_X: if (!NT) step_fc_bwd_x(d, tile, t, smem, red); break;
+    case K_FC_BWD_W: if (!NT) step_fc_bwd_w(d, tile, t, live); break;
     case K_NATURAL: if (!NT) step_natural(d, tile); break;
     default: break;
   }
