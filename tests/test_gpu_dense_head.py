@@ -38,3 +38,10 @@ def test_dense_head_with_other_updates(kw):
 
 def test_dense_head_without_a_norm_in_front():
     _follow(W._net("dense_head", W.vgg((16, 256), (0, 1), 4, n_classes=33, in_hw=8), 3, 8, 8, 33, 1e-3, 0.9, 8, 3, 8), dict(tile_budget_us=14.0))
+
+
+@pytest.mark.parametrize("delays", ["larger", "zero"])
+def test_dense_head_with_other_delays(delays):
+    """Zero delays: the passes of a sample one after the other, the head's backward phases behind all forward ones."""
+    from tests.test_gpu_delays import test_delays_in_networks_tiled_for_throughput as follow
+    follow(_basic(40), delays, {})
