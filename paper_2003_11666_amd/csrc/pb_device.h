@@ -54,11 +54,15 @@ enum StepKind : int32_t {
   // of 4): nothing for the matrix cores, a stream of the weight matrix.
   K_FC_FWD = 18,     // y = W x + b: a wavefront per output, four outputs per workgroup
   K_FC_BWD_X = 19,   // dx = W^T dy: FC_BX inputs per workgroup, the outputs dealt out to groups of lanes
-  K_FC_BWD_W = 20,   // gW = dy x^T: 4096 consecutive weights per workgroup (F_UPD_W: their update)
-  K_NATURAL = 21     // read-back of a layer stored in the order of F_W_PERM (w) in its own order (gw): NAT_TILE floats per workgroup
+  K_FC_BWD_W = 20    // gW = dy x^T: 4096 consecutive weights per workgroup (F_UPD_W: their update)
 };
 
-constexpr int NAT_TILE = 8192;
+// Layers stored in the order of F_W_PERM, for a read-back in their own order (k_natural): a table that travels with the launch.
+constexpr int NAT_TILE = 8192;      // floats per workgroup
+constexpr int NAT_LAYERS = 128;     // layers per launch (3 KB of launch arguments)
+struct NatLayer { int64_t off; int32_t K, C, first, pad_; };   // offset of the layer's weights, its first workgroup
+struct NatTable { int32_t n, tiles; NatLayer l[NAT_LAYERS]; };
+
 constexpr int LDS_FLOATS = 19456;   // 76 KB of LDS per workgroup (a compute unit has 160 KB and holds two workgroups); the
                                     // planner gives GEMM tiles all of it or 62 KB (pb_tuning.gemm_lds_kb)
 
@@ -235,6 +239,7 @@ void launch_update_flat(float* w, float* v, const float* g, float* what, int64_t
 void launch_set_globals(Globals* G, Globals val, hipStream_t s);
 // n floats of device memory to host-visible memory dst (16-byte aligned); err != nullptr: also *err_out = *err
 void launch_copy_out(float* dst, const float* src, int64_t n, const int32_t* err, int32_t* err_out, hipStream_t s);
+void launch_natural(float* dst, const float* src, const NatTable& t, hipStream_t s);   // weights at src + off to dst + off
 void launch_fill_zero(void* p, size_t bytes, hipStream_t s);   // bytes a multiple of 16, p 16-byte aligned
 
 // The library's own device array for contexts that must not allocate (pb_init_static): its

@@ -268,7 +268,6 @@ struct StageBufs {
 struct Layout {
   int64_t P = 0;                      // padded parameter count
   int64_t w = 0, v = 0, g = 0;
-  int64_t nat = -1;                   // [P]: parameters in their own order for a read-back, where a layer may store them otherwise
   int64_t gacc = -1;                  // update size above one: gradients added up since each stage's latest update
   std::vector<int64_t> what;          // per stage: ring [De - D + 2][padded] of predicted-weight versions
   std::vector<StageBufs> sb;
@@ -292,7 +291,7 @@ bool fwd_split_candidate(const Stage& a) {
 // 3x3 layers whose weights and velocities may be stored in the order of their backward-data tiles' lanes (F_W_PERM)
 bool perm_w_shape(const Stage& a) {
   return a.is_conv && a.k == 3 && a.pad == 1 && a.pre_gn && !a.post_gn && a.C % 32 == 0 && a.K % 32 == 0 && a.o_w % 4 == 0 &&
-         (int64_t)a.C * a.K < (1 << 21);   // (an index division of the read-back)
+         (int64_t)a.C * a.K < (1 << 21);   // (the read-back counts a layer's weights in 32 bits)
 }
 bool split_candidate(const Stage& a) { return a.is_conv && (int64_t)a.OH * a.OW >= 256 && a.padded <= 65536; }
 
@@ -356,8 +355,6 @@ void plan_arena(const std::vector<Stage>& st, bool stash, int loss_cap, Layout& 
   // stage's update.  Without weight prediction the forward copy simply equals the master weights.
   L.w = pl.alloc(L.P); L.v = pl.alloc(L.P); L.g = pl.alloc(L.P);
   if (update_size > 1) L.gacc = pl.alloc(L.P);
-  for (const Stage& a : st)
-    if (L.nat < 0 && update_size == 1 && !stash && perm_w_shape(a)) L.nat = pl.alloc(L.P);
   // Exception: a stage whose update computes the weight gradient itself needs nothing but the layer's two maps, which
   // are complete a phase before the stage's backward-data step has read the weights.  With a second copy of the
   // stage's master parameters (the update of tick t reads copy t mod 2 and writes the other) it runs beside that step.
@@ -469,8 +466,6 @@ struct pb_ctx {
   std::vector<Phase> plain_phases;     // fuse_from >= 0: the same steps, a launch per phase
   // device views
   StepDesc* recs_dev = nullptr;        // one descriptor copy per workgroup, in launch order
-  int64_t nat_first = 0;               // behind them the workgroups that put parameters into their own order for a read-back:
-  int nat_tiles = 0;                   // this many for the weights, as many for the velocities
   Globals* globals_dev = nullptr;
   int32_t* zero_dev = nullptr;
   int32_t* labels_dev = nullptr;
@@ -1712,7 +1707,7 @@ void compile_steps_once(pb_ctx* c, std::vector<std::pair<int, StepDesc>>& out) {
       const bool upd_w = !fuse_w && fuse_update(d, a.o_w, a.n_w);
       if (upd_w && perm_what) d.flags |= F_WHAT_PERM;
       GemmCfg gb;
-      if (upd_w && perm_what && s > 0 && L.nat >= 0 && perm_w_shape(a) && d.g.dc && b.w2 < 0 &&
+      if (upd_w && perm_what && s > 0 && perm_w_shape(a) && d.g.dc && b.w2 < 0 &&
           make_dc(c, 2, a.C, a.H, a.W, a.K, a.OH, a.OW, a.k, a.stride, a.pad, 1, true, &gb) && gb.dc == 3) {
         d.flags |= F_W_PERM;
         c->perm_w[s] = 1;
@@ -2418,7 +2413,7 @@ int validate_steps(const pb_ctx* c, const std::vector<std::pair<int, StepDesc>>&
           if (d.flags & F_WHAT_PERM) ok = ok && c->perm_what[d.stage] && !c->stash && (d.g.gm == 1 || (d.g.gm == 3 && (d.flags & F_UPD_W))) && (d.g.gm == 3 || (d.g.dc == 3) == (d.C % 32 == 0)) && d.K % 16 == 0;
           else if (d.g.gm == 1 || (d.flags & F_UPD_W)) ok = ok && (!c->perm_what[d.stage] || d.k != 3);
           if (d.flags & F_W_PERM)
-            ok = ok && c->perm_w[d.stage] && c->L.nat >= 0 && d.K % 32 == 0 && d.C % 32 == 0 && (d.g.gm == 2 ? d.g.dc == 3 && d.pmask == 0 : d.g.gm == 3 && (d.flags & F_UPD_W));
+            ok = ok && c->perm_w[d.stage] && c->N == 1 && d.K % 32 == 0 && d.C % 32 == 0 && (d.g.gm == 2 ? d.g.dc == 3 && d.pmask == 0 : d.g.gm == 3 && (d.flags & F_UPD_W));
           else if (d.g.gm == 2 || (d.flags & F_UPD_W)) ok = ok && !c->perm_w[d.stage];
           ok = ok && (d.g.dc != 3 || d.g.ni < 4 || (d.flags & (d.g.gm == 1 ? F_WHAT_PERM : F_W_PERM)));
           const TRef& pt = d.g.gm == 2 ? d.dy : d.x;
@@ -2752,13 +2747,32 @@ int64_t copy_params_out(pb_ctx* c, int64_t arena_off, float* dst, int64_t cap) {
     put(0, a.n_head);
     if (a.n_gn) put(a.o_gamma, 2 * a.n_gn);
   }
-  // layers that store them in another order: the whole block by way of a copy on the device
-  if (c->nat_tiles > 0) {
+  // Layers that store them in another order: the whole block by way of the gradients' (a tick leaves nothing there that a
+  // later one reads, but a stage that has had no gradient yet counts on zeros), so that the arena holds no copy for it.
+  struct ClearGradients {
+    pb_ctx* c = nullptr;
+    ~ClearGradients() {
+      if (!c) return;
+      launch_fill_zero(c->f(c->L.g), sizeof(float) * c->L.P, c->stream);
+      (void)hipStreamSynchronize(c->stream);
+    }
+  } clear;
+  if (std::find(c->perm_w.begin(), c->perm_w.end(), 1) != c->perm_w.end()) {
+    clear.c = c;
     for (size_t i = 0; i < runs.size(); ++i)
-      HIP_TRY(hipMemcpyAsync(c->f(c->L.nat + run_at[i]), runs[i].src, sizeof(float) * runs[i].n, hipMemcpyDeviceToDevice, c->stream));
-    launch_phase(c->recs_dev + c->nat_first + (arena_off == c->L.w ? 0 : c->nat_tiles), c->nat_tiles, c->globals_dev, 0, nullptr, 0, false, c->stream);
+      HIP_TRY(hipMemcpyAsync(c->f(c->L.g + run_at[i]), runs[i].src, sizeof(float) * runs[i].n, hipMemcpyDeviceToDevice, c->stream));
+    NatTable nt;
+    nt.n = nt.tiles = 0;
+    for (int s = 0; s < c->S; ++s) {
+      const Stage& a = c->st[s];
+      if (!c->perm_w[s]) continue;
+      if (nt.n == NAT_LAYERS) { launch_natural(c->f(c->L.g), c->f(arena_off), nt, c->stream); nt.n = nt.tiles = 0; }
+      nt.l[nt.n++] = NatLayer{a.off + a.o_w, a.K, a.C, nt.tiles, 0};
+      nt.tiles += (int)cdiv(a.n_w, NAT_TILE);
+    }
+    launch_natural(c->f(c->L.g), c->f(arena_off), nt, c->stream);
     HIP_TRY(hipGetLastError());
-    runs.assign(1, Run{c->f(c->L.nat), P});
+    runs.assign(1, Run{c->f(c->L.g), P});
     run_at.assign(1, 0);
   }
   // pieces inside [lo, hi) of the padded layout, of which src holds the floats from lo on
@@ -2924,8 +2938,6 @@ int run_one_tick(pb_ctx* c, const float* staging, int label) {
   return PB_OK;
 }
 
-int nat_tiles(const pb_ctx* c, int s) { return c->perm_w[s] ? (int)cdiv(c->st[s].n_w, NAT_TILE) : 0; }
-
 size_t arena_bytes(const pb_net_desc* net, const int32_t* delays) {
   std::vector<Stage> st;
   bool sequential = false;
@@ -2948,7 +2960,6 @@ size_t arena_bytes(const pb_net_desc* net, const int32_t* delays) {
   if (validate_steps(&tmp, steps, pl.total) != PB_OK) return 0;
   int64_t total_tiles = 0;
   for (auto& pr : steps) total_tiles += pr.second.ntiles;
-  for (int s = 0; s < tmp.S; ++s) total_tiles += 2 * nat_tiles(&tmp, s);
   pl.alloc(total_tiles * (int64_t)sizeof(StepDesc) / 4 + 64);
   return (size_t)pl.total * sizeof(float) + 256;
 }
@@ -3224,19 +3235,6 @@ int init_common(pb_ctx** out, const pb_net_desc* net, const int32_t* delays, flo
     m.tiles = (int)(recs.size() - (size_t)c->rec_first[m.first]);
     c->phases.resize(c->fuse_from + 1);
   }
-  c->nat_first = (int64_t)recs.size();
-  for (int v = 0; v < 2; ++v)
-    for (int s = 0; s < c->S; ++s) {
-      if (!c->perm_w[s]) continue;
-      StepDesc d;
-      memset(&d, 0, sizeof d);
-      d.kind = K_NATURAL; d.flags = F_ALWAYS; d.stage = s; d.sig_idx = -1;
-      d.K = st[s].K; d.C = st[s].C; d.ntiles = nat_tiles(c, s);
-      d.w = c->f((v ? c->L.v : c->L.w) + st[s].off + st[s].o_w);
-      d.gw = c->f(c->L.nat + st[s].off + st[s].o_w);
-      for (d.tile = 0; d.tile < d.ntiles; ++d.tile) recs.push_back(d);
-    }
-  c->nat_tiles = (int)((int64_t)recs.size() - c->nat_first) / 2;
   const int64_t o_recs = pl.alloc((int64_t)recs.size() * sizeof(StepDesc) / 4 + 64);
   if ((size_t)pl.total * sizeof(float) > need) return fail(PB_E_NOMEM, "internal: arena plan mismatch");
   c->recs_dev = (StepDesc*)c->f(o_recs);

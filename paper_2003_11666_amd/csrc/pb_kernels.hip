@@ -2454,20 +2454,6 @@ __device__ __forceinline__ void step_head(const LDesc& d, int t, lfloat* red, lf
   }
 }
 
-// 3x3 weights (or velocities) from the order of F_W_PERM to their own, for a read-back: 4 of every 16 bytes requested are used,
-// the rest of a line by the same workgroup.
-__device__ __forceinline__ void step_natural(const LDesc& d, int tile) {
-  const int C = UNI(d.C), K = UNI(d.K), n = K * C * 9;
-  const float ic = frcp(C);
-  const gfloat* src = GP(d.w);
-  gfloat* dst = GP(d.gw);
-  for (int i = tile * NAT_TILE + (int)threadIdx.x; i < n && i < (tile + 1) * NAT_TILE; i += BLK) {
-    const int kc = (int)((unsigned)i / 9u), tap = i - 9 * kc, k = fdiv(kc, ic), c = kc - k * C;
-    dst[i] = src[(((((c >> 4) * (K >> 5) + (k >> 5)) * 9 + tap) * 2 + ((k >> 4) & 1)) * 4 + (k & 3)) * 64 + (c & 15) * 4 + ((k >> 2) & 3)];
-  }
-}
-
-
 // ------------------------------------------------------------------ kernels
 // One workgroup = one tile of one step.  recs[] holds, per workgroup of the
 // phase, a full copy of its step descriptor with the tile index filled in, so
@@ -2586,7 +2572,6 @@ k_phase(const StepDesc* __restrict__ recs, const Globals* __restrict__ G, int k,
     case K_FC_FWD: if (!NT) step_fc_fwd(d, tile, t); break;
     case K_FC_BWD_X: if (!NT) step_fc_bwd_x(d, tile, t, smem, red); break;
     case K_FC_BWD_W: if (!NT) step_fc_bwd_w(d, tile, t, live); break;
-    case K_NATURAL: if (!NT) step_natural(d, tile); break;
     default: break;
   }
   }
@@ -2705,6 +2690,20 @@ k_copy_out(float* __restrict__ dst, const float* __restrict__ src, int64_t n, co
   if (err && i0 == 0) *err_out = *err;
 }
 
+// 3x3 weights (or velocities) from the order of F_W_PERM to their own, for a read-back: 4 of every 16 bytes requested are used,
+// the rest of a line by the same workgroup.
+__global__ void __launch_bounds__(BLK) k_natural(float* __restrict__ dst_, const float* __restrict__ src_, NatTable T) {
+  int q = 0;
+  while (q + 1 < T.n && (int)blockIdx.x >= T.l[q + 1].first) ++q;
+  const int C = T.l[q].C, K = T.l[q].K, n = K * C * 9, lo = ((int)blockIdx.x - T.l[q].first) * NAT_TILE;
+  const float* src = src_ + T.l[q].off;
+  float* dst = dst_ + T.l[q].off;
+  for (int i = lo + (int)threadIdx.x; i < n && i < lo + NAT_TILE; i += BLK) {
+    const int kc = i / 9, tap = i - 9 * kc, k = kc / C, c = kc - k * C;
+    dst[i] = src[(((((c >> 4) * (K >> 5) + (k >> 5)) * 9 + tap) * 2 + ((k >> 4) & 1)) * 4 + (k & 3)) * 64 + (c & 15) * 4 + ((k >> 2) & 3)];
+  }
+}
+
 // Device memory of contexts that must not allocate: one array per GPU, held from the moment the
 // library's code object is loaded on that GPU until the process ends.  Host code never uses the
 // array's name as an address: static_arena() asks the runtime for the array's address on the current
@@ -2737,6 +2736,10 @@ void launch_fill_zero(void* p, size_t bytes, hipStream_t s) {
   const size_t want = (n16 + BLK - 1) / BLK;
   const unsigned grid = (unsigned)(want < 4096 ? want : 4096);
   hipLaunchKernelGGL(k_fill_zero, dim3(grid), dim3(BLK), 0, s, (v4f*)p, n16);
+}
+
+void launch_natural(float* dst, const float* src, const NatTable& t, hipStream_t s) {
+  hipLaunchKernelGGL(k_natural, dim3((unsigned)t.tiles), dim3(BLK), 0, s, dst, src, t);
 }
 
 void launch_copy_out(float* dst, const float* src, int64_t n, const int32_t* err, int32_t* err_out, hipStream_t s) {

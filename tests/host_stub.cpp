@@ -82,6 +82,19 @@ void launch_copy_out(float* dst, const float* src, int64_t n, const int32_t* err
   memcpy(dst, src, sizeof(float) * n);
   if (err) *err_out = *err;
 }
+void launch_natural(float* dst, const float* src, const NatTable& t, hipStream_t) {
+  for (int i = 0; i < t.n; ++i) {   // (the order of F_W_PERM, its dimensions from the outermost in)
+    const int C = t.l[i].C, K = t.l[i].K;
+    const float* p = src + t.l[i].off;
+    for (int cb = 0; cb < C / 16; ++cb)
+      for (int kb = 0; kb < K / 32; ++kb)
+        for (int tap = 0; tap < 9; ++tap)
+          for (int kh = 0; kh < 2; ++kh)
+            for (int kq = 0; kq < 4; ++kq)
+              for (int c = 0; c < 16; ++c)
+                for (int e = 0; e < 4; ++e) dst[t.l[i].off + ((size_t)(32 * kb + 16 * kh + 4 * e + kq) * C + 16 * cb + c) * 9 + tap] = *p++;
+  }
+}
 void launch_fill_zero(void* p, size_t bytes, hipStream_t) { memset(p, 0, bytes); }
 void launch_set_globals(Globals* g, Globals v, hipStream_t) { *g = v; }
 void launch_update_flat(float*, float*, const float*, float*, int64_t, float, float, float, float, float, hipStream_t) {}

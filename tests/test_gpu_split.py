@@ -62,3 +62,19 @@ def test_weights_in_lane_order_read_back_in_their_own(ticks):
     want = O.PBOracle(net).read_weights().astype(np.float32)
     assert np.array_equal(eng.read_weights(), want) and not eng.read_velocity().any()
     eng.close()
+
+
+def test_a_read_back_leaves_the_training_as_it_was():
+    """Read-backs in canonical order go by way of the gradients' block, from ticks before a stage's first gradient on."""
+    import numpy as np
+    from paper_2003_11666_amd import PBEngine
+    net = _basic((64, 96), 12)
+    (xs, ys), S = W.sample_pool(net), len(net["stages"])
+    one, other = (PBEngine(net, tuning=dict(tile_budget_us=26.0)) for _ in range(2))
+    for t in range(2 * S + 4):
+        for e in (one, other):
+            e.tick(xs[t % len(ys)], ys[t % len(ys)])
+        one.read_weights(), one.read_velocity()
+    for k in ("read_weights", "read_velocity", "loss_history"):
+        assert np.array_equal(getattr(one, k)(), getattr(other, k)()), k
+    one.close(), other.close()

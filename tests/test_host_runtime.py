@@ -224,3 +224,23 @@ for _ in range(20):
     assert len(got) == 1
     got.pop().close()
 """)
+
+
+def test_weights_in_lane_order_take_no_memory_of_their_own(lib):
+    """A network whose 3x3 layers store weights in the order of their tiles' lanes: their read-back in canonical order goes by
+    way of the gradients' block, so that what fits the static arena without that order (61.3 MiB) fits with it."""
+    host_stub.run(lib, """
+import ctypes as C
+from oracle import pb_oracle as O
+net = W._net("lanes", W.preact_resnet_basic((32, 64, 128), 3, 4, in_c=3, n_classes=5), 3, 20, 20, 5, 1e-3, 0.9, 8, 3, 8)
+desc, keep = B.marshal_net(net)
+assert lib.pb_arena_bytes(C.byref(desc), None) <= lib.pb_static_arena_bytes()
+want = O.PBOracle(net).read_weights().astype(np.float32)
+for kw in (dict(), dict(tuning=dict(tile_budget_us=26.0))):
+    e = engine(net, **kw)
+    for cap in (want.size, 1000):
+        got = np.empty(cap, np.float32)
+        assert lib.pb_read_weights(e.ctx, got.ctypes.data, cap) == cap and np.array_equal(got, want[:cap])
+    assert not e.read_velocity().any()
+    e.close()
+""")
