@@ -914,7 +914,7 @@ __device__ __forceinline__ void step_dw_t(const LDesc& d, int tile_, int t, lflo
     if (perm) {
       // the predicted weights in the order of the forward tiles' lanes
       __syncthreads();
-      if ((C & 31) == 0) {
+      if (flags & F_WHAT_P32) {
         // (step_ds_t: 64 lanes x 4 channels per tap, 16 rows and 16 channels)
         const int np = 9 * (MT >> 4) * wn;
         for (int p = wv; p < np; p += 4) {

@@ -142,13 +142,14 @@ enum StepFlags : int32_t {
                       // computed inside the step from the layer's saved input (x) and output gradient (dy)
   F_UPD_W = 262144,   // K_GEMM backward weights: the tile's gradient stays in registers and the step updates the weights itself
                       // (w, v in place, what), a phase after the step that reads them for the data gradient
-  F_WHAT_PERM = 524288 // direct 3x3 form: the predicted weights are stored as the forward pass loads them; a multiple of 32
-                      // channels: [row / 16][channel / 32][tap][channel / 16 % 2][channel % 4][row % 16][channel / 4 % 4], else
-                      // [row / 16][channel / 4][channel % 4][row % 16][tap]
+  F_WHAT_PERM = 524288 // direct 3x3 form: the predicted weights are stored as the forward pass loads them,
+                      // [row / 16][channel / 4][channel % 4][row % 16][tap]; with F_WHAT_P32, where that runs on the bf16 pipes,
+                      // [row / 16][channel / 32][tap][channel / 16 % 2][channel % 4][row % 16][channel / 4 % 4]
   , F_W_PERM = 1048576 // ... weights and velocities as the backward-data tiles load the weights, K and C multiples of 32:
                       // [C / 16][K / 32][tap][K / 16 % 2][K % 4][C % 16][K / 4 % 4] (pb_read_weights sees the natural order)
   , F_UPD_GEN = 2097152 // K_GN_BWD that updates scale and shift: at an update size above one or with weight stashing
   , F_CE_DY = 4194304  // K_FC_BWD_X: dy holds the logits; the step works out their gradient itself (beside K_CE, not behind it)
+  , F_WHAT_P32 = 8388608
 };
 
 struct StepDesc {

@@ -451,7 +451,7 @@ struct pb_ctx {
   int wait_shares = 0;           // ... and take this many of a GPU's WAIT_SHARES equal parts
   bool wait_busy = false;        // such launches have been made which no call has waited for yet: the shares are held
   int64_t wait_retry = 0;        // the tick at which to ask for the shares again, after another process had them
-  std::vector<char> perm_what;   // per stage: the layer's predicted weights are stored in the lane order of its forward tiles
+  std::vector<char> perm_what;   // per stage: the layer's predicted weights are stored in the lane order of its forward tiles (2: F_WHAT_P32)
   std::vector<char> perm_w;      // ... its weights and velocities in that of its backward-data tiles
   std::vector<char> pp_active;   // per stage: the update alternates between two copies of the master parameters
   int fuse_from = -1;          // >= 0: the phases from this one on share one launch, dependencies through completion
@@ -1372,7 +1372,7 @@ void compile_steps_once(pb_ctx* c, std::vector<std::pair<int, StepDesc>>& out) {
       upd[s].push_back({o, o + n});
       return true;
     };
-    bool perm_what = false;   // the layer's predicted weights are stored in the order its forward tiles load them
+    int perm_what = 0;        // flags: the layer's predicted weights are stored in the order its forward tiles load them
     const bool seq = c->sequential;
     const int t_f = seq ? 0 : s, t_b = seq ? 0 : 2 * (S - 1) - s;
     const int ML = seq ? 0 : -1;                       // lag of the mailbox slot a producer writes (next tick's, or this tick's)
@@ -1545,8 +1545,9 @@ void compile_steps_once(pb_ctx* c, std::vector<std::pair<int, StepDesc>>& out) {
             make_dc(c, 1, a.C, a.H, a.W, a.K, a.OH, a.OW, a.k, a.stride, a.pad, zsplit ? FWD_PARTS : 1, lanes, &gd)) {
           d.kind = K_GEMM; d.g = gd; d.gp = gp; d.ntiles = gd.tiles;
           if (gd.parts > 1) { d.gw = c->f(b.zparts); d.gparts = gd.parts; d.gpstride = (int)a.z_elems(); fwd_parts = gd.parts; }
-          perm_what = lanes && (gd.dc == 3) == (a.C % 32 == 0);   // (the order goes with the number of channels)
-          if (perm_what) { d.flags |= F_WHAT_PERM; c->perm_what[s] = 1; }
+          if (lanes) perm_what = F_WHAT_PERM | (gd.dc == 3 ? F_WHAT_P32 : 0);
+          d.flags |= perm_what;
+          c->perm_what[s] = (perm_what != 0) + (gd.dc == 3 && perm_what);
         } else
         if (plain_src && !(d.flags & F_PROJ) && make_d1(c, 1, a.C, a.H, a.W, a.K, a.OH, a.OW, a.k, a.stride, a.pad, &gd)) {
           d.H = a.H; d.W = a.W; d.OH = a.OH; d.OW = a.OW;
@@ -1705,7 +1706,7 @@ void compile_steps_once(pb_ctx* c, std::vector<std::pair<int, StepDesc>>& out) {
         if (!dense) gemm_tables(c, g, d.C, d.H, d.W, d.K, d.OH, d.OW, d.k, d.stride, &d.tq, &d.tn);
       }
       const bool upd_w = !fuse_w && fuse_update(d, a.o_w, a.n_w);
-      if (upd_w && perm_what) d.flags |= F_WHAT_PERM;
+      if (upd_w) d.flags |= perm_what;
       GemmCfg gb;
       if (upd_w && perm_what && s > 0 && perm_w_shape(a) && d.g.dc && b.w2 < 0 &&
           make_dc(c, 2, a.C, a.H, a.W, a.K, a.OH, a.OW, a.k, a.stride, a.pad, 1, true, &gb) && gb.dc == 3) {
@@ -2410,7 +2411,7 @@ int validate_steps(const pb_ctx* c, const std::vector<std::pair<int, StepDesc>>&
           want.parts = d.g.parts; want.cpp = d.g.cpp; want.tiles = d.g.parts * want.tpp;
           ok = ok && memcmp(&want, &d.g, sizeof want) == 0 && d.g.parts >= 1 && (int64_t)d.g.parts * d.g.cpp >= d.g.n_chunks &&
                (int64_t)(d.g.parts - 1) * d.g.cpp < d.g.n_chunks;
-          if (d.flags & F_WHAT_PERM) ok = ok && c->perm_what[d.stage] && !c->stash && (d.g.gm == 1 || (d.g.gm == 3 && (d.flags & F_UPD_W))) && (d.g.gm == 3 || (d.g.dc == 3) == (d.C % 32 == 0)) && d.K % 16 == 0;
+          if (d.flags & F_WHAT_PERM) ok = ok && c->perm_what[d.stage] && !c->stash && (d.g.gm == 1 || (d.g.gm == 3 && (d.flags & F_UPD_W))) && ((d.flags & F_WHAT_P32) != 0) == (c->perm_what[d.stage] == 2) && (d.g.gm == 3 || (d.g.dc == 3) == ((d.flags & F_WHAT_P32) != 0)) && d.C % ((d.flags & F_WHAT_P32) ? 32 : 4) == 0 && d.K % 16 == 0;
           else if (d.g.gm == 1 || (d.flags & F_UPD_W)) ok = ok && (!c->perm_what[d.stage] || d.k != 3);
           if (d.flags & F_W_PERM)
             ok = ok && c->perm_w[d.stage] && c->N == 1 && d.K % 32 == 0 && d.C % 32 == 0 && (d.g.gm == 2 ? d.g.dc == 3 && d.pmask == 0 : d.g.gm == 3 && (d.flags & F_UPD_W));
@@ -2994,8 +2995,10 @@ int64_t plan_summary(const pb_net_desc* net, char* buf, int64_t cap) {
         snprintf(line, sizeof line, " | gm%d M%d N%d Q%d dense small waves %dx1x%d mi%d ni%d tile %dx%d est %.1f", g.gm, g.M, g.N, g.Q, g.wm, g.wk, g.mi, g.ni,
                  g.MT, g.NT, est_tile_us(g, 1));
       else if (g.dc)
-        snprintf(line, sizeof line, " | gm%d M%d N%d Q%d direct waves %dx%dx%d mi%d ni%d tile %dx%d chunks %d/%d CC%d PR%d Wp%d plane%d rows%d est %.1f%s", g.gm, g.M, g.N, g.Q,
-                 g.wm, g.wn, g.wk, g.mi, g.ni, g.MT, g.NT, g.n_chunks, g.parts, g.CC, g.PR, g.Wp, g.shw, g.rows_c, est_tile_us(g, 3), g.dc == 3 ? " split" : "");
+        snprintf(line, sizeof line, " | gm%d M%d N%d Q%d direct waves %dx%dx%d mi%d ni%d tile %dx%d chunks %d/%d CC%d PR%d Wp%d plane%d rows%d est %.1f%s%s%s", g.gm, g.M, g.N, g.Q,
+                 g.wm, g.wn, g.wk, g.mi, g.ni, g.MT, g.NT, g.n_chunks, g.parts, g.CC, g.PR, g.Wp, g.shw, g.rows_c, est_tile_us(g, 3), g.dc == 3 ? " split" : "",
+                 !(d.flags & F_WHAT_PERM) ? "" : (d.flags & F_WHAT_P32) ? " predicted in lanes/32" : " predicted in lanes/4",
+                 (d.flags & F_W_PERM) ? " weights in lanes" : "");
       else if (g.mm)
         snprintf(line, sizeof line, " | gm%d M%d N%d Q%d dense mi%d ni%d tile %dx%d chunks %d/%d QC%d lds %d", g.gm, g.M, g.N, g.Q, g.mi, g.ni,
                  g.MT, g.NT, g.n_chunks, g.parts, g.QC, mm_buffers(g.MT, g.NT) * mm_chunk_floats(g.MT, g.NT));
@@ -3251,7 +3254,7 @@ int init_common(pb_ctx** out, const pb_net_desc* net, const int32_t* delays, flo
       perm[s].assign(src, src + st[s].padded);
       for (int k = 0; k < K; ++k)
         for (int ci = 0; ci < C; ++ci)
-          if (C % 32 == 0)
+          if (c->perm_what[s] == 2)
             for (int tap = 0; tap < 9; ++tap)
               perm[s][((((size_t)(k / 16) * (C / 32) + ci / 32) * 9 + tap) * 2 + ci / 16 % 2) * 256 + (ci % 4 * 16 + k % 16) * 4 + ci / 4 % 4] = src[((size_t)k * C + ci) * 9 + tap];
           else

@@ -41,6 +41,17 @@ def _follow(net, tuning, tol=1e-4, **kw):
     eng.close()
 
 
+# maps of fewer than 16 pixels stay on the fp32 pipes at a multiple of 32 channels too, their predicted weights in those tiles' order
+@pytest.mark.parametrize("widths,hw", [((64, 128), 6), ((96, 160), 5), ((32, 64, 96), 9)])
+def test_lane_order_on_maps_of_a_few_pixels(widths, hw):
+    from paper_2003_11666_amd.binding import plan_summary
+    net, tuning = _net(widths, hw), dict(tile_budget_us=24.0)
+    steps = [l for l in plan_summary(net, tuning=tuning).splitlines() if "direct" in l and "k3" in l]
+    for gm in ("gm1", "gm3"):
+        assert any(f"| {gm} " in l and l.endswith("predicted in lanes/4") for l in steps), steps
+    _follow(net, tuning)
+
+
 @pytest.mark.parametrize("kw", [dict(lwp_form="w"), dict(bwd_weights=1), dict(update_size=2), dict(mitigation=0)])
 def test_direct_tiles_with_other_updates(kw):
     _follow(_net((32, 64), 8), dict(tile_budget_us=14.0), **kw)
