@@ -734,9 +734,11 @@ double est_tile_us(const GemmCfg& g, int k) {
   }
   if (g.mm) {
     // dense form: per chunk of 32 reduction entries 6 mi ni MFMAs per wave, two workgroups sharing the matrix pipes,
-    // and never less than the round trip of the next chunk's requests
+    // and never less than the round trip of the next chunk's requests; a weight gradient that gathers its input element by
+    // element (stride 2) takes 4.4 us a chunk (128 x 128 over 20x20 pixels, 13 chunks: 60 us in one part, the end of its
+    // launch, whose other tiles end at 27: 153 us per tick of a bottleneck network at 158 pixels instead of 126)
     const double t_mfma = 2.5 * 6.0 * g.mi * g.ni * 16.0 / 2400.0;
-    return 5.0 + g.n_chunks * std::max(1.2, t_mfma);
+    return 5.0 + g.n_chunks * std::max(g.gm == 3 && g.gather ? 4.4 : 1.2, t_mfma);
   }
   const int kk = k * k;
   const double a_fl = g.gm == 2 ? (double)((g.QCpad + kk - 1) / kk + 1) * g.MT * kk : (double)g.MT * g.QCpad;

@@ -244,3 +244,15 @@ for kw in (dict(), dict(tuning=dict(tile_budget_us=26.0))):
     assert not e.read_velocity().any()
     e.close()
 """)
+
+
+def test_a_gathered_weight_gradient_is_not_the_end_of_its_launch(lib):
+    """The projection of stride 2 in a bottleneck network at 158 pixels: 13 chunks at 4.4 us each, dealt out so that no tile takes
+    more than 30."""
+    host_stub.run(lib, """
+import re
+net = W._net("gathered", W.preact_resnet_bottleneck((2, 4), 32, 8, n_classes=340), 3, 158, 158, 340, 1e-3, 0.9, 8, 3, 8)
+steps = [l for l in B.plan_summary(net).splitlines() if " k1 s2 " in l and "gm3" in l]
+parts = [tuple(map(int, re.search(r"chunks (\\d+)/(\\d+)", l).groups())) for l in steps]
+assert parts and all(5.0 + 4.4 * -(-n // p) <= 30.0 for n, p in parts), steps
+""")
