@@ -106,10 +106,17 @@ __device__ __forceinline__ void step_mm_t(const LDesc& d, int tile_, int t, lflo
       const int v = tid + u * BLK, row = v >> 3, q = q0 + 4 * (v & 7);
       r[u] = (v4f){0.f, 0.f, 0.f, 0.f};
       if (q < Q) r[u] = *(const gv4u*)(g + (unsigned)((row0 + row) * Q + q));
-      if (MODE == 3 && (Q & 3)) {                     // (the entries past the end belong to the next row)
+    }
+  };
+  // Entries past the end of a row belong to the next one.  They are cleared on the way into LDS, in the last chunk: a select
+  // behind each request waits for it before the next one goes out (529 pixels, tile of 128 x 64: 17 chunks in 61 us).
+  auto clear_tail = [&](auto& r, int q0) {
+    constexpr int V = sizeof(r) / sizeof(r[0]);
 #pragma unroll
-        for (int e = 1; e < 4; ++e) r[u][e] = q + e < Q ? r[u][e] : 0.f;
-      }
+    for (int u = 0; u < V; ++u) {
+      const int q = q0 + 4 * ((tid + u * BLK) & 7);
+#pragma unroll
+      for (int e = 1; e < 4; ++e) r[u][e] = q + e < Q ? r[u][e] : 0.f;
     }
   };
   // rows along the result: vector u of a thread is four columns of entry V kb + u
@@ -222,6 +229,10 @@ __device__ __forceinline__ void step_mm_t(const LDesc& d, int tile_, int t, lflo
   for (int ch = ch0; ch < ch_end; ++ch) {
     lfloat* buf = smem + (NBUF > 1 ? ((ch - ch0) & 1) * CHUNK : 0);
     if (NBUF == 1) __syncthreads();                // every wave has contracted the chunk before
+    if (MODE == 3 && (Q & 3) && (ch + 1) * MM_QC > Q) {
+      clear_tail(ra, ch * MM_QC);
+      if (!gather) clear_tail(rb, ch * MM_QC);
+    }
     commit(buf);
     __syncthreads();
     if (ch + 1 < ch_end) issue(ch + 1);
