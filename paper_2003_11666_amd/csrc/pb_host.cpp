@@ -2889,7 +2889,8 @@ int run_mlp(pb_ctx* c, int n, const float* staging, int label) {
   a.recs = (const MlpRec*)c->f(c->mlp.recs);
   a.S = c->S; a.n_ticks = n; a.t0 = (int)c->ticks;
   a.dy_plain = c->mlp_messages ? 0 : 1;
-  a.pool = c->pool; a.pool_labels = c->pool_labels; a.n_pool = std::max(1, c->n_pool); a.idx_base = c->idx_base;
+  a.pool = c->pool; a.pool_labels = c->pool_labels; a.n_pool = std::max(1, c->n_pool);
+  a.item0 = (int)(((int64_t)c->idx_base + c->ticks) % a.n_pool);
   a.sample = staging; a.label = label;
   a.loss = c->f(c->L.loss); a.loss_cap = c->loss_cap;
   a.labels = c->labels_dev;

@@ -42,9 +42,9 @@ struct MlpArgs {
   const MlpRec* recs;
   int32_t S, n_ticks, t0;
   int32_t dy_plain;                      // the first tick's gradients lie in gradbox
-  const float* pool;                     // samples; tick t takes item (idx_base + t) mod n_pool
+  const float* pool;                     // samples; tick t takes item (item0 + t - t0) mod n_pool
   const int32_t* pool_labels;
-  int32_t n_pool, idx_base;
+  int32_t n_pool, item0;
   const float* sample;                   // one tick fed by the host: its sample and label
   int32_t label, loss_cap;
   float* loss;

@@ -67,7 +67,8 @@ struct MlpWait {
 
 // NQ: columns per lane; RW: rows per wavefront; WF: weight-difference form of the prediction (the predicted weights are
 // then state of their own: w' + T (w' - w); in the velocity form they are w - lr T v, worked out when used).
-template <int NQ, int RW, bool WF>
+// ONE: a launch of one tick (fed by the host): its instructions are fetched anew for that tick, so it holds no loop over ticks.
+template <int NQ, int RW, bool WF, bool ONE>
 __global__ void __launch_bounds__(MLP_BLK) __attribute__((amdgpu_waves_per_eu(2, 2))) k_mlp(MlpArgs A) {
   constexpr int CP = 64 * NQ, R = MLP_WAVES * RW, SLOTS = mlp_hist_slots(NQ);
   constexpr int XU = (CP + MLP_BLK - 1) / MLP_BLK, DU = MLP_DYB / MLP_BLK;
@@ -75,11 +76,11 @@ __global__ void __launch_bounds__(MLP_BLK) __attribute__((amdgpu_waves_per_eu(2,
   __shared__ float red[MLP_WAVES * CP];     // gradient of the input, one partial sum per wavefront
   __shared__ float dyb[MLP_DYB];            // partial gradients [part][row]
   __shared__ float lg[MLP_MAX_K];
-  __shared__ int lab[mlp_launch_ticks(NQ)];
+  __shared__ int lab[ONE ? 1 : mlp_launch_ticks(NQ)];
   __shared__ int stop;
   const MlpRec P = A.recs[blockIdx.x];
   const int tid = threadIdx.x, lane = tid & 63, wv = MLP_UNI(tid >> 6);
-  const int S = A.S, K = P.K, C = P.C, D = P.D, depth = D + 2, s = P.stage, r0 = P.r0, n = A.n_ticks, t0 = A.t0;
+  const int S = A.S, K = P.K, C = P.C, D = P.D, depth = D + 2, s = P.stage, r0 = P.r0, n = ONE ? 1 : A.n_ticks, t0 = A.t0;
   const bool first = s == 0, last = s == S - 1;
   const int parts = P.parts;
   const float fa = P.fa, fb = P.fb, lrT = P.flrT, lr = P.flr, fm = P.fm;
@@ -120,8 +121,8 @@ __global__ void __launch_bounds__(MLP_BLK) __attribute__((amdgpu_waves_per_eu(2,
     }
   }
   // (pool items, ring slots and the like are counted up from tick to tick: a division by a run-time value is some forty
-  // dependent instructions, with 64 bits far more)
-  int item = A.sample ? 0 : (int)(((int64_t)A.idx_base + t0) % A.n_pool);
+  // dependent instructions, with 64 bits some hundred more, all of them fetched anew in a launch of one tick)
+  int item = A.item0;
   auto sample_of = [&](int it) { return (const gfloat*)(A.sample ? A.sample : A.pool + (size_t)it * C); };
   float xs[XU];
   auto fetch_input = [&](const gfloat* src) {
@@ -141,7 +142,7 @@ __global__ void __launch_bounds__(MLP_BLK) __attribute__((amdgpu_waves_per_eu(2,
     loss_at = j0 > 0 ? j0 % A.loss_cap : 0;
     for (int i = tid; i < n; i += MLP_BLK) {
       const int j = j0 + i;
-      lab[i] = j >= t0 ? ((const gint*)A.pool_labels)[((int64_t)A.idx_base + j) % A.n_pool] : j >= 0 ? ((const gint*)A.labels)[j % S] : 0;
+      lab[i] = j >= t0 ? ((const gint*)A.pool_labels)[((unsigned)A.item0 + (unsigned)(j - t0)) % (unsigned)A.n_pool] : j >= 0 ? ((const gint*)A.labels)[j % S] : 0;
     }
   }
   int yslot = last ? 0 : (t0 + 1) % D;
@@ -317,8 +318,8 @@ __global__ void __launch_bounds__(MLP_BLK) __attribute__((amdgpu_waves_per_eu(2,
     if (!first) {
 #pragma unroll
       for (int u = 0; u < XU; ++u) {
-        // (with up to 256 columns the other half of the workgroup sends)
-        const int c = (tid ^ (MLP_BLK / 2)) + u * MLP_BLK;
+        // (with up to 256 columns the other half of the workgroup sends, where the first waits for another tick's messages)
+        const int c = (ONE ? tid : tid ^ (MLP_BLK / 2)) + u * MLP_BLK;
         if (c < C) {
           float a = 0.f;
 #pragma unroll
@@ -381,7 +382,7 @@ __global__ void __launch_bounds__(MLP_BLK) __attribute__((amdgpu_waves_per_eu(2,
   if (last && P.me == 0 && tid < S) {
     // label ring: the samples that entered in this launch
     const int j = t0 + n - 1 - tid;
-    if (j >= t0) A.labels[j % S] = A.sample ? A.label : A.pool_labels[((int64_t)A.idx_base + j) % A.n_pool];
+    if (j >= t0) A.labels[j % S] = A.sample ? A.label : A.pool_labels[((unsigned)A.item0 + (unsigned)(j - t0)) % (unsigned)A.n_pool];
   }
 }
 
@@ -406,9 +407,9 @@ __global__ void __launch_bounds__(256) k_mlp_flush(const MlpRec* __restrict__ re
     }
 }
 
-template <int NQ>
+template <int NQ, bool ONE>
 static void launch_nq(const MlpArgs& a, int grid, int rw, bool wf, hipStream_t s) {
-#define PB_MLP(RW, WF) hipLaunchKernelGGL((k_mlp<NQ, RW, WF>), dim3(grid), dim3(MLP_BLK), 0, s, a)
+#define PB_MLP(RW, WF) hipLaunchKernelGGL((k_mlp<NQ, RW, WF, ONE>), dim3(grid), dim3(MLP_BLK), 0, s, a)
   if (rw == 2) { if (wf) PB_MLP(2, true); else PB_MLP(2, false); return; }
   if constexpr (NQ == 16) {
     if (!wf) PB_MLP(3, false);
@@ -420,10 +421,15 @@ static void launch_nq(const MlpArgs& a, int grid, int rw, bool wf, hipStream_t s
 }
 
 void launch_mlp(const MlpArgs& a, int grid, int nq, int rw, bool lwp_w, hipStream_t s) {
-  if (nq == 2) launch_nq<2>(a, grid, rw, lwp_w, s);
-  else if (nq == 4) launch_nq<4>(a, grid, rw, lwp_w, s);
-  else if (nq == 8) launch_nq<8>(a, grid, rw, lwp_w, s);
-  else launch_nq<16>(a, grid, rw, lwp_w, s);
+  auto launch = [&](auto ONE) {
+    constexpr bool one = decltype(ONE)::value;
+    if (nq == 2) launch_nq<2, one>(a, grid, rw, lwp_w, s);
+    else if (nq == 4) launch_nq<4, one>(a, grid, rw, lwp_w, s);
+    else if (nq == 8) launch_nq<8, one>(a, grid, rw, lwp_w, s);
+    else launch_nq<16, one>(a, grid, rw, lwp_w, s);
+  };
+  if (a.n_ticks == 1) launch(std::true_type());
+  else launch(std::false_type());
 }
 
 void launch_mlp_flush(const MlpRec* recs, int grid, int rows, int t, hipStream_t s) {

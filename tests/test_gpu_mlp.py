@@ -161,3 +161,23 @@ e.close()
         e.close()
     finally:
         other.kill()
+
+
+@pytest.mark.parametrize("form", ["v", "w"])
+@pytest.mark.parametrize("dims", [(246, 226, 226, 12), (256, 256, 256, 20), (512,) * 9 + (600,)], ids=str)
+def test_launches_of_one_tick_give_the_bits_of_longer_ones(dims, form):
+    import torch
+    from paper_2003_11666_amd import PBEngine
+    net, n = _net(dims, 0.002), 2 * len(dims) + 9
+    xs, ys = W.sample_pool(net)
+    xd, yd = torch.from_numpy(xs).cuda(), torch.from_numpy(ys).cuda()
+    longer, host, pool = (PBEngine(net, lwp_form=form) for _ in range(3))
+    longer.run_resident(xd, yd, 3, n)
+    for t in range(3, 3 + n):
+        host.tick(xs[t % len(ys)], ys[t % len(ys)])
+        pool.run_resident(xd, yd, t, 1)
+    for k in ("read_weights", "read_velocity", "loss_history"):
+        want = getattr(longer, k)()
+        assert np.isfinite(want).all() and np.array_equal(getattr(host, k)(), want) and np.array_equal(getattr(pool, k)(), want), k
+    for e in (longer, host, pool):
+        e.close()
