@@ -970,12 +970,12 @@ bool make_d1(const pb_ctx* c, int mode, int C, int H, int W, int K, int OH, int 
 //   estimated tile duration stays within the budget, the one with the least total
 //   work (tiles x duration); if none does, the one with the shortest tile.  Work below
 //   small_work microseconds (256: half a microsecond of the chip's 512 places) counts
-//   alike there and the shortest tile wins: the first layer of a network with post-layer
-//   norms shares its phase with elementwise steps and is the longest workgroup in it.
-//   Measured, us per tick without and with: VGG-11 87.6 and 82.7; in three other VGG
-//   networks (32, 48 and 64 channels at 20-40 pixels) the plan is the same either way.
-//   In networks with pre-layer norms it makes little difference (0 there): seven basic
-//   ResNets -0.6 to +0.9 %, the wide one 125.7 without and 126.8 with.
+//   alike there and the shortest tile wins: the first layer of a network shares its phase
+//   with short steps and is the longest workgroup in it, the more so since the others' tiles
+//   run on the bf16 pipes.  Measured, us per tick without and with: VGG-11 87.6 and 82.7; of
+//   22 networks with pre-layer norms that are planned otherwise (in some 190) eight gain 1.1
+//   to 2.0 % (121.9 and 119.7, 243.8 and 239.8, 89.6 and 88.2), eleven stand within 0.2 % and
+//   three lose 0.4 to 0.8 % (the wide network 91.3 and 91.7, 107.4 and 108.2).
 bool make_gemm(int mode, int C, int H, int W, int K, int OH, int OW, int k, int s, int pad,
                const GemmCfg* like, GemmCfg* out, bool allow_vec = false, int max_sub = 16, bool flat = false,
                int max_parts = 1, double small_work = 0.0) {
@@ -1677,6 +1677,10 @@ void compile_steps_once(pb_ctx* c, std::vector<std::pair<int, StepDesc>>& out) {
         // the dense layer in front of the loss: its bias gradient is the logits' gradient, which K_CE writes twice, and the step
         // updates the weights itself, a phase behind backward data, which reads them.  Measured without and with this (and with
         // F_CE_DY below), head 2048 x 1000: ResNet-50 at 224 pixels 490 and 477 us per tick, its stages at 64 pixels 228 and 220.
+        // Backward data behind K_CE and, with F_CE_DY, beside it, four bottleneck networks, us per tick: head 256 x 100 81.2 and
+        // 78.3, x 1000 85.5 and 80.8, x 8000 131.9 and 117.9; 2048 x 10 165.7 and 162.3, x 1000 174.7 and 171.1, x 8000 290.2 and
+        // 272.6 (of 24 heads of 256 to 2048 inputs and 10 to 8000 classes 23 take 2.0 to 10.6 % less, the smallest the same): every workgroup's softmax of all
+        // classes costs less than a launch and K_CE's single workgroup in front of it, however many classes there are.
         // At update sizes above one the gradient is needed in memory.
         fc_upd = ce_at >= 0 && !a.add && !a.post_gn && c->N == 1;
         if (a.has_bias && fc_upd) out[ce_at].second.gb = gr + a.o_b;
