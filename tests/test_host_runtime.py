@@ -256,3 +256,14 @@ steps = [l for l in B.plan_summary(net).splitlines() if " k1 s2 " in l and "gm3"
 parts = [tuple(map(int, re.search(r"chunks (\\d+)/(\\d+)", l).groups())) for l in steps]
 assert parts and all(5.0 + 4.4 * -(-n // p) <= 30.0 for n, p in parts), steps
 """)
+
+
+def test_statistics_that_fit_no_registers_start_early(lib):
+    """Groups of 30 x 23 x 23 elements, no multiple of 4, take 35 us: in front of the weight-gradient tiles of 8 us."""
+    host_stub.run(lib, """
+net = W._net("odd groups", W.preact_resnet_basic((60, 120, 240), 3, 2, in_c=3, n_classes=9), 3, 23, 23, 9, 1e-3, 0.9, 8, 3, 8)
+steps = B.plan_summary(net, update_size=8).splitlines()
+stats = [i for i, l in enumerate(steps) if "phase 0 gn_stats" in l and "C60x23x23" in l]
+tiles = [i for i, l in enumerate(steps) if "phase 0 gemm" in l and "C240x6x6" in l and "gm3" in l]
+assert stats and tiles and max(stats) < min(tiles), steps
+""")
