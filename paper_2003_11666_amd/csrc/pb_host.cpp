@@ -887,41 +887,55 @@ bool fit_dc(const pb_ctx* c, int mode, int C, int H, int W, int K, int OH, int O
 // registers for the other order's requests)
 bool make_dc(const pb_ctx* c, int mode, int C, int H, int W, int K, int OH, int OW, int k, int stride, int pad, int max_parts,
              bool lanes, GemmCfg* out) {
-  bool have = false, best_within = false;
-  double best_work = 0, best_tile = 0;
   static const int shapes[4][2] = {{4, 2}, {2, 2}, {2, 1}, {1, 1}}, sshapes[5][2] = {{2, 4}, {2, 2}, {2, 1}, {1, 2}, {1, 1}},
                    wshapes[2][2] = {{2, 1}, {1, 1}};
   const int R = mode == 2 ? K : C;
+  struct Best { bool have = false, within = false; double work = 0, tile = 0; GemmCfg g; };
+  auto search = [&](bool split) {
+    Best b;
+    for (int si = 0; si < (mode == 3 ? 2 : split ? 5 : 4); ++si)
+      for (int wm = 1; wm <= 4; wm *= 2)
+        for (int wn = 1; wm * wn <= 4; wn *= 2)
+          for (int cc = split ? 32 : 64; cc <= (split ? 512 : 64); cc *= 2) {
+            const int* sh = (mode == 3 ? wshapes : split ? sshapes : shapes)[si];
+            GemmCfg g;
+            if (split && sh[1] == 4 && !lanes) continue;
+            if (!fit_dc(c, mode, C, H, W, K, OH, OW, k, stride, pad, sh[0], sh[1], wm, wn, split, cc, &g) || (split && 2 * g.CC <= cc)) continue;
+            double tt = est_tile_us(g, 3);
+            for (int want = 2; want <= max_parts && want <= g.n_chunks && tt > (mode == 3 ? 20.0 : 12.0); want *= 2) {
+              g.cpp = cdiv(g.n_chunks, want);
+              g.parts = cdiv(g.n_chunks, g.cpp);
+              GemmCfg one = g;
+              one.n_chunks = g.cpp;
+              tt = est_tile_us(one, 3);
+            }
+            g.tiles = g.parts * g.tpp;
+            const double work = tt * g.tiles;
+            // (a small tile costs little here, a long one the end of its phase: never more than 45 us)
+            const bool within = tt <= std::min(45.0, g_tile_budget_us * g_budget_scale[mode]);
+            const bool better = !b.have ? true : within != b.within ? within : within ? (work < b.work || (work == b.work && tt < b.tile)) : tt < b.tile;
+            if (better) { b.have = true; b.within = within; b.work = work; b.tile = tt; b.g = g; }
+          }
+    return b;
+  };
   // a reduction over a multiple of 32 channels runs on the bf16 pipes, chunks of 32 channels per wave and more; else on the
   // fp32 pipes, the largest chunk of up to 64 channels.  So do maps of fewer than 16 pixels, whose tiles stream weights and
   // little else: those of the fp32 pipes keep more of them in flight (512 channels on 2x2 maps: loops of 18-20 us there,
   // 26-31 here; 256 channels on 4x4 maps: 15-18 there, 9-12 here)
   const int px = mode == 2 && stride == 1 ? H * W : OH * OW;       // columns of the product
-  for (int split = mode != 3 && R % 32 == 0 && px >= 16; split >= 0 && !have; --split)
-  for (int si = 0; si < (mode == 3 ? 2 : split ? 5 : 4); ++si)
-    for (int wm = 1; wm <= 4; wm *= 2)
-      for (int wn = 1; wm * wn <= 4; wn *= 2)
-        for (int cc = split ? 32 : 64; cc <= (split ? 512 : 64); cc *= 2) {
-        const int* sh = (mode == 3 ? wshapes : split ? sshapes : shapes)[si];
-        GemmCfg g;
-        if (split && sh[1] == 4 && !lanes) continue;
-        if (!fit_dc(c, mode, C, H, W, K, OH, OW, k, stride, pad, sh[0], sh[1], wm, wn, split, cc, &g) || (split && 2 * g.CC <= cc)) continue;
-        double tt = est_tile_us(g, 3);
-        for (int want = 2; want <= max_parts && want <= g.n_chunks && tt > (mode == 3 ? 20.0 : 12.0); want *= 2) {
-          g.cpp = cdiv(g.n_chunks, want);
-          g.parts = cdiv(g.n_chunks, g.cpp);
-          GemmCfg one = g;
-          one.n_chunks = g.cpp;
-          tt = est_tile_us(one, 3);
-        }
-        g.tiles = g.parts * g.tpp;
-        const double work = tt * g.tiles;
-        // (a small tile costs little here, a long one the end of its phase: never more than 45 us)
-        const bool within = tt <= std::min(45.0, g_tile_budget_us * g_budget_scale[mode]);
-        const bool better = !have ? true : within != best_within ? within : within ? (work < best_work || (work == best_work && tt < best_tile)) : tt < best_tile;
-        if (better) { have = true; best_within = within; best_work = work; best_tile = tt; *out = g; }
-      }
-  return have;
+  Best b;
+  if (mode != 3 && R % 32 == 0 && px >= 16) b = search(true);
+  if (!b.have || (!b.within && b.tile > 24.0)) {
+    // A number of channels that is no multiple of 64 or 128 leaves the bf16 tiles no waves to split the reduction with: where
+    // their shortest is long and the fp32 pipes' a third shorter, it runs there (224 channels, 81 pixels: 34.8 and 17.0 us by
+    // the estimate).  Us per tick with all of these on the bf16 pipes and with this, three VGG networks of 56 to 448 channels:
+    // 93.8 and 79.6, 114.5 and 99.3, 108.2 and 91.4.  Among shorter tiles the estimate does not tell them apart (19.0 against
+    // 11.9 at 96 channels: six networks 1.2 % faster to 3.1 % slower on the fp32 pipes).
+    const Best f = search(false);
+    if (!b.have || (f.have && f.tile < 0.667 * b.tile)) b = f;
+  }
+  if (b.have) *out = b.g;
+  return b.have;
 }
 
 // Direct form of a 1x1 layer (stride 1, or 2 on even maps) whose product has fewer than 64 columns -- where the dense

@@ -267,3 +267,14 @@ stats = [i for i, l in enumerate(steps) if "phase 0 gn_stats" in l and "C60x23x2
 tiles = [i for i, l in enumerate(steps) if "phase 0 gemm" in l and "C240x6x6" in l and "gm3" in l]
 assert stats and tiles and max(stats) < min(tiles), steps
 """)
+
+
+def test_reductions_the_bf16_tiles_cannot_share_out_stay_on_the_fp32_pipes(lib):
+    """224 channels are seven blocks of 32: no two waves share them, and a tile of four waves side by side takes twice the time
+    of one that splits the reduction on the fp32 pipes.  256 channels stay on the bf16 pipes."""
+    host_stub.run(lib, """
+for width, split in ((56, False), (64, True)):
+    net = W._net("vgg", W.vgg(tuple(width * k for k in (1, 2, 4, 4, 8, 8, 8, 8)), (0, 1, 3, 5, 7), 4, n_classes=7, in_hw=33), 3, 33, 33, 7, 1e-3, 0.9, 8, 3, 8)
+    steps = [l for l in B.plan_summary(net).splitlines() if f"C{4 * width}x8x8 K{4 * width}x8x8" in l and "direct" in l and "gm3" not in l]
+    assert len(steps) == 2 and all((" split" in l) == split for l in steps), steps
+""")
