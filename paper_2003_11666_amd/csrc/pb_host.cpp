@@ -984,12 +984,14 @@ bool make_d1(const pb_ctx* c, int mode, int C, int H, int W, int K, int OH, int 
 //   estimated tile duration stays within the budget, the one with the least total
 //   work (tiles x duration); if none does, the one with the shortest tile.  Work below
 //   small_work microseconds (256: half a microsecond of the chip's 512 places) counts
-//   alike there and the shortest tile wins: the first layer of a network shares its phase
-//   with short steps and is the longest workgroup in it, the more so since the others' tiles
-//   run on the bf16 pipes.  Measured, us per tick without and with: VGG-11 87.6 and 82.7; of
-//   22 networks with pre-layer norms that are planned otherwise (in some 190) eight gain 1.1
-//   to 2.0 % (121.9 and 119.7, 243.8 and 239.8, 89.6 and 88.2), eleven stand within 0.2 % and
-//   three lose 0.4 to 0.8 % (the wide network 91.3 and 91.7, 107.4 and 108.2).
+//   alike there and the shortest tile wins: layers in front of a GroupNorm, a network's
+//   first layer, which shares its phase with short steps and is the longest workgroup in it,
+//   and its last one, whose chain the end of the tick waits for.  Measured, us per tick
+//   without and with: VGG-11 87.6 and 82.7; networks with pre-layer norms 0.7 to 2.0 % less in
+//   eight of 22 that are planned otherwise (122.4 and 120.3, 243.5 and 239.0, 141.4 and 139.2),
+//   0.4 to 0.8 % more in three (the wide network 91.3 and 91.7).  For every layer of those the
+//   whole pass may be planned with another budget: a bottleneck network at 222 pixels 154.2 and
+//   163.5, fourteen others within 0.2 %.
 bool make_gemm(int mode, int C, int H, int W, int K, int OH, int OW, int k, int s, int pad,
                const GemmCfg* like, GemmCfg* out, bool allow_vec = false, int max_sub = 16, bool flat = false,
                int max_parts = 1, double small_work = 0.0) {
@@ -1551,7 +1553,7 @@ void compile_steps_once(pb_ctx* c, std::vector<std::pair<int, StepDesc>>& out) {
         const bool zsplit = a.post_gn && b.zparts >= 0 && !c->bf16 && g_tile_budget_us > 0 && !(d.flags & (F_SKIP | F_PROJ)) &&
                             (a.K / a.G) * a.OH * a.OW % 4 == 0 && (int64_t)(a.K / a.G) * a.OH * a.OW <= 32768 && a.K / a.G <= BLK;
         bool ok = make_gemm(1, d.C, d.H, d.W, d.K, d.OH, d.OW, d.k, d.stride, d.pad, nullptr, &g, plain_src, (d.flags & F_PROJ) ? 1 : 16, flat,
-                            zsplit ? FWD_PARTS : 1, 256.0);
+                            zsplit ? FWD_PARTS : 1, a.post_gn || s == 0 || s == S - 1 ? 256.0 : 0.0);
         if (ok && (d.flags & F_PROJ)) ok = make_gemm(1, d.sC, d.sH, d.sW, d.K, d.OH, d.OW, 1, d.sstride, 0, &g, &gp, true);
         GemmCfg gd, gw;
         // (with weight stashing the backward pass reads the predicted weights too, in their natural order)

@@ -278,3 +278,12 @@ for width, split in ((56, False), (64, True)):
     steps = [l for l in B.plan_summary(net).splitlines() if f"C{4 * width}x8x8 K{4 * width}x8x8" in l and "direct" in l and "gm3" not in l]
     assert len(steps) == 2 and all((" split" in l) == split for l in steps), steps
 """)
+
+
+def test_short_steps_in_the_middle_of_a_network_do_not_shorten_the_others_tiles(lib):
+    """A bottleneck network at 222 pixels: the first layer's forward step keeps its 97 tiles of 128 columns."""
+    host_stub.run(lib, """
+net = W._net("stem", W.preact_resnet_bottleneck((3, 1), 16, 8, n_classes=171), 3, 222, 222, 171, 1e-3, 0.9, 8, 3, 8)
+steps = [l for l in B.plan_summary(net, mitigation=0).splitlines() if "C3x222x222" in l and "gm1" in l]
+assert len(steps) == 1 and "tile 16x128" in steps[0], steps
+""")
