@@ -631,41 +631,37 @@ __device__ __forceinline__ void step_ds_t(const LDesc& d, int tile_, int t, lflo
         else load_row(g + 1 < g_end ? g + 1 : g, 0);
         // window row of the kernel row (stride 2 backward: kh = 0 row 1, odd input row; 1 row 0, even; 2 row 0, odd)
         const int wy = S2 ? (kh == 0 ? 1 : 0) : MODE == 1 ? kh : 2 - kh;
-        // (two pixel subtiles at a time: NI = 4 has no registers for the sums and map values of all)
-        constexpr int NJ = NI < 2 ? NI : 2;
+        static_assert(PERM || NI <= 2, "no registers for the sums and map values of four pixel subtiles beside a row's requests");
+        v4f z[MI][NI];
 #pragma unroll
-        for (int j0 = 0; j0 < NI; j0 += NJ) {
-          v4f z[MI][NJ];
+        for (int kw = 0; kw < 3; ++kw) {
+          const int wx = S2 ? (kw == 0 ? 1 : 0) : MODE == 1 ? kw : 2 - kw;
+          bf8 b[NI][3];
 #pragma unroll
-          for (int kw = 0; kw < 3; ++kw) {
-            const int wx = S2 ? (kw == 0 ? 1 : 0) : MODE == 1 ? kw : 2 - kw;
-            bf8 b[NJ][3];
+          for (int j = 0; j < NI; ++j) {
+            const lfloat* q = base + (int)here(poff[j]);
 #pragma unroll
-            for (int j = 0; j < NJ; ++j) {
-              const lfloat* q = base + (int)here(poff[j0 + j]);
+            for (int p = 0; p < 3; ++p) b[j][p] = __builtin_bit_cast(bf8, *(const lw4*)(q + (wy * Wp + p * (piece >> 2)) * 4 + 4 * wx));
+          }
+          if (S2 || kw == 0) {
 #pragma unroll
-              for (int p = 0; p < 3; ++p) b[j][p] = __builtin_bit_cast(bf8, *(const lw4*)(q + (wy * Wp + p * (piece >> 2)) * 4 + 4 * wx));
-            }
-            if (S2 || kw == 0) {
+            for (int i = 0; i < MI; ++i)
 #pragma unroll
-              for (int i = 0; i < MI; ++i)
+              for (int j = 0; j < NI; ++j) z[i][j] = (v4f){0.f, 0.f, 0.f, 0.f};
+          }
 #pragma unroll
-                for (int j = 0; j < NJ; ++j) z[i][j] = (v4f){0.f, 0.f, 0.f, 0.f};
-            }
+          for (int q = 0; q < 6; ++q)
 #pragma unroll
-            for (int q = 0; q < 6; ++q)
+            for (int i = 0; i < MI; ++i)
 #pragma unroll
-              for (int i = 0; i < MI; ++i)
+              for (int j = 0; j < NI; ++j)
+                z[i][j] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(a[kw][i][split_pa(q)], b[j][split_pb(q)], z[i][j], 0, 0, 0);
+          if (S2 || kw == 2) {
+            const int cls = S2 ? (kh == 1 ? 0 : 2) + (kw == 1 ? 0 : 1) : 0;
 #pragma unroll
-                for (int j = 0; j < NJ; ++j)
-                  z[i][j] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(a[kw][i][split_pa(q)], b[j][split_pb(q)], z[i][j], 0, 0, 0);
-            if (S2 || kw == 2) {
-              const int cls = S2 ? (kh == 1 ? 0 : 2) + (kw == 1 ? 0 : 1) : 0;
+            for (int i = 0; i < MI; ++i)
 #pragma unroll
-              for (int i = 0; i < MI; ++i)
-#pragma unroll
-                for (int j = 0; j < NJ; ++j) acc[cls][i][j0 + j] += z[i][j];
-            }
+              for (int j = 0; j < NI; ++j) acc[cls][i][j] += z[i][j];
           }
         }
         __builtin_amdgcn_sched_barrier(0);
