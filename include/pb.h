@@ -21,7 +21,7 @@
  *
  * Waiting launches.  Some networks run in launches whose workgroups wait for
  * each other: perceptrons whose parameters fit the register files (a launch
- * runs up to 3-5 ms of ticks and may hold every compute unit, closed to other
+ * runs up to 1.5-3.3 ms of ticks and may hold every compute unit, closed to other
  * streams meanwhile) and small networks whose tick is one launch.  Such a launch needs
  * all of its workgroups resident at once.  The library keeps waiting launches
  * of this process's contexts, and of other processes on the same GPU that use
@@ -36,6 +36,12 @@
  * set pb_tuning.one_launch = -1.  A wait is bounded (4 s in perceptrons,
  * pb_tuning.spin_limit elsewhere): on expiry the launch ends and the next
  * synchronising call returns PB_E_HIP.
+ *
+ * Arithmetic.  32 bits throughout (act_dtype = 1 rounds tensors that cross a
+ * stage boundary).  In larger networks convolutions multiply on the bf16
+ * matrix pipes, every operand as three bf16 values that add up to it: nearer
+ * to exact sums than 32-bit products, but an infinite operand makes its sums
+ * NaN, not infinite.
  */
 #ifndef PB_H_
 #define PB_H_
