@@ -984,14 +984,14 @@ bool make_d1(const pb_ctx* c, int mode, int C, int H, int W, int K, int OH, int 
 //   estimated tile duration stays within the budget, the one with the least total
 //   work (tiles x duration); if none does, the one with the shortest tile.  Work below
 //   small_work microseconds (256: half a microsecond of the chip's 512 places) counts
-//   alike there and the shortest tile wins: layers in front of a GroupNorm, a network's
-//   first layer, which shares its phase with short steps and is the longest workgroup in it,
-//   and its last one, whose chain the end of the tick waits for.  Measured, us per tick
-//   without and with: VGG-11 87.6 and 82.7; networks with pre-layer norms 0.7 to 2.0 % less in
-//   eight of 22 that are planned otherwise (122.4 and 120.3, 243.5 and 239.0, 141.4 and 139.2),
-//   0.4 to 0.8 % more in three (the wide network 91.3 and 91.7).  For every layer of those the
-//   whole pass may be planned with another budget: a bottleneck network at 222 pixels 154.2 and
-//   163.5, fourteen others within 0.2 %.
+//   alike there and the shortest tile wins: the first layer of a network with post-layer
+//   norms shares its phase with elementwise steps and is the longest workgroup in it.
+//   Measured, us per tick without and with: VGG-11 87.6 and 82.7; in three other VGG
+//   networks (32, 48 and 64 channels at 20-40 pixels) the plan is the same either way.
+//   In networks with pre-layer norms (0 there) it is nothing in the mean of 420 random ones:
+//   by 0.7 to 2.1 % less in some twenty (243.5 and 239.0, 141.4 and 139.2), but a pass may be
+//   planned with another budget for it (108.8 and 114.8, 123.9 and 128.7, 154.2 and 163.5),
+//   and the wide one takes 91.3 without and 91.7 with.
 bool make_gemm(int mode, int C, int H, int W, int K, int OH, int OW, int k, int s, int pad,
                const GemmCfg* like, GemmCfg* out, bool allow_vec = false, int max_sub = 16, bool flat = false,
                int max_parts = 1, double small_work = 0.0) {
@@ -1553,7 +1553,7 @@ void compile_steps_once(pb_ctx* c, std::vector<std::pair<int, StepDesc>>& out) {
         const bool zsplit = a.post_gn && b.zparts >= 0 && !c->bf16 && g_tile_budget_us > 0 && !(d.flags & (F_SKIP | F_PROJ)) &&
                             (a.K / a.G) * a.OH * a.OW % 4 == 0 && (int64_t)(a.K / a.G) * a.OH * a.OW <= 32768 && a.K / a.G <= BLK;
         bool ok = make_gemm(1, d.C, d.H, d.W, d.K, d.OH, d.OW, d.k, d.stride, d.pad, nullptr, &g, plain_src, (d.flags & F_PROJ) ? 1 : 16, flat,
-                            zsplit ? FWD_PARTS : 1, a.post_gn || s == 0 || s == S - 1 ? 256.0 : 0.0);
+                            zsplit ? FWD_PARTS : 1, a.post_gn ? 256.0 : 0.0);
         if (ok && (d.flags & F_PROJ)) ok = make_gemm(1, d.sC, d.sH, d.sW, d.K, d.OH, d.OW, 1, d.sstride, 0, &g, &gp, true);
         GemmCfg gd, gw;
         // (with weight stashing the backward pass reads the predicted weights too, in their natural order)
