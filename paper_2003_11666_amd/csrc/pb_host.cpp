@@ -921,7 +921,10 @@ bool make_dc(const pb_ctx* c, int mode, int C, int H, int W, int K, int OH, int 
   // a reduction over a multiple of 32 channels runs on the bf16 pipes, chunks of 32 channels per wave and more; else on the
   // fp32 pipes, the largest chunk of up to 64 channels.  So do maps of fewer than 16 pixels, whose tiles stream weights and
   // little else: those of the fp32 pipes keep more of them in flight (512 channels on 2x2 maps: loops of 18-20 us there,
-  // 26-31 here; 256 channels on 4x4 maps: 15-18 there, 9-12 here)
+  // 26-31 here; 256 channels on 4x4 maps: 15-18 there, 9-12 here).  Us per tick with the line at 16 pixels, 17, 65 and 257:
+  // the wide network 91.6, 91.8, 99.7, 107.1; ResNet-50 448.0, 447.9, 456.0, 472.7, its stages at 64 pixels 203.6, 202.0, 203.3,
+  // 202.5; basic networks of 64, 128 and 256 channels at 20 pixels 89.3 at 16, 100.9 at 65, of 32, 64 and 128 at 32 pixels 52.3,
+  // 52.4, 51.6, 49.3, the one that would gain by another line.
   const int px = mode == 2 && stride == 1 ? H * W : OH * OW;       // columns of the product
   Best b;
   if (mode != 3 && R % 32 == 0 && px >= 16) b = search(true);
@@ -933,6 +936,15 @@ bool make_dc(const pb_ctx* c, int mode, int C, int H, int W, int K, int OH, int 
     // 11.9 at 96 channels: six networks 1.2 % faster to 3.1 % slower on the fp32 pipes).
     const Best f = search(false);
     if (!b.have || (f.have && f.tile < 0.667 * b.tile)) b = f;
+  } else if (c->tune.tile_budget_us == 0.f && b.g.tiles > 32) {
+    // Within a short budget (unless it is the caller's) the bf16 form may be left with its least tile, 16 x 16, which splits a
+    // weight for sixteen columns only.  Where the fp32 tiles are as short and their work is less by two fifths, the layer runs there (256
+    // channels, 81 pixels: 48 tiles of 16.4 us and 24 of 15.6).  Us per tick of VGG networks of 64 channels without and with:
+    // 92.8 and 85.6 at 38 pixels, 111.2 and 108.7 at 39; 165 other networks within their noise.  Steps of fewer tiles take
+    // places that would stay empty: with them, too, bottleneck networks of 32 channels at 123 pixels 112.1 instead of 108.5,
+    // basic ones of 64, 128 and 256 at 20 pixels 90.4 instead of 89.2.
+    const Best f = search(false);
+    if (f.have && (f.within || !b.within) && f.work < 0.6 * b.work && f.tile <= 1.2 * b.tile) b = f;
   }
   if (b.have) *out = b.g;
   return b.have;
@@ -1379,7 +1391,8 @@ void compile_steps_once(pb_ctx* c, std::vector<std::pair<int, StepDesc>>& out) {
     float* gr = c->f(b.gparts >= 0 ? b.gparts : L.g + a.off);
     // Weight gradients whose tiles hold whole sums (reduction not split over workgroups) update their weights themselves:
     // they run a phase after the data gradient, which reads the weights they overwrite.  (Not with a GroupNorm behind the
-    // layer: the phase after its backward GEMMs holds nothing else, and VGG-11 took 104 us instead of 94.)
+    // layer: the phase after its backward GEMMs holds nothing else.  Us per tick without and with it there: VGG-11 78.1 and
+    // 88.5, at 40 pixels 97.1 and 98.0.)
     bool fc_upd = false;   // the weights of the dense layer in front of the loss are updated by its weight-gradient step
     auto fuse_update = [&](StepDesc& d, int64_t o, int64_t n) {
       if (g_tile_budget_us <= 0 || c->N != 1 || a.post_gn || (d.kind == K_GEMM ? !(d.g.mm || d.g.dc) || d.g.parts != 1 : d.kind != K_FC_BWD_W || !fc_upd) || n % 4 || o % 4) return false;

@@ -287,3 +287,13 @@ net = W._net("stem", W.preact_resnet_bottleneck((3, 1), 16, 8, n_classes=171), 3
 steps = [l for l in B.plan_summary(net, mitigation=0).splitlines() if "C3x222x222" in l and "gm1" in l]
 assert len(steps) == 1 and "tile 16x128" in steps[0], steps
 """)
+
+
+def test_layers_left_with_the_least_bf16_tile_run_on_the_fp32_pipes(lib):
+    """256 channels on 81 pixels in a crowded launch: 48 and 96 tiles of 16 x 16 on the bf16 pipes, half as many, and no longer
+    ones, on the fp32 pipes."""
+    host_stub.run(lib, """
+net = W._net("vgg", W.vgg(tuple(64 * k for k in (1, 2, 4, 4, 8, 8, 8, 8)), (0, 1, 3, 5, 7), 4, n_classes=70, in_hw=38), 3, 38, 38, 70, 1e-3, 0.9, 8, 3, 8)
+steps = [l for l in B.plan_summary(net).splitlines() if "direct" in l and "gm2" in l]
+assert len(steps) == 3 and not any("tile 16x16" in l and " split" in l for l in steps), steps
+""")
