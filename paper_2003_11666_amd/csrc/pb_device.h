@@ -11,6 +11,7 @@ constexpr int BLK = 256;          // threads per workgroup (4 wavefronts of 64)
 constexpr int UPD_CHUNK = 1024;   // stages are padded to this many floats
 constexpr int UPD_TILE = 8192;    // floats per workgroup of an update step (8 float4 per thread and array in flight)
 constexpr float GN_EPS = 1e-5f;
+constexpr int GNB_WAVE_MAX_N = 2048; // elements of a group in the one-wavefront-per-group form of K_GN_BWD
 constexpr int GNB_WAVE_CH = 4;    // channels per wavefront in the one-wavefront-per-channel form of K_GNB_REDUCE
 constexpr int GNB_WAVE_HW = 256;  // ... whose maps have at most this many pixels
 constexpr int GNB_WAVE4_HW = 1020; // ... or at most this many, with 16-byte requests (grain 2)

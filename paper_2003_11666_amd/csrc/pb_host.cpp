@@ -1199,13 +1199,32 @@ void stream_apply(const pb_ctx* c, StepDesc& e) {
   e.ntiles = e.G * e.n;
 }
 
-// Networks tiled for latency: the GroupNorm statistics of a layer of four small groups
-// in one workgroup, a wavefront per group.
-void gn_stats_wave(StepDesc& d) {
+// Whether a tick's groups that fit a wavefront's registers are more than the chip has places for their workgroups (networks
+// tiled for throughput).  A wavefront takes longer for a group than a workgroup, which shows where they all run at once: VGG-11
+// (8 groups, 7 layers) 78.2 us per tick with a workgroup and 82.7 with a wavefront, a bottleneck network of 560 groups, 304 of
+// them small, 96.3 and 99.5.  Beyond: 1568 groups 203.3 and 188.8, 1120 183.9 and 181.5, 1024 145.6 and 144.6, 608 117.1 and 116.4.
+bool many_groups(const pb_ctx* c) {
+  int64_t n = 0;
+  for (const Stage& a : c->st)
+    if (a.pre_gn ? a.in_elems() <= (int64_t)a.G * GNB_WAVE_MAX_N : a.post_gn && a.z_elems() <= (int64_t)a.G * GNB_WAVE_MAX_N) n += a.G;
+  return c->kernel_set == 0 && g_tile_budget_us > 0 && n > 512;
+}
+
+// The GroupNorm statistics of four small groups in one workgroup, a wavefront per group.  Networks tiled for latency: layers of
+// up to four groups.  Networks tiled for throughput: where groups are many.
+void gn_stats_wave(const pb_ctx* c, StepDesc& d) {
   const int64_t n = d.G > 0 ? (int64_t)(d.C / d.G) * d.H * d.W : 0;
-  if (g_tile_budget_us > 0 || d.G < 1 || d.G > BLK / 64 || d.C / d.G > 64 || (d.H * d.W) % 4 || n > 4096) return;
+  if (d.G < 1 || d.C / d.G > 64 || n > 4096 || n % 4) return;
+  if (g_tile_budget_us > 0 ? !many_groups(c) || n > GNB_WAVE_MAX_N : d.G > BLK / 64 || (d.H * d.W) % 4) return;
   d.grain = 1;
-  d.ntiles = 1;
+  d.ntiles = cdiv(d.G, BLK / 64);
+}
+
+// The same for the backward pass of a GroupNorm whose groups fit a wavefront's registers.
+void gn_bwd_wave(const pb_ctx* c, StepDesc& d) {
+  if (!many_groups(c) || d.C / d.G > 64 || (int64_t)(d.C / d.G) * d.H * d.W > GNB_WAVE_MAX_N) return;
+  d.grain = 1;
+  d.ntiles = cdiv(d.G, BLK / 64);
 }
 
 // One wavefront per channel for a K_GNB_REDUCE step over a small map.
@@ -1470,7 +1489,7 @@ void compile_steps_once(pb_ctx* c, std::vector<std::pair<int, StepDesc>>& out) {
         if (a.pre_relu) d.flags |= F_PRE_RELU;
       }
       d.ntiles = a.G;
-      gn_stats_wave(d);
+      gn_stats_wave(c, d);
       out.push_back({ph++, d});
     }
     if (a.gap) {
@@ -1606,7 +1625,7 @@ void compile_steps_once(pb_ctx* c, std::vector<std::pair<int, StepDesc>>& out) {
       fwd_params(d, PF_GAMMA | PF_BETA);
       d.ntiles = a.G;
       if (fwd_parts > 1) { d.gw = c->f(b.zparts); d.gparts = fwd_parts; d.gpstride = (int)a.z_elems(); }
-      else gn_stats_wave(d);
+      else gn_stats_wave(c, d);
       out.push_back({ph++, d});
       StepDesc e = blank(K_POST_FWD, s, t_f);
       e.C = a.K; e.H = a.OH; e.W = a.OW; e.G = a.G;
@@ -1651,6 +1670,7 @@ void compile_steps_once(pb_ctx* c, std::vector<std::pair<int, StepDesc>>& out) {
         d.kind = K_GN_BWD;
         d.dx = ring(c, b.dz, 1, a.z_elems(), 0);
         d.ntiles = a.G;
+        gn_bwd_wave(c, d);
         out.push_back({pb, d});
         // keep the backward GEMMs of every post-norm stage in the same phase as those of the stages
         // that need the two-step GroupNorm backward: a phase lasts as long as its longest tile, so
@@ -1908,6 +1928,7 @@ void compile_steps_once(pb_ctx* c, std::vector<std::pair<int, StepDesc>>& out) {
           d.gacc = c->f(L.gacc + a.off + a.o_gamma);
         }
         d.ntiles = a.G;
+        gn_bwd_wave(c, d);
         out.push_back({pb++, d});
       } else {
         d.ntiles = a.Cin;
@@ -2046,7 +2067,7 @@ void compile_steps_once(pb_ctx* c, std::vector<std::pair<int, StepDesc>>& out) {
     if (pr.second.kind == K_GEMM && ((pr.second.g.gm != 3 && pr.second.g.parts > 1) || pr.second.g.nsub > 1 || pr.second.g.win > 0 || pr.second.g.mm || pr.second.g.dc ||
                                     pr.second.gp.nsub > 1 || pr.second.gp.win > 0)) c->nt_stores = false;
   for (auto& pr : out)
-    if ((pr.second.kind == K_UPDATE && (pr.second.flags & F_WGRAD)) || (pr.second.kind == K_GNB_REDUCE && pr.second.grain == 2) || pr.second.kind == K_DOT_FWD || pr.second.kind == K_DOT_BWD_X ||
+    if ((pr.second.kind == K_UPDATE && (pr.second.flags & F_WGRAD)) || (pr.second.kind == K_GNB_REDUCE && pr.second.grain == 2) || (pr.second.kind == K_GN_BWD && pr.second.grain == 1) || pr.second.kind == K_DOT_FWD || pr.second.kind == K_DOT_BWD_X ||
         pr.second.kind == K_FC_FWD || pr.second.kind == K_FC_BWD_X || pr.second.kind == K_FC_BWD_W)
       c->nt_stores = false;
   if (c->nt_stores) {
@@ -2192,9 +2213,9 @@ int validate_steps(const pb_ctx* c, const std::vector<std::pair<int, StepDesc>>&
     bool ok = d.ntiles > 0;
     switch (d.kind) {
       case K_GN_STATS:
-        if (d.grain == 1)   // one wavefront per group, one workgroup
-          ok = ok && d.G > 0 && d.G <= BLK / 64 && d.C % d.G == 0 && d.ntiles == 1 && d.C / d.G <= 64 && (d.H * d.W) % 4 == 0 &&
-               d.C / d.G * d.H * d.W <= 4096;
+        if (d.grain == 1)   // one wavefront per group
+          ok = ok && d.G > 0 && d.C % d.G == 0 && d.ntiles == cdiv(d.G, BLK / 64) && d.C / d.G <= 64 && (d.C / d.G * d.H * d.W) % 4 == 0 &&
+               (!c->nt_stores || (d.H * d.W) % 4 == 0) && d.C / d.G * d.H * d.W <= 4096;
         else
           ok = ok && d.ntiles == d.G;
         if (d.gparts > 1)   // sums the partial outputs of a split forward GEMM: register form only
@@ -2255,7 +2276,9 @@ int validate_steps(const pb_ctx* c, const std::vector<std::pair<int, StepDesc>>&
       }
       case K_GN_BWD: {
         const int64_t dyn = (d.flags & F_DU_BUF) ? in : d.C;
-        ok = ok && gn_bwd_fits(d.C, d.H * d.W, d.G) && d.ntiles == d.G && !(d.flags & F_DU_POOL) &&
+        if (d.grain == 1)   // one wavefront per group
+          ok = ok && !c->nt_stores && d.C / d.G <= 64 && d.C / d.G * d.H * d.W <= GNB_WAVE_MAX_N;
+        ok = ok && gn_bwd_fits(d.C, d.H * d.W, d.G) && d.ntiles == (d.grain == 1 ? cdiv(d.G, BLK / 64) : d.G) && !(d.flags & F_DU_POOL) &&
              ((d.flags & F_DU_BUF) || (d.flags & F_DU_GAP)) && ref_ok(d.x, in) && ref_ok(d.st, stn) && ref_ok(d.dy, dyn) &&
              ptr_ok(d.gamma, d.C) && ptr_ok(d.ggamma, d.C) && ptr_ok(d.gbeta, d.C) && (!d.dx.base || ref_ok(d.dx, in)) &&
              (!(d.flags & F_ADD_SKG) || (d.dx.base && ref_ok(d.skg, in)));

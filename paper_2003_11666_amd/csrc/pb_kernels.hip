@@ -247,13 +247,13 @@ __device__ __forceinline__ void step_gn_stats(const LDesc& d, int tile, int t, l
   }
 }
 
-// The same with one wavefront per group and all four groups of the layer in one
+// The same with one wavefront per group, four groups of the layer in one
 // workgroup (grain = 1; groups of at most 4096 elements, at most 64 channels per
 // group): sums across lanes only, no barrier, and a quarter of the workgroups.
 // LDS: per wavefront sc[64] | sh[64].
 constexpr int GNS_WAVE_MAX_N = 4096;
-__device__ __forceinline__ void step_gn_stats_wave(const LDesc& d, int t, lfloat* smem, const bool nt) {
-  const int lane = threadIdx.x & 63, g = UNI(threadIdx.x >> 6);
+__device__ __forceinline__ void step_gn_stats_wave(const LDesc& d, int tile, int t, lfloat* smem, const bool nt) {
+  const int lane = threadIdx.x & 63, wv = UNI(threadIdx.x >> 6), g = tile * (BLK / 64) + wv;
   const int C = UNI(d.C), G = UNI(d.G), HW = UNI(d.H) * UNI(d.W);
   const int cpg = UNI(fdiv(C, frcp(G))), n = cpg * HW;
   if (g >= G) return;
@@ -286,7 +286,7 @@ __device__ __forceinline__ void step_gn_stats_wave(const LDesc& d, int t, lfloat
   const float var = wave_sum(q) / (float)n;
   const float rstd = 1.0f / sqrtf(var + GN_EPS);
   if (lane == 0) { st[g] = mean; st[G + g] = rstd; }
-  lfloat* sc_l = smem + g * 128;
+  lfloat* sc_l = smem + wv * 128;
   lfloat* sh_l = sc_l + 64;
   if (lane < cpg) {
     const int ch = g * cpg + lane;
@@ -300,17 +300,20 @@ __device__ __forceinline__ void step_gn_stats_wave(const LDesc& d, int t, lfloat
   __builtin_amdgcn_wave_barrier();
   gfloat* yo = at(d.y, t) + (size_t)g * n;
   const float ihw = frcp(HW);
+  const bool whole = nt || (HW & 3) == 0;          // (networks tiled for latency: planned for such maps only)
 #pragma unroll
   for (int u = 0; u < WU; ++u) {
     const int i = (lane + u * 64) * 4;
     if (u * 256 < n) {
       if (i < n) {
-        const int c = fdiv(i, ihw);   // H*W is a multiple of 4: the four elements share a channel
+        const int c = fdiv(i, ihw);
         const float sc = sc_l[c], sh = sh_l[c];
         v4f o;
 #pragma unroll
         for (int e = 0; e < 4; ++e) {
-          float v = fmaf(sc, xr[u][e], sh);
+          // (H*W a multiple of 4: the four elements share a channel)
+          const int ce = whole ? c : fdiv(i + e, ihw);
+          float v = whole ? fmaf(sc, xr[u][e], sh) : fmaf(sc_l[ce], xr[u][e], sh_l[ce]);
           if (rl) v = fmaxf(v, 0.f);
           o[e] = v;
         }
@@ -1099,6 +1102,138 @@ __device__ __forceinline__ void step_gn_bwd(const LDesc& d, int tile, int t, boo
           o[e] = rbf_if(flags & F_BF16_OUT, rstd * (du[u][e] * gm - m1 - xh * m2) + sk[u][e]);
         }
         PB_ST(nt, (gv4*)(dx + 4 * sl), o);
+      }
+    }
+}
+
+// The same with one wavefront per group, four groups per workgroup (grain = 1; at most 2048 elements and 64 channels per
+// group): no barrier.  A small group's workgroup lives for its descriptor, one round trip of reads and the barriers between
+// the sums whatever it holds (256 to 2048 elements: 5.6 us), and a place of the chip is busy that long.  Bound by that round
+// trip; ResNet-50's stages at 64 pixels have 1536 such groups and as many statistics of 3.8 us: 203.3 us per tick with a
+// workgroup per group, 188.8 with a wavefront.
+// LDS, per wavefront: psum[512] | psum2[512] | sc[64] | sh[64] | sums, scale of the backward pass [3 x 64].
+__device__ __forceinline__ void step_gn_bwd_wave(const LDesc& d, int tile, int t, bool live, lfloat* smem) {
+  const int lane = threadIdx.x & 63, wv = UNI((int)threadIdx.x >> 6), g = tile * (BLK / 64) + wv;
+  const int C = UNI(d.C), G = UNI(d.G), HW = UNI(d.H) * UNI(d.W), flags = UNI(d.flags);
+  const int cpg = UNI(fdiv(C, frcp(G))), n = cpg * HW, ns = n >> 2, HW4 = HW >> 2;
+  if (g >= G) return;
+  const bool gen = flags & F_UPD_GEN, upd = (flags & F_UPD_GN) && lane < cpg;
+  UpdOld old0 = {0.f, 0.f, 0.f, 0.f}, old1 = old0;
+  if (upd) {
+    old0 = update_fetch(d, t, g * cpg + lane, gen);
+    old1 = update_fetch(d, t, C + g * cpg + lane, gen);
+  }
+  auto update = [&](float sg, float sb) {
+    if (gen) { update_one(d, t, g * cpg + lane, sg, old0, true); update_one(d, t, C + g * cpg + lane, sb, old1, true); }
+    else { update_one(d, t, g * cpg + lane, sg, old0, false); update_one(d, t, C + g * cpg + lane, sb, old1, false); }
+  };
+  if (!live) {
+    if (upd) update(0.f, 0.f);
+    return;
+  }
+  const bool rl = flags & F_GN_RELU, gapd = flags & F_DU_GAP;
+  const float ihw4 = frcp(HW4);
+  constexpr int GU = GNB_WAVE_MAX_N / 256;
+  lfloat* psum = smem + wv * (2 * GNB_WAVE_MAX_N / 4 + 5 * 64);
+  lfloat* psum2 = psum + GNB_WAVE_MAX_N / 4;
+  lfloat* cs = psum2 + GNB_WAVE_MAX_N / 4;
+  lfloat* cs2 = cs + 2 * 64;
+  const gfloat* st = at(d.st, t);
+  const gfloat* xg = at(d.x, t) + (size_t)g * n;
+  const gfloat* dy = at(d.dy, t);
+  const bool has_dx = d.dx.base != nullptr;
+  const gfloat* skg = ((flags & F_ADD_SKG) && has_dx) ? at(d.skg, t) + (size_t)g * n : nullptr;
+  v4f xr[GU], du[GU], sk[GU];
+#pragma unroll
+  for (int u = 0; u < GU; ++u) {
+    xr[u] = (v4f){0.f, 0.f, 0.f, 0.f}; du[u] = xr[u]; sk[u] = xr[u];
+    const int sl = lane + u * 64;
+    if (u * 64 < ns) {
+      if (sl < ns) {
+        xr[u] = *(const gv4*)(xg + 4 * sl);
+        if (gapd) { const float v = dy[g * cpg + fdiv(sl, ihw4)]; du[u] = (v4f){v, v, v, v}; }
+        else du[u] = *(const gv4*)(dy + (size_t)g * n + 4 * sl);
+        if (skg) sk[u] = *(const gv4*)(skg + 4 * sl);
+      }
+    }
+  }
+  const int gparts = UNI(d.gparts);
+  if (gparts > 1 && !gapd) {
+    // (partial sums of a backward-data GEMM split over its reduction, as above)
+    const size_t ps = (size_t)UNI(d.gpstride);
+    for (int u = 0; u < GU; ++u) {
+      const int sl = lane + u * 64;
+      if (sl < ns) du[u] = sum_parts<v4f, 2>((const gv4*)(GP(d.gw) + (size_t)g * n + 4 * sl), ps >> 2, gparts);
+    }
+  }
+  const float mean = st[g], rstd = st[G + g];
+  float gm_c = 0.f;                                 // lane c < cpg holds its channel's constants
+  if (lane < cpg) {
+    const float sc_c = st[2 * G + g * cpg + lane], sh_c = st[2 * G + C + g * cpg + lane];
+    gm_c = GP(d.gamma)[g * cpg + lane];
+    cs[lane] = sc_c; cs[64 + lane] = sh_c; cs2[2 * 64 + lane] = gm_c;
+  }
+  __builtin_amdgcn_wave_barrier();
+  const bool rows16 = (HW4 & 15) == 0;
+  const int per_c = rows16 ? HW4 >> 4 : HW4;
+#pragma unroll
+  for (int u = 0; u < GU; ++u)
+    if (u * 64 < ns) {
+      const int sl = lane + u * 64;
+      float sg = 0.f, sb = 0.f;
+      if (sl < ns) {
+        const int c = fdiv(sl, ihw4);
+        const float sc = cs[c], sh = cs[64 + c];
+        const float dpool = gapd ? du[u][0] / (float)HW : 0.f;
+#pragma unroll
+        for (int e = 0; e < 4; ++e) {
+          float dv = gapd ? dpool : du[u][e];
+          if (rl && !(fmaf(sc, xr[u][e], sh) > 0.f)) dv = 0.f;
+          du[u][e] = dv;
+          sg = fmaf(dv, (xr[u][e] - mean) * rstd, sg);
+          sb += dv;
+        }
+      }
+      if (rows16) {
+        sg = row_sum(sg); sb = row_sum(sb);
+        if (sl < ns && (lane & 15) == 0) { psum[sl >> 4] = sg; psum2[sl >> 4] = sb; }
+      } else if (sl < ns) {
+        psum[sl] = sg; psum2[sl] = sb;
+      }
+    }
+  __builtin_amdgcn_wave_barrier();
+  for (int j0 = 0; j0 < 4 * cpg; j0 += 64) {          // lanes 4c..4c+3 share channel c
+    const int j = j0 + lane, c = j >> 2, p = j & 3;
+    float sg = 0.f, sb = 0.f;
+    if (c < cpg)
+      for (int i = p; i < per_c; i += 4) { sg += psum[c * per_c + i]; sb += psum2[c * per_c + i]; }
+    sg += dpp_src<0xB1, 0xF>(sg); sb += dpp_src<0xB1, 0xF>(sb);
+    sg += dpp_src<0x4E, 0xF>(sg); sb += dpp_src<0x4E, 0xF>(sb);
+    if (p == 0 && c < cpg) { cs2[c] = sb; cs2[64 + c] = sg; }
+  }
+  __builtin_amdgcn_wave_barrier();
+  float sg = 0.f, sb = 0.f;
+  if (lane < cpg) {
+    sb = cs2[lane]; sg = cs2[64 + lane];
+    GP(d.ggamma)[g * cpg + lane] = sg; GP(d.gbeta)[g * cpg + lane] = sb;
+  }
+  if (upd) update(sg, sb);
+  if (!has_dx) return;
+  const float m1 = wave_sum(sb * gm_c) / (float)n, m2 = wave_sum(sg * gm_c) / (float)n;
+  gfloat* dx = at(d.dx, t) + (size_t)g * n;
+#pragma unroll
+  for (int u = 0; u < GU; ++u)
+    if (u * 64 < ns) {
+      const int sl = lane + u * 64;
+      if (sl < ns) {
+        const float gm = cs2[2 * 64 + fdiv(sl, ihw4)];
+        v4f o;
+#pragma unroll
+        for (int e = 0; e < 4; ++e) {
+          const float xh = (xr[u][e] - mean) * rstd;
+          o[e] = rbf_if(flags & F_BF16_OUT, rstd * (du[u][e] * gm - m1 - xh * m2) + sk[u][e]);
+        }
+        *(gv4*)(dx + 4 * sl) = o;
       }
     }
 }
@@ -2549,7 +2684,7 @@ k_phase(const StepDesc* __restrict__ recs, const Globals* __restrict__ G, int k,
   if (run) {
   switch (UNI(d.kind)) {
     case K_GN_STATS:
-      if (UNI(d.grain) == 1) step_gn_stats_wave(d, t, smem, NT); else step_gn_stats(d, tile, t, red, smem, NT);
+      if (UNI(d.grain) == 1) step_gn_stats_wave(d, tile, t, smem, NT); else step_gn_stats(d, tile, t, red, smem, NT);
       break;
     case K_GAP_FWD: step_gap_fwd(d, tile, t, red); break;
     case K_CONV_FWD: step_conv_fwd(d, tile, t); break;
@@ -2565,7 +2700,9 @@ k_phase(const StepDesc* __restrict__ recs, const Globals* __restrict__ G, int k,
     case K_INGEST: step_ingest(d, tile, t, G, k, sample_override, label_override); break;
     case K_UPDATE: step_update(d, tile, t, smem, NT); break;
     case K_HEAD: step_head(d, t, red, smem, NT); break;
-    case K_GN_BWD: step_gn_bwd(d, tile, t, live, smem, NT); break;
+    case K_GN_BWD:
+      if (!NT && UNI(d.grain) == 1) step_gn_bwd_wave(d, tile, t, live, smem); else step_gn_bwd(d, tile, t, live, smem, NT);
+      break;
     // (planned only for networks tiled for throughput: the other instantiation carries no code for them)
     case K_DOT_FWD: if (!NT) step_dot_fwd(d, tile, t, smem); break;
     case K_DOT_BWD_X: if (!NT) step_dot_bwd_x(d, tile, t, smem); break;
