@@ -2095,12 +2095,12 @@ void order_steps(std::vector<std::pair<int, StepDesc>>& tagged, bool one_launch 
         us = est_tile_us(one, d.k);
         if (d.gp.gm) us += est_tile_us(d.gp, 1);
       } else if (d.kind == K_GN_STATS || d.kind == K_GN_BWD) {
-        // (statistics of a group that no workgroup holds in its registers -- beyond 32768 elements, no multiple of 4 -- take three
-        // passes over memory: 15 870 elements 35 us.  Started behind weight-gradient tiles they were the end of a launch of a
+        // (statistics of a group that no workgroup holds in its registers, beyond 32768 elements, take three
+        // passes over memory: 15 870 elements took 35 us that way.  Started behind weight-gradient tiles they were the end of a launch of a
         // basic network of 60, 120 and 240 channels: 182 us per tick instead of 166)
         const int64_t cpg = d.C / std::max(1, d.G), n = cpg * d.H * d.W;
-        const bool passes = d.kind == K_GN_STATS && (n > 32768 || n % 4 || cpg > BLK);
-        us = 4.0 + (double)n / BLK * (!passes ? 0.05 : n > 32768 ? 1.0 : 0.5);
+        const bool passes = d.kind == K_GN_STATS && (n > 32768 || cpg > BLK);
+        us = 4.0 + (double)n / BLK * (!passes ? (d.kind == K_GN_STATS && n % 4 ? 0.1 : 0.05) : n > 32768 ? 1.0 : 0.5);
       } else if (d.kind == K_GNB_REDUCE) {
         // (routing the gradient back through a max-pool costs a window search per element: about 2 us per
         // 256 of them when the channel fits LDS, 7 us from global memory)

@@ -221,11 +221,53 @@ __device__ __forceinline__ void step_gn_stats(const LDesc& d, int tile, int t, l
     if (n <= 8 * 4 * BLK) { step_gn_stats_reg<8>(d, tile, t, red, smem, nt); return; }
     if (n <= 32 * 4 * BLK) { step_gn_stats_reg<32>(d, tile, t, red, smem, nt); return; }
   }
+  // Groups of no multiple of 4 elements, or of more than a workgroup's registers hold.  Their vectors may start anywhere (the
+  // last one goes element by element); what fits LDS waits there for the second and third pass.  Bound by the round trips of
+  // the first: 17 298 elements (36 channels of 31x31, two groups) read an element at a time in three passes over memory took
+  // 45.5 us, the end of a launch whose longest tile ends at 30: a network of eight stages of that map 109.1 us per tick, 87.6 now.
+  const bool stash = (n + 3) / 4 * 4 <= LDS_FLOATS;
+  auto each = [&](bool first, auto f) {
+    constexpr int U = 8;
+    for (int i0 = 4 * tid; i0 < n; i0 += 4 * U * BLK) {
+      v4f v[U];
+#pragma unroll
+      for (int u = 0; u < U; ++u) {
+        const int i = i0 + 4 * u * BLK;
+        v[u] = (v4f){0.f, 0.f, 0.f, 0.f};
+        if (!first && stash) {
+          if (i < n) v[u] = *(const lv4*)(smem + i);
+        } else if (i + 3 < n) {
+          v[u] = *(const gv4u*)(xp + i);
+        }
+      }
+      const int il = n & ~3;                         // the last vector, if it is not whole
+      if ((first || !stash) && il < n && il >= i0 && (il - i0) % (4 * BLK) == 0 && il < i0 + 4 * U * BLK) {
+        const int ul = (il - i0) / (4 * BLK);
+        const v4f x = {xp[il], il + 1 < n ? xp[il + 1] : 0.f, il + 2 < n ? xp[il + 2] : 0.f, 0.f};
+#pragma unroll
+        for (int u = 0; u < U; ++u) v[u] = u == ul ? x : v[u];
+      }
+#pragma unroll
+      for (int u = 0; u < U; ++u) {
+        const int i = i0 + 4 * u * BLK;
+        if (i < n) f(i, v[u]);
+      }
+    }
+  };
   float s = 0.f;
-  for (int i = tid; i < n; i += BLK) s += xp[i];
+  each(true, [&](int i, v4f v) {
+    s += (v[0] + v[1]) + (v[2] + v[3]);
+    if (stash) *(lv4*)(smem + i) = v;                // (read back by the thread that wrote it)
+  });
   const float mean = block_sum(s, red) / (float)n;
   float q = 0.f;
-  for (int i = tid; i < n; i += BLK) { float dl = xp[i] - mean; q = fmaf(dl, dl, q); }
+  each(false, [&](int i, v4f v) {
+#pragma unroll
+    for (int e = 0; e < 4; ++e) {
+      const float dl = i + e < n ? v[e] - mean : 0.f;
+      q = fmaf(dl, dl, q);
+    }
+  });
   const float var = block_sum(q, red) / (float)n;
   const float rstd = 1.0f / sqrtf(var + GN_EPS);
   if (tid == 0) { st[g] = mean; st[G + g] = rstd; }
@@ -237,13 +279,20 @@ __device__ __forceinline__ void step_gn_stats(const LDesc& d, int tile, int t, l
   }
   if (d.y.base) {
     gfloat* yo = at(d.y, t) + (size_t)g * n;
-    for (int i = tid; i < n; i += BLK) {
-      const int ch = g * cpg + i / HW;
-      const float sc = GP(d.gamma)[ch] * rstd;
-      float v = fmaf(sc, xp[i], fmaf(-mean, sc, GP(d.beta)[ch]));
-      if (rl) v = fmaxf(v, 0.f);
-      yo[i] = v;
-    }
+    const float ihw = frcp(HW);
+    each(false, [&](int i, v4f v) {
+      v4f o;
+#pragma unroll
+      for (int e = 0; e < 4; ++e) {
+        const int k = i + e < n ? i + e : n - 1, ch = g * cpg + (n < (1 << 21) ? fdiv(k, ihw) : k / HW);
+        const float sc = GP(d.gamma)[ch] * rstd;
+        o[e] = fmaf(sc, v[e], fmaf(-mean, sc, GP(d.beta)[ch]));
+        if (rl) o[e] = fmaxf(o[e], 0.f);
+      }
+      if (i + 3 < n) *(gv4u*)(yo + i) = o;
+      else
+        for (int e = 0; e < n - i; ++e) yo[i + e] = e == 0 ? o[0] : e == 1 ? o[1] : o[2];
+    });
   }
 }
 
