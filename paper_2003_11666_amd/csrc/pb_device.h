@@ -12,10 +12,11 @@ constexpr int UPD_CHUNK = 1024;   // stages are padded to this many floats
 constexpr int UPD_TILE = 8192;    // floats per workgroup of an update step (8 float4 per thread and array in flight)
 constexpr float GN_EPS = 1e-5f;
 constexpr int GNB_WAVE_MAX_N = 2048; // elements of a group in the one-wavefront-per-group form of K_GN_BWD
+constexpr int HEAD_FC_W = 32768;  // weights of the dense layer that K_HEAD_FC takes, its inputs at most 4 BLK
+constexpr int GAP_STATS_CPG = 4096; // channels per group of a K_GAP_STATS step
 constexpr int GNB_WAVE_CH = 4;    // channels per wavefront in the one-wavefront-per-channel form of K_GNB_REDUCE
 constexpr int GNB_WAVE_HW = 256;  // ... whose maps have at most this many pixels
 constexpr int GNB_WAVE4_HW = 1020; // ... or at most this many, with 16-byte requests (grain 2)
-constexpr int GAP_WAVE_CH = 4;    // channels per wavefront in the one-wavefront-per-channel form of K_GAP_FWD (at most 64 pixels)
 constexpr int FC_BX = 16;         // inputs per workgroup of K_FC_BWD_X
 
 // A tensor that lives in a ring of `depth` slots.  At tick t the slot in use
@@ -55,7 +56,9 @@ enum StepKind : int32_t {
   // of 4): nothing for the matrix cores, a stream of the weight matrix.
   K_FC_FWD = 18,     // y = W x + b: a wavefront per output, four outputs per workgroup
   K_FC_BWD_X = 19,   // dx = W^T dy: FC_BX inputs per workgroup, the outputs dealt out to groups of lanes
-  K_FC_BWD_W = 20    // gW = dy x^T: 4096 consecutive weights per workgroup (F_UPD_W: their update)
+  K_FC_BWD_W = 20,   // gW = dy x^T: 4096 consecutive weights per workgroup (F_UPD_W: their update)
+  K_GAP_STATS = 21,  // K_GN_STATS and K_GAP_FWD of one group, and what its channels' backward sums are per unit of gradient
+  K_HEAD_FC = 22     // dense layer behind a global average pool, loss and backward pass of both: one workgroup
 };
 
 // Layers stored in the order of F_W_PERM, for a read-back in their own order (k_natural): a table that travels with the launch.
@@ -181,7 +184,8 @@ struct StepDesc {
   int32_t sig_idx, nwait;
   int32_t wait_idx[3], wait_n[3];
   int32_t grain;            // > 0: streaming form of an elementwise step, floats per workgroup (K_COPY, K_GNB_APPLY);
-                            // K_GNB_REDUCE, K_GAP_FWD: 1 = one wavefront per channel; K_GNB_REDUCE: 2 = the same, 16-byte requests
+                            // K_GNB_REDUCE: 1 = one wavefront per channel, 2 = the same, 16-byte requests; K_GN_STATS, K_GN_BWD:
+                            // 1 = one wavefront per group
   GemmCfg g;     // main operand set of a K_GEMM step
   GemmCfg gp;    // projection of the skip tensor accumulated into the same tile (forward only)
   TRef x;        // op input (forward) / saved input (backward)

@@ -253,7 +253,7 @@ struct Plan {
 
 struct StageBufs {
   int64_t aring = -1;   // normalised + rectified stage input (pre-norm conv stages)
-  int64_t xring = -1, prest = -1, pooled = -1, zring = -1, postst = -1, gradbox = -1, skg = -1,
+  int64_t xring = -1, prest = -1, pooled = -1, gapunit = -1, zring = -1, postst = -1, gradbox = -1, skg = -1,
           da = -1, dz = -1, part = -1, logits = -1, dlogits = -1,
           projy = -1,   // output of the skip projection of the tick's forward sample (computed one phase ahead of the sum)
           dxparts = -1, // FWD_PARTS partial gradients with respect to the stage's output, left by the backward-data GEMM of
@@ -374,7 +374,7 @@ void plan_arena(const std::vector<Stage>& st, bool stash, int loss_cap, Layout& 
     if (a.pre_gn || a.post_gn) b.st_stride = st_stride_of(a);
     if (a.pre_gn) b.prest = pl.alloc((int64_t)(a.D + 1) * b.st_stride);
     if (a.pre_gn && !a.gap && use_aring) b.aring = pl.alloc((int64_t)(a.D + 1) * a.in_elems());
-    if (a.gap) b.pooled = pl.alloc((int64_t)(a.D + 1) * a.C);
+    if (a.gap) { b.pooled = pl.alloc((int64_t)(a.D + 1) * a.C); b.gapunit = pl.alloc((int64_t)(a.D + 1) * 2 * a.C); }
     if (a.post_gn) {
       b.zring = pl.alloc((int64_t)(a.D + 1) * a.z_elems());
       b.postst = pl.alloc((int64_t)(a.D + 1) * b.st_stride);
@@ -1412,6 +1412,7 @@ void compile_steps_once(pb_ctx* c, std::vector<std::pair<int, StepDesc>>& out) {
     // they run a phase after the data gradient, which reads the weights they overwrite.  (Not with a GroupNorm behind the
     // layer: the phase after its backward GEMMs holds nothing else.  Us per tick without and with it there: VGG-11 78.1 and
     // 88.5, at 40 pixels 97.1 and 98.0.)
+    bool gap_summed = false;   // the sums of the channels under a global average pool are taken by the dense layer's backward step
     bool fc_upd = false;   // the weights of the dense layer in front of the loss are updated by its weight-gradient step
     auto fuse_update = [&](StepDesc& d, int64_t o, int64_t n) {
       if (g_tile_budget_us <= 0 || c->N != 1 || a.post_gn || (d.kind == K_GEMM ? !(d.g.mm || d.g.dc) || d.g.parts != 1 : d.kind != K_FC_BWD_W || !fc_upd) || n % 4 || o % 4) return false;
@@ -1446,9 +1447,69 @@ void compile_steps_once(pb_ctx* c, std::vector<std::pair<int, StepDesc>>& out) {
       out.push_back({0, d});
       ph = 1;
     }
+    // the backward pass of the GroupNorm at the head of the stage; summed: an earlier step left the channels' sums
+    auto gn_backward = [&](int& pb, bool summed) {
+      StepDesc d = blank(K_GNB_REDUCE, s, t_b);
+      d.C = a.Cin; d.H = a.Hin; d.W = a.Win; d.G = a.G;
+      d.flags = (a.pre_relu ? F_GN_RELU : 0) | (a.gap ? F_DU_GAP : F_DU_BUF);
+      d.x = x_b;
+      d.st = ring(c, b.prest, D + 1, b.st_stride, D);
+      d.dy = ring(c, b.da, 1, a.gap ? a.C : a.in_elems(), 0);
+      d.gamma = wbk + a.o_gamma;
+      bwd_params(d, PF_GAMMA);
+      d.ggamma = gr + a.o_gamma; d.gbeta = gr + a.o_beta;
+      d.part = c->f(b.part);
+      if (c->kernel_set == 0 && gn_bwd_fits(d.C, d.H * d.W, d.G)) {
+        d.kind = K_GN_BWD;
+        if (c->bf16) d.flags |= F_BF16_OUT;
+        if (s > 0) {
+          d.dx = ring(c, L.sb[s - 1].gradbox, 2, a.in_elems(), ML);
+          if (a.tap_dist) { d.flags |= F_ADD_SKG; d.skg = ring(c, b.skg, a.tap_dist + 1, a.in_elems(), TL(a.tap_dist)); }
+        }
+        // this step ends the stage's backward chain and is the only producer of the scale / shift
+        // gradients: it updates those two tensors itself, so that the rest of the stage can be
+        // updated one phase earlier and no phase is left that holds nothing but updates
+        // (with weight stashing the step's ring fields address the version whose scale it reads: it works out the slot of the
+        // version it writes by itself.  ResNet-20, us per tick, with these updates a launch of their own and here: four samples
+        // per update 37.8 and 23.5, stashing 30.6 and 23.5, both 38.2 and 23.7)
+        d.flags |= F_UPD_GN | F_ALWAYS | (c->stash || c->N > 1 ? F_UPD_GEN : 0);
+        set_update_coeffs(c, a, &d);
+        d.v = c->f(L.v + a.off + a.o_gamma);
+        d.w = wb + a.o_gamma;                       // master scale and shift, updated in place
+        d.b = d.v;
+        d.what0 = c->f(L.what[s] + a.o_gamma);
+        d.what = c->f(L.what[s] + a.o_gamma);
+        if (!c->stash) writes_what(d);
+        if (c->N > 1) {
+          d.upd_n = c->N;
+          d.upd_t0 = seq ? 0 : 2 * (S - 1) - s;
+          d.gacc = c->f(L.gacc + a.off + a.o_gamma);
+        }
+        d.ntiles = a.G;
+        gn_bwd_wave(c, d);
+        out.push_back({pb++, d});
+      } else {
+        d.ntiles = a.Cin;
+        const StepDesc d_plain = d;
+        wave_reduce(d);
+        if (d.grain == 0 && wave4_fits(c, d)) { d.grain = 2; d.ntiles = cdiv(d.C, BLK / 64); }
+        if (!summed) out.push_back({pb++, d});
+        if (s > 0) {
+          StepDesc e = d_plain;
+          e.kind = K_GNB_APPLY;
+          if (c->bf16) e.flags |= F_BF16_OUT;
+          e.dx = ring(c, L.sb[s - 1].gradbox, 2, a.in_elems(), ML);
+          if (a.tap_dist) { e.flags |= F_ADD_SKG; e.skg = ring(c, b.skg, a.tap_dist + 1, a.in_elems(), TL(a.tap_dist)); }
+          e.ntiles = cdiv(a.in_elems(), BLK);
+          stream_apply(c, e);
+          out.push_back({pb++, e});
+        }
+      }
+    };
     // a small last stage runs as one workgroup: forward, loss and backward
     const bool fused_head = a.ce && c->kernel_set == 0 && !a.post_gn && !a.add && !a.is_conv && (a.gap ? a.pre_gn : !a.pre_gn) &&
-                            head_fits(a.Cin, a.Hin * a.Win, a.K, a.gap, a.pre_gn ? a.G : 1) && s > 0;
+                            head_fits(a.Cin, a.Hin * a.Win, a.K, a.gap, a.pre_gn ? a.G : 1) && s > 0 &&
+                            !(a.gap && a.Hin * a.Win % 4 && a.Cin > 32 && a.C % 4 == 0);
     if (fused_head) {
       StepDesc d = blank(K_HEAD, s, t_f);
       d.C = a.Cin; d.H = a.Hin; d.W = a.Win; d.K = a.K; d.G = a.pre_gn ? a.G : 1;
@@ -1478,7 +1539,52 @@ void compile_steps_once(pb_ctx* c, std::vector<std::pair<int, StepDesc>>& out) {
     }
     // ------------------------------------------------------------ forward
     int fwd_parts = 1;   // > 1: the layer's forward GEMM leaves partial outputs (see fwd_split_candidate)
-    if (a.pre_gn) {
+    const bool gap_stats = a.pre_gn && a.gap && a.ce && !a.post_gn && !a.add && c->kernel_set == 0 && s > 0 && a.Cin / a.G <= GAP_STATS_CPG;
+    if (gap_stats) {
+      StepDesc d = blank(K_GAP_STATS, s, t_f);
+      d.C = a.Cin; d.H = a.Hin; d.W = a.Win; d.G = a.G;
+      d.x = x_f; d.st = ring(c, b.prest, D + 1, b.st_stride, 0);
+      d.y = ring(c, b.pooled, D + 1, a.C, 0);
+      d.dx = ring(c, b.gapunit, D + 1, 2 * a.C, 0);
+      d.gamma = wf + a.o_gamma; d.beta = wf + a.o_beta;
+      fwd_params(d, PF_GAMMA | PF_BETA);
+      if (a.pre_relu) d.flags |= F_PRE_RELU;
+      d.ntiles = a.G;
+      out.push_back({ph++, d});
+    }
+    const bool two_step = !gn_bwd_fits(a.Cin, a.Hin * a.Win, a.G);   // (the one-step GroupNorm backward forms the channels' sums itself)
+    auto channel_sums = [&](StepDesc& d) {
+      d.n = a.Hin * a.Win;
+      d.skg = ring(c, b.gapunit, D + 1, 2 * a.C, D);
+      d.gamma = wbk + a.o_gamma;
+      d.ggamma = gr + a.o_gamma; d.gbeta = gr + a.o_beta;
+      d.part = c->f(b.part);
+    };
+    // (Beyond its limits the dense layer's weights are worth more than one workgroup's bandwidth, and networks tiled for
+    // throughput have steps for layers of 256 inputs and more that deal them out.)
+    if (gap_stats && !(g_tile_budget_us > 0 && a.C >= 256) && a.C % 4 == 0 && a.C <= 4 * BLK && (int64_t)a.K * a.C <= HEAD_FC_W && arena_aligned16(c, wf + a.o_w) &&
+        arena_aligned16(c, wbk + a.o_w) && arena_aligned16(c, gr + a.o_w)) {
+      StepDesc d = blank(K_HEAD_FC, s, t_f);
+      d.C = a.Cin; d.H = a.Hin; d.W = a.Win; d.K = a.K; d.G = a.G;
+      d.n_stages = NS; d.loss_cap = c->loss_cap;
+      d.x = ring(c, b.pooled, D + 1, a.C, 0);
+      d.w = wf + a.o_w; d.wp = wbk + a.o_w; d.gw = gr + a.o_w;
+      if (a.has_bias) { d.flags |= F_BIAS; d.b = wf + a.o_b; d.gb = gr + a.o_b; }
+      d.gamma = wbk + a.o_gamma;
+      fwd_params(d, PF_W | (a.has_bias ? PF_B : 0) | (c->stash ? PF_WP | PF_GAMMA : 0));
+      if (two_step) channel_sums(d);
+      d.dx = ring(c, b.da, 1, a.C, 0);
+      d.loss_log = c->f(L.loss);
+      d.labels = c->labels_dev;
+      d.ntiles = 1;
+      out.push_back({ph++, d});
+      int pb = ph;
+      bwd0[s] = pb;
+      gn_backward(pb, two_step);
+      continue;
+    }
+    if (gap_stats) {
+    } else if (a.pre_gn) {
       StepDesc d = blank(K_GN_STATS, s, t_f);
       d.C = a.Cin; d.H = a.Hin; d.W = a.Win; d.G = a.G;
       d.x = x_f; d.st = ring(c, b.prest, D + 1, b.st_stride, 0);
@@ -1492,14 +1598,13 @@ void compile_steps_once(pb_ctx* c, std::vector<std::pair<int, StepDesc>>& out) {
       gn_stats_wave(c, d);
       out.push_back({ph++, d});
     }
-    if (a.gap) {
+    if (a.gap && !gap_stats) {
       StepDesc d = blank(K_GAP_FWD, s, t_f);
       d.C = a.Cin; d.H = a.Hin; d.W = a.Win; d.G = a.G;
       d.flags = F_PRE_AFFINE | (a.pre_relu ? F_PRE_RELU : 0);
       d.x = x_f; d.st = ring(c, b.prest, D + 1, b.st_stride, 0);
       d.y = ring(c, b.pooled, D + 1, a.C, 0);
       d.ntiles = a.Cin;
-      if (g_tile_budget_us > 0 && a.Hin * a.Win <= 64) { d.grain = 1; d.ntiles = cdiv(a.Cin, GAP_WAVE_CH * (BLK / 64)); }
       out.push_back({ph++, d});
     }
     {
@@ -1799,6 +1904,11 @@ void compile_steps_once(pb_ctx* c, std::vector<std::pair<int, StepDesc>>& out) {
       if (fc_layer(c, d, d.w) && !(d.flags & (F_MASK_X | F_ADD_SKG)) && ref_vec4(c, d.dx)) {
         d.kind = K_FC_BWD_X;
         d.ntiles = cdiv(d.C, FC_BX);
+        if (gap_stats && two_step) {
+          channel_sums(d);
+          if (c->stash) d.pmask |= PF_GAMMA;
+          gap_summed = true;
+        }
         if (fc_upd && d.dy.base == dy_src.base) {   // in the phase of K_CE, from the logits
           d.flags |= F_CE_DY;
           d.dy = ring(c, b.logits, 1, a.K, 0);
@@ -1890,64 +2000,7 @@ void compile_steps_once(pb_ctx* c, std::vector<std::pair<int, StepDesc>>& out) {
       }
     }
     ++pb;
-    if (a.pre_gn) {
-      StepDesc d = blank(K_GNB_REDUCE, s, t_b);
-      d.C = a.Cin; d.H = a.Hin; d.W = a.Win; d.G = a.G;
-      d.flags = (a.pre_relu ? F_GN_RELU : 0) | (a.gap ? F_DU_GAP : F_DU_BUF);
-      d.x = x_b;
-      d.st = ring(c, b.prest, D + 1, b.st_stride, D);
-      d.dy = ring(c, b.da, 1, a.gap ? a.C : a.in_elems(), 0);
-      d.gamma = wbk + a.o_gamma;
-      bwd_params(d, PF_GAMMA);
-      d.ggamma = gr + a.o_gamma; d.gbeta = gr + a.o_beta;
-      d.part = c->f(b.part);
-      if (c->kernel_set == 0 && gn_bwd_fits(d.C, d.H * d.W, d.G)) {
-        d.kind = K_GN_BWD;
-        if (c->bf16) d.flags |= F_BF16_OUT;
-        if (s > 0) {
-          d.dx = ring(c, L.sb[s - 1].gradbox, 2, a.in_elems(), ML);
-          if (a.tap_dist) { d.flags |= F_ADD_SKG; d.skg = ring(c, b.skg, a.tap_dist + 1, a.in_elems(), TL(a.tap_dist)); }
-        }
-        // this step ends the stage's backward chain and is the only producer of the scale / shift
-        // gradients: it updates those two tensors itself, so that the rest of the stage can be
-        // updated one phase earlier and no phase is left that holds nothing but updates
-        // (with weight stashing the step's ring fields address the version whose scale it reads: it works out the slot of the
-        // version it writes by itself.  ResNet-20, us per tick, with these updates a launch of their own and here: four samples
-        // per update 37.8 and 23.5, stashing 30.6 and 23.5, both 38.2 and 23.7)
-        d.flags |= F_UPD_GN | F_ALWAYS | (c->stash || c->N > 1 ? F_UPD_GEN : 0);
-        set_update_coeffs(c, a, &d);
-        d.v = c->f(L.v + a.off + a.o_gamma);
-        d.w = wb + a.o_gamma;                       // master scale and shift, updated in place
-        d.b = d.v;
-        d.what0 = c->f(L.what[s] + a.o_gamma);
-        d.what = c->f(L.what[s] + a.o_gamma);
-        if (!c->stash) writes_what(d);
-        if (c->N > 1) {
-          d.upd_n = c->N;
-          d.upd_t0 = seq ? 0 : 2 * (S - 1) - s;
-          d.gacc = c->f(L.gacc + a.off + a.o_gamma);
-        }
-        d.ntiles = a.G;
-        gn_bwd_wave(c, d);
-        out.push_back({pb++, d});
-      } else {
-        d.ntiles = a.Cin;
-        const StepDesc d_plain = d;
-        wave_reduce(d);
-        if (d.grain == 0 && wave4_fits(c, d)) { d.grain = 2; d.ntiles = cdiv(d.C, BLK / 64); }
-        out.push_back({pb++, d});
-        if (s > 0) {
-          StepDesc e = d_plain;
-          e.kind = K_GNB_APPLY;
-          if (c->bf16) e.flags |= F_BF16_OUT;
-          e.dx = ring(c, L.sb[s - 1].gradbox, 2, a.in_elems(), ML);
-          if (a.tap_dist) { e.flags |= F_ADD_SKG; e.skg = ring(c, b.skg, a.tap_dist + 1, a.in_elems(), TL(a.tap_dist)); }
-          e.ntiles = cdiv(a.in_elems(), BLK);
-          stream_apply(c, e);
-          out.push_back({pb++, e});
-        }
-      }
-    }
+    if (a.pre_gn) gn_backward(pb, gap_summed);
   }
   // Sample-indexed form: the chains run one after the other -- forward of stage 0, 1, ..., then backward
   // of the last stage down to stage 0 -- instead of side by side.
@@ -2007,7 +2060,7 @@ void compile_steps_once(pb_ctx* c, std::vector<std::pair<int, StepDesc>>& out) {
       if (e.kind == K_GN_BWD && (e.flags & F_UPD_GN)) { gn_fused = true; continue; }
       if (e.flags & F_UPD_W) continue;
       const bool writes_grad = (e.kind == K_GEMM && e.g.gm == 3) || e.kind == K_CONV_BWD_W || e.kind == K_BIAS_GRAD ||
-                               e.kind == K_GNB_REDUCE || e.kind == K_GN_BWD || e.kind == K_HEAD || (e.kind == K_CE && e.gb);
+                               e.kind == K_GNB_REDUCE || e.kind == K_GN_BWD || e.kind == K_HEAD || e.kind == K_HEAD_FC || (e.kind == K_FC_BWD_X && e.part) || (e.kind == K_CE && e.gb);
       if (writes_grad) last_grad_phase = std::max(last_grad_phase, pr.first);
       if (e.kind == K_GEMM && e.g.gm == 3) gparts = std::max(gparts, e.g.parts);
     }
@@ -2109,8 +2162,10 @@ void order_steps(std::vector<std::pair<int, StepDesc>>& tagged, bool one_launch 
         us = 4.0 + (d.grain > 0 ? 1.0 : (double)d.H * d.W / BLK * ((d.flags & F_DU_POOL) ? (d.dx.base ? 0.3 : in_lds ? 2.0 : 7.0) : 0.05));
       } else if (d.kind == K_DOT_FWD || d.kind == K_DOT_BWD_X) {
         us = 8.0;
-      } else if (d.kind == K_FC_BWD_X) {
+      } else if (d.kind == K_FC_FWD || d.kind == K_FC_BWD_X || d.kind == K_HEAD_FC) {
         us = 8.0;
+      } else if (d.kind == K_GAP_STATS) {
+        us = 6.0 + (double)(d.C / std::max(1, d.G)) * d.H * d.W / BLK * 0.1;
       } else if (d.kind == K_UPDATE) {
         us = 15.0;
       } else if (d.kind == K_POST_FWD || d.kind == K_GNB_APPLY) {
@@ -2136,7 +2191,7 @@ void order_steps(std::vector<std::pair<int, StepDesc>>& tagged, bool one_launch 
   // sent to; the surplus itself is the cheapest GEMM tiles, the longer of them first.
   auto rank = [](const StepDesc& d) {
     if (g_tile_budget_us > 0) return d.kind == K_HEAD ? 0 : 1;
-    if (d.kind == K_HEAD) return 1;
+    if (d.kind == K_HEAD || d.kind == K_GAP_STATS || d.kind == K_HEAD_FC) return 1;
     return (d.kind == K_GEMM || d.kind == K_GN_BWD) ? 2 : 0;
   };
   // One launch per tick: the workgroups of a later phase take their places while the first phase still runs
@@ -2224,8 +2279,21 @@ int validate_steps(const pb_ctx* c, const std::vector<std::pair<int, StepDesc>>&
         ok = ok && d.G > 0 && d.C % d.G == 0 && ref_ok(d.x, in) && ref_ok(d.st, stn) &&
              ptr_ok(d.gamma, d.C) && ptr_ok(d.beta, d.C) && (!d.y.base || ref_ok(d.y, in));
         break;
+      case K_GAP_STATS:
+        ok = ok && d.G > 0 && d.C % d.G == 0 && d.ntiles == d.G && d.C / d.G <= GAP_STATS_CPG && ref_ok(d.x, in) && ref_ok(d.st, stn) &&
+             ref_ok(d.y, d.C) && ref_ok(d.dx, 2 * d.C) && ptr_ok(d.gamma, d.C) && ptr_ok(d.beta, d.C);
+        static_assert(2 * GAP_STATS_CPG <= LDS_FLOATS, "a group's scales and shifts in LDS");
+        break;
+      case K_HEAD_FC:
+        ok = ok && d.ntiles == 1 && d.K > 0 && d.C % 4 == 0 && d.C <= 4 * BLK && (int64_t)d.K * d.C <= HEAD_FC_W && d.n_stages > 0 && ref_ok(d.x, d.C) && ref_vec4(c, d.x) &&
+             ref_ok(d.dx, d.C) && ptr_ok(d.w, (int64_t)d.K * d.C) && ptr_ok(d.wp, (int64_t)d.K * d.C) && ptr_ok(d.gw, (int64_t)d.K * d.C) &&
+             arena_aligned16(c, d.w) && arena_aligned16(c, d.wp) && arena_aligned16(c, d.gw) && d.pstride % 4 == 0 &&
+             ptr_ok(d.loss_log, d.loss_cap) && ptr_ok((const float*)d.labels, d.n_stages) && (!(d.flags & F_BIAS) || (ptr_ok(d.b, d.K) && ptr_ok(d.gb, d.K))) &&
+             (!d.part || (d.n > 0 && ref_ok(d.skg, 2 * d.C) && ptr_ok(d.part, 3 * d.C) && ptr_ok(d.gamma, d.C) && ptr_ok(d.ggamma, d.C) && ptr_ok(d.gbeta, d.C)));
+        static_assert(HEAD_FC_W / 4 + HEAD_FC_W / 4 + 4 <= LDS_FLOATS && HEAD_FC_W / 4 + 4 + 4 * BLK <= LDS_FLOATS, "logits and a product per weight vector, or sums per row of threads, in LDS");
+        break;
       case K_GAP_FWD:
-        ok = ok && d.ntiles == (d.grain == 1 ? cdiv(d.C, GAP_WAVE_CH * (BLK / 64)) : d.C) && (d.grain != 1 || d.H * d.W <= 64) && ref_ok(d.x, in) && ref_ok(d.y, d.C) &&
+        ok = ok && d.ntiles == d.C && ref_ok(d.x, in) && ref_ok(d.y, d.C) &&
              (!(d.flags & F_PRE_AFFINE) || ref_ok(d.st, stn));
         break;
       case K_CONV_FWD:
@@ -2354,7 +2422,8 @@ int validate_steps(const pb_ctx* c, const std::vector<std::pair<int, StepDesc>>&
       case K_FC_BWD_X:
         ok = ok && !c->nt_stores && fc_layer(c, d, d.w) && !(d.flags & ~(F_ALWAYS | F_BF16_OUT | F_CE_DY)) && d.ntiles == cdiv(d.C, FC_BX) &&
              (!(d.flags & F_CE_DY) || (d.n_stages > 0 && ptr_ok((const float*)d.labels, d.n_stages))) &&
-             (d.K + 3) / 4 * 4 + 64 * FC_BX <= LDS_FLOATS && ref_ok(d.dy, d.K) && ref_ok(d.dx, d.C) && ptr_ok(d.w, (int64_t)d.K * d.C);
+             (d.K + 3) / 4 * 4 + 64 * FC_BX <= LDS_FLOATS && ref_ok(d.dy, d.K) && ref_ok(d.dx, d.C) &&
+             (!d.part || (d.n > 0 && ref_ok(d.skg, 2 * d.C) && ptr_ok(d.part, 3 * d.C) && ptr_ok(d.gamma, d.C) && ptr_ok(d.ggamma, d.C) && ptr_ok(d.gbeta, d.C))) && ptr_ok(d.w, (int64_t)d.K * d.C);
         break;
       case K_FC_BWD_W:
         ok = ok && !c->nt_stores && fc_layer(c, d, d.gw) && !(d.flags & ~(F_ALWAYS | F_UPD_W | F_LWP_W)) && d.ntiles == cdiv((int64_t)d.K * d.C, 4096) &&
@@ -3043,7 +3112,7 @@ int64_t plan_summary(const pb_net_desc* net, char* buf, int64_t cap) {
   compile_steps(&tmp, steps);
   order_steps(steps);
   static const char* names[] = {"gn_stats", "gap_fwd", "conv_fwd", "post_fwd", "ce", "gnb_reduce", "gnb_apply",
-                                "conv_bwd_x", "conv_bwd_w", "copy", "gemm", "bias_grad", "ingest", "update", "head", "gn_bwd", "dot_fwd", "dot_bwd_x", "fc_fwd", "fc_bwd_x", "fc_bwd_w"};
+                                "conv_bwd_x", "conv_bwd_w", "copy", "gemm", "bias_grad", "ingest", "update", "head", "gn_bwd", "dot_fwd", "dot_bwd_x", "fc_fwd", "fc_bwd_x", "fc_bwd_w", "gap_stats", "head_fc"};
   std::string o;
   char line[400];
   for (auto& pr : steps) {

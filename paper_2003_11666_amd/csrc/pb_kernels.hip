@@ -122,6 +122,39 @@ __device__ __forceinline__ T sum_parts(const P* p, size_t stride, int parts) {
   return a;
 }
 
+// A workgroup's walk over n floats that may start anywhere, four at a time and eight vectors of a thread in flight: f(i, v) for
+// every multiple of 4 below n; elements past the end are zero.  From memory, or from LDS where an earlier walk left them.
+template <class F>
+__device__ __forceinline__ void each_vec(const gfloat* xp, const lfloat* xs, int n, bool from_lds, F f) {
+  const int tid = threadIdx.x;
+  constexpr int U = 8;
+  for (int i0 = 4 * tid; i0 < n; i0 += 4 * U * BLK) {
+    v4f v[U];
+#pragma unroll
+    for (int u = 0; u < U; ++u) {
+      const int i = i0 + 4 * u * BLK;
+      v[u] = (v4f){0.f, 0.f, 0.f, 0.f};
+      if (from_lds) {
+        if (i < n) v[u] = *(const lv4*)(xs + i);
+      } else if (i + 3 < n) {
+        v[u] = *(const gv4u*)(xp + i);
+      }
+    }
+    const int il = n & ~3;                           // the last vector, if it is not whole
+    if (!from_lds && il < n && il >= i0 && (il - i0) % (4 * BLK) == 0 && il < i0 + 4 * U * BLK) {
+      const int ul = (il - i0) / (4 * BLK);
+      const v4f x = {xp[il], il + 1 < n ? xp[il + 1] : 0.f, il + 2 < n ? xp[il + 2] : 0.f, 0.f};
+#pragma unroll
+      for (int u = 0; u < U; ++u) v[u] = u == ul ? x : v[u];
+    }
+#pragma unroll
+    for (int u = 0; u < U; ++u) {
+      const int i = i0 + 4 * u * BLK;
+      if (i < n) f(i, v[u]);
+    }
+  }
+}
+
 // ------------------------------------------------------------ forward steps
 // GroupNorm statistics of one group (biased variance, two passes) and the
 // folded per-channel scale/shift built from the forward (predicted) affine
@@ -226,34 +259,7 @@ __device__ __forceinline__ void step_gn_stats(const LDesc& d, int tile, int t, l
   // the first: 17 298 elements (36 channels of 31x31, two groups) read an element at a time in three passes over memory took
   // 45.5 us, the end of a launch whose longest tile ends at 30: a network of eight stages of that map 109.1 us per tick, 87.6 now.
   const bool stash = (n + 3) / 4 * 4 <= LDS_FLOATS;
-  auto each = [&](bool first, auto f) {
-    constexpr int U = 8;
-    for (int i0 = 4 * tid; i0 < n; i0 += 4 * U * BLK) {
-      v4f v[U];
-#pragma unroll
-      for (int u = 0; u < U; ++u) {
-        const int i = i0 + 4 * u * BLK;
-        v[u] = (v4f){0.f, 0.f, 0.f, 0.f};
-        if (!first && stash) {
-          if (i < n) v[u] = *(const lv4*)(smem + i);
-        } else if (i + 3 < n) {
-          v[u] = *(const gv4u*)(xp + i);
-        }
-      }
-      const int il = n & ~3;                         // the last vector, if it is not whole
-      if ((first || !stash) && il < n && il >= i0 && (il - i0) % (4 * BLK) == 0 && il < i0 + 4 * U * BLK) {
-        const int ul = (il - i0) / (4 * BLK);
-        const v4f x = {xp[il], il + 1 < n ? xp[il + 1] : 0.f, il + 2 < n ? xp[il + 2] : 0.f, 0.f};
-#pragma unroll
-        for (int u = 0; u < U; ++u) v[u] = u == ul ? x : v[u];
-      }
-#pragma unroll
-      for (int u = 0; u < U; ++u) {
-        const int i = i0 + 4 * u * BLK;
-        if (i < n) f(i, v[u]);
-      }
-    }
-  };
+  auto each = [&](bool first, auto f) { each_vec(xp, smem, n, !first && stash, f); };
   float s = 0.f;
   each(true, [&](int i, v4f v) {
     s += (v[0] + v[1]) + (v[2] + v[3]);
@@ -372,32 +378,93 @@ __device__ __forceinline__ void step_gn_stats_wave(const LDesc& d, int tile, int
   }
 }
 
-// pooled[c] = mean_hw relu(sc*x+sh)
-// grain = 1 (small maps): a wavefront per channel, GAP_WAVE_CH channels per wavefront with their loads in flight together.
-__device__ __forceinline__ void step_gap_fwd(const LDesc& d, int tile, int t, lfloat* red) {
-  if (UNI(d.grain) == 1) {
-    const int lane = threadIdx.x & 63, c0 = (tile * (BLK / 64) + UNI((int)(threadIdx.x >> 6))) * GAP_WAVE_CH;
-    const int C = UNI(d.C), G = UNI(d.G), HW = UNI(d.H) * UNI(d.W);
-    const bool aff = UNI(d.flags) & F_PRE_AFFINE, rl = UNI(d.flags) & F_PRE_RELU;
-    const gfloat* x = at(d.x, t);
-    const gfloat* st = aff ? (const gfloat*)at(d.st, t) : x;
-    float v[GAP_WAVE_CH], sc[GAP_WAVE_CH], sh[GAP_WAVE_CH];
+// Statistics of one group of a layer that ends in a global average pool, and the pool: the pooled channels, and for the
+// backward pass what a channel's sums come to per unit of its pooled gradient -- how many elements the ReLU lets through, and
+// the sum of their normalised values (d.dx: [C] each) -- so that nothing reads the map again before the elementwise pass.
+// Bound by one burst of reads and the sums; as two steps, and the channel sums a third, each was a launch of 3 to 5 us and the
+// gap between launches in the chain that ends a tick.  With the dense layer's part of the chain (step_head_fc) in one workgroup
+// a tick is three launches in place of six or seven, us: basic networks of 12 and 24 channels at 12 pixels 32.1 and 19.8, of 40
+// channels at 32 70.2 and 46.0, of 48 and 96 at 39 129.5 and 85.7.
+// LDS: gamma[cpg] | beta[cpg] | the group, where it fits.
+__device__ __forceinline__ void step_gap_stats(const LDesc& d, int tile, int t, lfloat* red, lfloat* smem) {
+  const int tid = threadIdx.x, lane = tid & 63, wv = UNI(tid >> 6);
+  const int C = UNI(d.C), G = UNI(d.G), HW = UNI(d.H) * UNI(d.W);
+  const int g = tile, cpg = UNI(fdiv(C, frcp(G))), n = cpg * HW;
+  const gfloat* xp = at(d.x, t) + (size_t)g * n;
+  gfloat* st = at(d.st, t);
+  gfloat* y = at(d.y, t) + g * cpg;
+  gfloat* unit = at(d.dx, t) + g * cpg;
+  const bool rl = UNI(d.flags) & F_PRE_RELU;
+  lfloat* gl = smem;
+  lfloat* bl = gl + cpg;
+  lfloat* xs = smem + (2 * cpg + 3) / 4 * 4;
+  const bool stash = (2 * cpg + 3) / 4 * 4 + (n + 3) / 4 * 4 <= LDS_FLOATS;
+  for (int c = tid; c < cpg; c += BLK) { gl[c] = GP(d.gamma)[g * cpg + c]; bl[c] = GP(d.beta)[g * cpg + c]; }
+  float s = 0.f;
+  each_vec(xp, xs, n, false, [&](int i, v4f v) {
+    s += (v[0] + v[1]) + (v[2] + v[3]);
+    if (stash) *(lv4*)(xs + i) = v;
+  });
+  const float mean = block_sum(s, red) / (float)n;
+  float q = 0.f;
+  each_vec(xp, xs, n, stash, [&](int i, v4f v) {
 #pragma unroll
-    for (int q = 0; q < GAP_WAVE_CH; ++q) {
-      const int c = c0 + q < C ? c0 + q : C - 1;
-      v[q] = x[(size_t)c * HW + (lane < HW ? lane : 0)];
-      sc[q] = aff ? st[2 * G + c] : 1.f;
-      sh[q] = aff ? st[2 * G + C + c] : 0.f;
+    for (int e = 0; e < 4; ++e) {
+      const float dl = i + e < n ? v[e] - mean : 0.f;
+      q = fmaf(dl, dl, q);
     }
-#pragma unroll
-    for (int q = 0; q < GAP_WAVE_CH; ++q) {
-      float r = fmaf(sc[q], v[q], sh[q]);
-      if (rl) r = fmaxf(r, 0.f);
-      r = wave_sum(lane < HW ? r : 0.f);
-      if (lane == 0 && c0 + q < C) at(d.y, t)[c0 + q] = r / (float)HW;
+  });
+  const float var = block_sum(q, red) / (float)n;
+  const float rstd = 1.0f / sqrtf(var + GN_EPS);
+  if (tid == 0) { st[g] = mean; st[G + g] = rstd; }
+  // a wavefront per channel, or 16 lanes where a channel has fewer than 64 elements
+  const bool wide = HW >= 64;
+  const int step = wide ? 64 : 16, l = wide ? lane : tid & 15;
+  for (int c = wide ? wv : tid >> 4; c < cpg; c += wide ? BLK / 64 : BLK / 16) {
+    const float sc = gl[c] * rstd, sh = fmaf(-mean, sc, bl[c]);
+    float sy = 0.f, sn = 0.f, sx = 0.f;
+    auto add = [&](float v) {
+      const float yv = fmaf(sc, v, sh);
+      const bool on = !rl || yv > 0.f;
+      sy += on ? yv : 0.f;
+      sn += on ? 1.f : 0.f;
+      sx += on ? (v - mean) * rstd : 0.f;
+    };
+    if (stash) {
+#pragma unroll 4
+      for (int i = l; i < HW; i += step) add(xs[c * HW + i]);
+    } else {
+#pragma unroll 8
+      for (int i = l; i < HW; i += step) add(xp[(size_t)c * HW + i]);
     }
-    return;
+    if (wide) { sy = wave_sum(sy); sn = wave_sum(sn); sx = wave_sum(sx); }
+    else { sy = row_sum(sy); sn = row_sum(sn); sx = row_sum(sx); }
+    if (l == 0) {
+      const int ch = g * cpg + c;
+      st[2 * G + ch] = sc;
+      st[2 * G + C + ch] = sh;
+      y[c] = sy / (float)HW;
+      unit[c] = sn;
+      unit[C + c] = sx;
+    }
   }
+}
+
+// What the GroupNorm backward pass needs of channel c, under a global average pool of gradient p: its scale's and shift's
+// gradients and the sums of its group (d.n: elements of a channel; d.skg: see step_gap_stats).
+__device__ __forceinline__ void gap_channel_sums(const LDesc& d, int t, int c, float p) {
+  const int C = UNI(d.C);
+  const gfloat* unit = at(d.skg, t);
+  const float du = p / (float)UNI(d.n), sb = du * unit[c], sg = du * unit[C + c], gm = GP(d.gamma)[c];
+  GP(d.ggamma)[c] = sg;
+  GP(d.gbeta)[c] = sb;
+  GP(d.part)[c] = gm * sb;
+  GP(d.part)[C + c] = gm * sg;
+  GP(d.part)[2 * C + c] = gm;
+}
+
+// pooled[c] = mean_hw relu(sc*x+sh)  (the plain kernels, and groups of more channels than step_gap_stats takes)
+__device__ __forceinline__ void step_gap_fwd(const LDesc& d, int tile, int t, lfloat* red) {
   const int c = tile, HW = d.H * d.W;
   const gfloat* xp = at(d.x, t) + (size_t)c * HW;
   const bool aff = d.flags & F_PRE_AFFINE, rl = d.flags & F_PRE_RELU;
@@ -1895,6 +1962,7 @@ __device__ __forceinline__ void step_fc_bwd_x(const LDesc& d, int tile, int t, l
 #pragma unroll 16
     for (int q = 0; q < 64; ++q) s += part[q * FC_BX + tid];
     at(d.dx, t)[tile * FC_BX + tid] = rbf_if(UNI(d.flags) & F_BF16_OUT, s);
+    if (d.part) gap_channel_sums(d, t, tile * FC_BX + tid, s);
   }
 }
 
@@ -2638,6 +2706,84 @@ __device__ __forceinline__ void step_head(const LDesc& d, int t, lfloat* red, lf
   }
 }
 
+// The dense layer behind a global average pool, the loss, and the backward pass of both, in one workgroup (at most
+// HEAD_FC_W weights): thread (r, c4) of R rows of C / 4 threads takes inputs 4 c4 .. + 3 of the outputs r, r + R, ..., 16 weight
+// vectors in flight.  Bound by the two passes over the weights (6 to 9 us); as four steps -- product, loss, backward products,
+// channel sums -- it was four launches of 2 to 8 us each, with next to nothing beside them, at the end of a tick.
+// LDS: logits, then their gradient [K] | products of a row's vectors [K][C / 4], then sums of the inputs' gradients [R][C].
+__device__ __forceinline__ void step_head_fc(const LDesc& d, int t, lfloat* red, lfloat* smem) {
+  const int tid = threadIdx.x;
+  const int C = UNI(d.C), K = UNI(d.K), C4 = C >> 2, R = UNI(fdiv(BLK, frcp(C4))), flags = UNI(d.flags);
+  const int r = fdiv(tid, frcp(C4)), c4 = tid - r * C4;
+  const bool act = r < R;
+  const int sample = t - (UNI(d.n_stages) - 1);
+  const int label = ((const gint*)d.labels)[sample % UNI(d.n_stages)];
+  lfloat* dl = smem;
+  lfloat* ps = smem + (K + 3) / 4 * 4;
+  constexpr int U = 16;
+  const v4f xv = act ? *(const gv4*)(at(d.x, t) + 4 * c4) : (v4f){0.f, 0.f, 0.f, 0.f};
+  v4f w[U];
+  auto fetch = [&](const float* base, int k0) {
+#pragma unroll
+    for (int u = 0; u < U; ++u) {
+      const int k = k0 + R * u;
+      w[u] = *(const gv4*)(GP(base) + (unsigned)((act && k < K ? k : 0) * C + 4 * (act ? c4 : 0)));
+    }
+  };
+  for (int k0 = r; k0 < K; k0 += U * R) {
+    fetch(d.w, k0);
+#pragma unroll
+    for (int u = 0; u < U; ++u) {
+      const int k = k0 + R * u;
+      if (act && k < K) ps[k * C4 + c4] = fmaf(w[u][3], xv[3], fmaf(w[u][2], xv[2], fmaf(w[u][1], xv[1], w[u][0] * xv[0])));
+    }
+  }
+  fetch(d.wp, r);                                    // backward (current) weights: under way beside the loss
+  __syncthreads();
+  for (int k = tid >> 4; k < K; k += BLK / 16) {
+    float s = 0.f;
+    for (int i = tid & 15; i < C4; i += 16) s += ps[k * C4 + i];
+    s = row_sum(s);
+    if ((tid & 15) == 0) dl[k] = s + ((flags & F_BIAS) ? GP(d.b)[k] : 0.f);
+  }
+  __syncthreads();
+  float mx = -3.0e38f;
+  for (int k = tid; k < K; k += BLK) mx = fmaxf(mx, dl[k]);
+  mx = block_max(mx, red);
+  float sm = 0.f;
+  for (int k = tid; k < K; k += BLK) sm += expf(dl[k] - mx);
+  sm = block_sum(sm, red);
+  for (int k = tid; k < K; k += BLK) {               // (a thread reads and writes its own entries only)
+    const float z = dl[k], e = expf(z - mx) / sm - (k == label ? 1.f : 0.f);
+    if (k == label) GP(d.loss_log)[sample % UNI(d.loss_cap)] = logf(sm) + mx - z;
+    dl[k] = e;
+    if (flags & F_BIAS) GP(d.gb)[k] = e;
+  }
+  __syncthreads();
+  v4f acc = (v4f){0.f, 0.f, 0.f, 0.f};
+  for (int k0 = r; k0 < K; k0 += U * R) {
+    if (k0 > r) fetch(d.wp, k0);
+#pragma unroll
+    for (int u = 0; u < U; ++u) {
+      const int k = k0 + R * u;
+      if (act && k < K) {
+        const float e = dl[k];
+#pragma unroll
+        for (int j = 0; j < 4; ++j) acc[j] = fmaf(w[u][j], e, acc[j]);
+        *(gv4*)(GP(d.gw) + (unsigned)(k * C + 4 * c4)) = (v4f){e * xv[0], e * xv[1], e * xv[2], e * xv[3]};
+      }
+    }
+  }
+  if (act) *(lv4*)(ps + r * C + 4 * c4) = acc;
+  __syncthreads();
+  for (int c = tid; c < C; c += BLK) {
+    float s = 0.f;
+    for (int q = 0; q < R; ++q) s += ps[q * C + c];
+    at(d.dx, t)[c] = s;
+    if (d.part) gap_channel_sums(d, t, c, s);
+  }
+}
+
 // ------------------------------------------------------------------ kernels
 // One workgroup = one tile of one step.  recs[] holds, per workgroup of the
 // phase, a full copy of its step descriptor with the tile index filled in, so
@@ -2749,6 +2895,8 @@ k_phase(const StepDesc* __restrict__ recs, const Globals* __restrict__ G, int k,
     case K_INGEST: step_ingest(d, tile, t, G, k, sample_override, label_override); break;
     case K_UPDATE: step_update(d, tile, t, smem, NT); break;
     case K_HEAD: step_head(d, t, red, smem, NT); break;
+    case K_GAP_STATS: step_gap_stats(d, tile, t, red, smem); break;
+    case K_HEAD_FC: step_head_fc(d, t, red, smem); break;
     case K_GN_BWD:
       if (!NT && UNI(d.grain) == 1) step_gn_bwd_wave(d, tile, t, live, smem); else step_gn_bwd(d, tile, t, live, smem, NT);
       break;
