@@ -17,6 +17,7 @@ constexpr int GAP_STATS_CPG = 4096; // channels per group of a K_GAP_STATS step
 constexpr int GNB_WAVE_CH = 4;    // channels per wavefront in the one-wavefront-per-channel form of K_GNB_REDUCE
 constexpr int GNB_WAVE_HW = 256;  // ... whose maps have at most this many pixels
 constexpr int GNB_WAVE4_HW = 1020; // ... or at most this many, with 16-byte requests (grain 2)
+constexpr int GNB_WAVE4_MAX_HW = 4096; // ... where channels are many
 constexpr int FC_BX = 16;         // inputs per workgroup of K_FC_BWD_X
 
 // A tensor that lives in a ring of `depth` slots.  At tick t the slot in use

@@ -1194,8 +1194,16 @@ void stream_apply(const pb_ctx* c, StepDesc& e) {
       !ref_vec4(c, e.dx) || ((e.flags & F_ADD_SKG) && !ref_vec4(c, e.skg)))
     return;
   const int64_t gsz = (int64_t)(e.C / e.G) * HW;
-  e.grain = STREAM_GRAIN;
-  e.n = cdiv(gsz, e.grain);
+  // up to four rounds per workgroup where the tick's passes of this kind are more than the chip has places for (ResNet-50 at
+  // 224 pixels: 3482 workgroups of one round, and a wavefront in place of a workgroup for the sums of 1344 channels, 439.4 us per
+  // tick; 1500 of up to four 434.0)
+  int64_t all = 0;
+  for (const Stage& a : c->st)
+    if (a.pre_gn && !gn_bwd_fits(a.Cin, a.Hin * a.Win, a.G)) all += a.in_elems();
+  const int64_t rounds = std::max<int64_t>(1, std::min<int64_t>(4, all / (768 * STREAM_GRAIN)));
+  e.n = cdiv(gsz, rounds * STREAM_GRAIN);
+  e.grain = cdiv(cdiv(gsz, e.n), 4 * BLK) * 4 * BLK;
+  if (rounds == 1) { e.grain = STREAM_GRAIN; e.n = cdiv(gsz, e.grain); }
   e.ntiles = e.G * e.n;
 }
 
@@ -1240,7 +1248,10 @@ void wave_reduce(StepDesc& d) {
 // The same with 16-byte requests, for maps beyond that (see step_gnb_reduce_wave4).
 bool wave4_fits(const pb_ctx* c, const StepDesc& d) {
   const int HW = d.H * d.W;
-  return g_tile_budget_us > 0 && (d.flags & F_DU_BUF) && HW > GNB_WAVE_HW && HW <= GNB_WAVE4_HW && HW % 4 == 0 && ref_vec4(c, d.x) && ref_vec4(c, d.dy);
+  int64_t large = 0;   // channels of larger maps
+  for (const Stage& a : c->st)
+    if (a.pre_gn && a.Hin * a.Win > GNB_WAVE4_HW && a.Hin * a.Win <= GNB_WAVE4_MAX_HW) large += a.Cin;
+  return g_tile_budget_us > 0 && (d.flags & F_DU_BUF) && HW > GNB_WAVE_HW && HW <= (large > 1024 ? GNB_WAVE4_MAX_HW : GNB_WAVE4_HW) && HW % 4 == 0 && ref_vec4(c, d.x) && ref_vec4(c, d.dy);
 }
 
 // Whether a K_GNB_REDUCE step writes the gradient it routes back through a max-pool: the forms that search every window

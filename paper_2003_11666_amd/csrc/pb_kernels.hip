@@ -777,7 +777,7 @@ __device__ __forceinline__ void step_gnb_reduce_wave(const LDesc& d, int tile, i
 }
 
 // Maps of more than 256 and fewer than 1024 pixels (a multiple of 4) with a plain gradient buffer: one wavefront per
-// channel, the channel in four 16-byte requests per lane and operand, no barrier.  Bound by the memory round trip: a
+// channel, the channel in rounds of four 16-byte requests per lane and operand, no barrier.  Bound by the memory round trip: a
 // workgroup per channel holds a slot for 3.7 us with one request per lane.  Measured, us per tick with a workgroup per
 // channel and with a wavefront: ResNet-50 at 224 pixels (2816 channels of 28x28) 590.3 and 581.7; basic networks at 24, 28
 // and 40 pixels 87.3 and 86.8, 95.3 and 95.0, 133.8 and 134.3; a bottleneck network at 224 465.4 and 463.7.  At 1024 pixels,
@@ -791,27 +791,41 @@ __device__ __forceinline__ void step_gnb_reduce_wave4(const LDesc& d, int tile, 
   const gfloat* st = at(d.st, t);
   const gfloat* x = at(d.x, t) + (size_t)c * HW;
   const gfloat* dy = at(d.dy, t) + (size_t)c * HW;
-  constexpr int RU = (GNB_WAVE4_HW + 255) / 256;
-  v4f xv[RU], dv[RU];
+  constexpr int RU = 4, STEP = RU * 256;             // (a round: 1024 elements)
+  v4f xv[2][RU], dv[2][RU];
+  auto fetch = [&](auto B, int i0) {
+    constexpr int b = decltype(B)::value;
 #pragma unroll
-  for (int u = 0; u < RU; ++u) {
-    const int i = 4 * (lane + 64 * u);
-    xv[u] = (v4f){0.f, 0.f, 0.f, 0.f}; dv[u] = xv[u];
-    if (i < HW) { xv[u] = *(const gv4*)(x + i); dv[u] = *(const gv4*)(dy + i); }
-  }
+    for (int u = 0; u < RU; ++u) {
+      const int i = i0 + 4 * (lane + 64 * u);
+      xv[b][u] = (v4f){0.f, 0.f, 0.f, 0.f}; dv[b][u] = xv[b][u];
+      if (i < HW) { xv[b][u] = *(const gv4*)(x + i); dv[b][u] = *(const gv4*)(dy + i); }
+    }
+  };
+  fetch(IConst<0>(), 0);
   const int g = UNI(fdiv(c, frcp(UNI(fdiv(C, frcp(G))))));
   const float mean = st[g], rstd = st[G + g], sc = st[2 * G + c], sh = st[2 * G + C + c], gm = GP(d.gamma)[c];
   const bool rl = UNI(d.flags) & F_GN_RELU;
   float sg = 0.f, sb = 0.f;
+  auto add = [&](auto B, int i0) {
+    constexpr int b = decltype(B)::value;
 #pragma unroll
-  for (int u = 0; u < RU; ++u)     // (elements beyond the map: a gradient of zero)
+    for (int u = 0; u < RU; ++u)     // (elements beyond the map: a gradient of zero)
 #pragma unroll
-    for (int e = 0; e < 4; ++e) {
-      const float du = (rl && !(fmaf(sc, xv[u][e], sh) > 0.f)) ? 0.f : dv[u][e];
-      const float xh = (xv[u][e] - mean) * rstd;
-      sg = fmaf(du, 4 * (lane + 64 * u) < HW ? xh : 0.f, sg);
-      sb += du;
-    }
+      for (int e = 0; e < 4; ++e) {
+        const float du = (rl && !(fmaf(sc, xv[b][u][e], sh) > 0.f)) ? 0.f : dv[b][u][e];
+        const float xh = (xv[b][u][e] - mean) * rstd;
+        sg = fmaf(du, i0 + 4 * (lane + 64 * u) < HW ? xh : 0.f, sg);
+        sb += du;
+      }
+  };
+  for (int i0 = 0; i0 < HW; i0 += 2 * STEP) {
+    if (i0 + STEP < HW) fetch(IConst<1>(), i0 + STEP);
+    add(IConst<0>(), i0);
+    if (i0 + STEP >= HW) break;
+    if (i0 + 2 * STEP < HW) fetch(IConst<0>(), i0 + 2 * STEP);
+    add(IConst<1>(), i0 + STEP);
+  }
   sg = wave_sum(sg);
   sb = wave_sum(sb);
   if (lane == 0) {
@@ -959,6 +973,27 @@ __device__ __forceinline__ void step_gnb_apply_stream(const LDesc& d, int tile, 
   const gfloat* skg = (flags & F_ADD_SKG) ? (const gfloat*)at(d.skg, t) + gbase : nullptr;
   const gfloat* part = GP(d.part);
   const float ihw = frcp(HW);
+  constexpr int U = 4, STEP = U * 4 * BLK;
+  v4f xv[2][U], dv[2][U], sk[2][U];
+  float sc[2][U], sh[2][U], gm[2][U];
+  auto fetch = [&](auto B, int base) {
+    constexpr int b = decltype(B)::value;
+#pragma unroll
+    for (int u = 0; u < U; ++u) {
+      const int i = base + u * 4 * BLK;
+      xv[b][u] = (v4f){0.f, 0.f, 0.f, 0.f}; dv[b][u] = xv[b][u]; sk[b][u] = xv[b][u];
+      sc[b][u] = 0.f; sh[b][u] = 0.f; gm[b][u] = 0.f;
+      if (i < hi) {
+        const int c = g * cpg + fdiv(i, ihw);
+        xv[b][u] = *(const gv4*)(x + i);
+        dv[b][u] = *(const gv4*)(dy + i);
+        if (skg) sk[b][u] = *(const gv4*)(skg + i);
+        sc[b][u] = st[2 * G + c]; sh[b][u] = st[2 * G + C + c]; gm[b][u] = part[2 * C + c];
+      }
+    }
+  };
+  const int base0 = lo + tid * 4;
+  fetch(IConst<0>(), base0);
   // group sums of the per-channel partial sums (fixed order: lanes, then the wave
   // tree), taken while every lane is active
   float p1 = 0.f, p2 = 0.f;
@@ -966,23 +1001,8 @@ __device__ __forceinline__ void step_gnb_apply_stream(const LDesc& d, int tile, 
   const float mean = st[g], rstd = st[G + g];
   const float inv_n = 1.0f / (float)gsz;
   const float m1 = wave_sum(p1) * inv_n, m2 = wave_sum(p2) * inv_n;
-  constexpr int U = 4;
-  for (int base = lo + tid * 4; base < hi; base += U * 4 * BLK) {
-    v4f xv[U], dv[U], sk[U];
-    float sc[U], sh[U], gm[U];
-#pragma unroll
-    for (int u = 0; u < U; ++u) {
-      const int i = base + u * 4 * BLK;
-      xv[u] = (v4f){0.f, 0.f, 0.f, 0.f}; dv[u] = xv[u]; sk[u] = xv[u];
-      sc[u] = 0.f; sh[u] = 0.f; gm[u] = 0.f;
-      if (i < hi) {
-        const int c = g * cpg + fdiv(i, ihw);
-        xv[u] = *(const gv4*)(x + i);
-        dv[u] = *(const gv4*)(dy + i);
-        if (skg) sk[u] = *(const gv4*)(skg + i);
-        sc[u] = st[2 * G + c]; sh[u] = st[2 * G + C + c]; gm[u] = part[2 * C + c];
-      }
-    }
+  auto apply = [&](auto B, int base) {
+    constexpr int b = decltype(B)::value;
 #pragma unroll
     for (int u = 0; u < U; ++u) {
       const int i = base + u * 4 * BLK;
@@ -990,15 +1010,23 @@ __device__ __forceinline__ void step_gnb_apply_stream(const LDesc& d, int tile, 
         v4f r;
 #pragma unroll
         for (int e = 0; e < 4; ++e) {
-          const float yv = fmaf(sc[u], xv[u][e], sh[u]);
-          float du = dv[u][e];
+          const float yv = fmaf(sc[b][u], xv[b][u][e], sh[b][u]);
+          float du = dv[b][u][e];
           if ((flags & F_GN_RELU) && !(yv > 0.f)) du = 0.f;
-          const float xh = (xv[u][e] - mean) * rstd;
-          r[e] = rbf_if(flags & F_BF16_OUT, rstd * (du * gm[u] - m1 - xh * m2) + sk[u][e]);
+          const float xh = (xv[b][u][e] - mean) * rstd;
+          r[e] = rbf_if(flags & F_BF16_OUT, rstd * (du * gm[b][u] - m1 - xh * m2) + sk[b][u][e]);
         }
         *(gv4*)(dx + i) = r;
       }
     }
+  };
+  // (the next round's requests are in flight while this one is worked out)
+  for (int base = base0, k0 = lo; k0 < hi; base += 2 * STEP, k0 += 2 * STEP) {
+    if (k0 + STEP < hi) fetch(IConst<1>(), base + STEP);
+    apply(IConst<0>(), base);
+    if (k0 + STEP >= hi) break;
+    if (k0 + 2 * STEP < hi) fetch(IConst<0>(), base + 2 * STEP);
+    apply(IConst<1>(), base + STEP);
   }
 }
 
