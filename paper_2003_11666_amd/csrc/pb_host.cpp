@@ -17,6 +17,7 @@
 #include <mutex>
 #include <string>
 #include <thread>
+#include <map>
 #include <vector>
 
 #include "../../include/pb.h"
@@ -1006,7 +1007,7 @@ bool make_d1(const pb_ctx* c, int mode, int C, int H, int W, int K, int OH, int 
 //   and the wide one takes 91.3 without and 91.7 with.
 bool make_gemm(int mode, int C, int H, int W, int K, int OH, int OW, int k, int s, int pad,
                const GemmCfg* like, GemmCfg* out, bool allow_vec = false, int max_sub = 16, bool flat = false,
-               int max_parts = 1, double small_work = 0.0) {
+               int max_parts = 1, double small_work = 0.0, double split_us = 30.0) {
   const int target = (mode == 1) ? g_tile_target : g_tile_target_bwd;
   GemmCfg g;
   memset(&g, 0, sizeof g);
@@ -1062,12 +1063,12 @@ bool make_gemm(int mode, int C, int H, int W, int K, int OH, int OW, int k, int 
           if (!fit_gemm(c, C, H, W, K, OH, OW, k, s, pad, allow_vec, true)) continue;
           // backward weights of a stage with room for partial gradients: the chunks of the
           // reduction are dealt out to as many groups of workgroups (up to max_parts) as it
-          // takes to bring one workgroup's share under 30 us
+          // takes to bring one workgroup's share under split_us
           GemmCfg e = c;
           double tt = est_tile_us(c, k);
-          for (int want = 2; nsub == 1 && want <= max_parts && want <= c.n_chunks && tt > (mode == 3 ? 30.0 : 12.0); want *= 2) {
+          for (int want = 2; nsub == 1 && want <= max_parts && want < 2 * c.n_chunks && tt > (mode == 3 ? split_us : 12.0); want *= 2) {
             e = c;
-            e.cpp = cdiv(c.n_chunks, want);
+            e.cpp = cdiv(c.n_chunks, std::min(want, c.n_chunks));
             e.parts = cdiv(c.n_chunks, e.cpp);
             e.tiles = e.parts * e.tpp;
             GemmCfg one = e;
@@ -1276,7 +1277,7 @@ void compile_steps_once(pb_ctx* c, std::vector<std::pair<int, StepDesc>>& out);
 // longest tile while places stay free.  The GEMM steps of such a pass are planned again with other budgets and the
 // plan with the earliest estimated end of the phase is kept (wide network, forward pass: 205 tiles of 57 us -> 410 of
 // 42 us, launch 71 -> 64 us).
-void compile_steps(pb_ctx* c, std::vector<std::pair<int, StepDesc>>& out) {
+void plan_steps(pb_ctx* c, std::vector<std::pair<int, StepDesc>>& out) {
   for (double& f : g_budget_scale) f = 1.0;
   compile_steps_once(c, out);
   if (g_tile_budget_us <= 0 || c->tune.tile_budget_us != 0.f || c->kernel_set != 0) return;
@@ -1835,6 +1836,7 @@ void compile_steps_once(pb_ctx* c, std::vector<std::pair<int, StepDesc>>& out) {
       // product of two tiny maps per weight; the update step computes it while it streams the parameters.
       const bool fuse_w = c->kernel_set == 0 && g_tile_budget_us > 0 && c->N == 1 && fusew_shape(a) &&
                           !(d.flags & (F_PRE_AFFINE | F_PRE_RELU)) && b.gparts < 0 && ref_vec4(c, d.x) && ref_vec4(c, d.dy);
+      const bool stem_split = a.post_gn && s == 0;
       const bool fc_w = fc_layer(c, d, d.gw) && !(d.flags & (F_PRE_AFFINE | F_PRE_RELU)) && ref_vec4(c, d.x);
       if (fuse_w) {
         fusedw[s].phase = pb; fusedw[s].x = d.x; fusedw[s].dy = d.dy; fusedw[s].pp = pp_stride > 0 ? pp_stride : 0;
@@ -1858,8 +1860,11 @@ void compile_steps_once(pb_ctx* c, std::vector<std::pair<int, StepDesc>>& out) {
         d.kind = K_FC_BWD_W; d.flags &= ~F_BIAS;
         d.ntiles = cdiv((int64_t)d.K * d.C, 4096);
       } else
+      // (The first layer's gradient behind a GroupNorm: its tiles run two phases later than other layers', beside little else, and
+      // set the length of that launch.  A bottleneck network at 127 pixels: 90.1 us per tick with shares of up to 30 us, 84.6 so.)
       if (c->kernel_set == 0 && make_gemm(3, d.C, d.H, d.W, d.K, d.OH, d.OW, d.k, d.stride, d.pad, nullptr, &g,
-                                          !(d.flags & (F_PRE_AFFINE | F_PRE_RELU)), 16, false, b.gparts >= 0 ? GRAD_PARTS : 1)) {
+                                          !(d.flags & (F_PRE_AFFINE | F_PRE_RELU)), 16, false, b.gparts >= 0 ? GRAD_PARTS : 1, 0.0,
+                                          stem_split ? 8.0 : 30.0)) {
         if (a.has_bias) {
           StepDesc e = blank(K_BIAS_GRAD, s, t_b);
           e.K = a.K; e.OH = a.OH; e.OW = a.OW; e.dy = dz_src; e.gb = gr + a.o_b;
@@ -2145,44 +2150,154 @@ void compile_steps_once(pb_ctx* c, std::vector<std::pair<int, StepDesc>>& out) {
   }
 }
 
+// Networks tiled for throughput: estimated duration of a workgroup of a step, microseconds.
+double workgroup_us(const StepDesc& d) {
+  double us = 3.0;
+  if (d.kind == K_GEMM) {
+    GemmCfg one = d.g;
+    one.n_chunks = d.g.cpp;   // what one workgroup contracts (a split reduction: its share of the chunks)
+    us = est_tile_us(one, d.k);
+    if (d.gp.gm) us += est_tile_us(d.gp, 1);
+  } else if (d.kind == K_GN_STATS || d.kind == K_GN_BWD) {
+    // (statistics of a group that no workgroup holds in its registers, beyond 32768 elements, take three
+    // passes over memory: 15 870 elements took 35 us that way.  Started behind weight-gradient tiles they were the end of a launch of a
+    // basic network of 60, 120 and 240 channels: 182 us per tick instead of 166)
+    const int64_t cpg = d.C / std::max(1, d.G), n = cpg * d.H * d.W;
+    const bool passes = d.kind == K_GN_STATS && (n > 32768 || cpg > BLK);
+    us = 4.0 + (double)n / BLK * (!passes ? (d.kind == K_GN_STATS && n % 4 ? 0.1 : 0.05) : n > 32768 ? 1.0 : 0.5);
+  } else if (d.kind == K_GNB_REDUCE) {
+    // (routing the gradient back through a max-pool costs a window search per element: about 2 us per
+    // 256 of them when the channel fits LDS, 7 us from global memory)
+    const bool in_lds = (int64_t)d.H * d.W + (int64_t)d.PH * d.PW <= LDS_FLOATS;
+    // (0.3 us where every window is searched once)
+    us = 4.0 + (d.grain > 0 ? 1.0 : (double)d.H * d.W / BLK * ((d.flags & F_DU_POOL) ? (d.dx.base ? 0.3 : in_lds ? 2.0 : 7.0) : 0.05));
+  } else if (d.kind == K_DOT_FWD || d.kind == K_DOT_BWD_X) {
+    us = 8.0;
+  } else if (d.kind == K_FC_FWD || d.kind == K_FC_BWD_X || d.kind == K_HEAD_FC || d.kind == K_CE) {
+    us = 8.0;
+  } else if (d.kind == K_GAP_STATS) {
+    us = 6.0 + (double)(d.C / std::max(1, d.G)) * d.H * d.W / BLK * 0.1;
+  } else if (d.kind == K_UPDATE) {
+    us = 15.0;
+  } else if (d.kind == K_POST_FWD || d.kind == K_GNB_APPLY) {
+    us = (d.flags & (F_POOL | F_DU_POOL)) ? 8.0 : 5.0;
+  }
+  return us;
+}
+
+// Networks tiled for throughput: nothing else of the tick waits for its updates, which may run in any launch from the one their
+// gradients are complete in to the last.  Planned as early as they can run, they pile up in one launch, while those that hold
+// the ends of the dependency chains (the loss, the first stage) last as long as one workgroup with most of the chip's 512 places
+// empty.  Each launch's end is estimated by dealing its workgroups out, longest first, and updates are moved where that brings
+// the sum of the launches down.  us per tick before and now: VGG-11 77.8 and 75.3, ResNet-50's stages at 64 pixels 184.8 and 179.7.
+// Not weight-gradient tiles that update their weights (they take longer than those launches: the same stages 203 and 205), nor
+// updates that add gradients up over several ticks (a bottleneck network at 41 pixels 104.6 and 109.1).  A caller who asks for a
+// tile budget gets the plan as it is made (plan_steps too makes no second one then).
+void spread_steps(const pb_ctx* c, std::vector<std::pair<int, StepDesc>>& steps) {
+  if (g_tile_budget_us <= 0 || c->kernel_set != 0 || c->sequential || c->N != 1 || c->tune.one_launch > 0 || c->tune.tail_merge != 0 || c->tune.tile_budget_us != 0.f) return;
+  int n_ph = 0;
+  for (auto& p : steps) n_ph = std::max(n_ph, p.first + 1);
+  struct Mov { int step, lo; double us; };
+  std::vector<Mov> movs;
+  std::vector<double> us(steps.size());
+  for (size_t i = 0; i < steps.size(); ++i) {
+    const StepDesc& d = steps[i].second;
+    // (beside each other update workgroups share the memory's bandwidth: 8192 floats in 10 to 12 us, alone in 4)
+    us[i] = d.kind == K_UPDATE ? 11.0 : d.kind == K_DOT_FWD || d.kind == K_DOT_BWD_X ? 12.0 : workgroup_us(d);
+    if (d.flags & F_UPD_W) us[i] += d.kind == K_GEMM ? 10.0 * d.g.MT * d.g.NT / 16384.0 : 5.0;
+    if (d.kind != K_UPDATE) continue;
+    int lo = steps[i].first;
+    if (d.kind == K_UPDATE && d.ppstride > 0) {
+      // (two copies of the weights: it waits for its stage's gradients only, not for the step that reads the weights)
+      lo = 0;
+      for (auto& q : steps) {
+        const StepDesc& e = q.second;
+        if (e.stage == d.stage && (e.kind == K_GN_BWD || e.kind == K_GNB_REDUCE || e.kind == K_GNB_APPLY || e.kind == K_BIAS_GRAD ||
+                                   (e.kind == K_GEMM && e.g.gm == 3)))
+          lo = std::max(lo, q.first + 1);
+      }
+    }
+    if (lo < n_ph) movs.push_back({(int)i, lo, us[i]});
+  }
+  auto end_us = [&](int ph) {
+    std::vector<std::pair<double, int>> jobs;
+    for (size_t i = 0; i < steps.size(); ++i)
+      if (steps[i].first == ph) jobs.push_back({us[i], steps[i].second.ntiles});
+    std::sort(jobs.begin(), jobs.end(), std::greater<std::pair<double, int>>());
+    std::map<double, int> places = {{0.0, 512}};       // places by the time they are free
+    double end = 0;
+    for (auto& j : jobs)
+      for (int n = j.second; n > 0;) {
+        const double at = places.begin()->first;
+        const int k = std::min(n, places.begin()->second);
+        if ((places.begin()->second -= k) == 0) places.erase(places.begin());
+        places[at + j.first] += k;
+        end = std::max(end, at + j.first);
+        n -= k;
+      }
+    return end;
+  };
+  std::vector<double> len(n_ph);
+  std::vector<int> held(n_ph, 0);                      // steps of a launch
+  for (int p = 0; p < n_ph; ++p) len[p] = end_us(p);
+  for (auto& p : steps) ++held[p.first];
+  std::sort(movs.begin(), movs.end(), [&](const Mov& x, const Mov& y) { return x.us != y.us ? x.us > y.us : x.step < y.step; });
+  // into launch q, workgroups of at most `limit` us, step by step as long as the sum falls: of all (q, limit) the best, until none helps
+  for (int round = 0; round < 2 * n_ph; ++round) {
+    double total = 0, best = 0;
+    for (double l : len) total += l;
+    best = 0.99 * total - 1.0;
+    std::vector<std::pair<int, int>> best_moves;       // step, launch
+    for (int q = 1; q < n_ph; ++q) {
+      double limit = 1e30;
+      for (int cut = 0; cut < 6; ++cut) {
+        double next = 0;
+        std::vector<std::pair<int, int>> moved;        // step, where it was
+        std::vector<double> l = len;
+        std::vector<int> h = held;
+        double sum = total;
+        size_t good = 0;
+        for (auto& m : movs) {
+          if (m.us >= limit) continue;
+          next = std::max(next, m.us);
+          const int from = steps[m.step].first;
+          if (from == q || m.lo > q || h[from] < 2 || l[from] < l[q]) continue;
+          steps[m.step].first = q;
+          --h[from]; ++h[q];
+          const double lf = end_us(from), lq = end_us(q);
+          sum += lf - l[from] + lq - l[q];
+          l[from] = lf; l[q] = lq;
+          moved.push_back({m.step, from});
+          if (sum < best) {
+            best = sum;
+            good = moved.size();
+          }
+        }
+        if (good > 0) {
+          best_moves.clear();
+          for (size_t i = 0; i < good; ++i) best_moves.push_back({moved[i].first, q});
+        }
+        for (size_t i = moved.size(); i-- > 0;) steps[moved[i].first].first = moved[i].second;
+        if (next <= 0) break;
+        limit = next;
+      }
+    }
+    if (best_moves.empty()) break;
+    for (auto& m : best_moves) {
+      --held[steps[m.first].first]; ++held[m.second];
+      steps[m.first].first = m.second;
+    }
+    for (int p = 0; p < n_ph; ++p) len[p] = end_us(p);
+  }
+}
+
 // Launch order: by phase; inside a phase the steps are independent of each
 // other, and as its longest workgroups bound the phase they go first in the grid.
 void order_steps(std::vector<std::pair<int, StepDesc>>& tagged, bool one_launch = false) {   // one_launch: every phase in one launch
   auto step_cost = [](const StepDesc& d) -> int64_t {
     if (d.kind == K_HEAD) return (int64_t)1 << 40;
     if (g_tile_budget_us > 0) {
-      // networks tiled for throughput: estimated duration of one workgroup, nanoseconds
-      double us = 3.0;
-      if (d.kind == K_GEMM) {
-        GemmCfg one = d.g;
-        one.n_chunks = d.g.cpp;   // what one workgroup contracts (a split reduction: its share of the chunks)
-        us = est_tile_us(one, d.k);
-        if (d.gp.gm) us += est_tile_us(d.gp, 1);
-      } else if (d.kind == K_GN_STATS || d.kind == K_GN_BWD) {
-        // (statistics of a group that no workgroup holds in its registers, beyond 32768 elements, take three
-        // passes over memory: 15 870 elements took 35 us that way.  Started behind weight-gradient tiles they were the end of a launch of a
-        // basic network of 60, 120 and 240 channels: 182 us per tick instead of 166)
-        const int64_t cpg = d.C / std::max(1, d.G), n = cpg * d.H * d.W;
-        const bool passes = d.kind == K_GN_STATS && (n > 32768 || cpg > BLK);
-        us = 4.0 + (double)n / BLK * (!passes ? (d.kind == K_GN_STATS && n % 4 ? 0.1 : 0.05) : n > 32768 ? 1.0 : 0.5);
-      } else if (d.kind == K_GNB_REDUCE) {
-        // (routing the gradient back through a max-pool costs a window search per element: about 2 us per
-        // 256 of them when the channel fits LDS, 7 us from global memory)
-        const bool in_lds = (int64_t)d.H * d.W + (int64_t)d.PH * d.PW <= LDS_FLOATS;
-        // (0.3 us where every window is searched once)
-        us = 4.0 + (d.grain > 0 ? 1.0 : (double)d.H * d.W / BLK * ((d.flags & F_DU_POOL) ? (d.dx.base ? 0.3 : in_lds ? 2.0 : 7.0) : 0.05));
-      } else if (d.kind == K_DOT_FWD || d.kind == K_DOT_BWD_X) {
-        us = 8.0;
-      } else if (d.kind == K_FC_FWD || d.kind == K_FC_BWD_X || d.kind == K_HEAD_FC) {
-        us = 8.0;
-      } else if (d.kind == K_GAP_STATS) {
-        us = 6.0 + (double)(d.C / std::max(1, d.G)) * d.H * d.W / BLK * 0.1;
-      } else if (d.kind == K_UPDATE) {
-        us = 15.0;
-      } else if (d.kind == K_POST_FWD || d.kind == K_GNB_APPLY) {
-        us = (d.flags & (F_POOL | F_DU_POOL)) ? 8.0 : 5.0;
-      }
-      return (int64_t)(us * 1000.0);
+      return (int64_t)(workgroup_us(d) * 1000.0);   // networks tiled for throughput: nanoseconds
     }
     if (d.kind == K_GEMM) {
       const GemmCfg& g = d.g;
@@ -2247,6 +2362,11 @@ void order_steps(std::vector<std::pair<int, StepDesc>>& tagged, bool one_launch 
                      if (rx == 0 && g_tile_budget_us <= 0) return step_cost(x.second) < step_cost(y.second);
                      return step_cost(x.second) > step_cost(y.second);
                    });
+}
+
+void compile_steps(pb_ctx* c, std::vector<std::pair<int, StepDesc>>& out) {
+  plan_steps(c, out);
+  spread_steps(c, out);
 }
 
 // Host-side audit of the step table: every tensor reference a kernel will
