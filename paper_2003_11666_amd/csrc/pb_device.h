@@ -84,11 +84,11 @@ struct GemmCfg {
   int32_t CC;             // channels per patch
   int32_t rows_c;         // backward weights: output rows per chunk
   int32_t PR, Wp;         // patch rows / width
-  int32_t avec;           // 1: the A block is fetched with 16-byte loads (segments 16-byte aligned, lengths multiples of 4)
+  int32_t ragged;         // 1: patch rows, 2: segments of the A block start or end off 16-byte boundaries (the planner's estimate)
   int32_t o_offq, o_patch;   // LDS offsets (floats)
   int32_t n_chunks;
   int32_t LDA, o_A;        // row stride of the A block in LDS (forward, backward weights) and its LDS offset
-  int32_t vec;             // 1: patch rows are staged with 16-byte copies (source rows a multiple of 4 wide, no transform);
+  int32_t vec;             // 1: patch rows are staged with 16-byte copies (no transform), unaligned where a row is no multiple of 4 wide;
                            // 2: backward data of a strided layer: patch cleared, then the gradient scattered into it
   int32_t xoff;            // LDS column of logical patch column 0
   int32_t nsub;            // consecutive column tiles one workgroup runs (tiles_n counts groups of nsub)

@@ -295,7 +295,7 @@ __device__ __forceinline__ void step_gemm_t(const LDesc& d, int tile_, int t, lf
     const int ch0 = (GM == 3 || !nt) ? qpart * UNI(g.cpp) : 0;
     const int ch_end = ((GM == 3 || !nt) && ch0 + UNI(g.cpp) < n_chunks) ? ch0 + UNI(g.cpp) : n_chunks;
     const int nch = ch_end - ch0;
-    const int vec = UNI(g.vec), avec = UNI(g.avec);
+    const int vec = UNI(g.vec);
     const int border = gk - 1 - gpad;
 
     // first row (of the output map for forward / backward weights, of the input
@@ -329,7 +329,6 @@ __device__ __forceinline__ void step_gemm_t(const LDesc& d, int tile_, int t, lf
     // seg_len of the first nvalid segments come from memory and the rest is zero.
     // Requests (a_issue) and the stores into LDS (a_commit) are separate so that the
     // requests of chunk ch+1 can be in flight while chunk ch is contracted.
-    const int av = avec ? 4 : 1;                          // floats per request
     struct APar { int nvalid, seg_len, spr, slots; float ispr; };
     auto a_par = [&](int ch) {
       const int q0 = ch * QC;
@@ -344,7 +343,7 @@ __device__ __forceinline__ void step_gemm_t(const LDesc& d, int tile_, int t, lf
       } else {
         nseg = MT; p.nvalid = MT; p.seg_len = qe; seg_pad = q4;
       }
-      p.spr = avec ? (seg_pad + 3) >> 2 : seg_pad;        // requests per segment
+      p.spr = (seg_pad + 3) >> 2;                         // 16-byte requests per segment, unaligned ones where it starts anywhere
       p.ispr = frcp(p.spr);
       p.slots = nseg * p.spr;
       return p;
@@ -363,10 +362,7 @@ __device__ __forceinline__ void step_gemm_t(const LDesc& d, int tile_, int t, lf
 #pragma unroll
       for (int u = 0; u < AU; ++u) {
         ra[u] = (v4f){0.f, 0.f, 0.f, 0.f};
-        if (first_slot + u * BLK < p.slots && r < p.nvalid && c * av < p.seg_len) {
-          if (avec) ra[u] = *(const gv4*)a_src(ch, r, 4 * c);
-          else ra[u][0] = *a_src(ch, r, c);
-        }
+        if (first_slot + u * BLK < p.slots && r < p.nvalid && 4 * c < p.seg_len) ra[u] = *(const gv4u*)a_src(ch, r, 4 * c);
         c += a_dc; r += a_dr;
         if (c >= p.spr) { c -= p.spr; ++r; }
       }
@@ -375,11 +371,21 @@ __device__ __forceinline__ void step_gemm_t(const LDesc& d, int tile_, int t, lf
       const APar p = a_par(ch);
       const int a_dr = UNI(fdiv(BLK, p.ispr)), a_dc = BLK - a_dr * p.spr;
       int r = fdiv(first_slot, p.ispr), c = first_slot - r * p.spr;
+      if (UNI(p.seg_len) & 3) {
+        // a segment of no multiple of 4 entries: those behind its end belong to the next one
+        int cc = c;
+#pragma unroll
+        for (int u = 0; u < AU; ++u) {
+#pragma unroll
+          for (int e = 1; e < 4; ++e) ra[u][e] = 4 * cc + e < p.seg_len ? ra[u][e] : 0.f;
+          cc += a_dc;
+          if (cc >= p.spr) cc -= p.spr;
+        }
+      }
 #pragma unroll
       for (int u = 0; u < AU; ++u) {
         if (first_slot + u * BLK < p.slots) {
-          if (avec) *(lv4*)(Alds + r * lstride + 4 * c) = ra[u];
-          else Alds[r * lstride + c] = ra[u][0];
+          *(lv4*)(Alds + r * lstride + 4 * c) = ra[u];
         }
         c += a_dc; r += a_dr;
         if (c >= p.spr) { c -= p.spr; ++r; }
@@ -393,11 +399,16 @@ __device__ __forceinline__ void step_gemm_t(const LDesc& d, int tile_, int t, lf
     };
     // ---- patch staged with 16-byte copies (vec == 1): rows of the source map go to
     // LDS as they are; the interior of a patch row starts at column 4, columns 0..3
-    // and Wsrc+4..Wsrc+7 are halo.  Requests and stores separate, as for the A block.
+    // and the four behind its last vector are halo.  Rows of no multiple of 4 floats come in
+    // unaligned vectors, what the last one holds of the next row is cleared on the way into
+    // LDS.  Requests and stores separate, as for the A block.
+    // (Bound by round trips: element by element, eight requests of a thread in flight and none across a chunk, such rows, and
+    // segments of A of no multiple of 4 entries, held a tile of backward data on 36 channels of 31x31 for 27 us.  us per tick so
+    // and now: that network 67.7 and 55.1, 28 channels at 35 pixels 90.7 and 76.0, a bottleneck network at 195 pixels 720 and 639.)
     constexpr int VU = 6;
     const int Wsrc = (GM == 2) ? gOW : gW, Hsrc = (GM == 2) ? gOH : gH, Cred = (GM == 2) ? gK : gC;
     const int Wwin = win ? win : Wsrc;                    // columns of a source row that go into the patch
-    const int W4 = Wwin >> 2, pv_nrow = CC * PR, pv_nslot = pv_nrow * W4;
+    const int W4 = (Wwin + 3) >> 2, wtail = Wwin & 3, pv_nrow = CC * PR, pv_nslot = pv_nrow * W4;
     v4f pv[VU];
     int pdst[VU];
     auto p_issue = [&](int ch, int base, int clo, int trow, int pcol) {
@@ -415,8 +426,9 @@ __device__ __forceinline__ void step_gemm_t(const LDesc& d, int tile_, int t, lf
         if (base + u * BLK < pv_nslot) {
           const int chn = chan0 + c, srow = row0 + y - rshift;
           pdst[u] = c * PRW + y * Wp + 4 + 4 * xs;
+          if (wtail) pdst[u] |= xs == W4 - 1 ? 1 : 0;
           if (chn < Cred && srow >= 0 && srow < Hsrc && pcol + 4 * xs < Wsrc)
-            pv[u] = *(const gv4*)(src + ((size_t)chn * Hsrc + srow) * Wsrc + pcol + 4 * xs);
+            pv[u] = *(const gv4u*)(src + ((size_t)chn * Hsrc + srow) * Wsrc + pcol + 4 * xs);
         }
         xs += dxs; y += dy; c += dc;
         if (xs >= W4) { xs -= W4; ++y; }
@@ -425,6 +437,16 @@ __device__ __forceinline__ void step_gemm_t(const LDesc& d, int tile_, int t, lf
       }
     };
     auto p_commit = [&]() {
+      if (wtail) {
+#pragma unroll
+        for (int u = 0; u < VU; ++u)
+          if (pdst[u] >= 0) {
+            const bool last = pdst[u] & 1;
+#pragma unroll
+            for (int e = 1; e < 4; ++e) pv[u][e] = last && e >= wtail ? 0.f : pv[u][e];
+            pdst[u] &= ~1;
+          }
+      }
 #pragma unroll
       for (int u = 0; u < VU; ++u)
         if (pdst[u] >= 0) *(lv4*)(patch + pdst[u]) = pv[u];
@@ -463,7 +485,7 @@ __device__ __forceinline__ void step_gemm_t(const LDesc& d, int tile_, int t, lf
         for (int base = tid + BLK * VU; base < pv_nslot; base += BLK * VU) { p_issue(ch, base, c_lo, tile_row0, col0); p_commit(); }
         for (int h = tid; h < 2 * pv_nrow; h += BLK) {
           const int rr = h >> 1;
-          *(lv4*)(patch + rr * Wp + ((h & 1) ? Wwin + 4 : 0)) = (v4f){0.f, 0.f, 0.f, 0.f};
+          *(lv4*)(patch + rr * Wp + ((h & 1) ? 4 * W4 + 4 : 0)) = (v4f){0.f, 0.f, 0.f, 0.f};
         }
       } else if (GM == 2 && vec == 3) {
         // layer of stride 2 (border 0 or 1, even gradient width, patch width a multiple

@@ -614,16 +614,16 @@ bool fit_gemm(GemmCfg& g, int C, int H, int W, int K, int OH, int OW, int k, int
   g.nsub = std::min(g.nsub, cdiv(g.N, g.NT));
   g.tiles_n = cdiv(cdiv(g.N, g.NT), g.nsub);
   g.tiles = cdiv(g.M, g.MT) * g.tiles_n;
-  // 16-byte row copies: source rows a multiple of 4 floats wide, no transform
-  // while staging, and (backward data) unit stride so that no zeros interleave
+  // 16-byte row copies: no transform while staging, and (backward data) unit stride so that no zeros interleave; rows of no
+  // multiple of 4 floats come in unaligned vectors
   const int hl = (mode == 2) ? k - 1 - pad : pad;
   g.vec = 0;
   if (allow_vec && hl <= 4) {
-    if (mode == 2) g.vec = (s == 1 && OW % 4 == 0) ? 1 : 0;
-    else g.vec = (W % 4 == 0) ? 1 : 0;
+    g.vec = mode != 2 || s == 1 ? 1 : 0;
   }
   if (mode == 2 && s > 1) g.vec = (s == 2 && hl <= 1 && OW % 2 == 0) ? 3 : 2;   // 3: pairs of gradient values per 16-byte vector
   g.xoff = g.vec == 1 ? 4 - hl : 0;
+  g.ragged = g.vec == 1 && (mode == 2 ? OW : W) % 4 ? 1 : 0;
   // LDS per chunk: offset table, A block, patch
   auto a_size = [&](int QC) -> int64_t {
     const int QCpad = (QC + 15) / 16 * 16;
@@ -640,7 +640,7 @@ bool fit_gemm(GemmCfg& g, int C, int H, int W, int K, int OH, int OW, int k, int
     const int rows_max = tile_rows(g.NT, rowlen, nrows);
     g.PR = mode == 1 ? (rows_max - 1) * s + k : rows_max + k - 1;
     g.Wp = mode == 1 ? W + 2 * pad : W + k - 1;
-    if (g.vec == 1) g.Wp = (mode == 1 ? W : OW) + 8;
+    if (g.vec == 1) g.Wp = ((mode == 1 ? W : OW) + 3) / 4 * 4 + 8;
     if (g.vec == 3) g.Wp = (g.Wp + 3) / 4 * 4;
     if (g.win) {   // flattened 1x1 layer: one row, only the tile's own columns
       if (g.vec != 1 || H != 1 || OH != 1 || k != 1 || s != 1 || pad != 0) return false;
@@ -665,7 +665,7 @@ bool fit_gemm(GemmCfg& g, int C, int H, int W, int K, int OH, int OW, int k, int
     g.CC = CC; g.QC = CC * kk; g.n_chunks = cdiv(nch, CC); g.rows_c = 0;
   } else {
     g.CC = std::min(C, (g.NT + kk - 2) / kk + 1);
-    g.Wp = g.vec ? W + 8 : W + 2 * pad;
+    g.Wp = g.vec ? (W + 3) / 4 * 4 + 8 : W + 2 * pad;
     auto pr = [&](int r) { return (r - 1) * s + k; };
     // one chunk holding every output row, else the largest row count whose
     // pixel count is a multiple of 4 (chunks in the middle must not be padded)
@@ -687,16 +687,13 @@ bool fit_gemm(GemmCfg& g, int C, int H, int W, int K, int OH, int OW, int k, int
   }
   g.QCpad = (g.QC + 15) / 16 * 16;
   g.parts = 1; g.cpp = g.n_chunks; g.tpp = g.tiles;
-  // 16-byte fetches of the A block: every segment starts on a 16-byte boundary and
-  // has a length that is a multiple of 4 (the caller withdraws this if the operand's
-  // address does not allow it).  Forward / backward weights: segments are rows of the
-  // reduction range; backward data: the MT x k x k weights of one output channel.
-  if (mode == 2) g.avec = (C % 4 == 0) ? 1 : 0;
-  else g.avec = (g.Q % 4 == 0 && (g.n_chunks == 1 || g.QC % 4 == 0)) ? 1 : 0;
+  // 16-byte fetches of the A block, unaligned where a segment starts or ends anywhere.  Forward / backward weights: segments
+  // are rows of the reduction range; backward data: the MT x k x k weights of one output channel.
+  if (mode == 2 ? C % 4 : g.Q % 4 || (g.n_chunks > 1 && g.QC % 4)) g.ragged |= 2;
   {
     const int q4 = (mode == 2) ? (g.QC + 3) / 4 * 4 : g.QCpad;
     const int64_t nseg = (mode == 2) ? (q4 + kk - 1) / kk : g.MT, seg = (mode == 2) ? g.MT * kk : q4;
-    g.a_req = (int)cdiv(nseg * (g.avec ? (seg + 3) / 4 : seg), BLK);
+    g.a_req = (int)cdiv(nseg * ((seg + 3) / 4), BLK);
   }
   g.LDA = (mode == 2) ? g.MT * kk : g.QCpad + 4;   // QCpad + 4 = 4 * odd: the 16 rows of a wave fall into different banks
   g.o_offq = 0;
@@ -744,9 +741,12 @@ double est_tile_us(const GemmCfg& g, int k) {
   const int kk = k * k;
   const double a_fl = g.gm == 2 ? (double)((g.QCpad + kk - 1) / kk + 1) * g.MT * kk : (double)g.MT * g.QCpad;
   const double p_fl = (double)g.CC * g.PR * g.Wp;
-  const double a_sl = a_fl / (g.avec ? 4 : 1) / BLK, p_sl = p_fl / ((g.vec == 1 || g.vec == 3) ? 4 : 1) / BLK;
+  // (Ragged rows and segments are counted element by element, as they once were staged: with their vectors counted the plans
+  // of networks on odd maps turn to fewer, longer tiles.)
+  const bool p_vec = (g.vec == 1 && !(g.ragged & 1)) || g.vec == 3;
+  const double a_sl = a_fl / ((g.ragged & 2) ? 1 : 4) / BLK, p_sl = p_fl / (p_vec ? 4 : 1) / BLK;
   const double stage_a = 0.1 * std::min(a_sl, 6.0) + 0.3 * std::max(0.0, a_sl - 6.0);
-  const double stage_p = g.vec == 1 ? 0.1 * std::min(p_sl, 6.0) + 0.3 * std::max(0.0, p_sl - 6.0) : 0.3 * p_sl;
+  const double stage_p = g.vec == 1 && p_vec ? 0.1 * std::min(p_sl, 6.0) + 0.3 * std::max(0.0, p_sl - 6.0) : 0.3 * p_sl;
   const double mf = (double)cdiv(cdiv(std::min(g.QC, g.Q), 4), g.wk) * g.ni;
   const double t_mfma = mf * (32.0 + 70.0 / g.ni) / 2400.0;
   const double t_chunk = 3.0 + stage_a + stage_p + t_mfma;   // fixed part: two barriers, the request code, fill and drain of the MFMA pipeline
@@ -1144,14 +1144,6 @@ __attribute__((noinline)) bool fc_layer(const pb_ctx* c, const StepDesc& d, cons
   return c->kernel_set == 0 && g_tile_budget_us > 0 && d.H == 1 && d.W == 1 && d.OH == 1 && d.OW == 1 && d.k == 1 && d.stride == 1 &&
          d.pad == 0 && d.C % 4 == 0 && d.C >= 256 && d.K >= 1 && d.K <= 8192 && (int64_t)d.K * d.C < ((int64_t)1 << 30) &&
          w && ((uintptr_t)w - (uintptr_t)c->f(0)) % 16 == 0 && ((d.pmask & PF_W) == 0 || d.pstride % 4 == 0);
-}
-
-// Whether the A operand of a GEMM step (of its projection operand set if
-// `second`) starts on a 16-byte boundary in every ring slot.
-bool a_aligned(const pb_ctx* c, const StepDesc& d, bool second) {
-  const float* p = second ? d.wp : (d.g.gm == 3 ? d.dy.base : d.w);
-  if (!p || (p - c->f(0)) % 4) return false;
-  return second || d.g.gm != 3 || d.dy.stride % 4 == 0;
 }
 
 // Limits of the fused last stage (one workgroup; see step_head): sizes of its
@@ -2041,13 +2033,6 @@ void compile_steps_once(pb_ctx* c, std::vector<std::pair<int, StepDesc>>& out) {
     for (int s = 0; s < S; ++s)
       if (fusedw[s].phase >= 0) fusedw[s].phase += baseB[s] - bwd0[s];
   }
-  // 16-byte loads of the A operand need a 16-byte aligned operand (the arena is)
-  for (auto& pr : out) {
-    StepDesc& d = pr.second;
-    if (d.kind != K_GEMM) continue;
-    if (d.g.avec && !a_aligned(c, d, false)) { d.g.avec = 0; d.g.a_req *= 4; }
-    if (d.gp.gm && d.gp.avec && !a_aligned(c, d, true)) { d.gp.avec = 0; d.gp.a_req *= 4; }
-  }
   // ---- a backward-data GEMM that leaves partial gradients: its consumer, the channel sums of the
   // previous stage's GroupNorm (same gradient buffer), adds them up
   for (auto& pr : out) {
@@ -2602,10 +2587,9 @@ int validate_steps(const pb_ctx* c, const std::vector<std::pair<int, StepDesc>>&
           // chunk plus the zero segments the last k-step can reach
           if (g.gm == 2)
             o = o && g.LDA == g.MT * kk && (int64_t)g.o_A + (int64_t)((g.QCpad + kk - 1) / kk + 1) * g.MT * kk <= g.o_patch &&
-                (!g.avec || C % 4 == 0);
+                (g.MT * kk) % 4 == 0;
           else
-            o = o && g.LDA >= g.QCpad + 4 && g.LDA % 4 == 0 && (int64_t)g.o_A + (int64_t)g.MT * g.LDA <= g.o_patch &&
-                (!g.avec || (g.Q % 4 == 0 && (g.n_chunks == 1 || g.QC % 4 == 0)));
+            o = o && g.LDA >= g.QCpad + 4 && g.LDA % 4 == 0 && (int64_t)g.o_A + (int64_t)g.MT * g.LDA <= g.o_patch;
           const int hl_ = (g.gm == 2) ? k - 1 - pad : pad;
           if (g.vec == 2) {
             o = o && g.gm == 2 && s > 1 && g.xoff == 0;
@@ -2615,8 +2599,8 @@ int validate_steps(const pb_ctx* c, const std::vector<std::pair<int, StepDesc>>&
           } else if (g.vec) {
             const int wsrc = (g.gm == 2) ? d.OW : W;
             if (g.win) o = o && g.win == g.NT && g.Wp == g.NT + 8 && H == 1 && d.OH == 1 && k == 1 && s == 1 && pad == 0 && g.gm != 3;
-            else o = o && g.Wp == wsrc + 8;
-            o = o && wsrc % 4 == 0 && g.xoff == 4 - hl_ && hl_ <= 4 && (g.gm != 2 || s == 1) &&
+            else o = o && g.Wp == (wsrc + 3) / 4 * 4 + 8;
+            o = o && (!g.win || wsrc % 4 == 0) && g.xoff == 4 - hl_ && hl_ <= 4 && (g.gm != 2 || s == 1) &&
                 (g.o_patch % 4) == 0 && !(d.flags & (F_PRE_AFFINE | F_PRE_RELU) && g.gm != 2);
           } else {
             o = o && g.xoff == 0 && g.win == 0;
@@ -2684,7 +2668,10 @@ int validate_steps(const pb_ctx* c, const std::vector<std::pair<int, StepDesc>>&
         } else if (d.g.mm) {
           ok = ok && d.ntiles == d.g.tiles && mm_ok(d.g) && d.gp.gm == 0;
         } else {
-        ok = ok && (!d.g.avec || a_aligned(c, d, false)) && (!(d.flags & F_PROJ) || !d.gp.avec || a_aligned(c, d, true));
+        // vectors at the end of a row or a segment of no multiple of 4 floats reach up to 3 floats past their tensor
+        auto tail_ok = [&](const TRef& r) { return !r.base || r.base + (int64_t)r.depth * r.stride + 4 <= hi; };
+        ok = ok && tail_ok(d.x) && tail_ok(d.dy) && tail_ok(d.skip) &&
+             (d.g.gm == 3 || d.w + (int64_t)std::max(0, (d.pmask & PF_W) ? d.pdepth - 1 : 0) * d.pstride + (int64_t)d.K * d.C * d.k * d.k + 4 <= hi);
         ok = ok && d.ntiles == d.g.tiles && cfg_ok(d.g, d.C, d.H, d.W, d.k, d.stride, d.pad) &&
              ptr_ok((const float*)d.tq, d.g.QCpad) && ptr_ok((const float*)d.tn, d.g.N) &&
              (!(d.flags & F_PROJ) || d.g.gm != 1 || (ptr_ok((const float*)d.tq2, d.gp.QCpad) && ptr_ok((const float*)d.tn2, d.gp.N)));
