@@ -741,10 +741,16 @@ double est_tile_us(const GemmCfg& g, int k) {
   const int kk = k * k;
   const double a_fl = g.gm == 2 ? (double)((g.QCpad + kk - 1) / kk + 1) * g.MT * kk : (double)g.MT * g.QCpad;
   const double p_fl = (double)g.CC * g.PR * g.Wp;
-  // (Ragged rows and segments are counted element by element, as they once were staged: with their vectors counted the plans
-  // of networks on odd maps turn to fewer, longer tiles.)
-  const bool p_vec = (g.vec == 1 && !(g.ragged & 1)) || g.vec == 3;
-  const double a_sl = a_fl / ((g.ragged & 2) ? 1 : 4) / BLK, p_sl = p_fl / (p_vec ? 4 : 1) / BLK;
+  // Ragged rows and segments come in unaligned vectors, and backward data of a strided layer on an odd map (vec == 2) clears its
+  // patch in vectors and scatters the quarter of it that holds gradients: both cost what vectors do.  Us per tick with these
+  // counted element by element and so: bottleneck networks at 195 pixels 639 and 424, 146 pixels 449 and 334, 165 pixels 319 and
+  // 269, basic ones at 35 pixels 76 and 55, at 31 pixels 95 and 74; thirty others the same or up to 3 % less.
+  // The first layer (an image's channels: 4 at most) keeps the count by elements: its gradient is dealt out by this estimate, and
+  // with vectors it is left with fewer, longer shares (127 pixels 85.4 us per tick and 89.9, 95 pixels 136.8 and 139.5; at 31
+  // pixels 74 and 65).
+  const bool image = (g.gm == 1 ? g.Q : g.gm == 3 ? g.N : g.M * kk) <= 4 * kk;
+  const bool p_vec = (g.vec == 1 && !((g.ragged & 1) && image)) || g.vec >= 2;
+  const double a_sl = a_fl / ((g.ragged & 2) && image ? 1 : 4) / BLK, p_sl = p_fl / (p_vec ? 4 : 1) / BLK;
   const double stage_a = 0.1 * std::min(a_sl, 6.0) + 0.3 * std::max(0.0, a_sl - 6.0);
   const double stage_p = g.vec == 1 && p_vec ? 0.1 * std::min(p_sl, 6.0) + 0.3 * std::max(0.0, p_sl - 6.0) : 0.3 * p_sl;
   const double mf = (double)cdiv(cdiv(std::min(g.QC, g.Q), 4), g.wk) * g.ni;

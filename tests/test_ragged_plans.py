@@ -1,0 +1,22 @@
+"""Tiles of networks on odd maps: rows of no multiple of 4 pixels are staged in vectors and planned as such."""
+import re
+
+import pytest
+
+import pb_workloads as W
+from paper_2003_11666_amd.binding import plan_summary
+
+
+@pytest.mark.parametrize("hw,layers,groups", [(146, (1, 3, 1, 3), 32), (165, (2, 4, 2), 16), (195, (2, 2, 5), 16)])
+def test_strided_shortcuts_on_odd_maps_are_few_tiles(hw, layers, groups):
+    """512 to 1024 channels, stride 2: 448 to 704 tiles of 16 x 16 forward if an element cost what a vector does."""
+    net = W._net("odd", W.preact_resnet_bottleneck(layers, 64, groups, n_classes=19), 3, hw, hw, 19, 1e-3, 0.9, 8, 3, 8)
+    steps = [l for l in plan_summary(net).splitlines() if re.search(r"C512x\d+x\d+ K1024x\d+x\d+ k1 s2 \| gm1", l)]
+    assert len(steps) == 1 and int(re.search(r"tiles +(\d+)", steps[0])[1]) <= 256 and "tile 16x16" not in steps[0], steps
+
+
+def test_the_first_layers_gradient_keeps_its_shares():
+    """32 channels at 127 pixels: more, shorter shares than vectors alone would have it."""
+    net = W._net("stem", W.preact_resnet_bottleneck((1, 3, 6, 1), 32, 16, n_classes=76), 3, 127, 127, 76, 1e-3, 0.9, 8, 3, 8)
+    steps = [l for l in plan_summary(net).splitlines() if "C3x127x127" in l and "gm3" in l]
+    assert len(steps) == 1 and int(re.search(r"tiles +(\d+)", steps[0])[1]) >= 96, steps
