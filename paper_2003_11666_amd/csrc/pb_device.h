@@ -11,6 +11,8 @@ constexpr int BLK = 256;          // threads per workgroup (4 wavefronts of 64)
 constexpr int UPD_CHUNK = 1024;   // stages are padded to this many floats
 constexpr int UPD_TILE = 8192;    // floats per workgroup of an update step (8 float4 per thread and array in flight)
 constexpr float GN_EPS = 1e-5f;
+constexpr int GNB_STREAM_N = 32768; // elements of a group that one workgroup of K_GN_BWD walks twice (grain 2), its channels
+constexpr int GNB_STREAM_CPG = 1024;
 constexpr int GNB_WAVE_MAX_N = 2048; // elements of a group in the one-wavefront-per-group form of K_GN_BWD
 constexpr int HEAD_FC_W = 32768;  // weights of the dense layer that K_HEAD_FC takes, its inputs at most 4 BLK
 constexpr int GAP_STATS_CPG = 4096; // channels per group of a K_GAP_STATS step
@@ -186,7 +188,7 @@ struct StepDesc {
   int32_t wait_idx[3], wait_n[3];
   int32_t grain;            // > 0: streaming form of an elementwise step, floats per workgroup (K_COPY, K_GNB_APPLY);
                             // K_GNB_REDUCE: 1 = one wavefront per channel, 2 = the same, 16-byte requests; K_GN_STATS, K_GN_BWD:
-                            // 1 = one wavefront per group
+                            // 1 = one wavefront per group; K_GN_BWD: 2 = a group beyond a workgroup's registers
   GemmCfg g;     // main operand set of a K_GEMM step
   GemmCfg gp;    // projection of the skip tensor accumulated into the same tile (forward only)
   TRef x;        // op input (forward) / saved input (backward)

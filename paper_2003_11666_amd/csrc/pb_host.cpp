@@ -1185,6 +1185,26 @@ bool gn_bwd_fits(int C, int HW, int G) {
   return n <= GNB_MAX_N && cpg <= BLK && n / 2 + 5 * cpg + 2 <= LDS_FLOATS;
 }
 
+// Estimated duration of a group walked twice by one workgroup, microseconds (5184 elements 18, 11 250 18.6).
+double gn_walk_us(int64_t n) { return 13.0 + 0.62e-3 * (double)n; }
+
+// Whether a group beyond that, or of a map of no multiple of 4 pixels, is walked twice by one workgroup (step_gn_bwd_stream)
+// instead of in two steps a launch apart.  It must not become the end of its launch.  Networks tiled for throughput: the longest
+// tile they allow, less strictly from 4 groups on (with 2 groups, 5184 elements in launches of 16 us 50.7 us per tick in two steps
+// and 52.7, 17 150 elements 54.6 and 66.5), and only where the two steps have no vectors, on maps of no multiple of 4 pixels
+// (others, 5120 elements: 73.8 and 76.3).  Small networks: 4608 elements in two steps 54.4 and 47.0, 5760 elements 31.9 and 36.8.
+// Us per tick in two steps and so: bottleneck networks at 195 pixels 424 and 327, 219 pixels 227 and 178, 146 pixels 334 and 297,
+// 102 pixels 97 and 81, ResNet-50 434 and 427 (its 7x7 maps), basic ones at 37 pixels 98 and 88, at 15 pixels 37 and 31; up to
+// 131 072 elements at 195 pixels 332.
+bool gn_bwd_walks(const pb_ctx* c, int C, int HW, int G) {
+  if (c->kernel_set != 0 || G < 1 || C % G || gn_bwd_fits(C, HW, G)) return false;
+  const int cpg = C / G;
+  const int64_t n = (int64_t)cpg * HW;
+  if (n > GNB_STREAM_N || cpg > GNB_STREAM_CPG) return false;
+  if (g_tile_budget_us <= 0) return n <= 5120;
+  return HW % 4 && (G < 4 ? gn_walk_us(n) <= g_tile_budget_us : (double)n <= 1000.0 * (g_tile_budget_us - 3.0));
+}
+
 // Streaming form of a K_GNB_APPLY step (see step_gnb_apply_stream): workgroups
 // aligned to groups, STREAM_GRAIN floats each.
 void stream_apply(const pb_ctx* c, StepDesc& e) {
@@ -1469,7 +1489,8 @@ void compile_steps_once(pb_ctx* c, std::vector<std::pair<int, StepDesc>>& out) {
       bwd_params(d, PF_GAMMA);
       d.ggamma = gr + a.o_gamma; d.gbeta = gr + a.o_beta;
       d.part = c->f(b.part);
-      if (c->kernel_set == 0 && gn_bwd_fits(d.C, d.H * d.W, d.G)) {
+      const bool walk = gn_bwd_walks(c, d.C, d.H * d.W, d.G) && !summed;
+      if (c->kernel_set == 0 && (walk || gn_bwd_fits(d.C, d.H * d.W, d.G))) {
         d.kind = K_GN_BWD;
         if (c->bf16) d.flags |= F_BF16_OUT;
         if (s > 0) {
@@ -1496,7 +1517,8 @@ void compile_steps_once(pb_ctx* c, std::vector<std::pair<int, StepDesc>>& out) {
           d.gacc = c->f(L.gacc + a.off + a.o_gamma);
         }
         d.ntiles = a.G;
-        gn_bwd_wave(c, d);
+        if (walk) d.grain = 2;
+        else gn_bwd_wave(c, d);
         out.push_back({pb++, d});
       } else {
         d.ntiles = a.Cin;
@@ -2156,6 +2178,7 @@ double workgroup_us(const StepDesc& d) {
     const int64_t cpg = d.C / std::max(1, d.G), n = cpg * d.H * d.W;
     const bool passes = d.kind == K_GN_STATS && (n > 32768 || cpg > BLK);
     us = 4.0 + (double)n / BLK * (!passes ? (d.kind == K_GN_STATS && n % 4 ? 0.1 : 0.05) : n > 32768 ? 1.0 : 0.5);
+    if (d.kind == K_GN_BWD && d.grain == 2) us = gn_walk_us(n);
   } else if (d.kind == K_GNB_REDUCE) {
     // (routing the gradient back through a max-pool costs a window search per element: about 2 us per
     // 256 of them when the channel fits LDS, 7 us from global memory)
@@ -2468,7 +2491,12 @@ int validate_steps(const pb_ctx* c, const std::vector<std::pair<int, StepDesc>>&
         const int64_t dyn = (d.flags & F_DU_BUF) ? in : d.C;
         if (d.grain == 1)   // one wavefront per group
           ok = ok && !c->nt_stores && d.C / d.G <= 64 && d.C / d.G * d.H * d.W <= GNB_WAVE_MAX_N;
-        ok = ok && gn_bwd_fits(d.C, d.H * d.W, d.G) && d.ntiles == (d.grain == 1 ? cdiv(d.G, BLK / 64) : d.G) && !(d.flags & F_DU_POOL) &&
+        if (d.grain == 2) {   // (vectors reach up to 3 elements past a channel)
+          auto tail_ok = [&](const TRef& r) { return !r.base || r.base + (int64_t)r.depth * r.stride + 4 <= hi; };
+          ok = ok && c->kernel_set == 0 && d.gparts <= 1 && tail_ok(d.x) && tail_ok(d.dy) && tail_ok(d.skg);
+          static_assert(3 * GNB_STREAM_CPG + 2 * (GNB_STREAM_N / 256) <= LDS_FLOATS, "sums of channels and of shares in LDS");
+        }
+        ok = ok && (d.grain == 2 || gn_bwd_fits(d.C, d.H * d.W, d.G)) && d.ntiles == (d.grain == 1 ? cdiv(d.G, BLK / 64) : d.G) && !(d.flags & F_DU_POOL) &&
              ((d.flags & F_DU_BUF) || (d.flags & F_DU_GAP)) && ref_ok(d.x, in) && ref_ok(d.st, stn) && ref_ok(d.dy, dyn) &&
              ptr_ok(d.gamma, d.C) && ptr_ok(d.ggamma, d.C) && ptr_ok(d.gbeta, d.C) && (!d.dx.base || ref_ok(d.dx, in)) &&
              (!(d.flags & F_ADD_SKG) || (d.dx.base && ref_ok(d.skg, in)));

@@ -1382,6 +1382,159 @@ __device__ __forceinline__ void step_gn_bwd_wave(const LDesc& d, int tile, int t
     }
 }
 
+// The same for groups beyond a workgroup's registers, and for maps of no multiple of 4 pixels (grain = 2): one workgroup per
+// group walks it twice, once for the channels' sums and once for dx, which finds it in the L2.  A wavefront takes 1024 elements
+// of a channel at a time, or four channels of up to 256 elements (16 lanes each), the next ones' requests in flight; vectors
+// start anywhere.  Bound by those round trips, 18 to 20 us at 5000 to 11 000 elements, where the channels' sums (a workgroup each)
+// take 4.5 and the elementwise pass as long again, but a launch later: that launch, or at least its tail, goes.  (Passing over the
+// vectors of a round that lie beyond a small map altogether: 185.7 us per tick instead of 177.7 at 219 pixels.)
+// LDS: sums of the wavefronts' shares [2 units], sums of a channel and its scale in the backward pass [3 cpg].
+__device__ __forceinline__ void step_gn_bwd_stream(const LDesc& d, int tile, int t, bool live, lfloat* red, lfloat* smem, const bool nt) {
+  const int tid = threadIdx.x, lane = tid & 63, wv = UNI(tid >> 6);
+  const int C = UNI(d.C), G = UNI(d.G), HW = UNI(d.H) * UNI(d.W), flags = UNI(d.flags);
+  const int g = tile, cpg = UNI(fdiv(C, frcp(G))), n = cpg * HW;
+  const bool gen = flags & F_UPD_GEN, upd = flags & F_UPD_GN;
+  auto update = [&](int c, float sg, float sb, UpdOld o0, UpdOld o1) {
+    if (gen) { update_one(d, t, g * cpg + c, sg, o0, true); update_one(d, t, C + g * cpg + c, sb, o1, true); }
+    else { update_one(d, t, g * cpg + c, sg, o0, false); update_one(d, t, C + g * cpg + c, sb, o1, false); }
+  };
+  UpdOld old0 = {0.f, 0.f, 0.f, 0.f}, old1 = old0;   // (of channel tid: requested ahead of the sums)
+  if (upd && tid < cpg) { old0 = update_fetch(d, t, g * cpg + tid, gen); old1 = update_fetch(d, t, C + g * cpg + tid, gen); }
+  auto each_channel = [&](auto f) {
+    for (int c = tid; c < cpg; c += BLK) {
+      if (c != tid && upd) { old0 = update_fetch(d, t, g * cpg + c, gen); old1 = update_fetch(d, t, C + g * cpg + c, gen); }
+      f(c);
+    }
+  };
+  if (!live) {
+    if (upd) each_channel([&](int c) { update(c, 0.f, 0.f, old0, old1); });
+    return;
+  }
+  const bool rl = flags & F_GN_RELU, gapd = flags & F_DU_GAP;
+  const gfloat* st = at(d.st, t);
+  const gfloat* x = at(d.x, t) + (size_t)g * n;
+  const gfloat* dy = at(d.dy, t) + (size_t)g * (gapd ? cpg : n);
+  const bool has_dx = d.dx.base != nullptr;
+  const gfloat* skg = ((flags & F_ADD_SKG) && has_dx) ? (const gfloat*)at(d.skg, t) + (size_t)g * n : nullptr;
+  const float mean = st[g], rstd = st[G + g], inv_hw = 1.f / (float)HW;
+  const bool narrow = HW <= 256;
+  const int nseg = narrow ? 1 : (HW + 1023) >> 10, units = narrow ? (cpg + 3) >> 2 : cpg * nseg;
+  const float inseg = frcp(nseg);
+  const int step = narrow ? 64 : 256;
+  lfloat* ps = smem;
+  lfloat* cs = smem + (narrow ? 0 : 2 * units);
+  constexpr int V = 4;
+  v4f xv[2][V], dv[2][V], sk[2][V];
+  float sc[2], sh[2];
+  auto where = [&](int u, int& c, int& i0) {
+    if (narrow) { c = 4 * u + (lane >> 4); i0 = 4 * (lane & 15); }
+    else { c = UNI(fdiv(u, inseg)); i0 = ((u - c * nseg) << 10) + 4 * lane; }
+  };
+  auto fetch = [&](auto B, int u, bool second) {
+    constexpr int b = decltype(B)::value;
+    int c, i0;
+    where(u, c, i0);
+    const bool ok = c < cpg;
+    sc[b] = 0.f; sh[b] = 0.f;
+    if (ok) { sc[b] = st[2 * G + g * cpg + c]; sh[b] = st[2 * G + C + g * cpg + c]; }
+    float p = 0.f;
+    if (gapd && ok) p = dy[c] * inv_hw;
+#pragma unroll
+    for (int v = 0; v < V; ++v) {
+      const int i = i0 + step * v;
+      xv[b][v] = (v4f){0.f, 0.f, 0.f, 0.f};
+      dv[b][v] = (v4f){p, p, p, p};
+      sk[b][v] = xv[b][v];
+      // (a channel's last vector reaches up to 3 elements past it)
+      if (ok && i < HW) {
+        const unsigned o = (unsigned)(c * HW + i);
+        xv[b][v] = *(const gv4u*)(x + o);
+        if (!gapd) dv[b][v] = *(const gv4u*)(dy + o);
+        if (second && skg) sk[b][v] = *(const gv4u*)(skg + o);
+      }
+    }
+  };
+  auto units_of = [&](bool second, auto f) {       // units wv, wv + 4, ... of this wavefront, two sets of registers
+    if (wv >= units) return;
+    fetch(IConst<0>(), wv, second);
+    for (int u = wv; u < units; u += 8) {
+      if (u + 4 < units) fetch(IConst<1>(), u + 4, second);
+      f(IConst<0>(), u);
+      if (u + 4 >= units) break;
+      if (u + 8 < units) fetch(IConst<0>(), u + 8, second);
+      f(IConst<1>(), u + 4);
+    }
+  };
+  units_of(false, [&](auto B, int u) {
+    constexpr int b = decltype(B)::value;
+    int c, i0;
+    where(u, c, i0);
+    float sg = 0.f, sb = 0.f;
+#pragma unroll
+    for (int v = 0; v < V; ++v) {
+#pragma unroll
+      for (int e = 0; e < 4; ++e) {
+        const bool on = c < cpg && i0 + step * v + e < HW && !(rl && !(fmaf(sc[b], xv[b][v][e], sh[b]) > 0.f));
+        const float du = on ? dv[b][v][e] : 0.f;
+        sg = fmaf(du, on ? (xv[b][v][e] - mean) * rstd : 0.f, sg);
+        sb += du;
+      }
+    }
+    if (narrow) {
+      sg = row_sum(sg); sb = row_sum(sb);
+      if ((lane & 15) == 0 && c < cpg) { cs[c] = sb; cs[cpg + c] = sg; }
+    } else {
+      sg = wave_sum(sg); sb = wave_sum(sb);
+      if (lane == 0) { ps[u] = sb; ps[units + u] = sg; }
+    }
+  });
+  __syncthreads();
+  float p1 = 0.f, p2 = 0.f;
+  each_channel([&](int c) {
+    float sg = 0.f, sb = 0.f;
+    if (narrow) { sb = cs[c]; sg = cs[cpg + c]; }
+    else for (int q = 0; q < nseg; ++q) { sb += ps[c * nseg + q]; sg += ps[units + c * nseg + q]; }
+    const float gm = GP(d.gamma)[g * cpg + c];     // (before the update, which may overwrite it)
+    GP(d.ggamma)[g * cpg + c] = sg;
+    GP(d.gbeta)[g * cpg + c] = sb;
+    if (upd) update(c, sg, sb, old0, old1);
+    p1 = fmaf(gm, sb, p1);
+    p2 = fmaf(gm, sg, p2);
+    cs[2 * cpg + c] = gm;
+  });
+  if (!has_dx) return;
+  const float m1 = block_sum(p1, red) / (float)n, m2 = block_sum(p2, red) / (float)n;
+  gfloat* dx = at(d.dx, t) + (size_t)g * n;
+  units_of(true, [&](auto B, int u) {
+    constexpr int b = decltype(B)::value;
+    int c, i0;
+    where(u, c, i0);
+    if (c >= cpg) return;
+    const float gm = cs[2 * cpg + c];
+#pragma unroll
+    for (int v = 0; v < V; ++v) {
+      const int i = i0 + step * v;
+      if (i < HW) {
+        v4f o;
+#pragma unroll
+        for (int e = 0; e < 4; ++e) {
+          const float du = rl && !(fmaf(sc[b], xv[b][v][e], sh[b]) > 0.f) ? 0.f : dv[b][v][e];
+          const float xh = (xv[b][v][e] - mean) * rstd;
+          o[e] = rbf_if(flags & F_BF16_OUT, rstd * (du * gm - m1 - xh * m2) + sk[b][v][e]);
+        }
+        gfloat* p = dx + (unsigned)(c * HW + i);
+        if (i + 3 < HW) {
+          PB_ST(nt, (gv4u*)p, o);
+        } else {
+#pragma unroll
+          for (int e = 0; e < 3; ++e)
+            if (i + e < HW) p[e] = o[e];
+        }
+      }
+    }
+  });
+}
+
 // Backward data: dX = W^T dZ (transposed convolution), one thread per input
 // element, gathering.
 __device__ __forceinline__ void step_conv_bwd_x(const LDesc& d, int tile, int t) {
@@ -2926,7 +3079,9 @@ k_phase(const StepDesc* __restrict__ recs, const Globals* __restrict__ G, int k,
     case K_GAP_STATS: step_gap_stats(d, tile, t, red, smem); break;
     case K_HEAD_FC: step_head_fc(d, t, red, smem); break;
     case K_GN_BWD:
-      if (!NT && UNI(d.grain) == 1) step_gn_bwd_wave(d, tile, t, live, smem); else step_gn_bwd(d, tile, t, live, smem, NT);
+      if (!NT && UNI(d.grain) == 1) step_gn_bwd_wave(d, tile, t, live, smem);
+      else if (UNI(d.grain) == 2) step_gn_bwd_stream(d, tile, t, live, red, smem, NT);
+      else step_gn_bwd(d, tile, t, live, smem, NT);
       break;
     // (planned only for networks tiled for throughput: the other instantiation carries no code for them)
     case K_DOT_FWD: if (!NT) step_dot_fwd(d, tile, t, smem); break;
