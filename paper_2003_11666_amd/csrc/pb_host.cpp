@@ -1206,19 +1206,26 @@ bool gn_bwd_walks(const pb_ctx* c, int C, int HW, int G) {
 }
 
 // Streaming form of a K_GNB_APPLY step (see step_gnb_apply_stream): workgroups
-// aligned to groups, STREAM_GRAIN floats each.
+// aligned to groups, STREAM_GRAIN floats each, every channel padded to whole vectors; one vector per thread in small networks
+// (us per tick with an element per thread and so: a bottleneck network at 87 pixels 112.1 and 98.4, basic ones at 32 pixels 52.2
+// and 49.2, at 31 pixels 55.3 and 51.6).
 void stream_apply(const pb_ctx* c, StepDesc& e) {
   const int HW = e.H * e.W;
-  if (g_tile_budget_us <= 0 || !(e.flags & F_DU_BUF) || HW % 4 || !ref_vec4(c, e.x) || !ref_vec4(c, e.dy) ||
-      !ref_vec4(c, e.dx) || ((e.flags & F_ADD_SKG) && !ref_vec4(c, e.skg)))
-    return;
-  const int64_t gsz = (int64_t)(e.C / e.G) * HW;
+  if (!(e.flags & F_DU_BUF) || (c->kernel_set != 0 && (g_tile_budget_us <= 0 || HW % 4))) return;
+  if (HW % 4 == 0 && (!ref_vec4(c, e.x) || !ref_vec4(c, e.dy) || !ref_vec4(c, e.dx) || ((e.flags & F_ADD_SKG) && !ref_vec4(c, e.skg)))) return;
+  const int64_t gsz = (int64_t)(e.C / e.G) * ((HW + 3) / 4 * 4);
   // up to four rounds per workgroup where the tick's passes of this kind are more than the chip has places for (ResNet-50 at
   // 224 pixels: 3482 workgroups of one round, and a wavefront in place of a workgroup for the sums of 1344 channels, 439.4 us per
   // tick; 1500 of up to four 434.0)
   int64_t all = 0;
   for (const Stage& a : c->st)
     if (a.pre_gn && !gn_bwd_fits(a.Cin, a.Hin * a.Win, a.G)) all += a.in_elems();
+  if (g_tile_budget_us <= 0) {   // small networks: a vector per thread while the chip has places for them
+    e.grain = 4 * BLK * (int)std::max<int64_t>(1, std::min<int64_t>(4, all / (512 * 4 * BLK)));
+    e.n = cdiv(gsz, e.grain);
+    e.ntiles = e.G * e.n;
+    return;
+  }
   const int64_t rounds = std::max<int64_t>(1, std::min<int64_t>(4, all / (768 * STREAM_GRAIN)));
   e.n = cdiv(gsz, rounds * STREAM_GRAIN);
   e.grain = cdiv(cdiv(gsz, e.n), 4 * BLK) * 4 * BLK;
@@ -2394,6 +2401,8 @@ int validate_steps(const pb_ctx* c, const std::vector<std::pair<int, StepDesc>>&
     if (r.depth < 1 || r.stride < need) return false;
     return r.base >= lo && r.base + (int64_t)r.depth * r.stride <= hi;
   };
+  // (vectors that start anywhere reach up to 3 elements past a channel)
+  auto tail_ok = [&](const TRef& r) { return !r.base || r.base + (int64_t)r.depth * r.stride + 4 <= hi; };
   auto ptr_ok = [&](const float* p, int64_t need) { return p >= lo && p + need <= hi; };
   int idx = 0;
   for (const auto& pr : steps) {
@@ -2480,9 +2489,10 @@ int validate_steps(const pb_ctx* c, const std::vector<std::pair<int, StepDesc>>&
         } else {
           ok = ok && ref_ok(d.dx, in) && (!(d.flags & F_ADD_SKG) || ref_ok(d.skg, in));
           if (d.grain > 0)
-            ok = ok && d.grain % (4 * BLK) == 0 && (d.flags & F_DU_BUF) && (d.H * d.W) % 4 == 0 && d.n > 0 &&
-                 (int64_t)d.n * d.grain >= (int64_t)(d.C / d.G) * d.H * d.W && d.ntiles == d.G * d.n && ref_vec4(c, d.x) &&
-                 ref_vec4(c, d.dy) && ref_vec4(c, d.dx) && (!(d.flags & F_ADD_SKG) || ref_vec4(c, d.skg));
+            ok = ok && d.grain % (4 * BLK) == 0 && (d.flags & F_DU_BUF) && d.n > 0 && d.ntiles == d.G * d.n &&
+                 (int64_t)d.n * d.grain >= (int64_t)(d.C / d.G) * ((d.H * d.W + 3) / 4 * 4) && ((d.H * d.W) % 4 == 0
+                 ? ref_vec4(c, d.x) && ref_vec4(c, d.dy) && ref_vec4(c, d.dx) && (!(d.flags & F_ADD_SKG) || ref_vec4(c, d.skg))
+                 : tail_ok(d.x) && tail_ok(d.dy) && tail_ok(d.skg));
           else ok = ok && (int64_t)d.ntiles * BLK >= in;
         }
         break;
@@ -2491,8 +2501,7 @@ int validate_steps(const pb_ctx* c, const std::vector<std::pair<int, StepDesc>>&
         const int64_t dyn = (d.flags & F_DU_BUF) ? in : d.C;
         if (d.grain == 1)   // one wavefront per group
           ok = ok && !c->nt_stores && d.C / d.G <= 64 && d.C / d.G * d.H * d.W <= GNB_WAVE_MAX_N;
-        if (d.grain == 2) {   // (vectors reach up to 3 elements past a channel)
-          auto tail_ok = [&](const TRef& r) { return !r.base || r.base + (int64_t)r.depth * r.stride + 4 <= hi; };
+        if (d.grain == 2) {
           ok = ok && c->kernel_set == 0 && d.gparts <= 1 && tail_ok(d.x) && tail_ok(d.dy) && tail_ok(d.skg);
           static_assert(3 * GNB_STREAM_CPG + 2 * (GNB_STREAM_N / 256) <= LDS_FLOATS, "sums of channels and of shares in LDS");
         }
