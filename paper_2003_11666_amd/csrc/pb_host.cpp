@@ -1207,7 +1207,7 @@ bool gn_bwd_walks(const pb_ctx* c, int C, int HW, int G) {
 
 // Streaming form of a K_GNB_APPLY step (see step_gnb_apply_stream): workgroups
 // aligned to groups, STREAM_GRAIN floats each, every channel padded to whole vectors; one vector per thread in small networks
-// (us per tick with an element per thread and so: a bottleneck network at 87 pixels 112.1 and 98.4, basic ones at 32 pixels 52.2
+// (us per tick with an element per thread and so: a bottleneck network at 175 pixels 112.1 and 98.4, basic ones at 32 pixels 52.2
 // and 49.2, at 31 pixels 55.3 and 51.6).
 void stream_apply(const pb_ctx* c, StepDesc& e) {
   const int HW = e.H * e.W;

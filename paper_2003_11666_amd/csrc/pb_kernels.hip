@@ -1483,9 +1483,9 @@ __device__ __forceinline__ void step_gn_bwd_stream(const LDesc& d, int tile, int
     for (int v = 0; v < V; ++v) {
 #pragma unroll
       for (int e = 0; e < 4; ++e) {
-        const bool on = c < cpg && i0 + step * v + e < HW && !(rl && !(fmaf(sc[b], xv[b][v][e], sh[b]) > 0.f));
-        const float du = on ? dv[b][v][e] : 0.f;
-        sg = fmaf(du, on ? (xv[b][v][e] - mean) * rstd : 0.f, sg);
+        const bool in = c < cpg && i0 + step * v + e < HW;
+        const float du = in && !(rl && !(fmaf(sc[b], xv[b][v][e], sh[b]) > 0.f)) ? dv[b][v][e] : 0.f;
+        sg = fmaf(du, in ? (xv[b][v][e] - mean) * rstd : 0.f, sg);
         sb += du;
       }
     }
