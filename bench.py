@@ -30,7 +30,7 @@ HBM_PEAK_GBS = 8000.0      # MI355X published HBM3E bandwidth
 # `--pmc WRITE_SIZE` runs of this script (each scaled by what the counter reads for a plain copy of known size):
 # profiles/k_phase_counters_all_configs.md.  Figures from those runs, not a measurement of this one.  (The mlp's are of
 # k_mlp, in launches of 688 ticks on average.)
-TRAFFIC_PER_ALGORITHMIC_BYTE = {"resnet20": 2.59, "mlp": 4.8, "vgg11": 0.88, "wide": 1.12, "resnet50": 1.54}
+TRAFFIC_PER_ALGORITHMIC_BYTE = {"resnet20": 2.59, "mlp": 4.8, "vgg11": 0.88, "wide": 1.12, "resnet50": 1.53}
 TRAFFIC_SOURCE = "profiles/k_phase_counters_all_configs.md (rocprofv3 --pmc FETCH_SIZE / WRITE_SIZE passes over this command; not measured by this run)"
 UPDATE_TRAFFIC_PER_ALGORITHMIC_BYTE = 1.0   # profiles/k_update_flat_1GiB_arrays.md
 
