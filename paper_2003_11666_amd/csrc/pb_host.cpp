@@ -455,6 +455,7 @@ struct pb_ctx {
   std::vector<char> perm_what;   // per stage: the layer's predicted weights are stored in the lane order of its forward tiles (2: F_WHAT_P32)
   std::vector<char> perm_w;      // ... its weights and velocities in that of its backward-data tiles
   std::vector<char> pp_active;   // per stage: the update alternates between two copies of the master parameters
+  std::vector<int> upd_first;    // per stage: the first launch in which its update may run
   int fuse_from = -1;          // >= 0: the phases from this one on share one launch, dependencies through completion
                                // counters (0: one launch per tick)
   uint32_t fused_ticks = 0;    // ticks launched in that form so far
@@ -1288,6 +1289,19 @@ bool route_fits(const StepDesc& d) {
 }
 bool route_pool(const pb_ctx* c, const StepDesc& d) { return c->kernel_set == 0 && route_fits(d); }
 
+// Whether a step leaves a gradient in memory for its stage's K_UPDATE (others update what they have the gradient of, or none).
+bool writes_grad(const StepDesc& d) {
+  switch (d.kind) {
+    case K_GEMM: return d.g.gm == 3 && !(d.flags & F_UPD_W);
+    case K_FC_BWD_W: return !(d.flags & F_UPD_W);
+    case K_GN_BWD: return !(d.flags & F_UPD_GN);
+    case K_FC_BWD_X: return d.part != nullptr;   // (with the channel sums of a GroupNorm behind it)
+    case K_CE: return d.gb != nullptr;
+    case K_CONV_BWD_W: case K_BIAS_GRAD: case K_GNB_REDUCE: case K_HEAD: case K_HEAD_FC: return true;
+    default: return false;
+  }
+}
+
 // Compile the network into the step table.  Every step carries the phase it
 // may run in: steps of one stage's forward (or backward) chain depend on each
 // other and get consecutive phases; different stages and the two passes of
@@ -1410,14 +1424,15 @@ void compile_steps_once(pb_ctx* c, std::vector<std::pair<int, StepDesc>>& out) {
   }
   const Layout& L = c->L;
   std::vector<int> bwd0(S, 0);   // per stage: phase its backward chain starts in
-  // stages whose weight gradient is computed inside the update step (see F_WGRAD): the phase the
-  // gradient's operands are complete in, and the operands
   std::vector<std::vector<std::pair<int64_t, int64_t>>> upd(S);   // per stage: parameter ranges that other steps than K_UPDATE update
   c->perm_what.assign(S, 0);
   c->perm_w.assign(S, 0);
-  struct FusedW { int phase = -1; TRef x, dy; int64_t pp = 0; };
+  // stages whose weight gradient is computed inside the update step (see F_WGRAD): the phase of the backward-data step, which
+  // reads the weights, the one at whose start the gradient's operands are complete, and the operands
+  struct FusedW { int phase = -1, ready = 0; TRef x, dy; int64_t pp = 0; };
   std::vector<FusedW> fusedw(S);
   c->pp_active.assign(S, 0);
+  c->upd_first.assign(S, 0);
   for (int s = 0; s < S; ++s) {
     const Stage& a = c->st[s];
     const StageBufs& b = L.sb[s];
@@ -1798,6 +1813,7 @@ void compile_steps_once(pb_ctx* c, std::vector<std::pair<int, StepDesc>>& out) {
     const TRef dy_src = (s == S - 1) ? ring(c, b.dlogits, 1, a.K, 0)
                                      : ring(c, b.gradbox, 2, a.out_elems(), 0);
     TRef dz_src = dy_src;
+    int dz_ready = pb;   // the phase at whose start the layer's output gradient is complete
     if (a.post_gn) {
       StepDesc d = blank(K_GNB_REDUCE, s, t_b);
       d.C = a.K; d.H = a.OH; d.W = a.OW; d.G = a.G;
@@ -1819,6 +1835,7 @@ void compile_steps_once(pb_ctx* c, std::vector<std::pair<int, StepDesc>>& out) {
         // keep the backward GEMMs of every post-norm stage in the same phase as those of the stages
         // that need the two-step GroupNorm backward: a phase lasts as long as its longest tile, so
         // heavy steps spread over more phases cost more, not less
+        dz_ready = pb + 1;
         pb += 2;
         dz_src = d.dx;
       } else {
@@ -1836,6 +1853,7 @@ void compile_steps_once(pb_ctx* c, std::vector<std::pair<int, StepDesc>>& out) {
         e.ntiles = cdiv(a.z_elems(), BLK);
         stream_apply(c, e);
         out.push_back({pb++, e});
+        dz_ready = pb;
         dz_src = e.dx;
       }
     }
@@ -1866,7 +1884,7 @@ void compile_steps_once(pb_ctx* c, std::vector<std::pair<int, StepDesc>>& out) {
       const bool stem_split = a.post_gn && s == 0;
       const bool fc_w = fc_layer(c, d, d.gw) && !(d.flags & (F_PRE_AFFINE | F_PRE_RELU)) && ref_vec4(c, d.x);
       if (fuse_w) {
-        fusedw[s].phase = pb; fusedw[s].x = d.x; fusedw[s].dy = d.dy; fusedw[s].pp = pp_stride > 0 ? pp_stride : 0;
+        fusedw[s].phase = pb; fusedw[s].ready = dz_ready; fusedw[s].x = d.x; fusedw[s].dy = d.dy; fusedw[s].pp = pp_stride > 0 ? pp_stride : 0;
       } else if (fc_w) {
         // the dense layer in front of the loss: its bias gradient is the logits' gradient, which K_CE writes twice, and the step
         // updates the weights itself, a phase behind backward data, which reads them.  Measured without and with this (and with
@@ -2066,7 +2084,7 @@ void compile_steps_once(pb_ctx* c, std::vector<std::pair<int, StepDesc>>& out) {
       pr.first = is_bwd(pr.second) ? baseB[st_] + (pr.first - bwd0[st_]) : baseF[st_] + pr.first;
     }
     for (int s = 0; s < S; ++s)
-      if (fusedw[s].phase >= 0) fusedw[s].phase += baseB[s] - bwd0[s];
+      if (fusedw[s].phase >= 0) { fusedw[s].phase += baseB[s] - bwd0[s]; fusedw[s].ready += baseB[s] - bwd0[s]; }
   }
   // ---- a backward-data GEMM that leaves partial gradients: its consumer, the channel sums of the
   // previous stage's GroupNorm (same gradient buffer), adds them up
@@ -2093,17 +2111,17 @@ void compile_steps_once(pb_ctx* c, std::vector<std::pair<int, StepDesc>>& out) {
     for (auto& pr : out) {
       const StepDesc& e = pr.second;
       if (e.stage != s) continue;
-      if (e.kind == K_GN_BWD && (e.flags & F_UPD_GN)) { gn_fused = true; continue; }
-      if (e.flags & F_UPD_W) continue;
-      const bool writes_grad = (e.kind == K_GEMM && e.g.gm == 3) || e.kind == K_CONV_BWD_W || e.kind == K_BIAS_GRAD ||
-                               e.kind == K_GNB_REDUCE || e.kind == K_GN_BWD || e.kind == K_HEAD || e.kind == K_HEAD_FC || (e.kind == K_FC_BWD_X && e.part) || (e.kind == K_CE && e.gb);
-      if (writes_grad) last_grad_phase = std::max(last_grad_phase, pr.first);
-      if (e.kind == K_GEMM && e.g.gm == 3) gparts = std::max(gparts, e.g.parts);
+      if (e.kind == K_GN_BWD && (e.flags & F_UPD_GN)) gn_fused = true;
+      if (!writes_grad(e)) continue;
+      last_grad_phase = std::max(last_grad_phase, pr.first);
+      if (e.kind == K_GEMM) gparts = std::max(gparts, e.g.parts);
     }
+    c->upd_first[s] = last_grad_phase + 1;
     StepDesc d = blank(K_UPDATE, s, 0);
     if (fusedw[s].phase >= 0) {
       // (its operands are complete at the start of that phase; the stage's backward-data step, which reads the
       // weights, runs in it: the update follows a phase later unless it writes the other copy of the parameters)
+      c->upd_first[s] = std::max(last_grad_phase + 1, fusedw[s].pp > 0 ? fusedw[s].ready : fusedw[s].phase + 1);
       last_grad_phase = std::max(last_grad_phase, fusedw[s].pp > 0 ? fusedw[s].phase - 1 : fusedw[s].phase);
       d.ppstride = (int)fusedw[s].pp;
       d.flags |= F_WGRAD;
@@ -2227,17 +2245,7 @@ void spread_steps(const pb_ctx* c, std::vector<std::pair<int, StepDesc>>& steps)
     us[i] = d.kind == K_UPDATE ? 11.0 : d.kind == K_DOT_FWD || d.kind == K_DOT_BWD_X ? 12.0 : workgroup_us(d);
     if (d.flags & F_UPD_W) us[i] += d.kind == K_GEMM ? 10.0 * d.g.MT * d.g.NT / 16384.0 : 5.0;
     if (d.kind != K_UPDATE) continue;
-    int lo = steps[i].first;
-    if (d.kind == K_UPDATE && d.ppstride > 0) {
-      // (two copies of the weights: it waits for its stage's gradients only, not for the step that reads the weights)
-      lo = 0;
-      for (auto& q : steps) {
-        const StepDesc& e = q.second;
-        if (e.stage == d.stage && (e.kind == K_GN_BWD || e.kind == K_GNB_REDUCE || e.kind == K_GNB_APPLY || e.kind == K_BIAS_GRAD ||
-                                   (e.kind == K_GEMM && e.g.gm == 3)))
-          lo = std::max(lo, q.first + 1);
-      }
-    }
+    const int lo = c->upd_first[d.stage];
     if (lo < n_ph) movs.push_back({(int)i, lo, us[i]});
   }
   auto end_us = [&](int ph) {
@@ -2767,6 +2775,13 @@ int validate_steps(const pb_ctx* c, const std::vector<std::pair<int, StepDesc>>&
     if (!ok) return fail(PB_E_INVALID, "internal: step %d (kind %d, stage %d) fails the bounds audit", idx, d.kind, d.stage);
     ++idx;
   }
+  // an update reads its stage's gradients: it runs in a later launch than everything that writes one of them
+  std::vector<int> last(c->st.size(), -1);
+  for (const auto& pr : steps)
+    if (writes_grad(pr.second)) last[pr.second.stage] = std::max(last[pr.second.stage], pr.first);
+  for (const auto& pr : steps)
+    if (pr.second.kind == K_UPDATE && (pr.first <= last[pr.second.stage] || pr.first < c->upd_first[pr.second.stage]))
+      return fail(PB_E_INVALID, "internal: the update of stage %d runs ahead of its gradients", pr.second.stage);
   return PB_OK;
 }
 

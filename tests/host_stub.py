@@ -7,10 +7,21 @@ import sys
 ROOT = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
 
 
-def build(path):
+def build(path, planted=None):
+    """planted: texts of pb_host.cpp and what stands in their place, for tests of its own checks."""
     csrc = os.path.join(ROOT, "paper_2003_11666_amd", "csrc")
+    source = os.path.join(csrc, "pb_host.cpp")
+    if planted:
+        with open(source) as f:
+            text = f.read()
+        for old, new in planted.items():
+            assert text.count(old) == 1, old
+            text = text.replace(old, new)
+        source = os.path.join(os.path.dirname(path), "pb_host.cpp")
+        with open(source, "w") as f:
+            f.write(text.replace('"../../include/', '"%s/include/' % ROOT))
     subprocess.run(["g++", "-O1", "-std=c++17", "-fPIC", "-shared", "-D__HIP_PLATFORM_AMD__", "-I/opt/rocm/include", "-I" + csrc, "-w",
-                    os.path.join(csrc, "pb_host.cpp"), os.path.join(ROOT, "tests", "host_stub.cpp"),
+                    source, os.path.join(ROOT, "tests", "host_stub.cpp"),
                     # (the library's own pthread_create and hip* functions, whatever else the process has loaded)
                     "-static-libstdc++", "-Wl,-Bsymbolic", "-ldl", "-lpthread", "-o", path], check=True)
     return path

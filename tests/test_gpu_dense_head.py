@@ -45,3 +45,25 @@ def test_dense_head_with_other_delays(delays):
     """Zero delays: the passes of a sample one after the other, the head's backward phases behind all forward ones."""
     from tests.test_gpu_delays import test_delays_in_networks_tiled_for_throughput as follow
     follow(_basic(40), delays, {})
+
+
+def _without_biases(net):
+    return dict(net, stages=[[dict(o, bias=0) for o in st] for st in net["stages"]])
+
+
+PERCEPTRON = W._net("dense_layers", W.mlp((256, 260, 512, 17)), 256, 1, 1, 17, 1e-2, 0.9, 8, 3, 8)
+
+
+# (the weight gradient is then the only one of its stage, or the only one that its update waits for)
+@pytest.mark.parametrize("kw", [dict(update_size=2), dict(update_size=3, bwd_weights=1), dict(update_size=2, lwp_form="w"), {}], ids=str)
+@pytest.mark.parametrize("net", [_basic(40), _basic(40, hw=5), PERCEPTRON], ids=["one-step norm", "two-step norm", "no norm"])
+def test_dense_layers_without_a_bias(net, kw):
+    _follow(_without_biases(net), dict(tile_budget_us=14.0), **kw)
+
+
+@pytest.mark.parametrize("kw", [{}, dict(update_size=2)], ids=str)
+@pytest.mark.parametrize("delays", ["larger", "zero", "mixed"])
+def test_dense_layers_without_a_bias_with_other_delays(delays, kw):
+    from tests.test_gpu_delays import test_delays_in_networks_tiled_for_throughput as follow
+    for net in (_basic(40), PERCEPTRON):
+        follow(_without_biases(net), delays, kw)

@@ -27,3 +27,35 @@ def test_updates_run_behind_their_gradients(net):
             moved += p > last.get(s, 0) + 1
     big = [p for s, p, kind, l in steps if kind == "update" and int(re.search(r"tiles +(\d+)", l)[1]) >= 128]
     assert len(set(big)) > 1 or not big, "one launch holds every large update"
+
+
+def _mlp(*dims):
+    return W._net("dense", W.mlp(dims), dims[0], 1, 1, dims[-1], 1e-2, 0.9, 8, 3, 8)
+
+
+@pytest.mark.parametrize("kw", [dict(update_size=2), dict(update_size=2, bwd_weights=1), dict(update_size=2, lwp_form="w")], ids=str)
+@pytest.mark.parametrize("net", [W._net("basic", W.preact_resnet_basic((256,), 1, 4, n_classes=40), 3, 4, 4, 40, 1e-3, 0.9, 8, 3, 8),
+                                 _mlp(256, 260, 512, 17), _mlp(1024, 5)], ids=["basic", "mlp", "one-layer"])
+def test_updates_wait_for_dense_layers_without_a_bias(net, kw):
+    """No other step of such a stage need write a gradient that its update waits for."""
+    from paper_2003_11666_amd.binding import plan_summary
+    net = dict(net, stages=[[dict(o, bias=0) for o in st] for st in net["stages"]])
+    steps = re.findall(r"stage +(\d+) phase (\d+) (\w+)", plan_summary(net, tuning=dict(tile_budget_us=14.0), **kw))
+    dense = {s: int(p) for s, p, kind in steps if kind == "fc_bwd_w"}
+    assert dense, steps
+    for s, p, kind in steps:
+        assert kind != "update" or int(p) > dense.get(s, -1), steps
+
+
+def test_a_plan_whose_update_runs_ahead_of_its_gradients_is_refused(tmp_path):
+    """The audit of the step table, on a planner that puts every update into the tick's first launch."""
+    from tests import host_stub
+    path = host_stub.build(str(tmp_path / "early.so"), {"out.push_back({last_grad_phase + 1, e});": "out.push_back({0, e});"})
+    host_stub.run(path, """
+try:
+    engine(W.config('small_resnet'))
+except B.PBError as e:
+    assert 'ahead of its gradients' in str(e), e
+else:
+    raise AssertionError('accepted')
+""")
