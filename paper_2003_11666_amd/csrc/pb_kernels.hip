@@ -428,7 +428,7 @@ __device__ __forceinline__ void step_gap_stats(const LDesc& d, int tile, int t, 
       const bool on = !rl || yv > 0.f;
       sy += on ? yv : 0.f;
       sn += on ? 1.f : 0.f;
-      sx += on ? (v - mean) * rstd : 0.f;
+      sx = fmaf(on ? 1.f : 0.f, (v - mean) * rstd, sx);   // (NaN where a masked element is none the less not finite)
     };
     if (stash) {
 #pragma unroll 4
@@ -455,7 +455,8 @@ __device__ __forceinline__ void step_gap_stats(const LDesc& d, int tile, int t, 
 __device__ __forceinline__ void gap_channel_sums(const LDesc& d, int t, int c, float p) {
   const int C = UNI(d.C);
   const gfloat* unit = at(d.skg, t);
-  const float du = p / (float)UNI(d.n), sb = du * unit[c], sg = du * unit[C + c], gm = GP(d.gamma)[c];
+  // (Where no element gets through, the gradient of each is 0, whatever p is: sums of 0, or NaN where a value is not finite.)
+  const float on = unit[c], du = on > 0.f ? p / (float)UNI(d.n) : 1.f, sb = du * on, sg = du * unit[C + c], gm = GP(d.gamma)[c];
   GP(d.ggamma)[c] = sg;
   GP(d.gbeta)[c] = sb;
   GP(d.part)[c] = gm * sb;
