@@ -2174,7 +2174,8 @@ void compile_steps_once(pb_ctx* c, std::vector<std::pair<int, StepDesc>>& out) {
     if (pr.second.kind == K_GEMM && ((pr.second.g.gm != 3 && pr.second.g.parts > 1) || pr.second.g.nsub > 1 || pr.second.g.win > 0 || pr.second.g.mm || pr.second.g.dc ||
                                     pr.second.gp.nsub > 1 || pr.second.gp.win > 0)) c->nt_stores = false;
   for (auto& pr : out)
-    if ((pr.second.kind == K_UPDATE && (pr.second.flags & F_WGRAD)) || (pr.second.kind == K_GNB_REDUCE && pr.second.grain == 2) || (pr.second.kind == K_GN_BWD && pr.second.grain == 1) || pr.second.kind == K_DOT_FWD || pr.second.kind == K_DOT_BWD_X ||
+    if ((pr.second.kind == K_UPDATE && (pr.second.flags & F_WGRAD)) || (pr.second.kind == K_GNB_REDUCE && pr.second.grain == 2) || (pr.second.kind == K_GN_BWD && pr.second.grain == 1) ||
+        (pr.second.kind == K_GN_STATS && pr.second.grain == 1 && (pr.second.H * pr.second.W) % 4 != 0) || pr.second.kind == K_DOT_FWD || pr.second.kind == K_DOT_BWD_X ||
         pr.second.kind == K_FC_FWD || pr.second.kind == K_FC_BWD_X || pr.second.kind == K_FC_BWD_W)
       c->nt_stores = false;
   if (c->nt_stores) {

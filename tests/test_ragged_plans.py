@@ -1,4 +1,5 @@
 """Tiles of networks on odd maps: rows of no multiple of 4 pixels are staged in vectors and planned as such."""
+import ctypes
 import re
 
 import pytest
@@ -20,3 +21,15 @@ def test_the_first_layers_gradient_keeps_its_shares():
     net = W._net("stem", W.preact_resnet_bottleneck((1, 3, 6, 1), 32, 16, n_classes=76), 3, 127, 127, 76, 1e-3, 0.9, 8, 3, 8)
     steps = [l for l in plan_summary(net).splitlines() if "C3x127x127" in l and "gm3" in l]
     assert len(steps) == 1 and int(re.search(r"tiles +(\d+)", steps[0])[1]) >= 96, steps
+
+
+@pytest.mark.parametrize("hw", [(7, 7), (6, 6), (5, 8), (14, 14)])
+@pytest.mark.parametrize("budget", [-1.0, 14.0])
+def test_many_small_groups_are_planned_with_non_temporal_stores_asked_for(hw, budget):
+    """33 groups of 4 channels in 17 layers: a wavefront takes a group's statistics on maps of no multiple of 4 pixels too."""
+    from paper_2003_11666_amd import binding as B
+    st = [[W.conv(3, 132, 1, 1, 0)]] + [[W.gn(33, 132), W.relu(), W.conv(132, 132, 1, 1, 0)] for _ in range(16)]
+    st.append([W.gn(33, 132), W.relu(), W.gap(), W.linear(132, 5), W.ce()])
+    desc, keep = B.marshal_net(W._net("groups", st, 3, *hw, 5, 1e-3, 0.9, 8, 3, 8), tuning=dict(tile_budget_us=budget, nt_stores=1))
+    lib = B.load_library()
+    assert lib.pb_arena_bytes(ctypes.byref(desc), None) > 0, lib.pb_last_error()
