@@ -2511,7 +2511,7 @@ int validate_steps(const pb_ctx* c, const std::vector<std::pair<int, StepDesc>>&
         if (d.grain == 1)   // one wavefront per group
           ok = ok && !c->nt_stores && d.C / d.G <= 64 && d.C / d.G * d.H * d.W <= GNB_WAVE_MAX_N;
         if (d.grain == 2) {
-          ok = ok && c->kernel_set == 0 && d.gparts <= 1 && tail_ok(d.x) && tail_ok(d.dy) && tail_ok(d.skg);
+          ok = ok && d.G > 0 && d.C % d.G == 0 && d.C / d.G <= GNB_STREAM_CPG && (int64_t)(d.C / d.G) * d.H * d.W <= GNB_STREAM_N && c->kernel_set == 0 && d.gparts <= 1 && tail_ok(d.x) && tail_ok(d.dy) && tail_ok(d.skg);
           static_assert(3 * GNB_STREAM_CPG + 2 * (GNB_STREAM_N / 256) <= LDS_FLOATS, "sums of channels and of shares in LDS");
         }
         ok = ok && (d.grain == 2 || gn_bwd_fits(d.C, d.H * d.W, d.G)) && d.ntiles == (d.grain == 1 ? cdiv(d.G, BLK / 64) : d.G) && !(d.flags & F_DU_POOL) &&
