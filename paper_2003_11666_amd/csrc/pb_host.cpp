@@ -2723,7 +2723,8 @@ int validate_steps(const pb_ctx* c, const std::vector<std::pair<int, StepDesc>>&
         // vectors at the end of a row or a segment of no multiple of 4 floats reach up to 3 floats past their tensor
         auto tail_ok = [&](const TRef& r) { return !r.base || r.base + (int64_t)r.depth * r.stride + 4 <= hi; };
         ok = ok && tail_ok(d.x) && tail_ok(d.dy) && tail_ok(d.skip) &&
-             (d.g.gm == 3 || d.w + (int64_t)std::max(0, (d.pmask & PF_W) ? d.pdepth - 1 : 0) * d.pstride + (int64_t)d.K * d.C * d.k * d.k + 4 <= hi);
+             (d.g.gm == 3 || d.w + (int64_t)std::max(0, (d.pmask & PF_W) ? d.pdepth - 1 : 0) * d.pstride + (int64_t)d.K * d.C * d.k * d.k + 4 <= hi) &&
+             (!(d.flags & F_PROJ) || d.g.gm != 1 || d.wp + (int64_t)std::max(0, (d.pmask & PF_WP) ? d.pdepth - 1 : 0) * d.pstride + (int64_t)d.K * d.sC + 4 <= hi);
         ok = ok && d.ntiles == d.g.tiles && cfg_ok(d.g, d.C, d.H, d.W, d.k, d.stride, d.pad) &&
              ptr_ok((const float*)d.tq, d.g.QCpad) && ptr_ok((const float*)d.tn, d.g.N) &&
              (!(d.flags & F_PROJ) || d.g.gm != 1 || (ptr_ok((const float*)d.tq2, d.gp.QCpad) && ptr_ok((const float*)d.tn2, d.gp.N)));
