@@ -2626,6 +2626,7 @@ int validate_steps(const pb_ctx* c, const std::vector<std::pair<int, StepDesc>>&
       }
       case K_GEMM: {
         auto cfg_ok = [&](const GemmCfg& g, int C, int H, int W, int k, int s, int pad) {
+          const int pre = &g == &d.gp ? 0 : d.flags & (F_PRE_AFFINE | F_PRE_RELU);   // (the skip tensor is projected as it is)
           const int kk = k * k;
           bool o = g.wm * g.wn * g.wk == 4 && (g.ni == 1 || g.ni == 2 || g.ni == 4) && g.MT == 16 * g.wm && g.NT == 16 * g.ni * g.wn &&
                    g.nsub >= 1 && (g.nsub == 1 || (g.wk == 1 && !(d.flags & F_PROJ && g.gm == 1))) && g.tiles_n == cdiv(cdiv(g.N, g.NT), g.nsub) &&
@@ -2653,7 +2654,7 @@ int validate_steps(const pb_ctx* c, const std::vector<std::pair<int, StepDesc>>&
             if (g.win) o = o && g.win == g.NT && g.Wp == g.NT + 8 && H == 1 && d.OH == 1 && k == 1 && s == 1 && pad == 0 && g.gm != 3;
             else o = o && g.Wp == (wsrc + 3) / 4 * 4 + 8;
             o = o && (!g.win || wsrc % 4 == 0) && g.xoff == 4 - hl_ && hl_ <= 4 && (g.gm != 2 || s == 1) &&
-                (g.o_patch % 4) == 0 && !(d.flags & (F_PRE_AFFINE | F_PRE_RELU) && g.gm != 2);
+                (g.o_patch % 4) == 0 && !(pre && g.gm != 2);
           } else {
             o = o && g.xoff == 0 && g.win == 0;
           }

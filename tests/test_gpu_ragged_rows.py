@@ -33,3 +33,13 @@ def test_ragged_stems_and_pools_follow_the_oracle(hw):
     # (a ReLU or a pooling window decided the other way by the last bit shows in the gradients of 200 000 activations)
     for tuning in ({}, dict(tile_budget_us=14.0)):
         _follow(net, tuning, tol=2e-3)
+
+
+@pytest.mark.parametrize("tuning", [{}, dict(tile_budget_us=14.0)], ids=["latency", "throughput"])
+@pytest.mark.parametrize("stride", [1, 2])
+@pytest.mark.parametrize("hw,c", [(5, 5), (6, 9), (7, 16), (8, 6), (12, 20), (33, 18)])
+def test_projections_beside_a_layer_behind_a_relu_follow_the_oracle(hw, c, stride, tuning):
+    st = [[W.conv(3, c, 3, 1, 1)], [W.relu(), W.conv(c, 2 * c + 1, 3, stride, 1)],
+          [W.relu(), W.conv(2 * c + 1, 2 * c + 1, 3, 1, 1), W.add(1, c, 2 * c + 1, stride, 1)],
+          [W.gn(1, 2 * c + 1), W.relu(), W.gap(), W.linear(2 * c + 1, 5, bias=1), W.ce()]]
+    _follow(_net(st, hw, hw), tuning, tol=5e-4)

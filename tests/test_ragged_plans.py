@@ -33,3 +33,16 @@ def test_many_small_groups_are_planned_with_non_temporal_stores_asked_for(hw, bu
     desc, keep = B.marshal_net(W._net("groups", st, 3, *hw, 5, 1e-3, 0.9, 8, 3, 8), tuning=dict(tile_budget_us=budget, nt_stores=1))
     lib = B.load_library()
     assert lib.pb_arena_bytes(ctypes.byref(desc), None) > 0, lib.pb_last_error()
+
+
+@pytest.mark.parametrize("stride", [1, 2])
+@pytest.mark.parametrize("hw", range(4, 13))
+def test_projections_beside_a_layer_behind_a_relu_are_planned(hw, stride):
+    """The layer's own rows are rectified on their way into LDS, element by element; the skip tensor's come in vectors."""
+    from paper_2003_11666_amd import binding as B
+    st = [[W.conv(3, 5, 3, 1, 1)], [W.relu(), W.conv(5, 7, 3, stride, 1)], [W.relu(), W.conv(7, 7, 3, 1, 1), W.add(1, 5, 7, stride, 1)],
+          [W.gn(1, 7), W.relu(), W.gap(), W.linear(7, 5), W.ce()]]
+    lib = B.load_library()
+    for tuning in (None, dict(tile_budget_us=14.0)):
+        desc, keep = B.marshal_net(W._net("projection", st, 3, hw, hw, 5, 1e-3, 0.9, 8, 3, 8), tuning=tuning)
+        assert lib.pb_arena_bytes(ctypes.byref(desc), None) > 0, lib.pb_last_error()
