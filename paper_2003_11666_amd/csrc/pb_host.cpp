@@ -608,6 +608,7 @@ static int tile_rows(int NT, int rowlen, int nrows) {
 
 bool fit_gemm(GemmCfg& g, int C, int H, int W, int K, int OH, int OW, int k, int s, int pad, bool allow_vec, bool fine,
               int rows_cap = 0) {
+  const GemmCfg asked = g;
   const int mode = g.gm, kk = k * k;
   g.MT = 16 * g.wm; g.NT = 16 * g.ni * g.wn;
   if (g.nsub < 1 || g.wk != 1) g.nsub = 1;   // the split of the reduction reuses the A block's LDS
@@ -701,6 +702,14 @@ bool fit_gemm(GemmCfg& g, int C, int H, int W, int K, int OH, int OW, int k, int
   g.o_A = g.QCpad;
   g.o_patch = (int)(g.o_A + a_size(g.QC));
   if (g.o_patch % 4 || g.o_patch + (g.CC * g.PR * g.Wp + 3) / 4 * 4 > g_gemm_lds) return false;
+  // Rows of one pixel take 12 floats of the patch as a vector and its halo, 3 element by element: where LDS holds fewer channels
+  // per chunk for that, they go element by element.  Us per tick in vectors and so: VGG of 24 to 192 channels at 6 pixels 61.0 and
+  // 57.8, of 48 to 384 114.5 and 108.4; every width of one pixel so, also in as many chunks: 16 to 128 channels 43.1 and 43.9, 40 to
+  // 320 91.0 and 92.4.  Rows of 2 and 3 pixels keep their vectors (bottleneck networks at 40 pixels 75.8 and 76.7).
+  if (g.vec == 1 && g.n_chunks > 1 && (mode == 2 ? OW : W) == 1 && !g.win) {
+    GemmCfg e = asked;
+    if (fit_gemm(e, C, H, W, K, OH, OW, k, s, pad, false, fine, rows_cap) && e.n_chunks < g.n_chunks) g = e;
+  }
   return true;
 }
 

@@ -43,3 +43,10 @@ def test_projections_beside_a_layer_behind_a_relu_follow_the_oracle(hw, c, strid
           [W.relu(), W.conv(2 * c + 1, 2 * c + 1, 3, 1, 1), W.add(1, c, 2 * c + 1, stride, 1)],
           [W.gn(1, 2 * c + 1), W.relu(), W.gap(), W.linear(2 * c + 1, 5, bias=1), W.ce()]]
     _follow(_net(st, hw, hw), tuning, tol=5e-4)
+
+
+@pytest.mark.parametrize("tuning", [{}, dict(tile_budget_us=14.0)], ids=["latency", "throughput"])
+@pytest.mark.parametrize("net", [_plain(192, 200, 3, 1, 1, 1), _plain(130, 192, 3, 2, 2, 1), _plain(192, 96, 3, 1, 5, 1), _plain(70, 200, 5, 1, 1, 1)],
+                         ids=["1x1", "stride", "5x1", "k5"])
+def test_rows_of_one_pixel_in_several_chunks_follow_the_oracle(net, tuning):
+    _follow(net, tuning, tol=5e-4)

@@ -46,3 +46,14 @@ def test_projections_beside_a_layer_behind_a_relu_are_planned(hw, stride):
     for tuning in (None, dict(tile_budget_us=14.0)):
         desc, keep = B.marshal_net(W._net("projection", st, 3, hw, hw, 5, 1e-3, 0.9, 8, 3, 8), tuning=tuning)
         assert lib.pb_arena_bytes(ctypes.byref(desc), None) > 0, lib.pb_last_error()
+
+
+@pytest.mark.parametrize("width", [24, 48])
+def test_rows_of_one_pixel_are_no_more_chunks_for_their_vectors(width):
+    """3x3 layers of 8 x width channels on 1x1 maps: as many channels per chunk as LDS holds element by element."""
+    from perf.cases import _network, _train
+    net = _network(_train(None, "vgg", 0, hw=6, width=width, groups=8))
+    c = 8 * width
+    steps = [l for l in plan_summary(net).splitlines() if re.search(rf"C{c}x1x1 K{c}x1x1 k3 s1 \| gm[12]", l)]
+    assert len(steps) >= 4, steps
+    assert all(int(re.search(r"chunks (\d+)/", l)[1]) == width // 12 for l in steps), steps
