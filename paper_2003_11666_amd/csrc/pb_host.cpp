@@ -2207,12 +2207,15 @@ double workgroup_us(const StepDesc& d) {
     us = est_tile_us(one, d.k);
     if (d.gp.gm) us += est_tile_us(d.gp, 1);
   } else if (d.kind == K_GN_STATS || d.kind == K_GN_BWD) {
-    // (statistics of a group that no workgroup holds in its registers, beyond 32768 elements, take three
-    // passes over memory: 15 870 elements took 35 us that way.  Started behind weight-gradient tiles they were the end of a launch of a
-    // basic network of 60, 120 and 240 channels: 182 us per tick instead of 166)
+    // (statistics of a group that step_gn_stats does not hold in registers -- no multiple of 4 elements, more than 32768 or more than
+    // 256 channels -- by way of LDS or in three passes over memory: 17 298 elements 21 us, 12 800 of 512 channels 13, 27 378 25, 50 176
+    // 45, 131 072 96.  Priced at 0.1 us per 256 elements where they are ragged, 0.5 behind many channels and 1.0 beyond registers, they
+    // started behind shorter tiles, or ahead of longer ones: basic networks of 36 channels at 31 and 39 pixels 74.9 and 91.4 us per
+    // tick, 70.4 and 84.9 so, of 52 at 31 81.3 and 73.8; of 101 others 19 faster by 0.8 to 8, four slower by 0.7 to 1.7 %, the most
+    // 36, 72 and 144 channels at 39 pixels, 97.1 and 98.8)
     const int64_t cpg = d.C / std::max(1, d.G), n = cpg * d.H * d.W;
-    const bool passes = d.kind == K_GN_STATS && (n > 32768 || cpg > BLK);
-    us = 4.0 + (double)n / BLK * (!passes ? (d.kind == K_GN_STATS && n % 4 ? 0.1 : 0.05) : n > 32768 ? 1.0 : 0.5);
+    const bool regs = d.kind == K_GN_BWD || (n % 4 == 0 && n <= 32768 && cpg <= BLK);
+    us = 4.0 + (double)n / BLK * (regs ? 0.05 : 0.2);
     if (d.kind == K_GN_BWD && d.grain == 2) us = gn_walk_us(n);
   } else if (d.kind == K_GNB_REDUCE) {
     // (routing the gradient back through a max-pool costs a window search per element: about 2 us per

@@ -57,3 +57,15 @@ def test_rows_of_one_pixel_are_no_more_chunks_for_their_vectors(width):
     steps = [l for l in plan_summary(net).splitlines() if re.search(rf"C{c}x1x1 K{c}x1x1 k3 s1 \| gm[12]", l)]
     assert len(steps) >= 4, steps
     assert all(int(re.search(r"chunks (\d+)/", l)[1]) == width // 12 for l in steps), steps
+
+
+def test_statistics_start_by_how_long_their_form_takes():
+    """24 642 elements of a map of no multiple of 4 pixels, in three passes over memory, ahead of 12 800 elements of 512 channels by way
+    of LDS, and those ahead of as many in registers."""
+    st = [[W.conv(3, 36, 3, 1, 1)], [W.gn(2, 36), W.relu(), W.conv(36, 512, 1, 8, 0)], [W.gn(1, 512), W.relu(), W.conv(512, 512, 1, 1, 0)],
+          [W.gn(4, 512), W.relu(), W.conv(512, 8, 1, 1, 0)], [W.gn(1, 8), W.relu(), W.gap(), W.linear(8, 5), W.ce()]]
+    plan = plan_summary(W._net("stats", st, 3, 37, 37, 5, 1e-3, 0.9, 8, 3, 8), tuning=dict(tile_budget_us=16.0))
+    order = [(m[2], m[1]) for m in re.finditer(r"phase (\d+) gn_stats .* C(\d+x\d+x\d+) ", plan)]
+    assert order == [("36x37x37", "0"), ("512x5x5", "0"), ("512x5x5", "0")], order
+    stages = [int(m[1]) for m in re.finditer(r"stage +(\d+) phase 0 gn_stats", plan)]
+    assert stages == [1, 2, 3], stages
