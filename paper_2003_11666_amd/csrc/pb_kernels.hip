@@ -424,29 +424,22 @@ __device__ __forceinline__ void step_gap_stats(const LDesc& d, int tile, int t, 
     const float sc = gl[c] * rstd, sh = fmaf(-mean, sc, bl[c]);
     // (four sums per lane, as short as those of a workgroup per channel: see step_head_fc on what a long one costs)
     float sn = 0.f, sy4[4] = {0.f, 0.f, 0.f, 0.f}, sx4[4] = {0.f, 0.f, 0.f, 0.f};
-    // V values of a lane in flight; past the channel's end its last one again, which counts for nothing.  (A guard around each read
-    // made every one a round trip: 64 channels in two groups at 40 pixels 139 us per tick instead of 96.)
-    auto each = [&](auto VV, auto at_) {
-      constexpr int V = decltype(VV)::value;
-      for (int i = l; i < HW + l; i += V * step) {
-        float v[V];
+    auto add = [&](int u, float v) {
+      const float yv = fmaf(sc, v, sh);
+      const bool on = !rl || yv > 0.f;
+      sy4[u] += on ? yv : 0.f;
+      sn += on ? 1.f : 0.f;
+      sx4[u] = fmaf(on ? 1.f : 0.f, (v - mean) * rstd, sx4[u]);   // (NaN where a masked element is none the less not finite)
+    };
+    auto each = [&](auto at_) {
+      for (int i = l; i < HW; i += 4 * step) {
 #pragma unroll
-        for (int u = 0; u < V; ++u) v[u] = at_(i + u * step < HW ? i + u * step : HW - 1);
-#pragma unroll
-        for (int u = 0; u < V; ++u) {
-          const float yv = fmaf(sc, v[u], sh);
-          const bool on = i + u * step < HW && (!rl || yv > 0.f);
-          sy4[u & 3] += on ? yv : 0.f;
-          sn += on ? 1.f : 0.f;
-          sx4[u & 3] = fmaf(on ? 1.f : 0.f, (v[u] - mean) * rstd, sx4[u & 3]);   // (NaN where a masked element is none the less not finite)
-        }
+        for (int u = 0; u < 4; ++u)
+          if (i + u * step < HW) add(u, at_(i + u * step));
       }
     };
-    // (no more forms than these: what a launch runs once comes from memory, and with eight of them basic networks of 24 channels at 12
-    // pixels took 19.1 us per tick, 18.4 so)
-    if (!stash) each(IConst<8>(), [&](int i) { return xp[(size_t)c * HW + i]; });
-    else if (HW <= step) each(IConst<1>(), [&](int i) { return xs[c * HW + i]; });
-    else each(IConst<4>(), [&](int i) { return xs[c * HW + i]; });
+    if (stash) each([&](int i) { return xs[c * HW + i]; });
+    else each([&](int i) { return xp[(size_t)c * HW + i]; });
     float sy = (sy4[0] + sy4[1]) + (sy4[2] + sy4[3]), sx = (sx4[0] + sx4[1]) + (sx4[2] + sx4[3]);
     if (wide) { sy = wave_sum(sy); sn = wave_sum(sn); sx = wave_sum(sx); }
     else { sy = row_sum(sy); sn = row_sum(sn); sx = row_sum(sx); }
@@ -2984,11 +2977,9 @@ __device__ __forceinline__ void step_head_fc(const LDesc& d, int t, lfloat* red,
     // matrix cores: 40 channels at 32 pixels 1.56e-7, 1.16e-7, 1.30e-7, 24 channels at 20 1.85e-7, 1.51e-7, 1.58e-7.)
     float p[8] = {0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f};
     for (int q = 0; q < R; q += 8) {
-      float v[8];
 #pragma unroll
-      for (int u = 0; u < 8; ++u) v[u] = ps[(q + u < R ? q + u : q) * C + c];
-#pragma unroll
-      for (int u = 0; u < 8; ++u) p[u] += q + u < R ? v[u] : 0.f;
+      for (int u = 0; u < 8; ++u)
+        if (q + u < R) p[u] += ps[(q + u) * C + c];
     }
     const float s = ((p[0] + p[1]) + (p[2] + p[3])) + ((p[4] + p[5]) + (p[6] + p[7]));
     at(d.dx, t)[c] = s;
