@@ -422,25 +422,21 @@ __device__ __forceinline__ void step_gap_stats(const LDesc& d, int tile, int t, 
   const int step = wide ? 64 : 16, l = wide ? lane : tid & 15;
   for (int c = wide ? wv : tid >> 4; c < cpg; c += wide ? BLK / 64 : BLK / 16) {
     const float sc = gl[c] * rstd, sh = fmaf(-mean, sc, bl[c]);
-    // (four sums per lane, as short as those of a workgroup per channel: see step_head_fc on what a long one costs)
-    float sn = 0.f, sy4[4] = {0.f, 0.f, 0.f, 0.f}, sx4[4] = {0.f, 0.f, 0.f, 0.f};
-    auto add = [&](int u, float v) {
+    float sy = 0.f, sn = 0.f, sx = 0.f;
+    auto add = [&](float v) {
       const float yv = fmaf(sc, v, sh);
       const bool on = !rl || yv > 0.f;
-      sy4[u] += on ? yv : 0.f;
+      sy += on ? yv : 0.f;
       sn += on ? 1.f : 0.f;
-      sx4[u] = fmaf(on ? 1.f : 0.f, (v - mean) * rstd, sx4[u]);   // (NaN where a masked element is none the less not finite)
+      sx = fmaf(on ? 1.f : 0.f, (v - mean) * rstd, sx);   // (NaN where a masked element is none the less not finite)
     };
-    auto each = [&](auto at_) {
-      for (int i = l; i < HW; i += 4 * step) {
-#pragma unroll
-        for (int u = 0; u < 4; ++u)
-          if (i + u * step < HW) add(u, at_(i + u * step));
-      }
-    };
-    if (stash) each([&](int i) { return xs[c * HW + i]; });
-    else each([&](int i) { return xp[(size_t)c * HW + i]; });
-    float sy = (sy4[0] + sy4[1]) + (sy4[2] + sy4[3]), sx = (sx4[0] + sx4[1]) + (sx4[2] + sx4[3]);
+    if (stash) {
+#pragma unroll 4
+      for (int i = l; i < HW; i += step) add(xs[c * HW + i]);
+    } else {
+#pragma unroll 8
+      for (int i = l; i < HW; i += step) add(xp[(size_t)c * HW + i]);
+    }
     if (wide) { sy = wave_sum(sy); sn = wave_sum(sn); sx = wave_sum(sx); }
     else { sy = row_sum(sy); sn = row_sum(sn); sx = row_sum(sx); }
     if (l == 0) {
@@ -2972,16 +2968,8 @@ __device__ __forceinline__ void step_head_fc(const LDesc& d, int t, lfloat* red,
   if (act) *(lv4*)(ps + r * C + 4 * c4) = acc;
   __syncthreads();
   for (int c = tid; c < C; c += BLK) {
-    // Every gradient of the network is a multiple of these: eight chains, not one of up to 256 terms.  (Error of all gradients
-    // against float64, weights held fixed, with one chain and one sum per lane in step_gap_stats, so, and with the layer on the
-    // matrix cores: 40 channels at 32 pixels 1.56e-7, 1.16e-7, 1.30e-7, 24 channels at 20 1.85e-7, 1.51e-7, 1.58e-7.)
-    float p[8] = {0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f};
-    for (int q = 0; q < R; q += 8) {
-#pragma unroll
-      for (int u = 0; u < 8; ++u)
-        if (q + u < R) p[u] += ps[(q + u) * C + c];
-    }
-    const float s = ((p[0] + p[1]) + (p[2] + p[3])) + ((p[4] + p[5]) + (p[6] + p[7]));
+    float s = 0.f;
+    for (int q = 0; q < R; ++q) s += ps[q * C + c];
     at(d.dx, t)[c] = s;
     if (d.part) gap_channel_sums(d, t, c, s);
   }

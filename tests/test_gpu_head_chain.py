@@ -78,29 +78,3 @@ def test_head_chain_with_bf16_activations():
         assert np.linalg.norm(eng.read_weights() - ref["read_weights"]) < 1e-4 * np.linalg.norm(ref["read_weights"])
         assert np.linalg.norm(eng.loss_history() - ref["loss_history"]) < 1e-3 * np.linalg.norm(ref["loss_history"])
         eng.close()
-
-
-@pytest.mark.parametrize("c,k", [(8, 128), (24, 42), (40, 30)])
-def test_pooled_gradients_are_sums_of_short_chains(c, k):
-    """Weights held fixed and no momentum: the velocity of the head's shift is the pooled gradient, a sum over the outputs, times the
-    share of a channel that gets through.  One chain of 128 terms of either sign is off by 2^-24 sqrt(128 / 6), 2.7e-7 of the sum,
-    eight of 16 by 0.9e-7; the loss and its gradient in front add about 1e-7 (independent: 1.35e-7 together)."""
-    import numpy as np
-    from oracle import pb_oracle as O
-    from paper_2003_11666_amd import PBEngine
-    from tests.parity_util import tensor_slices
-    net = _net(c, 1, k, 3)
-    assert ("1", "head_fc") in _kinds(net, {})
-    (xs, ys), S = W.sample_pool(net), len(net["stages"])
-    lo, hi = next((a, b) for s, name, a, b in tensor_slices(net) if s == S - 1 and name == "beta")
-    eng, ref, err = PBEngine(net, lr=0.0, momentum=0.0), O.PBOracle(net, lr=0.0, momentum=0.0), []
-    for t in range(2 * S + 32):
-        for e in (eng, ref):
-            e.tick(xs[t % len(ys)], ys[(t * 5) % len(ys)])
-        if t >= 2 * S:
-            want = ref.read_velocity()[lo:hi]
-            err.append(np.linalg.norm(eng.read_velocity()[lo:hi].astype(np.float64) - want) / np.linalg.norm(want))
-    eng.close()
-    rms = np.sqrt(np.mean(np.square(err)))
-    print(f"error of the pooled gradients against float64: {rms:.2e}")
-    assert rms < 1.35e-7, err
