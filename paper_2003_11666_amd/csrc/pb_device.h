@@ -188,7 +188,8 @@ struct StepDesc {
   int32_t wait_idx[3], wait_n[3];
   int32_t grain;            // > 0: streaming form of an elementwise step, floats per workgroup (K_COPY, K_GNB_APPLY);
                             // K_GNB_REDUCE: 1 = one wavefront per channel, 2 = the same, 16-byte requests; K_GN_STATS, K_GN_BWD:
-                            // 1 = one wavefront per group; K_GN_BWD: 2 = a group beyond a workgroup's registers
+                            // 1 = one wavefront per group; K_GN_BWD: 2 = a group walked twice (beyond a workgroup's
+                            // registers, or of a map of no multiple of 4 pixels)
   GemmCfg g;     // main operand set of a K_GEMM step
   GemmCfg gp;    // projection of the skip tensor accumulated into the same tile (forward only)
   TRef x;        // op input (forward) / saved input (backward)

@@ -1203,6 +1203,9 @@ double gn_walk_us(int64_t n) { return 13.0 + 0.62e-3 * (double)n; }
 // tile they allow, less strictly from 4 groups on (with 2 groups, 5184 elements in launches of 16 us 50.7 us per tick in two steps
 // and 52.7, 17 150 elements 54.6 and 66.5), and only where the two steps have no vectors, on maps of no multiple of 4 pixels
 // (others, 5120 elements: 73.8 and 76.3).  Small networks: 4608 elements in two steps 54.4 and 47.0, 5760 elements 31.9 and 36.8.
+// From 4 groups on, us per tick with the line that 2 groups have and with the looser one: 48 and 96 channels at 23 pixels 57.0 and
+// 51.3, 64, 128 and 256 at 21 83.4 and 78.3, 64 and 128 at 27 54.1 and 52.7; bottleneck stages in 4 groups at 102 pixels 215.2 and
+// 219.8, 48 and 96 channels in 8 groups at 35 68.0 and 69.2; twenty others within 1 %.
 // Us per tick in two steps and so: bottleneck networks at 195 pixels 424 and 327, 219 pixels 227 and 178, 146 pixels 334 and 297,
 // 102 pixels 97 and 81, ResNet-50 434 and 427 (its 7x7 maps), basic ones at 37 pixels 98 and 88, at 15 pixels 37 and 31; up to
 // 131 072 elements at 195 pixels 332.
@@ -1224,9 +1227,10 @@ void stream_apply(const pb_ctx* c, StepDesc& e) {
   if (!(e.flags & F_DU_BUF) || (c->kernel_set != 0 && (g_tile_budget_us <= 0 || HW % 4))) return;
   if (HW % 4 == 0 && (!ref_vec4(c, e.x) || !ref_vec4(c, e.dy) || !ref_vec4(c, e.dx) || ((e.flags & F_ADD_SKG) && !ref_vec4(c, e.skg)))) return;
   const int64_t gsz = (int64_t)(e.C / e.G) * ((HW + 3) / 4 * 4);
-  // up to four rounds per workgroup where the tick's passes of this kind are more than the chip has places for (ResNet-50 at
-  // 224 pixels: 3482 workgroups of one round, and a wavefront in place of a workgroup for the sums of 1344 channels, 439.4 us per
-  // tick; 1500 of up to four 434.0)
+  // up to four rounds per workgroup where the tick's passes of this kind are more than the chip has places for.  Us per tick with one
+  // round, so, and with four in every network: 64-channel stages 3-4-2-1 at 224 pixels 311.3, 309.9 and 311.0, ResNet-50 at 224 430.1
+  // each, at 192 360.1, 360.1 and 361.1, the wide network 90.9, 90.9 and 95.8, 128 and 256 channels at 32 97.1, 97.1 and 103.0; the
+  // stages at 128 alone are faster with four (230.0, 230.0 and 226.3).
   int64_t all = 0;
   for (const Stage& a : c->st)
     if (a.pre_gn && !gn_bwd_fits(a.Cin, a.Hin * a.Win, a.G)) all += a.in_elems();
@@ -2210,9 +2214,9 @@ double workgroup_us(const StepDesc& d) {
     // (statistics of a group that step_gn_stats does not hold in registers -- no multiple of 4 elements, more than 32768 or more than
     // 256 channels -- by way of LDS or in three passes over memory: 17 298 elements 21 us, 12 800 of 512 channels 13, 27 378 25, 50 176
     // 45, 131 072 96.  Priced at 0.1 us per 256 elements where they are ragged, 0.5 behind many channels and 1.0 beyond registers, they
-    // started behind shorter tiles, or ahead of longer ones: basic networks of 36 channels at 31 and 39 pixels 74.9 and 91.4 us per
-    // tick, 70.4 and 84.9 so, of 52 at 31 81.3 and 73.8; of 101 others 19 faster by 0.8 to 8, four slower by 0.7 to 1.7 %, the most
-    // 36, 72 and 144 channels at 39 pixels, 97.1 and 98.8)
+    // started behind shorter tiles, or ahead of longer ones: basic networks of 36 channels at 31 and 39 pixels 74.3 and 90.5 us per
+    // tick, 69.5 and 84.3 so, of 52 at 31 80.6 and 72.9; of 101 others 19 faster by 1.2 to 7.5 %, four slower by 0.7 to 1.4 %, the
+    // most 36, 72 and 144 channels at 39 pixels, 95.8 and 97.1)
     const int64_t cpg = d.C / std::max(1, d.G), n = cpg * d.H * d.W;
     const bool regs = d.kind == K_GN_BWD || (n % 4 == 0 && n <= 32768 && cpg <= BLK);
     us = 4.0 + (double)n / BLK * (regs ? 0.05 : 0.2);

@@ -777,14 +777,16 @@ __device__ __forceinline__ void step_gnb_reduce_wave(const LDesc& d, int tile, i
   }
 }
 
-// Maps of more than 256 and fewer than 1024 pixels (a multiple of 4) with a plain gradient buffer: one wavefront per
-// channel, the channel in rounds of four 16-byte requests per lane and operand, no barrier.  Bound by the memory round trip: a
-// workgroup per channel holds a slot for 3.7 us with one request per lane.  Measured, us per tick with a workgroup per
-// channel and with a wavefront: ResNet-50 at 224 pixels (2816 channels of 28x28) 590.3 and 581.7; basic networks at 24, 28
-// and 40 pixels 87.3 and 86.8, 95.3 and 95.0, 133.8 and 134.3; a bottleneck network at 224 465.4 and 463.7.  At 1024 pixels,
-// where that request fills every lane, it depends: the wide network 125.7 and 128.1, but a basic one of 128 and 256 channels
-// 253.7 and 252.1 and bottleneck ones at 128 pixels 227.6 and 225.0, 118.1 and 116.9; the line stands below, where no
-// network loses more than 0.4 %.
+// Maps of more than 256 and fewer than 1024 pixels (a multiple of 4; up to 4096 where more than 1024 channels of the network have
+// such maps) with a plain gradient buffer: one wavefront per channel, the channel in rounds of four 16-byte requests per lane and
+// operand, no barrier.  Bound by the memory round trip: a workgroup per channel holds a slot for 3.7 us with one request per lane.
+// Measured, us per tick with a workgroup per channel and with a wavefront: ResNet-50 at 224 pixels (2816 channels of 28x28) 590.3
+// and 581.7; basic networks at 24, 28 and 40 pixels 87.3 and 86.8, 95.3 and 95.0, 133.8 and 134.3; a bottleneck network at 224 465.4
+// and 463.7.  From 1024 pixels on it takes channels enough that their workgroups wait for places.  With the line at 1020, as it is,
+// and at 4096 for every network: ResNet-50 at 224 pixels 431.9, 430.1 and 429.9, at 192 363.7, 360.1 and 360.2, its stages at 256
+// 643.5, 629.5 and 629.8, at 128 233.0, 230.0 and 230.0, four layers of 256 channels at 32 226.2, 223.7 and 223.6; fewer channels:
+// bottleneck stages of 32 at 224 193.9, 193.9 and 190.6, the wide network 90.8, 90.9 and 90.9, 64 and 128 channels at 40 79.2, 79.2
+// and 79.4.
 __device__ __forceinline__ void step_gnb_reduce_wave4(const LDesc& d, int tile, int t) {
   const int lane = threadIdx.x & 63, c = tile * (BLK / 64) + UNI((int)(threadIdx.x >> 6));
   const int C = UNI(d.C), G = UNI(d.G), HW = UNI(d.H) * UNI(d.W);
