@@ -6,7 +6,7 @@ import pytest
 
 import pb_workloads as W
 from tests.test_gpu_conv3 import _follow
-from tests.test_update_launches import moved_updates
+from tests.test_moved_update_plans import moved_updates
 
 pytestmark = pytest.mark.gpu
 
